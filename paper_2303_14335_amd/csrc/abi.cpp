@@ -50,7 +50,7 @@ void check_options(const mpld_options* opt) {
   if (opt->min_budget < 0) fail(MPLD_E_INVALID, "min_budget must be >= 0 (0 = 10000)");
 }
 
-constexpr int32_t kDeviceSplitMinNodes = 32768;
+constexpr int32_t kFlowMinNodes = 4096;
 
 void use_device(mpld_context* ctx) {
   if (!ctx) fail(MPLD_E_INVALID, "context is NULL");
@@ -64,14 +64,19 @@ void batch_build(mpld_context* ctx, const mpld_graph* g, const mpld_options* opt
   check_options(opt);
   b->ctx = ctx;
   b->opt = *opt;
-  b->g = make_graph(*g);
-  // large sparse graphs are simplified and split on the device (identical
-  // result; at 50k nodes about half the host's time, at 5k nodes slower)
-  if (device_split_pays(b->g.n, b->g.ptr[(size_t)b->g.n], opt->k) && b->g.n >= kDeviceSplitMinNodes) {
+  const bool simplify = opt->flags & MPLD_SIMPLIFY;
+  // large sparse graphs are validated, simplified, split and packed on the
+  // device (identical results)
+  if (g->num_nodes >= kFlowMinNodes && device_split_pays(g->num_nodes, 2 * g->num_ce, opt->k)) {
     if (!ctx->graph_builder) ctx->graph_builder = graph_builder_create(ctx, false);
-    split_graph_device(*ctx->graph_builder, b->g, opt->k, opt->flags & MPLD_SIMPLIFY, b->s);
+    (void)flow_build(b->flow, *ctx->graph_builder, *g, opt->k, simplify);
+  }
+  if (b->flow.active) {
+    b->s.comp_ptr.assign(1, 0);
+    for (const FlowComp& c : b->flow.comps) b->s.comp_ptr.push_back(b->s.comp_ptr.back() + c.n);
   } else {
-    b->s = simplify_and_split(b->g, opt->k, opt->flags & MPLD_SIMPLIFY);
+    b->g = make_graph(*g);
+    b->s = simplify_and_split(b->g, opt->k, simplify);
   }
   Tune t;
   tune_from_cache(b, nullptr, &t);
@@ -83,6 +88,12 @@ uint32_t min_budget_of(const mpld_options* opt) {
 }
 
 void batch_collect(mpld_batch* b, mpld_result* r) {
+  if (b->flow.active) {
+    if (flow_collect(b->flow, *b->ctx->graph_builder, b->im, b->opt, b->db, r)) return;
+    // a recovery that the device gave up: this batch's host form from now on
+    // (the packed components stay as they are)
+    if (b->s.removal.empty()) flow_to_host(b->flow, b->ctx->stream, b->g, b->s);
+  }
   std::vector<DevRecord> recs;
   std::vector<int8_t> lcol;
   std::vector<int32_t> mins;
@@ -250,6 +261,8 @@ int32_t mpld_batch_create(mpld_context* ctx, const mpld_graph* g, const mpld_opt
     auto* b = new mpld_batch();
     try {
       batch_build(ctx, g, opt, b);
+      // a batch is ready when the call returns
+      check_hip(hipStreamSynchronize(ctx->stream), "batch");
     } catch (...) {
       delete b;
       throw;

@@ -28,12 +28,17 @@ void batch_pack(mpld_batch* b, const Tune& t) {
   const bool stitch = b->opt.flags & MPLD_STITCH_ORDER;
   const bool partners = stitch || (b->opt.flags & MPLD_MINIMIZE);
   for (int32_t c = 0; c < nc; ++c) {
-    local_edges(b->g, b->s, c, pairs);
     const int32_t n = b->s.comp_ptr[c + 1] - b->s.comp_ptr[c];
     uint32_t flags = b->opt.flags;
     if (t.giant_device && n >= t.giant_min_nodes && !stitch &&
         !(flags & (MPLD_FORCE_WAVE | MPLD_FORCE_LDS | MPLD_FORCE_GLOBAL)))
       flags |= MPLD_FORCE_DEVICE;
+    if (b->flow.active) {   // the device packs it
+      const FlowComp& fc = b->flow.comps[(size_t)c];
+      image_place(im, b->ctx, n, fc.m2 / 2, fc.max_deg, b->opt.k, b->opt.node_budget, flags);
+      continue;
+    }
+    local_edges(b->g, b->s, c, pairs);
     if (partners) {   // stitch partners inside the component, in its local numbering
       part.assign((size_t)n, -1);
       for (int32_t i = 0; i < n; ++i) {
@@ -46,7 +51,8 @@ void batch_pack(mpld_batch* b, const Tune& t) {
   }
   image_finish(im, t.order);
   b->im = std::move(im);
-  device_upload(b->ctx, b->im, b->db, t);   // reallocates every buffer it uses
+  // reallocates every buffer it uses
+  device_upload(b->ctx, b->im, b->db, t, b->flow.active ? &b->flow : nullptr);
   b->db.min_budget = b->opt.min_budget > 0 ? (uint32_t)b->opt.min_budget : 10000u;
 }
 

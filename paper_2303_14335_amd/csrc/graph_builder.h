@@ -1,0 +1,73 @@
+// graph_builder.h - the device front-end's workspace and the pieces that its
+// two files share: scans, the simplification and split of a CSR graph
+// (graph_device.hip) and the whole-layout flow (flow_device.hip).
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <mutex>
+
+#include "internal.h"
+#include "runtime.h"
+
+namespace mpld {
+
+struct GraphBuilder {
+  mpld_context* ctx = nullptr;
+  hipStream_t stream = nullptr;
+  bool own_stream = false;
+  std::mutex mu;
+  DevBuf box, partner, cell_of, cnt, start, fill, ids, sbox, smate, deg, ptr, adj, sums, offs;
+  DevBuf split_ws;   // split outputs then scratch (int32)
+  DevBuf flow_ws;    // scratch of the whole-layout flow
+  PinnedBuf hin, hout;
+  ~GraphBuilder() {
+    if (own_stream && stream) (void)hipStreamDestroy(stream);
+  }
+};
+
+// Buffers grow geometrically: a reallocation (and, for pinned host memory,
+// hipHostMalloc) costs milliseconds, so it should happen rarely.
+inline void grow(DevBuf& b, mpld_context* ctx, size_t bytes) {
+  if (b.bytes < bytes) b.alloc(ctx, std::max(bytes + bytes / 4, 2 * b.bytes));
+}
+inline bool grow_pinned(PinnedBuf& b, size_t bytes) {
+  return bytes <= b.bytes || b.reserve(std::max(bytes + bytes / 4, 2 * b.bytes));
+}
+
+// Exclusive scan of in[0 .. n) into out[0 .. n], out[n] = the total.
+void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out);
+
+struct SplitArgs {
+  int32_t n, k, simplify;
+  const int32_t* ptr;   // n + 1 CSR offsets
+  const int32_t* adj;   // ascending neighbour lists
+  // outputs (one contiguous region)
+  int32_t* counts;      // [0] removed, [1] components
+  int32_t* queue;       // n: removal order
+  int32_t* comp_of;     // n: component, -1 if removed
+  int32_t* order;       // n: core nodes by component, local order
+  int32_t* comp_ptr;    // n + 1
+  int32_t* local;       // n: local index, -1 if removed
+  // scratch: n each, pos0 / off0 / cid n + 1
+  int32_t *f0, *pos0, *cnt0, *off0, *qpos, *lvl, *stamp, *trig, *cand, *parent, *root, *rflag,
+      *cid, *csize, *fill, *list, *rank, *fa, *fb, *gex, *cnt, *cbase, *tail, *cntA, *cntB, *offL;
+  int32_t* ctl;         // [2L], [2L+1]: queue range of level L (1 .. kWideLevels + 1)
+};
+
+// int32 words of the split's outputs (counts (2), queue, comp_of, order (n
+// each), comp_ptr (n + 1), local (n)) and of its scratch.
+inline size_t split_out_words(int64_t n) { return 2 + 5 * (size_t)n + 1; }
+constexpr int kSplitScratch = 27;
+inline size_t split_scratch_words(int64_t n) {   // ctl needs 2 * (kWideLevels + 2)
+  return kSplitScratch * std::max<size_t>((size_t)n + 1, 64);
+}
+
+// Enqueues the split of the CSR at dptr / dadj (device, int32) on the
+// builder's stream, outputs at `out`; no host synchronisation.  Returns the
+// addresses it used.
+SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
+                        int32_t k, bool simplify, int32_t* out, int32_t* scratch);
+
+}  // namespace mpld

@@ -28,10 +28,8 @@
 
 #include <algorithm>
 #include <cstring>
-#include <mutex>
 
-#include "internal.h"
-#include "runtime.h"
+#include "graph_builder.h"
 
 namespace mpld {
 
@@ -235,23 +233,6 @@ __global__ __launch_bounds__(256) void neighbours_kernel(
 // parent being its numbered neighbour of smallest local position.
 constexpr int kSplitThreads = 1024;   // the one-workgroup kernels
 constexpr int kSplitGrid = 2048;      // grid-stride kernels: blocks of 256
-
-struct SplitArgs {
-  int32_t n, k, simplify;
-  const int32_t* ptr;   // n + 1 CSR offsets
-  const int32_t* adj;   // ascending neighbour lists
-  // outputs (one contiguous region)
-  int32_t* counts;      // [0] removed, [1] components
-  int32_t* queue;       // n: removal order
-  int32_t* comp_of;     // n: component, -1 if removed
-  int32_t* order;       // n: core nodes by component, local order
-  int32_t* comp_ptr;    // n + 1
-  int32_t* local;       // n: local index, -1 if removed
-  // scratch: n each, pos0 / off0 / cid n + 1
-  int32_t *f0, *pos0, *cnt0, *off0, *qpos, *lvl, *stamp, *trig, *cand, *parent, *root, *rflag,
-      *cid, *csize, *fill, *list, *rank, *fa, *fb, *gex, *cnt, *cbase, *tail, *cntA, *cntB, *offL;
-  int32_t* ctl;         // [2L], [2L+1]: queue range of level L (1 .. kWideLevels + 1)
-};
 
 // Peel levels 1 .. kWideLevels take their next level with device-wide
 // launches; the one-workgroup kernel goes on from level kWideLevels + 1.
@@ -756,28 +737,6 @@ __global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
 
 // ---- host side --------------------------------------------------------------
 
-struct GraphBuilder {
-  mpld_context* ctx = nullptr;
-  hipStream_t stream = nullptr;
-  bool own_stream = false;
-  std::mutex mu;
-  DevBuf box, partner, cell_of, cnt, start, fill, ids, sbox, smate, deg, ptr, adj, sums, offs;
-  DevBuf split_ws;   // split outputs then scratch (int32)
-  PinnedBuf hin, hout;
-  ~GraphBuilder() {
-    if (own_stream && stream) (void)hipStreamDestroy(stream);
-  }
-};
-
-// Buffers grow geometrically: a reallocation (and, for pinned host memory,
-// hipHostMalloc) costs milliseconds, so it should happen rarely.
-static void grow(DevBuf& b, mpld_context* ctx, size_t bytes) {
-  if (b.bytes < bytes) b.alloc(ctx, std::max(bytes + bytes / 4, 2 * b.bytes));
-}
-static bool grow_pinned(PinnedBuf& b, size_t bytes) {
-  return bytes <= b.bytes || b.reserve(std::max(bytes + bytes / 4, 2 * b.bytes));
-}
-
 GraphBuilder* graph_builder_create(mpld_context* ctx, bool own_stream) {
   auto* gb = new GraphBuilder();
   gb->ctx = ctx;
@@ -798,7 +757,7 @@ GraphBuilder* graph_builder_create(mpld_context* ctx, bool own_stream) {
 void graph_builder_destroy(GraphBuilder* gb) { delete gb; }
 
 
-static void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
+void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
   const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
   grow(gb.sums, gb.ctx, sizeof(int32_t) * (size_t)(ntiles + 1));
   grow(gb.offs, gb.ctx, sizeof(int32_t) * (size_t)(ntiles + 1));
@@ -812,33 +771,23 @@ static void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
   check_hip(hipGetLastError(), "graph builder: scan");
 }
 
-// split_ws layout (int32): counts (2), queue, comp_of, order (n each),
-// comp_ptr (n + 1), local (n) -- the part copied back, split_out_words(n)
-// words -- then the scratch arrays, n + 1 words each.
-static size_t split_out_words(int64_t n) { return 2 + 5 * (size_t)n + 1; }
-static constexpr int kSplitScratch = 27;
-
-// Enqueues the split of the CSR at dptr / dadj (device, int32); no host
-// synchronisation.
-static void enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                          int32_t k, bool simplify) {
+SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
+                        int32_t k, bool simplify, int32_t* out, int32_t* scratch_at) {
   const size_t nn = (size_t)n;
-  const size_t stride = std::max<size_t>(nn + 1, 64);   // ctl needs 2 * (kWideLevels + 2)
-  grow(gb.split_ws, gb.ctx, sizeof(int32_t) * (split_out_words(n) + kSplitScratch * stride));
-  int32_t* w = gb.split_ws.as<int32_t>();
   SplitArgs a{};
   a.n = n;
   a.k = k;
   a.simplify = simplify ? 1 : 0;
   a.ptr = dptr;
   a.adj = dadj;
-  a.counts = w;
-  a.queue = w + 2;
+  a.counts = out;
+  a.queue = out + 2;
   a.comp_of = a.queue + nn;
   a.order = a.comp_of + nn;
   a.comp_ptr = a.order + nn;
   a.local = a.comp_ptr + nn + 1;
-  int32_t* q = a.local + nn;
+  const size_t stride = split_scratch_words(n) / kSplitScratch;
+  int32_t* q = scratch_at;
   int32_t** scratch[kSplitScratch] = {&a.f0,   &a.pos0,  &a.cnt0, &a.off0,  &a.qpos,  &a.lvl,
                                       &a.stamp, &a.trig,  &a.cand, &a.parent, &a.root, &a.rflag,
                                       &a.cid,  &a.csize, &a.fill, &a.list,  &a.rank,  &a.fa,
@@ -876,6 +825,15 @@ static void enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, cons
   wide(bfs_small_kernel);
   hipLaunchKernelGGL(bfs_big_kernel, dim3(1), dim3(kSplitThreads), 0, st, a);
   check_hip(hipGetLastError(), "device split");
+  return a;
+}
+
+// The same in the builder's own workspace: outputs at its front.
+static void enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
+                          int32_t k, bool simplify) {
+  grow(gb.split_ws, gb.ctx, sizeof(int32_t) * (split_out_words(n) + split_scratch_words(n)));
+  int32_t* w = gb.split_ws.as<int32_t>();
+  enqueue_split(gb, n, dptr, dadj, k, simplify, w, w + split_out_words(n));
 }
 
 // Split from the copied-back words of split_ws.
@@ -911,7 +869,7 @@ void graph_builder_reserve(GraphBuilder& gb, int32_t nodes) {
   const size_t tiles = (cells + kScanTile - 1) / kScanTile + 1;
   grow(gb.sums, ctx, 4 * tiles);
   grow(gb.offs, ctx, 4 * tiles);
-  grow(gb.split_ws, ctx, 4 * (split_out_words((int64_t)n) + kSplitScratch * std::max<size_t>(n + 1, 64)));
+  grow(gb.split_ws, ctx, 4 * (split_out_words((int64_t)n) + split_scratch_words((int64_t)n)));
   if (!grow_pinned(gb.hin, 20 * n + 4 * (n + 1 + adj)) ||
       !grow_pinned(gb.hout, 4 * (n + 1 + adj + split_out_words((int64_t)n))))
     fail(MPLD_E_NOMEM, "graph builder: pinned host memory");

@@ -24,8 +24,15 @@ void check_hip(hipError_t e, const char* what) {
 // with the stitch-aware order each node's stitch partner (local id, -1
 // none).
 
-void image_add(Image& im, mpld_context* ctx, int32_t n, const int32_t* pairs, int64_t m, int32_t k,
-               int64_t budget, uint32_t flags, const int32_t* partner) {
+static bool takes_register_tier(int32_t n, uint32_t flags) {
+  return n <= 64 && !(flags & (MPLD_FORCE_LDS | MPLD_FORCE_GLOBAL | MPLD_FORCE_DEVICE));
+}
+
+// Chooses the tier of a component of m pairs (max_deg: CSR tiers only) and
+// enters its descriptor; d.nbr_off is where its data go in masks or adj32,
+// whose sizes grow by what it needs.
+static DevDesc image_enter(Image& im, mpld_context* ctx, int32_t n, int64_t m, int32_t max_deg,
+                           int32_t k, int64_t budget, uint32_t flags) {
   DevDesc d{};
   d.n = n;
   d.k = k;
@@ -44,58 +51,23 @@ void image_add(Image& im, mpld_context* ctx, int32_t n, const int32_t* pairs, in
   if (stitch && force_dev)
     fail(MPLD_E_UNSUPPORTED, "the stitch-aware order runs on the register, LDS and big tiers, not "
                              "on the device-wide tier");
-  if (n <= 64 && !force_lds && !force_glb && !force_dev) {
-    d.nbr_off = (int64_t)im.masks.size();
-    im.masks.resize(im.masks.size() + (size_t)n, 0ull);
-    im.partner8.resize(im.masks.size(), 0xffu);
+  if (takes_register_tier(n, flags)) {
+    d.nbr_off = im.mask_words;
+    im.mask_words += n;
     if (stitch) im.stitch = true;
-    if (stitch || minimize) {
-      if (partner)
-        for (int32_t v = 0; v < n; ++v)
-          if (partner[v] >= 0) im.partner8[(size_t)d.nbr_off + v] = (uint8_t)partner[v];
-    }
-    uint64_t* mk = im.masks.data() + d.nbr_off;
-    for (int64_t e = 0; e < m; ++e) {
-      const int32_t a = pairs[2 * e], b = pairs[2 * e + 1];
-      mk[a] |= 1ull << b;
-      mk[b] |= 1ull << a;
-    }
     im.q_reg.push_back(id);
   } else {
     if (force_reg) fail(MPLD_E_UNSUPPORTED, "register tier takes at most 64 nodes, component has " + std::to_string(n));
-    d.nbr_off = (int64_t)im.adj32.size();
+    d.nbr_off = im.adj_words;
     const int64_t adj_words = (int64_t)n + 1 + 2 * m;
-    im.adj32.resize(im.adj32.size() + (size_t)adj_words + 1 + (stitch ? (size_t)n : 0u), 0u);
-    if (stitch) {
-      im.csr_stitch = true;
-      uint32_t* pw = im.adj32.data() + d.nbr_off + adj_words + 1;
-      for (int32_t v = 0; v < n; ++v) pw[v] = partner && partner[v] >= 0 ? (uint32_t)partner[v] : 0xffffffffu;
-    }
-    uint32_t* ptr = im.adj32.data() + d.nbr_off;
-    uint32_t* ids = ptr + n + 1;
-    for (int64_t e = 0; e < m; ++e) {
-      ++ptr[pairs[2 * e] + 1];
-      ++ptr[pairs[2 * e + 1] + 1];
-    }
-    uint32_t maxdeg = 0;
-    for (int32_t v = 0; v < n; ++v) {
-      maxdeg = std::max(maxdeg, ptr[v + 1]);
-      ptr[v + 1] += ptr[v];
-    }
-    std::vector<uint32_t> fill(ptr, ptr + n);
-    for (int64_t e = 0; e < m; ++e) {
-      const int32_t a = pairs[2 * e], b = pairs[2 * e + 1];
-      ids[fill[a]++] = (uint32_t)b;
-      ids[fill[b]++] = (uint32_t)a;
-    }
-    for (int32_t v = 0; v < n; ++v) std::sort(ids + ptr[v], ids + ptr[v + 1]);
-    ids[2 * m] = maxdeg;
-    const int64_t small = lds_bytes_for(n, k, adj_words, (int32_t)maxdeg, false, stitch);
-    const int64_t big = lds_bytes_for(n, k, adj_words, (int32_t)maxdeg, true, stitch);
+    im.adj_words += adj_words + 1 + (stitch ? n : 0);
+    if (stitch) im.csr_stitch = true;
+    const int64_t small = lds_bytes_for(n, k, adj_words, max_deg, false, stitch);
+    const int64_t big = lds_bytes_for(n, k, adj_words, max_deg, true, stitch);
     const int64_t limit = std::min<int64_t>(kLdsSmallLimit, ctx->lds_per_block);
     im.mark_lds = std::max(im.mark_lds, mark_lds_bytes(n, k));
     if (force_dev) {
-      im.dev_stack_words = std::max(im.dev_stack_words, device_tier_stack_words(n, (int32_t)maxdeg));
+      im.dev_stack_words = std::max(im.dev_stack_words, device_tier_stack_words(n, max_deg));
       im.dev_max_n = std::max(im.dev_max_n, n);
       im.q_dev.push_back(id);
     } else if (!force_glb && small <= limit && n <= kLds1MaxN) {
@@ -103,7 +75,7 @@ void image_add(Image& im, mpld_context* ctx, int32_t n, const int32_t* pairs, in
       im.q_lds.push_back(id);
     } else if (big <= ctx->lds_per_block) {
       im.lds_bytes_big = std::max(im.lds_bytes_big, big);
-      const int64_t wide = lds_wide_bytes(n, k, adj_words, (int32_t)maxdeg, stitch);
+      const int64_t wide = lds_wide_bytes(n, k, adj_words, max_deg, stitch);
       if (im.big_bytes_wg.size() <= (size_t)id) {
         im.big_bytes_wg.resize((size_t)id + 1, 0);
         im.big_bytes_wide.resize((size_t)id + 1, -1);
@@ -123,6 +95,53 @@ void image_add(Image& im, mpld_context* ctx, int32_t n, const int32_t* pairs, in
   im.total_nodes += n;
   im.max_size = std::max(im.max_size, n);
   im.core_edges += m;
+  return d;
+}
+
+void image_place(Image& im, mpld_context* ctx, int32_t n, int64_t m, int32_t max_deg, int32_t k,
+                 int64_t budget, uint32_t flags) {
+  (void)image_enter(im, ctx, n, m, max_deg, k, budget, flags);
+}
+
+void image_add(Image& im, mpld_context* ctx, int32_t n, const int32_t* pairs, int64_t m, int32_t k,
+               int64_t budget, uint32_t flags, const int32_t* partner) {
+  const bool stitch = flags & MPLD_STITCH_ORDER;
+  if (takes_register_tier(n, flags)) {
+    const DevDesc d = image_enter(im, ctx, n, m, 0, k, budget, flags);
+    im.masks.resize(im.masks.size() + (size_t)n, 0ull);
+    im.partner8.resize(im.masks.size(), 0xffu);
+    if ((stitch || (flags & MPLD_MINIMIZE)) && partner)
+      for (int32_t v = 0; v < n; ++v)
+        if (partner[v] >= 0) im.partner8[(size_t)d.nbr_off + v] = (uint8_t)partner[v];
+    uint64_t* mk = im.masks.data() + d.nbr_off;
+    for (int64_t e = 0; e < m; ++e) {
+      const int32_t a = pairs[2 * e], b = pairs[2 * e + 1];
+      mk[a] |= 1ull << b;
+      mk[b] |= 1ull << a;
+    }
+    return;
+  }
+  std::vector<int32_t> deg((size_t)n, 0);
+  for (int64_t e = 0; e < 2 * m; ++e) ++deg[(size_t)pairs[e]];
+  int32_t maxdeg = 0;
+  for (int32_t v = 0; v < n; ++v) maxdeg = std::max(maxdeg, deg[(size_t)v]);
+  const DevDesc d = image_enter(im, ctx, n, m, maxdeg, k, budget, flags);
+  im.adj32.resize((size_t)im.adj_words, 0u);
+  uint32_t* ptr = im.adj32.data() + d.nbr_off;
+  uint32_t* ids = ptr + n + 1;
+  if (stitch) {
+    uint32_t* pw = ids + 2 * m + 1;
+    for (int32_t v = 0; v < n; ++v) pw[v] = partner && partner[v] >= 0 ? (uint32_t)partner[v] : 0xffffffffu;
+  }
+  for (int32_t v = 0; v < n; ++v) ptr[v + 1] = ptr[v] + (uint32_t)deg[(size_t)v];
+  std::vector<uint32_t> fill(ptr, ptr + n);
+  for (int64_t e = 0; e < m; ++e) {
+    const int32_t a = pairs[2 * e], b = pairs[2 * e + 1];
+    ids[fill[a]++] = (uint32_t)b;
+    ids[fill[b]++] = (uint32_t)a;
+  }
+  for (int32_t v = 0; v < n; ++v) std::sort(ids + ptr[v], ids + ptr[v + 1]);
+  ids[2 * m] = (uint32_t)maxdeg;
 }
 
 void image_finish(Image& im, int order) {
@@ -153,7 +172,8 @@ static int blocks_for_lds(mpld_context* ctx, int lds_bytes) {
   return by_lds * ctx->num_cus;
 }
 
-void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tune& tune) {
+void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tune& tune,
+                   FlowGraph* flow) {
   db.ctx = ctx;
   db.tune = tune;
   if (db.graph) {
@@ -254,8 +274,9 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   db.csr_stitch = im.csr_stitch;
   const RegItems shape = db.reg_items();
   const size_t stride = shape.stride;
-  std::vector<uint8_t> items(stride * (size_t)db.n_reg, 0);
-  for (int32_t i = 0; i < db.n_reg; ++i) {
+  const size_t item_bytes = stride * (size_t)db.n_reg;
+  std::vector<uint8_t> items(flow ? 0 : item_bytes, 0);
+  for (int32_t i = 0; i < (flow ? 0 : db.n_reg); ++i) {
     uint8_t* it = items.data() + stride * (size_t)i;
     const DevDesc& d = ordered[(size_t)i];
     std::memcpy(it, &d, sizeof(DevDesc));
@@ -267,8 +288,8 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   }
 
   db.desc.alloc(ctx, sizeof(DevDesc) * ordered.size());
-  db.regitems.alloc(ctx, items.size());
-  db.adj32.alloc(ctx, sizeof(uint32_t) * im.adj32.size());
+  db.regitems.alloc(ctx, item_bytes);
+  db.adj32.alloc(ctx, sizeof(uint32_t) * (size_t)im.adj_words);
   db.counters.alloc(ctx, sizeof(int32_t) * 8);
   db.recs.alloc(ctx, sizeof(DevRecord) * im.desc.size());
   db.colors.alloc(ctx, (size_t)im.total_nodes);
@@ -295,14 +316,22 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   check_hip(hipMemsetAsync(db.counters.p, 0, sizeof(int32_t) * 8, s), "clear counters");
   if (db.n_dev)
     check_hip(hipMemsetAsync(db.dev_keys.p, 0xff, sizeof(uint64_t) * 4, s), "clear keys");
-  check_hip(hipStreamSynchronize(s), "upload");
-  db.host_items = std::move(items);
+  db.device_packed = flow != nullptr;
   db.rt_ready = false;
   db.partners.release();
   db.min_out.release();
   if (im.minimize) {
-    db.partners.alloc(ctx, std::max<size_t>(im.partner8.size(), 1));
+    db.partners.alloc(ctx, std::max<size_t>((size_t)im.mask_words, 1));
     db.min_out.alloc(ctx, sizeof(int32_t) * std::max<size_t>(im.desc.size(), 1));
+  }
+  if (flow) {   // the descriptors' copy is staged; nothing else waits
+    db.host_items.clear();
+    flow_pack(*flow, db, s);
+    return;
+  }
+  check_hip(hipStreamSynchronize(s), "upload");
+  db.host_items = std::move(items);
+  if (im.minimize) {
     if (!im.partner8.empty())
       check_hip(hipMemcpyAsync(db.partners.p, im.partner8.data(), im.partner8.size(),
                                hipMemcpyHostToDevice, s), "upload stitch partners");
@@ -315,8 +344,9 @@ static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 void device_roundtrip(DeviceBatch& db, const Image& im, uint32_t flags) {
   mpld_context* ctx = db.ctx;
   hipStream_t s = ctx->stream;
-  const size_t nd = sizeof(DevDesc) * db.host_desc.size(), ni = db.host_items.size(),
-               na = sizeof(uint32_t) * im.adj32.size();
+  const size_t nd = sizeof(DevDesc) * db.host_desc.size(),
+               ni = (size_t)db.reg_items().stride * (size_t)db.n_reg,
+               na = sizeof(uint32_t) * (size_t)im.adj_words;
   const size_t nr = sizeof(DevRecord) * (size_t)db.num_comps, nc = (size_t)db.total_nodes;
   if (!db.rt_ready) {
     if (!db.rt_up.reserve(align256(nd) + align256(ni) + align256(na) + 256) ||
@@ -324,8 +354,18 @@ void device_roundtrip(DeviceBatch& db, const Image& im, uint32_t flags) {
       fail(MPLD_E_NOMEM, "page-locked staging of the round trip");
     auto* up = db.rt_up.as<uint8_t>();
     if (nd) std::memcpy(up, db.host_desc.data(), nd);
-    if (ni) std::memcpy(up + align256(nd), db.host_items.data(), ni);
-    if (na) std::memcpy(up + align256(nd) + align256(ni), im.adj32.data(), na);
+    if (db.device_packed) {
+      if (ni)
+        check_hip(hipMemcpyAsync(up + align256(nd), db.regitems.p, ni, hipMemcpyDeviceToHost, s),
+                  "round trip: register items");
+      if (na)
+        check_hip(hipMemcpyAsync(up + align256(nd) + align256(ni), db.adj32.p, na,
+                                 hipMemcpyDeviceToHost, s), "round trip: adjacency");
+      check_hip(hipStreamSynchronize(s), "round trip: image");
+    } else {
+      if (ni) std::memcpy(up + align256(nd), db.host_items.data(), ni);
+      if (na) std::memcpy(up + align256(nd) + align256(ni), im.adj32.data(), na);
+    }
     for (hipEvent_t& e : db.rt_ev)
       if (!e) check_hip(hipEventCreate(&e), "round-trip event");
     db.rt_ready = true;

@@ -198,6 +198,8 @@ struct Image {
   bool csr_stitch = false;         // MPLD_STITCH_ORDER: CSR blocks end with the partners
   bool minimize = false;           // MPLD_MINIMIZE: partner8 holds the partners
   std::vector<uint32_t> adj32;     // LDS tiers: row offsets, ids, max degree
+  int64_t mask_words = 0, adj_words = 0;   // sizes of masks and adj32 (which stay empty when the
+                                           // device packs the components)
   std::vector<int32_t> q_reg, q_lds, q_big, q_dev;   // component ids per tier
   int32_t total_nodes = 0;
   int32_t max_size = 0;
@@ -242,6 +244,9 @@ struct Tune {
 // partner: local stitch partner per node (-1 none), for MPLD_STITCH_ORDER.
 void image_add(Image& im, mpld_context* ctx, int32_t n, const int32_t* pairs, int64_t m,
                int32_t k, int64_t budget, uint32_t flags, const int32_t* partner = nullptr);
+// The same for a component whose data the device packs: its shape alone.
+void image_place(Image& im, mpld_context* ctx, int32_t n, int64_t m, int32_t max_deg, int32_t k,
+                 int64_t budget, uint32_t flags);
 // Sorts each tier's queue by size (descending, or ascending when order = 1),
 // ties by id.
 void image_finish(Image& im, int order = 0);
@@ -291,6 +296,7 @@ struct DeviceBatch {
   uint32_t graph_flags = 0xffffffffu;
   bool timed = false;               // events of the last solve not read yet
   std::vector<uint8_t> host_items;  // register-tier items as uploaded
+  bool device_packed = false;       // items and adjacency were packed on the device
   // MPLD_ROUNDTRIP: page-locked copies of the image and the results, and
   // the two events around the whole solve
   PinnedBuf rt_up, rt_down;
@@ -302,7 +308,40 @@ struct DeviceBatch {
   ~DeviceBatch();
 };
 
-void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tune& tune = Tune());
+// A layout graph on the device (flow_device.hip): the CSR of the caller's
+// pairs and its split, kept for the packing and for collecting results.
+struct FlowComp {
+  int32_t n, m2, max_deg, first;   // nodes, adjacency entries, largest degree, smallest id
+};
+struct FlowGraph {
+  bool active = false;
+  int32_t n = 0, removed = 0, ncomp = 0;
+  int64_t m = 0;
+  bool simplify = true;
+  DevBuf keep;   // everything below
+  int32_t *ptr = nullptr, *adj = nullptr, *partner = nullptr, *queue = nullptr, *comp_of = nullptr,
+          *order = nullptr, *comp_ptr = nullptr, *local = nullptr;
+  int32_t *cpre = nullptr, *cmax = nullptr;   // core degrees' prefix over `order`; largest per component
+  std::vector<FlowComp> comps;
+};
+struct GraphBuilder;
+// Validates and splits a caller's graph on the device.  False: the host path
+// is to take it (a fault to report, or nothing that the flow is made for).
+bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k, bool simplify);
+// Enqueues the packing of the batch's components (db laid out from their
+// shapes, its descriptors on the device).
+void flow_pack(FlowGraph& f, DeviceBatch& db, hipStream_t st);
+// Recovery, tallies and the result of a solved batch; waits.  False: the
+// recovery was given up (nothing in *r): the host does it.
+bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_options& opt, DeviceBatch& db,
+                  mpld_result* r);
+// The host forms of the graph and its split.
+void flow_to_host(FlowGraph& f, hipStream_t st, Graph& g, Split& s);
+
+// flow: the components' data are packed by the device from that graph (im
+// then holds their shapes only); the copies are not waited for.
+void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tune& tune = Tune(),
+                   FlowGraph* flow = nullptr);
 // Enqueues the search of every component on the context stream (no wait).
 void device_solve(DeviceBatch& db, uint32_t flags);
 // Result of a decomposition from the device records and local colors: maps
@@ -330,11 +369,17 @@ struct mpld_batch {
   mpld_context* ctx = nullptr;
   mpld::Graph g;
   mpld::Split s;
+  mpld::FlowGraph flow;   // active: the graph and its split are on the device
+                          // instead (s.comp_ptr is filled all the same)
   mpld_options opt{};
   mpld::Image im;
   mpld::DeviceBatch db;
   bool solved = false;
   bool tuned_from_cache = false;
+  // its buffers go back while nothing on the stream uses them
+  ~mpld_batch() {
+    if (ctx) (void)hipStreamSynchronize(ctx->stream);
+  }
 };
 
 namespace mpld {

@@ -1,0 +1,166 @@
+"""Whole-layout decomposition of graphs large enough that the device
+validates, splits, packs and recovers them, against the oracle: clusters on
+both sides of every tier border, stitch pairs inside and across components,
+each option, the batch calls on such a graph, and the graphs that the host
+takes back (a fault, a hub, a recovery that is one long chain).  All outputs
+are whole numbers: equal or wrong.
+"""
+import numpy as np
+import pytest
+
+import oracle
+from algx_literal import random_graph
+
+pytestmark = pytest.mark.gpu
+
+SIMPLIFY, TRACE, FORCE_LDS, FORCE_GLOBAL = 1, 2, 16, 32
+MARK, STITCH, MINIMIZE = 1 << 10, 1 << 11, 1 << 13
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+def clustered(n, sizes, degree, stitch, seed):
+    """n nodes with shuffled ids: a connected random graph on each cluster, a
+    sparse forest-like rest tied to clusters and to itself, stitch pairs."""
+    rng = np.random.default_rng(seed)
+    ids = rng.permutation(n)
+    pairs, at = set(), 0
+    for s in sizes:
+        e = {(i, i + 1) for i in range(s - 1)}
+        want = min(max(int(s * degree / 2), s - 1), s * (s - 1) // 2)
+        while len(e) < want:
+            a, b = sorted(rng.integers(0, s, 2).tolist())
+            if a != b:
+                e.add((a, b))
+        pairs |= {(at + a, at + b) for a, b in e}
+        at += s
+    for v in range(at, n):   # a few of the rest hang on anything before them
+        if v and rng.random() < 0.7:
+            pairs.add((int(rng.integers(0, v)), v))
+    ce = np.array([(ids[a], ids[b]) for a, b in sorted(pairs)], np.int32).reshape(-1, 2)
+    flip = rng.random(len(ce)) < 0.5
+    ce[flip] = ce[flip][:, ::-1]
+    ce = ce[rng.permutation(len(ce))]
+    se = []
+    if stitch:
+        have = {tuple(sorted(p)) for p in ce.tolist()}
+        perm = rng.permutation(n)[: n // 4 * 2].reshape(-1, 2)
+        near = np.stack([ids[np.arange(0, at - 1, 2)], ids[np.arange(1, at, 2)]], 1)
+        used = set()
+        for a, b in np.concatenate([near, perm]).tolist():
+            if a not in used and b not in used and tuple(sorted((a, b))) not in have:
+                used |= {a, b}
+                se.append((a, b))
+    return n, ce, np.array(se, np.int32).reshape(-1, 2)
+
+
+def compare(got, ref):
+    assert np.array_equal(got.component_of, ref.comp_of)
+    assert len(got.components) == len(ref.comps)
+    for f in got.components.dtype.names:
+        assert np.array_equal(got.components[f], ref.comps[f]), f
+    assert np.array_equal(got.colors, ref.colors)
+    assert (got.stitches, got.conflicts, got.uncolored) == (ref.stitches, ref.conflicts, ref.uncolored)
+
+
+SMALL = [5, 6, 7, 30, 31, 63, 64, 64, 12, 9, 8] * 3
+MIXED = SMALL + [65, 100, 700, 2047, 2048, 2049]
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 6])
+@pytest.mark.parametrize("n,sizes,flags", [
+    (4096, SMALL, SIMPLIFY | TRACE), (4097, SMALL, TRACE), (5001, SMALL, SIMPLIFY | TRACE | STITCH),
+    (20000, MIXED, SIMPLIFY | TRACE), (20001, MIXED, SIMPLIFY | TRACE | STITCH | MARK),
+    (6000, SMALL, SIMPLIFY | TRACE | STITCH | MINIMIZE), (7000, SMALL, SIMPLIFY | TRACE | FORCE_LDS),
+    (20000, [17] * 5 + [40] * 4, SIMPLIFY | TRACE)])
+def test_clusters(ctx, k, n, sizes, flags):
+    import paper_2303_14335_amd as mp
+    degree = min(1.25 * k + 0.9, 2.3 * k - 2.0)
+    say("clusters", k, n, len(sizes), flags)
+    n, ce, se = clustered(n, sizes, degree, True, 7 * n + k)
+    ref = oracle.decompose(oracle.Graph(n, ce, se), k, 300, bool(flags & SIMPLIFY), bool(flags & MARK),
+                           bool(flags & STITCH), bool(flags & MINIMIZE), 60)
+    got = mp.mpld_decompose(ctx, mp.Graph(n, ce, se), k, 300, flags, 60)
+    compare(got, ref)
+    b = mp.Batch(ctx, mp.Graph(n, ce, se), k, 300, flags, 60)
+    for how in ({}, {"split": True}, {"roundtrip": True}):
+        b.solve(**how)
+        compare(b.result(), ref)
+    if not flags & FORCE_LDS:   # laid out again with another schedule
+        b.set_tune(order=1, waves_per_block=2, big_one_wave=0)
+        b.solve(roundtrip=True)
+        compare(b.result(), ref)
+    b.close()
+
+
+def test_no_pairs_and_no_core(ctx):
+    import paper_2303_14335_amd as mp
+    say("no pairs; a forest")
+    none = np.zeros((0, 2), np.int32)
+    n, ce, se = clustered(4500, [], 0, True, 3)
+    for args in ((5000, none, none), (5000, none, np.array([[4999, 0]], np.int32)), (n, ce, se)):
+        for flags in (SIMPLIFY | TRACE, TRACE):
+            ref = oracle.decompose(oracle.Graph(*args), 3, 1000, bool(flags & SIMPLIFY))
+            compare(mp.mpld_decompose(ctx, mp.Graph(*args), 3, 1000, flags), ref)
+
+
+@pytest.mark.parametrize("order", ["up", "down", "zigzag"])
+def test_long_chain(ctx, order):
+    """Every node of a path waits for its neighbour: past the device's wait
+    the host recovers it."""
+    import paper_2303_14335_amd as mp
+    n = 9001
+    ids = {"up": np.arange(n), "down": np.arange(n)[::-1],
+           "zigzag": np.argsort(np.concatenate([np.arange(0, n, 2), np.arange(1, n, 2)]))}[order]
+    ce = np.stack([ids[:-1], ids[1:]], 1).astype(np.int32)
+    se = np.stack([ids[0:n - 3:4], ids[2:n - 1:4]], 1).astype(np.int32)
+    say("path", order)
+    ref = oracle.decompose(oracle.Graph(n, ce, se), 3, 1000)
+    b = mp.Batch(ctx, mp.Graph(n, ce, se), 3, 1000, SIMPLIFY | TRACE)
+    for _ in range(2):
+        b.solve()
+        compare(b.result(), ref)
+    b.close()
+
+
+def test_hub(ctx):
+    """Nodes of more neighbours than the device ranks: the host's graph."""
+    import paper_2303_14335_amd as mp
+    say("hubs of 2048, 2049 and 4000 neighbours")
+    for d in (2048, 2049, 4000):
+        hub = np.stack([np.zeros(d), np.arange(1, d + 1)], 1)
+        ring = np.stack([np.arange(1, 400), np.arange(2, 401)], 1)
+        ce = np.concatenate([hub, ring]).astype(np.int32)
+        args = (6000, ce, np.array([[0, 5999]], np.int32))
+        ref = oracle.decompose(oracle.Graph(*args), 2, 1000)
+        compare(mp.mpld_decompose(ctx, mp.Graph(*args), 2, 1000, SIMPLIFY | TRACE), ref)
+
+
+def test_faults(ctx):
+    import paper_2303_14335_amd as mp
+    say("faults in a large graph")
+    n, ce, se = clustered(5000, SMALL, 4.0, True, 11)
+
+    def refused(ce, se, what):
+        with pytest.raises(mp.MpldError) as e:
+            mp.mpld_decompose(ctx, mp.Graph(n, ce, se), 3, 1000)
+        assert e.value.code == -1 and what in str(e.value)
+
+    def put(a, i, pair):
+        a = a.copy()
+        a[i] = pair
+        return a
+
+    refused(put(ce, 77, (3, n)), se, "conflict edge 77 has a node id out of range")
+    refused(put(ce, 5, (-1, 2)), se, "conflict edge 5 has a node id out of range")
+    refused(put(ce, 0, (9, 9)), se, "conflict edge 0 is a self loop")
+    refused(put(ce, 10, ce[900][::-1]), se, "duplicate conflict edge")
+    refused(ce, put(se, 3, (n, 0)), "stitch edge 3 is out of range")
+    refused(ce, put(se, 4, (se[9][1], se[9][1])), "or a loop")
+    refused(ce, put(se, 4, (se[9][1], se[4][0])), "two stitch pairs")
+    last = np.array([[ce[40][0], ce[40][1]]], np.int32)
+    refused(ce, last, "both stitch and conflict")
+    ref = oracle.decompose(oracle.Graph(n, ce, se), 3, 1000)   # and the graph itself still goes through
+    compare(mp.mpld_decompose(ctx, mp.Graph(n, ce, se), 3, 1000, SIMPLIFY | TRACE), ref)
