@@ -55,12 +55,12 @@ static_assert(sizeof(FlowHead) == 40, "head is 40 bytes");
 // ---- the CSR graph of the caller's pairs -----------------------------------
 
 __global__ __launch_bounds__(256) void flow_init_kernel(int32_t n, FlowHead* head, int32_t* deg,
-                                                        int32_t* fill, int32_t* partner) {
+                                                        int32_t* partner, int32_t* cmax) {
   if (blockIdx.x == 0 && threadIdx.x == 0) *head = FlowHead{};
   FLOW_FOR(v, n) {
     deg[v] = 0;
-    fill[v] = 0;
     partner[v] = -1;
+    cmax[v] = 0;
   }
 }
 
@@ -68,29 +68,30 @@ __device__ __forceinline__ bool flow_pair_ok(int2 e, int32_t n) {
   return e.x >= 0 && e.y >= 0 && e.x < n && e.y < n && e.x != e.y;
 }
 
+// Degrees; each pair's places in the two lists are the counts it found, so
+// that the scatter needs no atomics of its own.
 __global__ __launch_bounds__(256) void flow_count_kernel(int32_t n, int32_t m, const int2* ce,
-                                                         int32_t* deg, FlowHead* head) {
+                                                         int32_t* deg, int2* place, FlowHead* head) {
   FLOW_FOR(i, m) {
     const int2 e = ce[i];
     if (!flow_pair_ok(e, n)) {
       atomicOr(&head->flags, kFlowBadPair);
       continue;
     }
-    atomicAdd(deg + e.x, 1);
-    atomicAdd(deg + e.y, 1);
+    place[i] = int2{atomicAdd(deg + e.x, 1), atomicAdd(deg + e.y, 1)};
   }
 }
 
 // Both directions of every pair into its node's list, in any order; src is
 // the list's node, so that the ranking below has one thread per entry.
 __global__ __launch_bounds__(256) void flow_scatter_kernel(int32_t n, int32_t m, const int2* ce,
-                                                           const int32_t* ptr, int32_t* fill,
+                                                           const int32_t* ptr, const int2* place,
                                                            int32_t* tmp, int32_t* src) {
   FLOW_FOR(i, m) {
     const int2 e = ce[i];
     if (!flow_pair_ok(e, n)) continue;
-    const int32_t a = ptr[e.x] + atomicAdd(fill + e.x, 1);
-    const int32_t b = ptr[e.y] + atomicAdd(fill + e.y, 1);
+    const int2 at = place[i];
+    const int32_t a = ptr[e.x] + at.x, b = ptr[e.y] + at.y;
     tmp[a] = e.y;
     src[a] = e.x;
     tmp[b] = e.x;
@@ -143,17 +144,6 @@ __global__ __launch_bounds__(256) void flow_partner_kernel(int32_t n, int32_t m,
     }
     if (bad) atomicOr(&head->flags, kFlowBadPair);
   }
-}
-
-// A graph with a fault becomes one without pairs: the split's kernels take
-// ascending, symmetric lists for granted.
-__global__ __launch_bounds__(256) void flow_guard_kernel(int32_t n, const FlowHead* head, int32_t* ptr) {
-  if (head->flags == 0) return;
-  FLOW_FOR(v, n + 1) ptr[v] = 0;
-}
-
-__global__ __launch_bounds__(256) void flow_zero_kernel(int32_t* p, int32_t n) {
-  FLOW_FOR(v, n) p[v] = 0;
 }
 
 // ---- components ---------------------------------------------------------------
@@ -309,41 +299,54 @@ __global__ __launch_bounds__(256) void flow_recover_kernel(int32_t removed, int3
   __syncthreads();
   const int32_t i = removed - 1 - (base + (int32_t)threadIdx.x);
   bool done = i < 0;
-  int32_t x = 0, t0 = 0, t1 = 0, q = -1;
+  int32_t x = 0, t = 0, t1 = 0, q = -1, w = -1, q_col = -1;
+  uint32_t used = 0;
+  // the next node whose color x needs, from its list, then its partner
+  auto next = [&] {
+    for (w = -1; t < t1 && w < 0; ++t) {
+      const int32_t y = adj[t], py = qpos[y];
+      if (py < 0 || py > i) w = y;
+    }
+    if (w < 0) {
+      w = q;
+      q = -1;
+      t = t1 + 1;   // w, if any, is the partner
+    }
+  };
   if (!done) {
     x = queue[i];
-    t0 = ptr[x];
+    t = ptr[x];
     t1 = ptr[x + 1];
     q = partner[x];
     if (q >= 0) {
       const int32_t pq = qpos[q];
       if (pq >= 0 && pq < i) q = -1;   // removed before x: not colored yet
     }
+    next();
   }
-  // a lane stores its color inside the loop, not on its way out: lanes of
-  // its own wave may be waiting for it
+  // A lane keeps what it has read and asks for one color a round.  It stores
+  // its own inside the loop, not on its way out: lanes of its own wave may
+  // be waiting for it.
   for (int32_t spin = 0; spin < kRecoverSpin; ++spin) {
-    if (!done) {
-      uint32_t used = 0;
-      bool ready = true;
-      for (int32_t t = t0; t < t1; ++t) {
-        const int32_t w = adj[t], pw = qpos[w];
-        if (pw >= 0 && pw < i) continue;
+    while (!done) {
+      if (w >= 0) {
         const int32_t c = ld_color(col + w);
-        if (c >= 0) used |= 1u << c;
-        ready &= c != kPending;
-      }
-      const int32_t cq = q >= 0 ? ld_color(col + q) : -1;
-      if (ready && cq != kPending) {
-        int32_t c = cq;
-        if (cq < 0 || ((used >> cq) & 1u)) {
-          const uint32_t free_mask = ~used & ((1u << k) - 1u);
-          if (!free_mask) atomicOr(&head->flags, kFlowNoColor);
-          c = free_mask ? (int32_t)__builtin_ctz(free_mask) : 0;
+        if (c == kPending) break;
+        if (t > t1) q_col = c;
+        else if (c >= 0) used |= 1u << c;
+        if (t <= t1) {
+          next();
+          continue;
         }
-        __hip_atomic_store(col + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        done = true;
       }
+      int32_t c = q_col;
+      if (c < 0 || ((used >> c) & 1u)) {
+        const uint32_t free_mask = ~used & ((1u << k) - 1u);
+        if (!free_mask) atomicOr(&head->flags, kFlowNoColor);
+        c = free_mask ? (int32_t)__builtin_ctz(free_mask) : 0;
+      }
+      __hip_atomic_store(col + x, c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      done = true;
     }
     if (__ballot(!done) == 0ull) break;
     if ((spin & 63) == 63 && (ld_color(&head->flags) & kFlowChain)) break;
@@ -385,10 +388,19 @@ __global__ __launch_bounds__(256) void flow_tally_kernel(int32_t n, const int32_
     cn += __shfl_down(cn, off, 64);
     un += __shfl_down(un, off, 64);
   }
+  // one addition a block: thousands of waves adding to one address had taken
+  // most of this kernel's time (82 us on 296k nodes)
+  __shared__ uint32_t sum[3][4];
   if ((threadIdx.x & 63) == 0) {
-    if (st) atomicAdd(&head->stitches, (unsigned long long)st);
-    if (cn) atomicAdd(&head->conflicts, (unsigned long long)cn);
-    if (un) atomicAdd(&head->uncolored, (unsigned long long)un);
+    sum[0][threadIdx.x >> 6] = st;
+    sum[1][threadIdx.x >> 6] = cn;
+    sum[2][threadIdx.x >> 6] = un;
+  }
+  __syncthreads();
+  if (threadIdx.x < 3) {
+    const uint32_t* s = sum[threadIdx.x];
+    const unsigned long long v = (unsigned long long)s[0] + s[1] + s[2] + s[3];
+    if (v) atomicAdd(&head->stitches + threadIdx.x, v);
   }
 }
 
@@ -423,7 +435,7 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
   const size_t head_words = (sizeof(FlowHead) + 24) / 4;   // the summary behind it, 16-byte aligned
   const size_t pair_words = 2 * (mm + (size_t)ns);
   const size_t scratch =
-      head_words + 4 * (nn + 1) + pair_words + 3 * (nn + 1) + 4 * mm + split_scratch_words(n);
+      head_words + 4 * (nn + 1) + pair_words + 2 * mm + 2 * (nn + 1) + 4 * mm + split_scratch_words(n);
   grow(gb.flow_ws, ctx, 4 * scratch);
   int32_t* w = gb.flow_ws.as<int32_t>();
   auto* head = reinterpret_cast<FlowHead*>(w);
@@ -433,9 +445,10 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
   auto* ce = reinterpret_cast<int2*>(w);
   auto* se = ce + mm;
   w += pair_words;
+  auto* place = reinterpret_cast<int2*>(w);
+  w += 2 * mm;
   int32_t* deg = w;
-  int32_t* fill = deg + nn + 1;
-  int32_t* cdeg = fill + nn + 1;
+  int32_t* cdeg = deg + nn + 1;
   int32_t* tmp = cdeg + nn + 1;
   int32_t* src = tmp + 2 * mm;
   int32_t* split_scratch = src + 2 * mm;
@@ -443,16 +456,17 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
       !grow_pinned(gb.hout, sizeof(FlowHead) + 24 + sizeof(FlowComp) * nn + 5 * nn + 256))
     fail(MPLD_E_NOMEM, "layout flow: pinned host memory");
   const unsigned gn = flow_grid(n);
-  hipLaunchKernelGGL(flow_init_kernel, dim3(gn), dim3(256), 0, st, n, head, deg, fill, f.partner);
+  hipLaunchKernelGGL(flow_init_kernel, dim3(gn), dim3(256), 0, st, n, head, deg, f.partner, f.cmax);
   if (m) {
     std::memcpy(gb.hin.p, in.ce, 8 * mm);
     check_hip(hipMemcpyAsync(ce, gb.hin.p, 8 * mm, hipMemcpyHostToDevice, st), "layout flow: pairs");
-    hipLaunchKernelGGL(flow_count_kernel, dim3(flow_grid(m)), dim3(256), 0, st, n, (int32_t)m, ce, deg, head);
+    hipLaunchKernelGGL(flow_count_kernel, dim3(flow_grid(m)), dim3(256), 0, st, n, (int32_t)m, ce, deg, place,
+                       head);
   }
   scan(gb, deg, n, f.ptr);
   if (m) {
     hipLaunchKernelGGL(flow_scatter_kernel, dim3(flow_grid(m)), dim3(256), 0, st, n, (int32_t)m, ce, f.ptr,
-                       fill, tmp, src);
+                       place, tmp, src);
     hipLaunchKernelGGL(flow_rank_kernel, dim3(flow_grid(2 * m)), dim3(256), 0, st, n, f.ptr, tmp, src, f.adj,
                        head);
   }
@@ -463,15 +477,13 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
     hipLaunchKernelGGL(flow_partner_kernel, dim3(flow_grid(ns)), dim3(256), 0, st, n, (int32_t)ns, se, f.ptr,
                        f.adj, f.partner, head);
   }
-  if (m || ns)
-    hipLaunchKernelGGL(flow_guard_kernel, dim3(gn), dim3(256), 0, st, n, head, f.ptr);
-  const SplitArgs a = enqueue_split(gb, n, f.ptr, f.adj, k, simplify, out, split_scratch);
+  const SplitArgs a = enqueue_split(gb, n, f.ptr, f.adj, k, simplify, out, split_scratch, &head->flags,
+                                    f.ptr);
   f.queue = a.queue;
   f.comp_of = a.comp_of;
   f.order = a.order;
   f.comp_ptr = a.comp_ptr;
   f.local = a.local;
-  hipLaunchKernelGGL(flow_zero_kernel, dim3(gn), dim3(256), 0, st, f.cmax, n);
   hipLaunchKernelGGL(flow_core_kernel, dim3(gn), dim3(256), 0, st, n, a.counts, f.ptr, f.adj, f.comp_of,
                      f.order, cdeg, f.cmax);
   scan(gb, cdeg, n, f.cpre);
@@ -541,7 +553,7 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_op
   if (f.simplify && f.removed)
     hipLaunchKernelGGL(flow_recover_kernel, dim3((unsigned)((f.removed + 255) / 256)), dim3(256), 0, st,
                        f.removed, opt.k, head, f.ptr, f.adj, f.partner, f.queue, qpos, col);
-  hipLaunchKernelGGL(flow_tally_kernel, dim3(gn), dim3(256), 0, st, f.n, f.ptr, f.adj, f.partner, f.comp_of,
+  hipLaunchKernelGGL(flow_tally_kernel, dim3(std::min(gn, 512u)), dim3(256), 0, st, f.n, f.ptr, f.adj, f.partner, f.comp_of,
                      col, colors, cstat, head);
   check_hip(hipGetLastError(), "layout flow: recovery");
   // page-locked staging: components of the nodes, head and tallies, records,

@@ -18,7 +18,9 @@ struct GraphBuilder {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::mutex mu;
-  DevBuf box, partner, cell_of, cnt, start, fill, ids, sbox, smate, deg, ptr, adj, sums, offs;
+  DevBuf box, partner, cell_of, cnt, start, fill, ids, sbox, smate, deg, ptr, adj;
+  DevBuf tiles;            // scans: the ticket, then a word per tile
+  uint32_t epoch = 0, tickets = 0;   // launches so far, tickets they took
   DevBuf split_ws;   // split outputs then scratch (int32)
   DevBuf flow_ws;    // scratch of the whole-layout flow
   PinnedBuf hin, hout;
@@ -50,24 +52,26 @@ struct SplitArgs {
   int32_t* order;       // n: core nodes by component, local order
   int32_t* comp_ptr;    // n + 1
   int32_t* local;       // n: local index, -1 if removed
-  // scratch: n each, pos0 / off0 / cid n + 1
-  int32_t *f0, *pos0, *cnt0, *off0, *qpos, *lvl, *stamp, *trig, *cand, *parent, *root, *rflag,
-      *cid, *csize, *fill, *list, *rank, *fa, *fb, *gex, *cnt, *cbase, *tail, *cntA, *cntB, *offL;
-  int32_t* ctl;         // [2L], [2L+1]: queue range of level L (1 .. kWideLevels + 1)
+  // scratch: n + 1 each
+  int32_t *qpos, *stamp, *trig, *cand, *parent, *root, *cid, *csize, *fill, *list, *rank, *fa, *fb,
+      *gex, *cnt, *cbase, *tail;
+  int32_t* ctl;         // the peeling's level ranges and tickets
 };
 
 // int32 words of the split's outputs (counts (2), queue, comp_of, order (n
 // each), comp_ptr (n + 1), local (n)) and of its scratch.
 inline size_t split_out_words(int64_t n) { return 2 + 5 * (size_t)n + 1; }
-constexpr int kSplitScratch = 27;
-inline size_t split_scratch_words(int64_t n) {   // ctl needs 2 * (kWideLevels + 2)
+constexpr int kSplitScratch = 18;
+inline size_t split_scratch_words(int64_t n) {   // ctl needs up to 64
   return kSplitScratch * std::max<size_t>((size_t)n + 1, 64);
 }
 
 // Enqueues the split of the CSR at dptr / dadj (device, int32) on the
 // builder's stream, outputs at `out`; no host synchronisation.  Returns the
-// addresses it used.
+// addresses it used.  fault (may be null): a device word that, nonzero, makes
+// the graph one without pairs (dptr, as ptr_w, is cleared).
 SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                        int32_t k, bool simplify, int32_t* out, int32_t* scratch);
+                        int32_t k, bool simplify, int32_t* out, int32_t* scratch, const int32_t* fault,
+                        int32_t* ptr_w);
 
 }  // namespace mpld

@@ -16,8 +16,7 @@
 //      geometric graph).
 // The result is the CSR the rest of the front-end consumes: adjacency
 // ascending per node, symmetric, no self loops or duplicates by
-// construction.  Scans are three-phase (per-block sums, one block over the
-// sums, per-block scan plus offset).
+// construction.
 //
 // The simplification and sub-graph split that follow (Sec. 2.2; Algorithm 1
 // splits the graph into sub-graphs) can run here too, on the CSR while it is
@@ -32,10 +31,6 @@
 #include "graph_builder.h"
 
 namespace mpld {
-
-static constexpr int kScanBlock = 256;               // threads per scan block
-static constexpr int kScanItems = 4;                 // elements per thread
-static constexpr int kScanTile = kScanBlock * kScanItems;
 
 struct GridParams {
   int64_t minx, miny, cell;
@@ -63,82 +58,128 @@ __global__ __launch_bounds__(256) void cell_count_kernel(const int4* __restrict_
   atomicAdd(&cnt[c], 1);
 }
 
-// Scan phase 1: sum of each tile of kScanTile elements.
-__global__ __launch_bounds__(kScanBlock) void scan_sums_kernel(const int32_t* __restrict__ in,
-                                                               int64_t n, int32_t* __restrict__ sums) {
-  __shared__ int32_t red[kScanBlock / 64];
-  const int64_t base = (int64_t)blockIdx.x * kScanTile + (int64_t)threadIdx.x * kScanItems;
-  int32_t s = 0;
-#pragma unroll
-  for (int j = 0; j < kScanItems; ++j) s += base + j < n ? in[base + j] : 0;
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int32_t t = 0;
-    for (int w = 0; w < kScanBlock / 64; ++w) t += red[w];
-    sums[blockIdx.x] = t;
-  }
+// ---- scans --------------------------------------------------------------------
+//
+// One launch a scan: a block takes the next tile by a ticket, publishes the
+// tile's sum, and its first wave looks back over the published tiles, 64 at
+// a time, to the nearest one that already knows its prefix.  Blocks only
+// wait for tiles with smaller tickets, whose blocks run.  A published word
+// holds an epoch (one per launch, so that nothing is cleared between
+// launches), a state and a value, written and read whole.  Three launches a
+// scan (tile sums, their scan, the tiles again) took 9 to 13 us of a split
+// of 50k to 300k nodes, one takes 4 to 5.
+static constexpr int kScanBlock = 256;               // threads per scan block
+static constexpr int kScanItems = 8;                 // elements per thread
+static constexpr int kScanTile = kScanBlock * kScanItems;
+
+enum : uint64_t { kTileSum = 1, kTilePrefix = 2 };
+__device__ __forceinline__ uint64_t tile_word(uint32_t epoch, uint64_t state, int32_t value) {
+  return ((uint64_t)epoch << 34) | (state << 32) | (uint32_t)value;
 }
 
-// Exclusive scan of one block's kScanTile elements starting at `carry`.
-__device__ void block_scan_tile(const int32_t* __restrict__ in, int64_t n, int64_t base_tile,
-                                int32_t carry, int32_t* __restrict__ out, int32_t* lds) {
-  const int64_t base = base_tile + (int64_t)threadIdx.x * kScanItems;
+// Exclusive prefix of tile `tile` (its sum: `sum`), by the lanes of one
+// wave; every lane gets it.
+__device__ int32_t look_back(uint64_t* status, uint32_t epoch, int32_t tile, int32_t sum) {
+  const int32_t lane = (int32_t)(threadIdx.x & 63u);
+  if (lane == 0)
+    __hip_atomic_store(status + tile, tile_word(epoch, tile == 0 ? kTilePrefix : kTileSum, sum),
+                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (tile == 0) return 0;
+  int32_t prefix = 0;
+  for (int32_t end = tile - 1;; end -= 64) {
+    const int32_t at = end - lane;
+    uint64_t w = tile_word(epoch, kTilePrefix, 0);   // before tile 0: nothing
+    for (;;) {
+      if (at >= 0) w = __hip_atomic_load(status + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (__ballot((uint32_t)(w >> 34) != epoch || ((w >> 32) & 3u) == 0) == 0ull) break;
+    }
+    const uint64_t known = __ballot(((w >> 32) & 3u) == kTilePrefix);
+    const int32_t stop = known ? (int32_t)__builtin_ctzll(known) : 63;
+    int32_t v = lane <= stop ? (int32_t)(uint32_t)w : 0;
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+    prefix += v;
+    if (known) break;
+  }
+  if (lane == 0)
+    __hip_atomic_store(status + tile, tile_word(epoch, kTilePrefix, prefix + sum), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+  return prefix;
+}
+
+// Exclusive prefix of x over a block of THREADS; `total` = the sum.
+template <int THREADS>
+__device__ __forceinline__ int32_t block_excl_scan(int32_t x, int32_t* wsum, int32_t& total) {
+  const int32_t lane = (int32_t)(threadIdx.x & 63u), w = (int32_t)(threadIdx.x >> 6);
+  int32_t incl = x;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const int32_t t = __shfl_up(incl, off, 64);
+    if (lane >= off) incl += t;
+  }
+  if (lane == 63) wsum[w] = incl;
+  __syncthreads();
+  int32_t before = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < THREADS / 64; ++i) {
+    const int32_t v = wsum[i];
+    before += i < w ? v : 0;
+    tot += v;
+  }
+  __syncthreads();   // wsum is reused by the next scan
+  total = tot;
+  return before + incl - x;
+}
+
+// What a scanning block shares.
+struct ScanShared {
+  int32_t wsum[kScanBlock / 64];
+  int32_t tile, prefix;
+};
+
+// The block's tile: the next ticket past `base` (every thread gets it).
+__device__ __forceinline__ int32_t take_tile(int32_t* ticket, uint32_t base, ScanShared& sh) {
+  __syncthreads();   // the last tile's users are done
+  if (threadIdx.x == 0) sh.tile = (int32_t)((uint32_t)atomicAdd(ticket, 1) - base);
+  __syncthreads();
+  return sh.tile;
+}
+
+// Exclusive prefix, over the whole launch, of this thread's x; `end` =
+// prefix behind the block's last thread.
+__device__ __forceinline__ int32_t device_excl_scan(int32_t x, uint64_t* status, uint32_t epoch, int32_t tile,
+                                                    ScanShared& sh, int32_t& end) {
+  int32_t total;
+  const int32_t ex = block_excl_scan<kScanBlock>(x, sh.wsum, total);
+  if (threadIdx.x < 64) {
+    const int32_t p = look_back(status, epoch, tile, total);
+    if (threadIdx.x == 0) sh.prefix = p;
+  }
+  __syncthreads();
+  end = sh.prefix + total;
+  return sh.prefix + ex;
+}
+
+__global__ __launch_bounds__(kScanBlock) void scan_kernel(const int32_t* __restrict__ in, int64_t n,
+                                                          int32_t* __restrict__ out, int32_t* ticket,
+                                                          uint32_t ticket_base, uint64_t* status,
+                                                          uint32_t epoch) {
+  __shared__ ScanShared sh;
+  const int32_t tile = take_tile(ticket, ticket_base, sh);
+  const int64_t base = (int64_t)tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
   int32_t v[kScanItems], s = 0;
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
     v[j] = base + j < n ? in[base + j] : 0;
     s += v[j];
   }
-  lds[threadIdx.x] = s;
-  __syncthreads();
-  // Hillis-Steele over the block's per-thread sums
-  for (int off = 1; off < kScanBlock; off <<= 1) {
-    const int32_t t = threadIdx.x >= (unsigned)off ? lds[threadIdx.x - off] : 0;
-    __syncthreads();
-    lds[threadIdx.x] += t;
-    __syncthreads();
-  }
-  int32_t run = carry + lds[threadIdx.x] - s;   // exclusive prefix of this thread
+  int32_t end;
+  int32_t run = device_excl_scan(s, status, epoch, tile, sh, end);
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
     if (base + j < n) out[base + j] = run;
     run += v[j];
   }
-  __syncthreads();
-}
-
-// Scan phase 2: exclusive scan of the tile sums (one block, looping), and
-// the grand total at sums_out[ntiles].
-__global__ __launch_bounds__(kScanBlock) void scan_tiles_kernel(const int32_t* __restrict__ sums,
-                                                                int64_t ntiles,
-                                                                int32_t* __restrict__ sums_out) {
-  __shared__ int32_t lds[kScanBlock];
-  __shared__ int32_t carry;
-  if (threadIdx.x == 0) carry = 0;
-  __syncthreads();
-  for (int64_t t0 = 0; t0 < ntiles; t0 += kScanTile) {
-    const int32_t c = carry;
-    block_scan_tile(sums, ntiles, t0, c, sums_out, lds);
-    if (threadIdx.x == kScanBlock - 1) {
-      const int64_t last = std::min<int64_t>(t0 + kScanTile, ntiles) - 1;
-      carry = sums_out[last] + sums[last];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) sums_out[ntiles] = carry;
-}
-
-// Scan phase 3: each tile scanned from its offset; out[n] = total.
-__global__ __launch_bounds__(kScanBlock) void scan_apply_kernel(const int32_t* __restrict__ in,
-                                                                int64_t n,
-                                                                const int32_t* __restrict__ offs,
-                                                                int64_t ntiles,
-                                                                int32_t* __restrict__ out) {
-  __shared__ int32_t lds[kScanBlock];
-  block_scan_tile(in, n, (int64_t)blockIdx.x * kScanTile, offs[blockIdx.x], out, lds);
-  if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = offs[ntiles];
+  if (tile == (int32_t)gridDim.x - 1 && threadIdx.x == 0) out[n] = end;
 }
 
 __global__ __launch_bounds__(256) void cell_scatter_kernel(const int4* __restrict__ box,
@@ -213,17 +254,18 @@ __global__ __launch_bounds__(256) void neighbours_kernel(
 // local numbering by BFS from that node, neighbours in ascending id) are
 // reproduced exactly, in level-synchronous form:
 //
-// Peeling.  The queue falls into levels: level 0 is the seed; level L+1
-// holds the nodes queued while level L is popped (the rounds of synchronous
-// peeling).  A node w outside levels 0..L with deg0(w) = d is queued when
-// its (d - k + 1)-th neighbour is popped; if that neighbour (its trigger) is
-// in level L, it is the one of rank (d - k + 1 - before) among w's level-L
-// neighbours by queue position, `before` counting w's neighbours in earlier
-// levels.  Level L+1 is ordered by (trigger's queue position, w's place in
-// the trigger's ascending list): one exclusive scan of per-trigger counts.
-// Level 0 is ordered by id, so level 1's triggers need only the level-0
-// flags: the wide levels 0 and 1 run on the whole device; the rest, usually
-// small, on one workgroup whose rounds are separated by barriers.
+// Peeling.  Node w of d = deg(w) neighbours is queued when its
+// (d - k + 1)-th neighbour is popped, and pops follow the queue: a popped
+// node u at place p queues exactly those neighbours w of which d(w) - k
+// neighbours have a place before p.  That needs no levels and no order
+// within one: it holds for one u alone (the count grows along w's popped
+// neighbours), and places given at the same time are behind p and do not
+// count.  So a level of the queue (the nodes queued while the level before
+// it is popped) is one launch: count each node's children, scan over the
+// level in queue order, write the children in the node's ascending list
+// order.  Level 0 is the seed in id order.  The first levels, which hold
+// nearly every node, take the whole device; what is left, usually small, goes
+// on in one workgroup whose levels are separated by barriers.
 //
 // Components: union-find over the whole device, the larger root hooked
 // under the smaller (so each root is its component's smallest id), numbered
@@ -233,25 +275,34 @@ __global__ __launch_bounds__(256) void neighbours_kernel(
 // parent being its numbered neighbour of smallest local position.
 constexpr int kSplitThreads = 1024;   // the one-workgroup kernels
 constexpr int kSplitGrid = 2048;      // grid-stride kernels: blocks of 256
+constexpr int kLevelGrid = 1024;      // level kernels: blocks of 256 taking tiles by ticket
 
-// Peel levels 1 .. kWideLevels take their next level with device-wide
-// launches; the one-workgroup kernel goes on from level kWideLevels + 1.
-constexpr int kWideLevels = 4;
+// Levels 1 .. kWideLevels are found by launches over the device.
+constexpr int kWideLevels = 5;
+// SplitArgs.ctl: [2L], [2L + 1] the queue range of level L, [kCtlTicket + L]
+// the ticket of the launch that pops level L.
+constexpr int kCtlTicket = 2 * (kWideLevels + 2);
+constexpr int kCtlWords = kCtlTicket + kWideLevels + 2;
+static_assert(kCtlWords <= 64, "ctl is 64 words at least");
 
 #define SPLIT_FOR(v, n)                                                                 \
   for (int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); v < (n);          \
        v += (int32_t)(gridDim.x * blockDim.x))
 
-__global__ __launch_bounds__(256) void split_init_kernel(SplitArgs a) {
+// fault (may be null): a nonzero word makes the graph one without pairs (the
+// kernels behind take ascending, symmetric lists for granted).
+__global__ __launch_bounds__(256) void split_init_kernel(SplitArgs a, const int32_t* fault, int32_t* ptr) {
+  if (blockIdx.x == 0 && threadIdx.x < kCtlWords) a.ctl[threadIdx.x] = 0;
+  const bool none = fault && *fault;
   SPLIT_FOR(v, a.n) {
-    a.f0[v] = a.simplify && a.ptr[v + 1] - a.ptr[v] < a.k ? 1 : 0;
-    a.cnt0[v] = 0;
-    a.cntA[v] = 0;
-    a.cntB[v] = 0;
+    if (none) {
+      ptr[v] = 0;
+      if (v == 0) ptr[a.n] = 0;
+    }
     a.csize[v] = 0;
     a.fill[v] = 0;
     a.qpos[v] = -1;
-    a.lvl[v] = -1;
+    a.parent[v] = v;
     a.stamp[v] = -1;
     a.trig[v] = -1;
     a.local[v] = -1;
@@ -259,225 +310,128 @@ __global__ __launch_bounds__(256) void split_init_kernel(SplitArgs a) {
   }
 }
 
-// Level 0 in id order, and each other node's level-1 trigger: the
-// (d - k + 1)-th level-0 neighbour in its ascending list (level-0 queue
-// order is id order), counted per trigger.
-__global__ __launch_bounds__(256) void split_level0_kernel(SplitArgs a) {
-  SPLIT_FOR(v, a.n) {
-    if (a.f0[v]) {
-      const int32_t p = a.pos0[v];
-      a.queue[p] = v;
-      a.qpos[v] = p;
-      a.lvl[v] = 0;
-    } else if (a.simplify) {
-      int32_t need = a.ptr[v + 1] - a.ptr[v] - a.k + 1;
-      for (int32_t t = a.ptr[v]; t < a.ptr[v + 1]; ++t) {
-        const int32_t x = a.adj[t];
-        if (a.f0[x] && --need == 0) {
-          a.trig[v] = x;
-          atomicAdd(a.cnt0 + a.pos0[x], 1);
-          break;
-        }
+// Level 0: the nodes of degree < k in id order.
+__global__ __launch_bounds__(kScanBlock) void split_seed_kernel(SplitArgs a, int32_t* ticket,
+                                                                uint32_t ticket_base, uint64_t* status,
+                                                                uint32_t epoch) {
+  __shared__ ScanShared sh;
+  const int32_t tile = take_tile(ticket, ticket_base, sh);
+  const int64_t base = (int64_t)tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  uint32_t seeds = 0;
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j)
+    if (base + j < a.n && a.simplify && a.ptr[base + j + 1] - a.ptr[base + j] < a.k) seeds |= 1u << j;
+  int32_t end;
+  int32_t run = device_excl_scan(__builtin_popcount(seeds), status, epoch, tile, sh, end);
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j)
+    if ((seeds >> j) & 1u) {
+      a.queue[run] = (int32_t)(base + j);
+      a.qpos[base + j] = run++;
+    }
+  if (tile == (int32_t)gridDim.x - 1 && threadIdx.x == 0) a.ctl[1] = end;   // level 0 = [0, end)
+}
+
+// Whether the node popped at place p queues its neighbour w.
+__device__ __forceinline__ bool queues(const SplitArgs& a, int32_t w, int32_t p) {
+  const int32_t t0 = a.ptr[w], t1 = a.ptr[w + 1], want = t1 - t0 - a.k;
+  if (want < 0) return false;   // a seed
+  int32_t r = 0;
+  for (int32_t t = t0; t < t1; ++t) r += (uint32_t)a.qpos[a.adj[t]] < (uint32_t)p ? 1 : 0;   // -1: no place
+  return r == want;
+}
+
+// The children of one node per group of G lanes (the lanes share its list,
+// chunk by chunk).  `hit` keeps the first 64 neighbours' answers.
+template <int G>
+__device__ __forceinline__ int32_t count_children(const SplitArgs& a, int32_t u, int32_t p, uint64_t& hit) {
+  const int32_t j = (int32_t)threadIdx.x & (G - 1), shift = (int32_t)(threadIdx.x & 63u) - j;
+  const int32_t t0 = u >= 0 ? a.ptr[u] : 0, t1 = u >= 0 ? a.ptr[u + 1] : 0;
+  int32_t c = 0;
+  hit = 0;
+  for (int32_t t = t0, ch = 0; t < t1; t += G, ch += G) {
+    const bool h = t + j < t1 && queues(a, a.adj[t + j], p);
+    const uint64_t b = (__ballot(h) >> shift) & ((1ull << G) - 1);
+    c += __builtin_popcountll(b);
+    if (ch < 64) hit |= b << ch;
+  }
+  return c;
+}
+template <int G>
+__device__ __forceinline__ void write_children(const SplitArgs& a, int32_t u, int32_t p, uint64_t hit, int32_t at) {
+  const int32_t j = (int32_t)threadIdx.x & (G - 1), shift = (int32_t)(threadIdx.x & 63u) - j;
+  const int32_t t0 = a.ptr[u], t1 = a.ptr[u + 1];
+  for (int32_t t = t0, ch = 0; t < t1; t += G, ch += G) {
+    uint64_t b = (hit >> (ch & 63)) & ((1ull << G) - 1);
+    if (ch >= 64)
+      b = (__ballot(t + j < t1 && queues(a, a.adj[t + j], p)) >> shift) & ((1ull << G) - 1);
+    if ((b >> j) & 1u) {
+      const int32_t w = a.adj[t + j], q = at + __builtin_popcountll(b & ((1ull << j) - 1));
+      if (q < a.n) {   // always: places are a permutation
+        a.queue[q] = w;
+        a.qpos[w] = q;
       }
     }
+    at += __builtin_popcountll(b);
   }
 }
 
-// Level 1: the children of level-0 node x go, in x's list order, at
-// |level 0| + off0[position of x].
-__global__ __launch_bounds__(256) void split_level1_kernel(SplitArgs a) {
-  const int32_t base = a.pos0[a.n];
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    a.ctl[2] = base;
-    a.ctl[3] = base + a.off0[a.n];
-  }
-  SPLIT_FOR(w, a.n) {
-    const int32_t x = a.trig[w];
-    if (x < 0) continue;
-    int32_t r = 0;
-    for (int32_t t = a.ptr[x]; t < a.ptr[x + 1]; ++t) {
-      const int32_t y = a.adj[t];
-      if (y >= w) break;
-      r += !a.f0[y] && a.trig[y] == x ? 1 : 0;
-    }
-    const int32_t p = base + a.off0[a.qpos[x]] + r;
-    if (p >= a.n) continue;   // cannot happen: positions are a permutation
-    a.queue[p] = w;
-    a.qpos[w] = p;
-    a.lvl[w] = 1;
-  }
-}
-
-// Wide level L (>= 1): the trigger of every unqueued node next to level L,
-// counted per trigger at its position within the level.
-__global__ __launch_bounds__(256) void split_trig_kernel(SplitArgs a, int32_t L, int32_t* cnt) {
-  const int32_t lo = a.ctl[2 * L], hi = a.ctl[2 * L + 1];
-  if (lo >= hi) return;
-  SPLIT_FOR(w, a.n) {
-    if (a.qpos[w] >= 0) continue;
-    const int32_t t0 = a.ptr[w], t1 = a.ptr[w + 1];
-    int32_t before = 0, at = 0;
-    for (int32_t t = t0; t < t1; ++t) {
-      const int32_t l = a.lvl[a.adj[t]];
-      before += l >= 0 && l < L ? 1 : 0;
-      at += l == L ? 1 : 0;
-    }
-    if (at == 0) continue;   // not next to level L: its trigger stays -1
-    const int32_t need = t1 - t0 - a.k + 1;
-    int32_t tr = -1;
-    if (before + at >= need) {
-      const int32_t rank = need - before - 1;   // among level-L neighbours by queue position
-      for (int32_t t = t0; t < t1 && tr < 0; ++t) {
-        const int32_t x = a.adj[t];
-        if (a.lvl[x] != L) continue;
-        const int32_t px = a.qpos[x];
-        int32_t r = 0;
-        for (int32_t q = t0; q < t1; ++q) {
-          const int32_t y = a.adj[q];
-          r += a.lvl[y] == L && a.qpos[y] < px ? 1 : 0;
-        }
-        if (r == rank) tr = x;
-      }
-    }
-    a.trig[w] = tr;
-    if (tr >= 0) atomicAdd(cnt + (a.qpos[tr] - lo), 1);
-  }
-}
-
-// Wide level L: level L+1 in (trigger position, trigger's list order); the
-// range of level L+1 goes to ctl, the other count array is cleared for it.
-__global__ __launch_bounds__(256) void split_place_kernel(SplitArgs a, int32_t L,
-                                                          const int32_t* off, int32_t* cnt_next) {
-  const int32_t lo = a.ctl[2 * L], hi = a.ctl[2 * L + 1];
-  SPLIT_FOR(v, a.n) cnt_next[v] = 0;
-  const int32_t total = lo < hi ? off[a.n] : 0;
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
+// Pops level L: level L + 1 behind it.  Groups of G lanes share a node (one
+// lane each on level 0, whose nodes have fewer than k neighbours).
+template <int G>
+__global__ __launch_bounds__(kScanBlock) void split_level_kernel(SplitArgs a, int32_t L, uint64_t* status,
+                                                                 uint32_t epoch) {
+  __shared__ ScanShared sh;
+  constexpr int32_t kNodes = kScanBlock / G;
+  const int32_t lo = a.ctl[2 * L], hi = a.ctl[2 * L + 1], tiles = (hi - lo + kNodes - 1) / kNodes;
+  if (tiles == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
     a.ctl[2 * L + 2] = hi;
-    a.ctl[2 * L + 3] = hi + total;
+    a.ctl[2 * L + 3] = hi;
   }
-  if (lo >= hi) return;
-  SPLIT_FOR(w, a.n) {
-    const int32_t x = a.trig[w];
-    if (x < 0 || a.qpos[w] >= 0 || a.lvl[x] != L) continue;
-    // x's children this level are exactly the y with trig[y] == x
-    int32_t r = 0;
-    for (int32_t t = a.ptr[x]; t < a.ptr[x + 1]; ++t) {
-      const int32_t y = a.adj[t];
-      if (y >= w) break;
-      r += a.trig[y] == x ? 1 : 0;
+  for (;;) {
+    if (tiles <= (int32_t)blockIdx.x) break;   // no tile can be left for this block
+    const int32_t tile = take_tile(a.ctl + kCtlTicket + L, 0, sh);
+    if (tile >= tiles) break;
+    const int32_t p = lo + tile * kNodes + (int32_t)threadIdx.x / G;
+    const int32_t u = p < hi ? a.queue[p] : -1;
+    uint64_t hit;
+    const int32_t c = count_children<G>(a, u, p, hit);
+    const bool lead = ((int32_t)threadIdx.x & (G - 1)) == 0;
+    int32_t end;
+    int32_t at = hi + device_excl_scan(lead ? c : 0, status, epoch, tile, sh, end);
+    if (G > 1) at = __shfl(at, (int32_t)(threadIdx.x & 63u) & ~(G - 1), 64);
+    if (c) write_children<G>(a, u, p, hit, at);
+    if (tile == tiles - 1 && threadIdx.x == 0) {
+      a.ctl[2 * L + 2] = hi;
+      a.ctl[2 * L + 3] = hi + end;
     }
-    const int32_t p = hi + off[a.qpos[x] - lo] + r;
-    if (p >= a.n) continue;   // cannot happen: positions are a permutation
-    a.queue[p] = w;
-    a.qpos[w] = p;
-    a.lvl[w] = L + 1;
   }
 }
 
-// Exclusive prefix of x over the workgroup (16 waves); `total` = the sum.
-__device__ __forceinline__ int32_t wg_excl_scan(int32_t x, int32_t* wsum, int32_t& total) {
-  const int32_t lane = (int32_t)(threadIdx.x & 63u), w = (int32_t)(threadIdx.x >> 6);
-  int32_t incl = x;
-#pragma unroll
-  for (int off = 1; off < 64; off <<= 1) {
-    const int32_t t = __shfl_up(incl, off, 64);
-    if (lane >= off) incl += t;
-  }
-  if (lane == 63) wsum[w] = incl;
-  __syncthreads();
-  int32_t before = 0, tot = 0;
-#pragma unroll
-  for (int i = 0; i < kSplitThreads / 64; ++i) {
-    const int32_t v = wsum[i];
-    before += i < w ? v : 0;
-    tot += v;
-  }
-  __syncthreads();   // wsum is reused by the next scan
-  total = tot;
-  return before + incl - x;
-}
-
-// The remaining levels on one workgroup, from level kWideLevels + 1.
+// The remaining levels on one workgroup.
 __global__ __launch_bounds__(kSplitThreads) void split_peel_kernel(SplitArgs a) {
   __shared__ int32_t wsum[kSplitThreads / 64];
-  __shared__ int32_t ncand;
-  const int32_t tid = (int32_t)threadIdx.x, T = kSplitThreads, n = a.n;
-  const int32_t* __restrict__ ptr = a.ptr;
-  const int32_t* __restrict__ adj = a.adj;
+  constexpr int32_t G = 8, kNodes = kSplitThreads / G;
   int32_t lo = a.ctl[2 * (kWideLevels + 1)], hi = a.ctl[2 * (kWideLevels + 1) + 1];
-  for (int32_t L = kWideLevels + 1; lo < hi; ++L) {
-    // candidates: the unqueued neighbours of level L, each listed once
-    if (tid == 0) ncand = 0;
-    __syncthreads();
-    for (int32_t i = lo + tid; i < hi; i += T) {
-      const int32_t u = a.queue[i];
-      for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
-        const int32_t w = adj[t];
-        if (a.qpos[w] < 0 && atomicMax(a.stamp + w, L) < L) a.cand[atomicAdd(&ncand, 1)] = w;
-      }
-    }
-    __syncthreads();
-    const int32_t nc = ncand;
-    // trigger of each candidate in level L, or -1
-    for (int32_t j = tid; j < nc; j += T) {
-      const int32_t w = a.cand[j];
-      const int32_t t0 = ptr[w], t1 = ptr[w + 1];
-      const int32_t need = t1 - t0 - a.k + 1;
-      int32_t before = 0, at = 0;
-      for (int32_t t = t0; t < t1; ++t) {
-        const int32_t l = a.lvl[adj[t]];
-        before += l >= 0 && l < L ? 1 : 0;
-        at += l == L ? 1 : 0;
-      }
-      int32_t tr = -1;
-      if (before + at >= need) {
-        const int32_t rank = need - before - 1;   // among level-L neighbours by queue position
-        for (int32_t t = t0; t < t1 && tr < 0; ++t) {
-          const int32_t x = adj[t];
-          if (a.lvl[x] != L) continue;
-          const int32_t px = a.qpos[x];
-          int32_t r = 0;
-          for (int32_t q = t0; q < t1; ++q) {
-            const int32_t y = adj[q];
-            r += a.lvl[y] == L && a.qpos[y] < px ? 1 : 0;
-          }
-          if (r == rank) tr = x;
-        }
-      }
-      a.trig[w] = tr;
-    }
-    __syncthreads();
-    // level L+1: each level-L node in queue order appends the nodes it
-    // triggered, in its ascending list order
+  while (lo < hi) {
     int32_t next = hi;
-    for (int32_t base = lo; base < hi; base += T) {
-      const int32_t i = base + tid;
-      const int32_t u = i < hi ? a.queue[i] : -1;
-      int32_t c = 0;
-      if (u >= 0)
-        for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
-          const int32_t w = adj[t];
-          c += a.qpos[w] < 0 && a.trig[w] == u ? 1 : 0;
-        }
+    for (int32_t base = lo; base < hi; base += kNodes) {
+      const int32_t p = base + (int32_t)threadIdx.x / G;
+      const int32_t u = p < hi ? a.queue[p] : -1;
+      uint64_t hit;
+      const int32_t c = count_children<G>(a, u, p, hit);
+      const bool lead = ((int32_t)threadIdx.x & (G - 1)) == 0;
       int32_t total;
-      int32_t pos = next + wg_excl_scan(c, wsum, total);
-      if (c)
-        for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
-          const int32_t w = adj[t];
-          if (a.qpos[w] < 0 && a.trig[w] == u && pos < n) {
-            a.queue[pos] = w;
-            a.qpos[w] = pos;
-            a.lvl[w] = L + 1;
-            ++pos;
-          }
-        }
+      int32_t at = next + block_excl_scan<kSplitThreads>(lead ? c : 0, wsum, total);
+      at = __shfl(at, (int32_t)(threadIdx.x & 63u) & ~(G - 1), 64);
+      if (c) write_children<G>(a, u, p, hit, at);
       next += total;
     }
-    __syncthreads();
+    __syncthreads();   // the next level reads what this one wrote
     lo = hi;
     hi = next;
   }
-  if (tid == 0) a.counts[0] = hi;
+  if (threadIdx.x == 0) a.counts[0] = hi;
 }
 
 __device__ __forceinline__ int32_t ld_agent(const int32_t* p) {
@@ -497,24 +451,14 @@ __device__ int32_t uf_find(int32_t* parent, int32_t x) {
   }
 }
 
-// Union-find start; the candidate stamps and triggers of the peeling are
-// reset for the BFS of the big components.
-__global__ __launch_bounds__(256) void uf_init_kernel(SplitArgs a) {
-  SPLIT_FOR(v, a.n) {
-    a.parent[v] = a.lvl[v] < 0 ? v : -1;
-    a.stamp[v] = -1;
-    a.trig[v] = -1;
-  }
-}
-
 // Hooks the larger of two roots under the smaller; a failed CAS means that
 // root was just hooked elsewhere: find again.
 __global__ __launch_bounds__(256) void uf_unite_kernel(SplitArgs a) {
   SPLIT_FOR(v, a.n) {
-    if (a.lvl[v] >= 0) continue;
+    if (a.qpos[v] >= 0) continue;
     for (int32_t t = a.ptr[v]; t < a.ptr[v + 1]; ++t) {
       const int32_t w = a.adj[t];
-      if (w < v || a.lvl[w] >= 0) continue;
+      if (w < v || a.qpos[w] >= 0) continue;
       for (;;) {
         const int32_t ra = uf_find(a.parent, v), rb = uf_find(a.parent, w);
         if (ra == rb) break;
@@ -525,18 +469,40 @@ __global__ __launch_bounds__(256) void uf_unite_kernel(SplitArgs a) {
   }
 }
 
-// Every core node's root (read-only walks: the forest is final here) and
-// the root flags to be numbered.
-__global__ __launch_bounds__(256) void uf_root_kernel(SplitArgs a) {
-  SPLIT_FOR(v, a.n) {
+// Every core node's root (read-only walks: the forest is final here), the
+// roots numbered in id order.
+__global__ __launch_bounds__(kScanBlock) void uf_root_kernel(SplitArgs a, int32_t* ticket, uint32_t ticket_base,
+                                                             uint64_t* status, uint32_t epoch) {
+  __shared__ ScanShared sh;
+  const int32_t tile = take_tile(ticket, ticket_base, sh);
+  // a thread's nodes are kScanBlock apart: neighbouring threads read
+  // neighbouring parents, and the tile's order is kept by its rounds
+  int32_t carry = 0;
+  int32_t num[kScanItems];
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j) {
+    const int64_t v = (int64_t)tile * kScanTile + j * kScanBlock + threadIdx.x;
     int32_t r = -1;
-    if (a.lvl[v] < 0) {
-      r = v;
+    if (v < a.n && a.qpos[v] < 0) {
+      r = (int32_t)v;
       for (int32_t p = a.parent[r]; p != r; p = a.parent[r]) r = p;
     }
-    a.root[v] = r;
-    a.rflag[v] = r == v ? 1 : 0;
+    if (v < a.n) a.root[v] = r;
+    const int32_t flag = v < a.n && r == (int32_t)v ? 1 : 0;
+    int32_t total;
+    const int32_t ex = block_excl_scan<kScanBlock>(flag, sh.wsum, total);
+    num[j] = flag ? carry + ex : -1;
+    carry += total;
   }
+  if (threadIdx.x < 64) {
+    const int32_t p = look_back(status, epoch, tile, carry);
+    if (threadIdx.x == 0) sh.prefix = p;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j)
+    if (num[j] >= 0) a.cid[(int64_t)tile * kScanTile + j * kScanBlock + threadIdx.x] = sh.prefix + num[j];
+  if (tile == (int32_t)gridDim.x - 1 && threadIdx.x == 0) a.cid[a.n] = sh.prefix + carry;
 }
 
 // Component of every core node (roots numbered in id order), its size, and
@@ -644,7 +610,7 @@ __global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
     const int32_t c = base + tid;
     const int32_t big = c < ncomp && a.comp_ptr[c + 1] - a.comp_ptr[c] > 64 ? 1 : 0;
     int32_t total;
-    const int32_t ex = wg_excl_scan(big, wsum, total);
+    const int32_t ex = block_excl_scan<kSplitThreads>(big, wsum, total);
     if (big) {
       const int32_t r = a.parent[c];
       F[fn + ex] = r;
@@ -662,7 +628,7 @@ __global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
       const int32_t u = F[i];
       for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
         const int32_t w = adj[t];
-        if (a.lvl[w] < 0 && a.local[w] < 0 && atomicMax(a.stamp + w, d) < d)
+        if (a.qpos[w] < 0 && a.local[w] < 0 && atomicMax(a.stamp + w, d) < d)
           a.cand[atomicAdd(&ncand, 1)] = w;
       }
     }
@@ -676,7 +642,7 @@ __global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
       for (int32_t t = ptr[w]; t < ptr[w + 1]; ++t) {
         const int32_t x = adj[t];
         const int32_t p = a.local[x];
-        if (a.lvl[x] < 0 && p >= 0 && p < bp) {
+        if (a.qpos[x] < 0 && p >= 0 && p < bp) {
           bp = p;
           best = x;
         }
@@ -692,10 +658,10 @@ __global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
       if (u >= 0)
         for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
           const int32_t w = adj[t];
-          c += a.lvl[w] < 0 && a.local[w] < 0 && a.trig[w] == u ? 1 : 0;
+          c += a.qpos[w] < 0 && a.local[w] < 0 && a.trig[w] == u ? 1 : 0;
         }
       int32_t total;
-      const int32_t ex = carry + wg_excl_scan(c, wsum, total);
+      const int32_t ex = carry + block_excl_scan<kSplitThreads>(c, wsum, total);
       if (u >= 0) {
         a.gex[i] = ex;
         a.cnt[i] = c;
@@ -711,7 +677,7 @@ __global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
       int32_t p = a.tail[cu] + a.gex[i] - a.cbase[cu], g = a.gex[i];
       for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
         const int32_t w = adj[t];
-        if (a.lvl[w] < 0 && a.local[w] < 0 && a.trig[w] == u && g < a.n &&
+        if (a.qpos[w] < 0 && a.local[w] < 0 && a.trig[w] == u && g < a.n &&
             a.comp_ptr[cu] + p < a.comp_ptr[cu + 1]) {
           a.local[w] = p;
           a.order[a.comp_ptr[cu] + p] = w;
@@ -757,22 +723,41 @@ GraphBuilder* graph_builder_create(mpld_context* ctx, bool own_stream) {
 void graph_builder_destroy(GraphBuilder* gb) { delete gb; }
 
 
+// What a scanning launch of `tiles` tiles works with: the ticket and the
+// value it starts from, the tiles' words and the launch's epoch.
+struct ScanArgs {
+  int32_t* ticket;
+  uint32_t base;
+  uint64_t* status;
+  uint32_t epoch;
+};
+
+// tickets: how many the launch takes (one a block), 0 when it has its own.
+static ScanArgs scan_args(GraphBuilder& gb, int64_t tiles, int64_t tickets) {
+  const size_t bytes = 64 + 8 * (size_t)tiles;
+  if (gb.tiles.bytes < bytes || gb.epoch >= (1u << 30) - 1) {
+    grow(gb.tiles, gb.ctx, bytes);
+    gb.epoch = 0;
+    gb.tickets = 0;
+    hipLaunchKernelGGL(fill_i32_kernel, dim3(256), dim3(256), 0, gb.stream, gb.tiles.as<int32_t>(),
+                       (int64_t)(gb.tiles.bytes / 4), 0);
+  }
+  ScanArgs a{gb.tiles.as<int32_t>(), gb.tickets, gb.tiles.as<uint64_t>() + 8, ++gb.epoch};
+  gb.tickets += (uint32_t)tickets;
+  return a;
+}
+
 void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
-  const int64_t ntiles = (n + kScanTile - 1) / kScanTile;
-  grow(gb.sums, gb.ctx, sizeof(int32_t) * (size_t)(ntiles + 1));
-  grow(gb.offs, gb.ctx, sizeof(int32_t) * (size_t)(ntiles + 1));
-  hipStream_t s = gb.stream;
-  hipLaunchKernelGGL(scan_sums_kernel, dim3((unsigned)ntiles), dim3(kScanBlock), 0, s, in, n,
-                     gb.sums.as<int32_t>());
-  hipLaunchKernelGGL(scan_tiles_kernel, dim3(1), dim3(kScanBlock), 0, s, gb.sums.as<int32_t>(),
-                     ntiles, gb.offs.as<int32_t>());
-  hipLaunchKernelGGL(scan_apply_kernel, dim3((unsigned)ntiles), dim3(kScanBlock), 0, s, in, n,
-                     gb.offs.as<int32_t>(), ntiles, out);
+  const int64_t tiles = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
+  const ScanArgs sa = scan_args(gb, tiles, tiles);
+  hipLaunchKernelGGL(scan_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, gb.stream, in, n, out, sa.ticket,
+                     sa.base, sa.status, sa.epoch);
   check_hip(hipGetLastError(), "graph builder: scan");
 }
 
 SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                        int32_t k, bool simplify, int32_t* out, int32_t* scratch_at) {
+                        int32_t k, bool simplify, int32_t* out, int32_t* scratch_at, const int32_t* fault,
+                        int32_t* ptr_w) {
   const size_t nn = (size_t)n;
   SplitArgs a{};
   a.n = n;
@@ -788,11 +773,9 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
   a.local = a.comp_ptr + nn + 1;
   const size_t stride = split_scratch_words(n) / kSplitScratch;
   int32_t* q = scratch_at;
-  int32_t** scratch[kSplitScratch] = {&a.f0,   &a.pos0,  &a.cnt0, &a.off0,  &a.qpos,  &a.lvl,
-                                      &a.stamp, &a.trig,  &a.cand, &a.parent, &a.root, &a.rflag,
-                                      &a.cid,  &a.csize, &a.fill, &a.list,  &a.rank,  &a.fa,
-                                      &a.fb,   &a.gex,   &a.cnt,  &a.cbase, &a.tail,
-                                      &a.cntA, &a.cntB,  &a.offL, &a.ctl};
+  int32_t** scratch[kSplitScratch] = {&a.qpos, &a.stamp, &a.trig, &a.cand,  &a.parent, &a.root, &a.cid,
+                                      &a.csize, &a.fill, &a.list, &a.rank,  &a.fa,     &a.fb,   &a.gex,
+                                      &a.cnt,  &a.cbase, &a.tail, &a.ctl};
   for (int32_t** d : scratch) {
     *d = q;
     q += stride;
@@ -802,23 +785,25 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
   auto wide = [&](void (*kern)(SplitArgs)) {
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), 0, st, a);
   };
-  wide(split_init_kernel);
-  scan(gb, a.f0, n, a.pos0);            // level-0 positions; pos0[n] = |level 0|
-  wide(split_level0_kernel);
-  scan(gb, a.cnt0, n, a.off0);          // level-1 offsets per level-0 position
-  wide(split_level1_kernel);
-  for (int32_t L = 1; L <= kWideLevels; ++L) {
-    int32_t* cur = (L & 1) ? a.cntA : a.cntB;
-    int32_t* nxt = (L & 1) ? a.cntB : a.cntA;
-    hipLaunchKernelGGL(split_trig_kernel, dim3(grid), dim3(256), 0, st, a, L, cur);
-    scan(gb, cur, n, a.offL);
-    hipLaunchKernelGGL(split_place_kernel, dim3(grid), dim3(256), 0, st, a, L, a.offL, nxt);
+  const int64_t tiles = (n + kScanTile - 1) / kScanTile;
+  hipLaunchKernelGGL(split_init_kernel, dim3(grid), dim3(256), 0, st, a, fault, ptr_w);
+  ScanArgs sa = scan_args(gb, tiles, tiles);
+  hipLaunchKernelGGL(split_seed_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, st, a, sa.ticket, sa.base,
+                     sa.status, sa.epoch);
+  for (int32_t L = 0; simplify && L <= kWideLevels; ++L) {
+    const int64_t most = L == 0 ? (n + kScanBlock - 1) / kScanBlock : (n + 31) / 32;
+    sa = scan_args(gb, most, 0);
+    const dim3 lg((unsigned)std::min<int64_t>(most, kLevelGrid));
+    if (L == 0)
+      hipLaunchKernelGGL(split_level_kernel<1>, lg, dim3(kScanBlock), 0, st, a, L, sa.status, sa.epoch);
+    else
+      hipLaunchKernelGGL(split_level_kernel<8>, lg, dim3(kScanBlock), 0, st, a, L, sa.status, sa.epoch);
   }
   hipLaunchKernelGGL(split_peel_kernel, dim3(1), dim3(kSplitThreads), 0, st, a);
-  wide(uf_init_kernel);
   wide(uf_unite_kernel);
-  wide(uf_root_kernel);
-  scan(gb, a.rflag, n, a.cid);          // component ids; cid[n] = components
+  sa = scan_args(gb, tiles, tiles);     // component ids; cid[n] = components
+  hipLaunchKernelGGL(uf_root_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, st, a, sa.ticket, sa.base,
+                     sa.status, sa.epoch);
   wide(comp_kernel);
   scan(gb, a.csize, n, a.comp_ptr);
   wide(comp_list_kernel);
@@ -833,7 +818,7 @@ static void enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, cons
                           int32_t k, bool simplify) {
   grow(gb.split_ws, gb.ctx, sizeof(int32_t) * (split_out_words(n) + split_scratch_words(n)));
   int32_t* w = gb.split_ws.as<int32_t>();
-  enqueue_split(gb, n, dptr, dadj, k, simplify, w, w + split_out_words(n));
+  enqueue_split(gb, n, dptr, dadj, k, simplify, w, w + split_out_words(n), nullptr, nullptr);
 }
 
 // Split from the copied-back words of split_ws.
@@ -866,9 +851,7 @@ void graph_builder_reserve(GraphBuilder& gb, int32_t nodes) {
   for (DevBuf* b : {&gb.cnt, &gb.start, &gb.fill}) grow(*b, ctx, 4 * (cells + 1));
   for (DevBuf* b : {&gb.deg, &gb.ptr}) grow(*b, ctx, 4 * (n + 1));
   grow(gb.adj, ctx, 4 * adj);
-  const size_t tiles = (cells + kScanTile - 1) / kScanTile + 1;
-  grow(gb.sums, ctx, 4 * tiles);
-  grow(gb.offs, ctx, 4 * tiles);
+  (void)scan_args(gb, (int64_t)std::max(cells / kScanTile, n / 32) + 1, 0);
   grow(gb.split_ws, ctx, 4 * (split_out_words((int64_t)n) + split_scratch_words((int64_t)n)));
   if (!grow_pinned(gb.hin, 20 * n + 4 * (n + 1 + adj)) ||
       !grow_pinned(gb.hout, 4 * (n + 1 + adj + split_out_words((int64_t)n))))
