@@ -151,20 +151,10 @@ int32_t mpld_build_graph_device(mpld_context* ctx, const mpld_rect* rects, int32
     *out = nullptr;
     use_device(ctx);
     if (!ctx->graph_builder) ctx->graph_builder = graph_builder_create(ctx, false);
-    Graph g;
-    std::vector<int32_t> se;
-    build_layout_graph_device(*ctx->graph_builder, rects, n, dmin_nm, split_len_nm, g, &se);
-    auto* og = new mpld_owned_graph();
-    og->g.num_nodes = g.n;
-    og->g.se.swap(se);
-    og->g.ce.reserve((size_t)g.num_ce * 2);
-    for (int32_t a = 0; a < g.n; ++a)
-      for (int64_t t = g.ptr[a]; t < g.ptr[a + 1]; ++t)
-        if (g.adj[t] > a) {
-          og->g.ce.push_back(a);
-          og->g.ce.push_back(g.adj[t]);
-        }
-    *out = og;
+    std::unique_ptr<mpld_owned_graph> og(new mpld_owned_graph());
+    og->from_device = true;
+    build_layout_pairs_device(*ctx->graph_builder, rects, n, dmin_nm, split_len_nm, og->d);
+    *out = og.release();
   });
 }
 
@@ -177,6 +167,13 @@ int32_t mpld_split_graph_device(mpld_context* ctx, const mpld_graph* g, int32_t 
     if (k < 2 || k > MPLD_MAX_K) fail(MPLD_E_INVALID, "k outside [2, MPLD_MAX_K]");
     use_device(ctx);
     if (!ctx->graph_builder) ctx->graph_builder = graph_builder_create(ctx, false);
+    FlowGraph f;
+    if (flow_build(f, *ctx->graph_builder, *g, k, flags & MPLD_SIMPLIFY)) {
+      flow_split_out(f, *ctx->graph_builder, removal_order, comp_of, bfs_order, comp_ptr);
+      *num_removed = f.removed;
+      *num_comps = f.ncomp;
+      return;
+    }
     const Graph gr = make_graph(*g);
     Split s;
     split_graph_device(*ctx->graph_builder, gr, k, flags & MPLD_SIMPLIFY, s);
@@ -192,8 +189,16 @@ int32_t mpld_split_graph_device(mpld_context* ctx, const mpld_graph* g, int32_t 
 int32_t mpld_owned_graph_view(const mpld_owned_graph* g, mpld_graph* view) {
   return guard([&] {
     if (!g || !view) fail(MPLD_E_INVALID, "NULL argument");
-    view->num_nodes = g->g.num_nodes;
     view->reserved = 0;
+    if (g->from_device) {
+      view->num_nodes = g->d.num_nodes;
+      view->num_ce = g->d.num_ce;
+      view->ce = g->d.ce.get();
+      view->num_se = g->d.num_se;
+      view->se = g->d.ce ? g->d.ce.get() + 2 * g->d.num_ce : nullptr;
+      return;
+    }
+    view->num_nodes = g->g.num_nodes;
     view->num_ce = (int64_t)g->g.ce.size() / 2;
     view->ce = g->g.ce.data();
     view->num_se = (int64_t)g->g.se.size() / 2;

@@ -614,6 +614,31 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_op
   return true;
 }
 
+FlowGraph::~FlowGraph() {
+  if (keep.p && keep.ctx) (void)hipStreamSynchronize(keep.ctx->stream);
+}
+
+void flow_split_out(FlowGraph& f, GraphBuilder& gb, int32_t* removal, int32_t* comp_of, int32_t* order,
+                    int32_t* comp_ptr) {
+  std::lock_guard<std::mutex> lk(gb.mu);
+  hipStream_t st = gb.stream;
+  const size_t nn = (size_t)f.n, nrem = (size_t)f.removed, nptr = (size_t)f.ncomp + 1;
+  if (!grow_pinned(gb.hout, 4 * (2 * nn + nptr))) fail(MPLD_E_NOMEM, "layout flow: pinned host memory");
+  int32_t* h = gb.hout.as<int32_t>();
+  auto down = [&](int32_t* to, const int32_t* p, size_t count) {
+    if (count) check_hip(hipMemcpyAsync(to, p, 4 * count, hipMemcpyDeviceToHost, st), "layout flow: split");
+  };
+  down(h, f.comp_of, nn);
+  down(h + nn, f.queue, nrem);
+  down(h + nn + nrem, f.order, nn - nrem);
+  down(h + 2 * nn, f.comp_ptr, nptr);
+  check_hip(hipStreamSynchronize(st), "layout flow: split");
+  std::memcpy(comp_of, h, 4 * nn);
+  std::memcpy(removal, h + nn, 4 * nrem);
+  std::memcpy(order, h + nn + nrem, 4 * (nn - nrem));
+  std::memcpy(comp_ptr, h + 2 * nn, 4 * nptr);
+}
+
 void flow_to_host(FlowGraph& f, hipStream_t st, Graph& g, Split& s) {
   const size_t nn = (size_t)f.n;
   std::vector<int32_t> ptr(nn + 1);

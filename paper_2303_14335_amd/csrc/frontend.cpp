@@ -237,6 +237,11 @@ void prepare_layout(const mpld_rect* rects, int32_t n, int32_t dmin, int32_t spl
     maxy = std::max<int64_t>(maxy, r.y0);
     ext = std::max<int64_t>(ext, std::max<int64_t>((int64_t)r.x1 - r.x0, (int64_t)r.y1 - r.y0));
   }
+  layout_grid(minx, miny, maxx, maxy, ext, nn, dmin, lp);
+}
+
+void layout_grid(int64_t minx, int64_t miny, int64_t maxx, int64_t maxy, int64_t ext, int32_t nn,
+                 int32_t dmin, LayoutPrep& lp) {
   // cells of side > largest extent + d_min: every conflict pair has its
   // lower-left corners in the same or adjacent cells
   int64_t cell = ext + dmin + 1;

@@ -18,7 +18,7 @@ struct GraphBuilder {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::mutex mu;
-  DevBuf box, partner, cell_of, cnt, start, fill, ids, sbox, smate, deg, ptr, adj;
+  DevBuf rects, box, partner, se, cell_of, cnt, start, sbox, sid, kept, deg, ptr, adj;
   DevBuf tiles;            // scans: the ticket, then a word per tile
   uint32_t epoch = 0, tickets = 0;   // launches so far, tickets they took
   DevBuf split_ws;   // split outputs then scratch (int32)

@@ -2,18 +2,18 @@
 // features closer than d_min) built on the device, for requests large
 // enough that the host's pair search dominates their front-end latency.
 //
-// The host validates the rectangles, applies the midpoint stitch split and
-// picks the search grid (prepare_layout, shared with the host builder); the
-// device then
-//   1. counts the nodes per grid cell (atomics), scans the counts into cell
-//      starts, and scatters node ids and boxes into cell order;
-//   2. gives every node one thread that tests the nodes of its 3x3 cell
+// The host copies the rectangles in; the device then
+//   1. validates them, applies the midpoint stitch split (a scan gives the
+//      nodes' ids) and takes the bounds, from which the host picks the search
+//      grid;
+//   2. counts the nodes per grid cell (atomics), scans the counts into cell
+//      starts, and scatters ids and boxes into cell order;
+//   3. gives every node one thread that tests the nodes of its 3x3 cell
 //      neighbourhood (three contiguous runs of the cell order) with the
 //      closed-box gap test, skipping its own stitch partner, and counts its
-//      neighbours; a scan of the counts gives the CSR row offsets;
-//   3. repeats the test writing the neighbour ids, and sorts each node's
-//      list in place (lists are short: the graph is a unit-disk-like
-//      geometric graph).
+//      neighbours; a scan of the counts gives the row offsets;
+//   4. writes the neighbour ids, each node's list sorted in place (lists are
+//      short: the graph is a unit-disk-like geometric graph).
 // The result is the CSR the rest of the front-end consumes: adjacency
 // ascending per node, symmetric, no self loops or duplicates by
 // construction.
@@ -41,21 +41,6 @@ __global__ __launch_bounds__(256) void fill_i32_kernel(int32_t* __restrict__ p, 
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
     p[i] = v;
-}
-
-__device__ __forceinline__ int32_t cell_index(const int4 b, const GridParams& g) {
-  const int64_t cx = ((int64_t)b.x - g.minx) / g.cell, cy = ((int64_t)b.y - g.miny) / g.cell;
-  return (int32_t)(cy * g.gx + cx);
-}
-
-__global__ __launch_bounds__(256) void cell_count_kernel(const int4* __restrict__ box, int32_t nn,
-                                                         GridParams g, int32_t* __restrict__ cell_of,
-                                                         int32_t* __restrict__ cnt) {
-  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= nn) return;
-  const int32_t c = cell_index(box[i], g);
-  cell_of[i] = c;
-  atomicAdd(&cnt[c], 1);
 }
 
 // ---- scans --------------------------------------------------------------------
@@ -182,69 +167,203 @@ __global__ __launch_bounds__(kScanBlock) void scan_kernel(const int32_t* __restr
   if (tile == (int32_t)gridDim.x - 1 && threadIdx.x == 0) out[n] = end;
 }
 
-__global__ __launch_bounds__(256) void cell_scatter_kernel(const int4* __restrict__ box,
-                                                           const int32_t* __restrict__ partner,
-                                                           int32_t nn,
-                                                           const int32_t* __restrict__ cell_of,
-                                                           int32_t* __restrict__ fill,
-                                                           int32_t* __restrict__ ids,
-                                                           int4* __restrict__ sbox,
-                                                           int32_t* __restrict__ smate) {
-  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (i >= nn) return;
-  const int32_t pos = atomicAdd(&fill[cell_of[i]], 1);
-  ids[pos] = i;
-  sbox[pos] = box[i];
-  smate[pos] = partner[i];
+// ---- the layout graph ---------------------------------------------------------
+
+struct LayoutHead {
+  int32_t bad, splits;                     // a box with x1 < x0 or y1 < y0; rectangles cut in two
+  int32_t minx, miny, maxx, maxy;          // of the nodes' lower-left corners
+  uint32_t ext;                            // largest side
+  int32_t pad;
+};
+
+// Rectangles to nodes, as prepare_layout on the host: a rectangle whose long
+// side exceeds split_len becomes two nodes, cut at floor(L / 2), lower or left
+// first; a node's id is its rectangle's plus the cuts before it.  The bounds
+// for the search grid on the way.
+__global__ __launch_bounds__(kScanBlock) void layout_nodes_kernel(const int4* __restrict__ rects, int32_t n,
+                                                                  int32_t split_len, int4* __restrict__ box,
+                                                                  int32_t* __restrict__ partner,
+                                                                  int2* __restrict__ se, LayoutHead* head,
+                                                                  int32_t* ticket, uint32_t ticket_base,
+                                                                  uint64_t* status, uint32_t epoch) {
+  __shared__ ScanShared sh;
+  const int32_t tile = take_tile(ticket, ticket_base, sh);
+  const int64_t base = (int64_t)tile * kScanTile + (int64_t)threadIdx.x * kScanItems;
+  uint32_t cut = 0;
+  bool bad = false;
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j)
+    if (base + j < n) {
+      const int4 r = rects[base + j];
+      bad |= r.z < r.x || r.w < r.y;
+      const int32_t len = max((int32_t)((uint32_t)r.z - (uint32_t)r.x), (int32_t)((uint32_t)r.w - (uint32_t)r.y));
+      if (split_len > 0 && len > split_len) cut |= 1u << j;
+    }
+  int32_t end;
+  int32_t before = device_excl_scan(__builtin_popcount(cut), status, epoch, tile, sh, end);
+  int32_t minx = INT32_MAX, miny = INT32_MAX, maxx = INT32_MIN, maxy = INT32_MIN;
+  uint32_t ext = 0;
+  auto put = [&](int32_t id, const int4 r, int32_t mate) {
+    box[id] = r;
+    partner[id] = mate;
+    minx = min(minx, r.x);
+    miny = min(miny, r.y);
+    maxx = max(maxx, r.x);
+    maxy = max(maxy, r.y);
+    ext = max(ext, max((uint32_t)r.z - (uint32_t)r.x, (uint32_t)r.w - (uint32_t)r.y));
+  };
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j)
+    if (base + j < n) {
+      const int4 r = rects[base + j];
+      const int32_t id = (int32_t)(base + j) + before;
+      if ((cut >> j) & 1u) {
+        const int32_t w = (int32_t)((uint32_t)r.z - (uint32_t)r.x), h = (int32_t)((uint32_t)r.w - (uint32_t)r.y);
+        int4 lo = r, up = r;
+        if (w >= h) up.x = lo.z = r.x + max(w, h) / 2;
+        else up.y = lo.w = r.y + max(w, h) / 2;
+        put(id, lo, id + 1);
+        put(id + 1, up, id);
+        se[before++] = int2{id, id + 1};
+      } else {
+        put(id, r, -1);
+      }
+    }
+  for (int off = 32; off > 0; off >>= 1) {
+    minx = min(minx, __shfl_xor(minx, off, 64));
+    miny = min(miny, __shfl_xor(miny, off, 64));
+    maxx = max(maxx, __shfl_xor(maxx, off, 64));
+    maxy = max(maxy, __shfl_xor(maxy, off, 64));
+    ext = max(ext, (uint32_t)__shfl_xor((int)ext, off, 64));
+  }
+  const bool any_bad = __ballot(bad) != 0ull;
+  if ((threadIdx.x & 63) == 0) {
+    if (any_bad) atomicOr(&head->bad, 1);
+    atomicMin(&head->minx, minx);
+    atomicMin(&head->miny, miny);
+    atomicMax(&head->maxx, maxx);
+    atomicMax(&head->maxy, maxy);
+    atomicMax(&head->ext, ext);
+  }
+  if (tile == (int32_t)gridDim.x - 1 && threadIdx.x == 0) head->splits = end;
 }
 
-// One thread per node (cell order): test the 3x3 cell neighbourhood.  WRITE
-// = false counts the neighbours into deg[id]; WRITE = true writes them at
-// adj[ptr[id]] and sorts the list.
-template <bool WRITE>
-__global__ __launch_bounds__(256) void neighbours_kernel(
-    const int4* __restrict__ sbox, const int32_t* __restrict__ ids,
-    const int32_t* __restrict__ smate, const int32_t* __restrict__ start, int32_t nn,
-    GridParams g, int64_t d2, int32_t* __restrict__ deg, const int32_t* __restrict__ ptr,
-    int32_t* __restrict__ adj) {
-  const int32_t p = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (p >= nn) return;
+__global__ void layout_head_kernel(LayoutHead* head) {
+  *head = LayoutHead{0, 0, INT32_MAX, INT32_MAX, INT32_MIN, INT32_MIN, 0, 0};
+}
+
+// Nodes per cell; a node's place within its cell is the count it found.
+__global__ __launch_bounds__(256) void cell_count_kernel(const int4* __restrict__ box, int32_t nn,
+                                                         GridParams g, int2* __restrict__ cell_of,
+                                                         int32_t* __restrict__ cnt) {
+  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= nn) return;
+  const int4 b = box[i];
+  const int64_t cx = ((int64_t)b.x - g.minx) / g.cell, cy = ((int64_t)b.y - g.miny) / g.cell;
+  const int32_t c = (int32_t)(cy * g.gx + cx);
+  cell_of[i] = int2{c, atomicAdd(&cnt[c], 1)};
+}
+
+// Boxes, ids and stitch partners in cell order ({id, partner, cell}: one
+// 16-byte word).
+__global__ __launch_bounds__(256) void cell_scatter_kernel(const int4* __restrict__ box,
+                                                           const int32_t* __restrict__ partner,
+                                                           int32_t nn, const int2* __restrict__ cell_of,
+                                                           const int32_t* __restrict__ start,
+                                                           int4* __restrict__ sbox, int4* __restrict__ sid) {
+  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (i >= nn) return;
+  const int2 c = cell_of[i];
+  const int32_t pos = start[c.x] + c.y;
+  sbox[pos] = box[i];
+  sid[pos] = int4{i, partner[i], c.x, 0};
+}
+
+// Tests the node at place p of the cell order against its 3x3 cell
+// neighbourhood: three contiguous runs of the cell order.  f(id) for every
+// conflict partner, in no order.
+template <class F>
+__device__ __forceinline__ void for_partners(const int4* __restrict__ sbox, const int4* __restrict__ sid,
+                                             const int32_t* __restrict__ start, int32_t p, const int4 me,
+                                             const GridParams& g, int64_t d2, F&& f) {
   const int4 a = sbox[p];
-  const int32_t id = ids[p], mate = smate[p];
-  const int64_t cx = ((int64_t)a.x - g.minx) / g.cell, cy = ((int64_t)a.y - g.miny) / g.cell;
-  const int64_t x0 = cx > 0 ? cx - 1 : 0, x1 = cx + 1 < g.gx ? cx + 1 : g.gx - 1;
-  const int64_t y0 = cy > 0 ? cy - 1 : 0, y1 = cy + 1 < g.gy ? cy + 1 : g.gy - 1;
-  int32_t k = 0;
-  int32_t* out = WRITE ? adj + ptr[id] : nullptr;
-  for (int64_t yy = y0; yy <= y1; ++yy) {
+  const int32_t cy = me.z / g.gx, cx = me.z - cy * g.gx;
+  const int32_t x0 = cx > 0 ? cx - 1 : 0, x1 = cx + 1 < g.gx ? cx + 1 : g.gx - 1;
+  const int32_t y0 = cy > 0 ? cy - 1 : 0, y1 = cy + 1 < g.gy ? cy + 1 : g.gy - 1;
+  for (int32_t yy = y0; yy <= y1; ++yy) {
     const int32_t q0 = start[yy * g.gx + x0], q1 = start[yy * g.gx + x1 + 1];
     for (int32_t q = q0; q < q1; ++q) {
-      if (q == p) continue;
       const int4 b = sbox[q];
       const int64_t dx = max(max((int64_t)0, (int64_t)b.x - a.z), (int64_t)a.x - b.z);
       const int64_t dy = max(max((int64_t)0, (int64_t)b.y - a.w), (int64_t)a.y - b.w);
-      if (dx * dx + dy * dy >= d2) continue;
-      const int32_t qid = ids[q];
-      if (qid == mate) continue;   // the two halves of a split feature
-      if (WRITE) out[k] = qid;
-      ++k;
-    }
-  }
-  if (!WRITE) {
-    deg[id] = k;
-  } else {
-    for (int32_t i = 1; i < k; ++i) {   // insertion sort of the short list
-      const int32_t x = out[i];
-      int32_t j = i - 1;
-      while (j >= 0 && out[j] > x) {
-        out[j + 1] = out[j];
-        --j;
-      }
-      out[j + 1] = x;
+      if (q == p || dx * dx + dy * dy >= d2) continue;
+      const int32_t id = sid[q].x;
+      if (id != me.y) f(id);   // not the other half of a split feature
     }
   }
 }
 
+// Neighbour lists up to this long stay in the scratch that the counting pass
+// writes them to; the writing pass searches again for longer ones only.
+// 16 entries hold every list of the sparse layouts (mean degree 1 to 3); the
+// second search of all nodes had made the writing pass 41 us at 296k nodes.
+static constexpr int kKeptNeighbours = 16;
+
+// One thread per node (cell order): counts its neighbours into deg[id], and
+// keeps the first ones (kept[j * nn + p]).  UP: only neighbours of larger id.
+template <bool UP>
+__global__ __launch_bounds__(256) void neighbour_count_kernel(
+    const int4* __restrict__ sbox, const int4* __restrict__ sid, const int32_t* __restrict__ start,
+    int32_t nn, GridParams g, int64_t d2, int32_t* __restrict__ deg, int32_t* __restrict__ kept) {
+  const int32_t p = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (p >= nn) return;
+  const int4 me = sid[p];
+  int32_t k = 0;
+  for_partners(sbox, sid, start, p, me, g, d2, [&](int32_t id) {
+    if (UP && id < me.x) return;
+    if (k < kKeptNeighbours) kept[(int64_t)k * nn + p] = id;
+    ++k;
+  });
+  deg[me.x] = k;
+}
+
+// Each node's list, ascending.  UP: as pairs (id, larger id); out then holds
+// two words an entry.
+template <bool UP>
+__global__ __launch_bounds__(256) void neighbour_write_kernel(
+    const int4* __restrict__ sbox, const int4* __restrict__ sid, const int32_t* __restrict__ start,
+    int32_t nn, GridParams g, int64_t d2, const int32_t* __restrict__ ptr,
+    const int32_t* __restrict__ kept, int32_t* __restrict__ out, int64_t room) {
+  const int32_t p = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (p >= nn) return;
+  const int4 me = sid[p];
+  const int64_t t0 = ptr[me.x];
+  const int32_t k = (int32_t)(ptr[me.x + 1] - t0);
+  if (k == 0 || t0 + k > room) return;   // no room: the host sees the total and asks again
+  constexpr int S = UP ? 2 : 1;
+  int32_t* list = out + S * t0 + (S - 1);
+  int32_t have = 0;
+  auto insert = [&](int32_t id) {   // insertion sort of the short list
+    int32_t j = have++;
+    for (; j > 0 && list[S * (j - 1)] > id; --j) list[S * j] = list[S * (j - 1)];
+    list[S * j] = id;
+  };
+  if (k <= kKeptNeighbours) {
+    for (int32_t i = 0; i < k; ++i) {
+      // the place of an entry is the number of smaller ones
+      const int32_t id = kept[(int64_t)i * nn + p];
+      int32_t r = 0;
+      for (int32_t j = 0; j < k; ++j) r += kept[(int64_t)j * nn + p] < id ? 1 : 0;
+      list[S * r] = id;
+    }
+  } else {
+    for_partners(sbox, sid, start, p, me, g, d2, [&](int32_t id) {
+      if (!UP || id > me.x) insert(id);
+    });
+  }
+  if (UP)
+    for (int32_t i = 0; i < k; ++i) list[2 * i - 1] = me.x;
+}
 
 // ---- simplification and sub-graph split ------------------------------------
 //
@@ -846,15 +965,18 @@ void graph_builder_reserve(GraphBuilder& gb, int32_t nodes) {
   std::lock_guard<std::mutex> lk(gb.mu);
   mpld_context* ctx = gb.ctx;
   const size_t n = (size_t)std::max(nodes, 1), cells = 4 * n, adj = 8 * n;
-  for (DevBuf* b : {&gb.partner, &gb.cell_of, &gb.ids, &gb.smate}) grow(*b, ctx, 4 * n);
-  for (DevBuf* b : {&gb.box, &gb.sbox}) grow(*b, ctx, 16 * n);
-  for (DevBuf* b : {&gb.cnt, &gb.start, &gb.fill}) grow(*b, ctx, 4 * (cells + 1));
+  grow(gb.rects, ctx, 16 * n + sizeof(LayoutHead));
+  for (DevBuf* b : {&gb.partner, &gb.se}) grow(*b, ctx, 4 * n);
+  grow(gb.cell_of, ctx, 8 * n);
+  for (DevBuf* b : {&gb.box, &gb.sbox, &gb.sid}) grow(*b, ctx, 16 * n);
+  for (DevBuf* b : {&gb.cnt, &gb.start}) grow(*b, ctx, 4 * (cells + 1));
+  grow(gb.kept, ctx, 4 * n * kKeptNeighbours);
   for (DevBuf* b : {&gb.deg, &gb.ptr}) grow(*b, ctx, 4 * (n + 1));
   grow(gb.adj, ctx, 4 * adj);
   (void)scan_args(gb, (int64_t)std::max(cells / kScanTile, n / 32) + 1, 0);
   grow(gb.split_ws, ctx, 4 * (split_out_words((int64_t)n) + split_scratch_words((int64_t)n)));
-  if (!grow_pinned(gb.hin, 20 * n + 4 * (n + 1 + adj)) ||
-      !grow_pinned(gb.hout, 4 * (n + 1 + adj + split_out_words((int64_t)n))))
+  if (!grow_pinned(gb.hin, 16 * n + 4 * (n + 1 + adj)) ||
+      !grow_pinned(gb.hout, 4 * (2 * n + 1 + adj + split_out_words((int64_t)n))))
     fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
 }
 
@@ -894,93 +1016,145 @@ void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simpli
   collect_split(gb.hout.as<int32_t>(), nn, s);
 }
 
-bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
-                               int32_t split_len, Graph& g, std::vector<int32_t>* se, Split* split,
-                               int32_t k, bool simplify) {
+// Nodes, stitch pairs and search grid of a layout, on the device, and its
+// nodes in cell order; waits once, for the grid's bounds.  Returns the number
+// of nodes.  Caller holds the lock.
+struct LayoutGrid {
+  GridParams g{};
+  int32_t nn = 0, nse = 0;
+  int64_t d2 = 0;
+};
+static LayoutGrid layout_cells(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
+                               int32_t split_len) {
+  mpld_context* ctx = gb.ctx;
+  hipStream_t s = gb.stream;
+  check_hip(hipSetDevice(ctx->device), "hipSetDevice");
+  if (2 * (int64_t)n >= INT32_MAX)
+    fail(MPLD_E_INVALID, "layout too large for the device graph builder");
+  const size_t nr = (size_t)n, most = nr * (split_len > 0 ? 2 : 1);
+  grow(gb.rects, ctx, sizeof(int4) * nr + sizeof(LayoutHead));
+  grow(gb.box, ctx, sizeof(int4) * most);
+  grow(gb.partner, ctx, sizeof(int32_t) * most);
+  grow(gb.se, ctx, sizeof(int32_t) * most);
+  if (!grow_pinned(gb.hin, sizeof(int4) * nr) || !grow_pinned(gb.hout, sizeof(LayoutHead)))
+    fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+  auto* head = gb.rects.as<LayoutHead>();
+  auto* drects = reinterpret_cast<int4*>(gb.rects.as<uint8_t>() + sizeof(LayoutHead));
+  hipLaunchKernelGGL(layout_head_kernel, dim3(1), dim3(1), 0, s, head);
+  std::memcpy(gb.hin.p, rects, sizeof(int4) * nr);
+  check_hip(hipMemcpyAsync(drects, gb.hin.p, sizeof(int4) * nr, hipMemcpyHostToDevice, s),
+            "graph builder: upload rectangles");
+  const int64_t tiles = (n + kScanTile - 1) / kScanTile;
+  const ScanArgs sa = scan_args(gb, tiles, tiles);
+  hipLaunchKernelGGL(layout_nodes_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, drects, n, split_len,
+                     gb.box.as<int4>(), gb.partner.as<int32_t>(), gb.se.as<int2>(), head, sa.ticket, sa.base,
+                     sa.status, sa.epoch);
+  check_hip(hipGetLastError(), "graph builder: nodes");
+  check_hip(hipMemcpyAsync(gb.hout.p, head, sizeof(LayoutHead), hipMemcpyDeviceToHost, s),
+            "graph builder: bounds");
+  check_hip(hipStreamSynchronize(s), "graph builder: bounds");
+  LayoutHead h;
+  std::memcpy(&h, gb.hout.p, sizeof(h));
+  if (h.bad) {   // the host names the rectangle
+    LayoutPrep lp;
+    prepare_layout(rects, n, dmin, split_len, lp);
+    fail(MPLD_E_INTERNAL, "the device refused a layout that the host takes");
+  }
+  LayoutGrid out;
+  if (2 * ((int64_t)n + h.splits) >= INT32_MAX)
+    fail(MPLD_E_INVALID, "layout too large for the device graph builder");
+  out.nn = n + h.splits;
+  out.nse = h.splits;
+  out.d2 = (int64_t)dmin * dmin;
   LayoutPrep lp;
-  prepare_layout(rects, n, dmin, split_len, lp);
-  const int32_t nn = (int32_t)lp.nd.size();
+  layout_grid(h.minx, h.miny, h.maxx, h.maxy, std::max<int64_t>(1, h.ext), out.nn, dmin, lp);
+  const int64_t ncell = lp.gx * lp.gy;
+  if (ncell >= INT32_MAX) fail(MPLD_E_INVALID, "layout too large for the device graph builder");
+  const GridParams g{lp.minx, lp.miny, lp.cell, (int32_t)lp.gx, (int32_t)lp.gy};
+  out.g = g;
+  const int32_t nn = out.nn;
+  const size_t nb = (size_t)nn;
+  grow(gb.cell_of, ctx, sizeof(int2) * nb);
+  grow(gb.cnt, ctx, sizeof(int32_t) * (size_t)(ncell + 1));
+  grow(gb.start, ctx, sizeof(int32_t) * (size_t)(ncell + 1));
+  grow(gb.sbox, ctx, sizeof(int4) * nb);
+  grow(gb.sid, ctx, sizeof(int4) * nb);
+  grow(gb.kept, ctx, sizeof(int32_t) * nb * kKeptNeighbours);
+  grow(gb.deg, ctx, sizeof(int32_t) * (nb + 1));
+  grow(gb.ptr, ctx, sizeof(int32_t) * (nb + 1));
+  const dim3 blocks((unsigned)((nn + 255) / 256));
+  const unsigned cblocks = (unsigned)std::min<int64_t>((ncell + 255) / 256, 4096);
+  hipLaunchKernelGGL(fill_i32_kernel, dim3(cblocks), dim3(256), 0, s, gb.cnt.as<int32_t>(), ncell, 0);
+  hipLaunchKernelGGL(cell_count_kernel, blocks, dim3(256), 0, s, gb.box.as<int4>(), nn, g,
+                     gb.cell_of.as<int2>(), gb.cnt.as<int32_t>());
+  scan(gb, gb.cnt.as<int32_t>(), ncell, gb.start.as<int32_t>());
+  hipLaunchKernelGGL(cell_scatter_kernel, blocks, dim3(256), 0, s, gb.box.as<int4>(),
+                     gb.partner.as<int32_t>(), nn, gb.cell_of.as<int2>(), gb.start.as<int32_t>(),
+                     gb.sbox.as<int4>(), gb.sid.as<int4>());
+  check_hip(hipGetLastError(), "graph builder: cells");
+  return out;
+}
+
+// Neighbour lists (CSR, or with UP the pairs of smaller and larger id) of the
+// nodes in cell order: offsets in gb.ptr, lists in gb.adj; waits for their
+// total, which it returns.
+template <bool UP>
+static int32_t layout_lists(GraphBuilder& gb, const LayoutGrid& L) {
+  hipStream_t s = gb.stream;
+  const dim3 blocks((unsigned)((L.nn + 255) / 256));
+  constexpr int64_t kWords = UP ? 2 : 1;
+  hipLaunchKernelGGL(neighbour_count_kernel<UP>, blocks, dim3(256), 0, s, gb.sbox.as<int4>(), gb.sid.as<int4>(),
+                     gb.start.as<int32_t>(), L.nn, L.g, L.d2, gb.deg.as<int32_t>(), gb.kept.as<int32_t>());
+  scan(gb, gb.deg.as<int32_t>(), L.nn, gb.ptr.as<int32_t>());
+  int32_t total = 0;
+  check_hip(hipMemcpyAsync(gb.hout.p, gb.ptr.as<int32_t>() + L.nn, sizeof(int32_t), hipMemcpyDeviceToHost, s),
+            "graph builder: edge total");
+  // the lists go where the last layouts' went while the total is on its way;
+  // a longer one is written again once its room is known
+  for (int pass = 0; pass < 2; ++pass) {
+    const int64_t room = (int64_t)(gb.adj.bytes / (4 * kWords));
+    if (room > 0)
+      hipLaunchKernelGGL(neighbour_write_kernel<UP>, blocks, dim3(256), 0, s, gb.sbox.as<int4>(),
+                         gb.sid.as<int4>(), gb.start.as<int32_t>(), L.nn, L.g, L.d2, gb.ptr.as<int32_t>(),
+                         gb.kept.as<int32_t>(), gb.adj.as<int32_t>(), room);
+    check_hip(hipGetLastError(), "graph builder: neighbours");
+    if (pass == 0) {
+      check_hip(hipStreamSynchronize(s), "graph builder: counts");
+      std::memcpy(&total, gb.hout.p, sizeof(total));
+      if (total <= room) break;
+      grow(gb.adj, gb.ctx, 4 * (size_t)kWords * (size_t)total);
+    }
+  }
+  return total;
+}
+
+bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
+                               int32_t split_len, Graph& g, Split* split, int32_t k, bool simplify) {
   g = Graph();
-  g.n = nn;
-  g.partner = lp.partner;
-  g.ptr.assign((size_t)nn + 1, 0);
-  if (se) *se = lp.se;
-  if (nn == 0) {
+  if (n <= 0 || !rects || dmin < 0 || split_len < 0) {   // a fault, or nothing to do
+    LayoutPrep lp;
+    prepare_layout(rects, n, dmin, split_len, lp);
+    g.ptr.assign(1, 0);
     if (split) {
       *split = Split();
       split->comp_ptr.push_back(0);
     }
     return split != nullptr;
   }
-  const int64_t ncell = lp.gx * lp.gy;
-  if (ncell >= INT32_MAX || 2 * (int64_t)nn >= INT32_MAX)
-    fail(MPLD_E_INVALID, "layout too large for the device graph builder");
   std::lock_guard<std::mutex> lk(gb.mu);
-  mpld_context* ctx = gb.ctx;
+  const LayoutGrid L = layout_cells(gb, rects, n, dmin, split_len);
   hipStream_t s = gb.stream;
-  check_hip(hipSetDevice(ctx->device), "hipSetDevice");
-  GridParams gp{lp.minx, lp.miny, lp.cell, (int32_t)lp.gx, (int32_t)lp.gy};
+  const int32_t nn = L.nn;
   const size_t nb = (size_t)nn;
-  grow(gb.box, ctx, sizeof(int4) * nb);
-  grow(gb.partner, ctx, sizeof(int32_t) * nb);
-  grow(gb.cell_of, ctx, sizeof(int32_t) * nb);
-  grow(gb.cnt, ctx, sizeof(int32_t) * (size_t)(ncell + 1));
-  grow(gb.start, ctx, sizeof(int32_t) * (size_t)(ncell + 1));
-  grow(gb.fill, ctx, sizeof(int32_t) * (size_t)(ncell + 1));
-  grow(gb.ids, ctx, sizeof(int32_t) * nb);
-  grow(gb.sbox, ctx, sizeof(int4) * nb);
-  grow(gb.smate, ctx, sizeof(int32_t) * nb);
-  grow(gb.deg, ctx, sizeof(int32_t) * (nb + 1));
-  grow(gb.ptr, ctx, sizeof(int32_t) * (nb + 1));
-  // boxes and partners in one pinned staging copy
-  const size_t in_bytes = sizeof(int4) * nb + sizeof(int32_t) * nb;
-  if (!grow_pinned(gb.hin, in_bytes)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
-  std::memcpy(gb.hin.p, lp.nd.data(), sizeof(int4) * nb);
-  std::memcpy(static_cast<char*>(gb.hin.p) + sizeof(int4) * nb, lp.partner.data(),
-              sizeof(int32_t) * nb);
-  check_hip(hipMemcpyAsync(gb.box.p, gb.hin.p, sizeof(int4) * nb, hipMemcpyHostToDevice, s),
-            "graph builder: upload boxes");
-  check_hip(hipMemcpyAsync(gb.partner.p, static_cast<char*>(gb.hin.p) + sizeof(int4) * nb,
-                           sizeof(int32_t) * nb, hipMemcpyHostToDevice, s),
-            "graph builder: upload partners");
-  const unsigned blocks = (unsigned)((nn + 255) / 256);
-  const unsigned cblocks = (unsigned)std::min<int64_t>((ncell + 255) / 256, 4096);
-  hipLaunchKernelGGL(fill_i32_kernel, dim3(cblocks), dim3(256), 0, s, gb.cnt.as<int32_t>(), ncell, 0);
-  hipLaunchKernelGGL(cell_count_kernel, dim3(blocks), dim3(256), 0, s, gb.box.as<int4>(), nn, gp,
-                     gb.cell_of.as<int32_t>(), gb.cnt.as<int32_t>());
-  check_hip(hipGetLastError(), "graph builder: cell count");
-  scan(gb, gb.cnt.as<int32_t>(), ncell, gb.start.as<int32_t>());
-  check_hip(hipMemcpyAsync(gb.fill.p, gb.start.p, sizeof(int32_t) * (size_t)ncell,
-                           hipMemcpyDeviceToDevice, s),
-            "graph builder: cell fill positions");
-  hipLaunchKernelGGL(cell_scatter_kernel, dim3(blocks), dim3(256), 0, s, gb.box.as<int4>(),
-                     gb.partner.as<int32_t>(), nn, gb.cell_of.as<int32_t>(),
-                     gb.fill.as<int32_t>(), gb.ids.as<int32_t>(), gb.sbox.as<int4>(),
-                     gb.smate.as<int32_t>());
-  const int64_t d2 = (int64_t)dmin * dmin;
-  hipLaunchKernelGGL(neighbours_kernel<false>, dim3(blocks), dim3(256), 0, s, gb.sbox.as<int4>(),
-                     gb.ids.as<int32_t>(), gb.smate.as<int32_t>(), gb.start.as<int32_t>(), nn, gp,
-                     d2, gb.deg.as<int32_t>(), nullptr, nullptr);
-  check_hip(hipGetLastError(), "graph builder: neighbour counts");
-  scan(gb, gb.deg.as<int32_t>(), nn, gb.ptr.as<int32_t>());
-  // the edge total decides the adjacency size
-  int32_t total = 0;
-  check_hip(hipMemcpyAsync(&total, gb.ptr.as<int32_t>() + nn, sizeof(int32_t),
-                           hipMemcpyDeviceToHost, s),
-            "graph builder: edge total");
-  check_hip(hipStreamSynchronize(s), "graph builder: counts");
-  grow(gb.adj, ctx, sizeof(int32_t) * (size_t)std::max(total, 1));
-  hipLaunchKernelGGL(neighbours_kernel<true>, dim3(blocks), dim3(256), 0, s, gb.sbox.as<int4>(),
-                     gb.ids.as<int32_t>(), gb.smate.as<int32_t>(), gb.start.as<int32_t>(), nn, gp,
-                     d2, nullptr, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>());
-  check_hip(hipGetLastError(), "graph builder: neighbour lists");
+  const int32_t total = layout_lists<false>(gb, L);
   if (split && !device_split_pays(nn, total, k)) split = nullptr;   // the caller splits on the host
   if (split) enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), k, simplify);
   const size_t split_words = split ? split_out_words(nn) : 0;
-  const size_t out_bytes = sizeof(int32_t) * ((nb + 1) + (size_t)total + split_words);
+  const size_t out_bytes = sizeof(int32_t) * ((nb + 1) + nb + (size_t)total + split_words);
   if (!grow_pinned(gb.hout, out_bytes)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
   int32_t* hptr = static_cast<int32_t*>(gb.hout.p);
-  int32_t* hadj = hptr + nb + 1;
+  int32_t* hmate = hptr + nb + 1;
+  int32_t* hadj = hmate + nb;
   int32_t* hsplit = hadj + total;
   if (split)
     check_hip(hipMemcpyAsync(hsplit, gb.split_ws.p, sizeof(int32_t) * split_words,
@@ -988,16 +1162,47 @@ bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
               "graph builder: download split");
   check_hip(hipMemcpyAsync(hptr, gb.ptr.p, sizeof(int32_t) * (nb + 1), hipMemcpyDeviceToHost, s),
             "graph builder: download offsets");
+  check_hip(hipMemcpyAsync(hmate, gb.partner.p, sizeof(int32_t) * nb, hipMemcpyDeviceToHost, s),
+            "graph builder: download partners");
   if (total)
     check_hip(hipMemcpyAsync(hadj, gb.adj.p, sizeof(int32_t) * (size_t)total,
                              hipMemcpyDeviceToHost, s),
               "graph builder: download lists");
   check_hip(hipStreamSynchronize(s), "graph builder");
-  for (size_t i = 0; i <= nb; ++i) g.ptr[i] = hptr[i];
+  g.n = nn;
+  g.ptr.assign(hptr, hptr + nb + 1);
+  g.partner.assign(hmate, hmate + nb);
   g.adj.assign(hadj, hadj + total);
   g.num_ce = total / 2;
   if (split) collect_split(hsplit, nn, *split);
   return split != nullptr;
+}
+
+void build_layout_pairs_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
+                               int32_t split_len, DevicePairs& out) {
+  out = DevicePairs();
+  if (n <= 0 || !rects || dmin < 0 || split_len < 0) {   // a fault, or nothing to do
+    LayoutPrep lp;
+    prepare_layout(rects, n, dmin, split_len, lp);
+    return;
+  }
+  std::lock_guard<std::mutex> lk(gb.mu);
+  const LayoutGrid L = layout_cells(gb, rects, n, dmin, split_len);
+  hipStream_t s = gb.stream;
+  const size_t total = (size_t)layout_lists<true>(gb, L), nse = (size_t)L.nse;
+  if (!grow_pinned(gb.hout, 8 * (total + nse) + 8)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+  int32_t* h = gb.hout.as<int32_t>();
+  if (total)
+    check_hip(hipMemcpyAsync(h, gb.adj.p, 8 * total, hipMemcpyDeviceToHost, s), "graph builder: download pairs");
+  if (nse)
+    check_hip(hipMemcpyAsync(h + 2 * total, gb.se.p, 8 * nse, hipMemcpyDeviceToHost, s),
+              "graph builder: download stitch pairs");
+  out.num_nodes = L.nn;
+  out.num_ce = (int64_t)total;
+  out.num_se = (int64_t)nse;
+  out.ce.reset(new int32_t[2 * (total + nse) + 1]);
+  check_hip(hipStreamSynchronize(s), "graph builder");
+  std::memcpy(out.ce.get(), h, 8 * (total + nse));
 }
 
 }  // namespace mpld

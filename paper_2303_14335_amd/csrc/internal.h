@@ -3,6 +3,7 @@
 #pragma once
 
 #include <cstdint>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -78,12 +79,26 @@ struct LayoutPrep {
 void prepare_layout(const mpld_rect* rects, int32_t n, int32_t dmin, int32_t split_len,
                     LayoutPrep& lp);
 
+// The search grid from the nodes' bounds (lower-left corners, largest side).
+void layout_grid(int64_t minx, int64_t miny, int64_t maxx, int64_t maxy, int64_t ext, int32_t nodes,
+                 int32_t dmin, LayoutPrep& lp);
+
+// Pairs of a device-built graph: num_ce conflict pairs, then num_se stitch
+// pairs, in one array that is not cleared before it is filled.
+struct DevicePairs {
+  int32_t num_nodes = 0;
+  int64_t num_ce = 0, num_se = 0;
+  std::unique_ptr<int32_t[]> ce;
+};
+
 int host_threads();
 
 }  // namespace mpld
 
 struct mpld_owned_graph {
   mpld::OwnedGraph g;
+  mpld::DevicePairs d;   // of a device-built graph, instead of g
+  bool from_device = false;
 };
 
 struct mpld_result {

@@ -323,6 +323,7 @@ struct FlowGraph {
           *order = nullptr, *comp_ptr = nullptr, *local = nullptr;
   int32_t *cpre = nullptr, *cmax = nullptr;   // core degrees' prefix over `order`; largest per component
   std::vector<FlowComp> comps;
+  ~FlowGraph();   // waits for the stream: its memory may be in use
 };
 struct GraphBuilder;
 // Validates and splits a caller's graph on the device.  False: the host path
@@ -335,6 +336,9 @@ void flow_pack(FlowGraph& f, DeviceBatch& db, hipStream_t st);
 // recovery was given up (nothing in *r): the host does it.
 bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_options& opt, DeviceBatch& db,
                   mpld_result* r);
+// The split in a caller's arrays (n, n, n, n + 1 entries; as many as it has are written); waits.
+void flow_split_out(FlowGraph& f, GraphBuilder& gb, int32_t* removal, int32_t* comp_of, int32_t* order,
+                    int32_t* comp_ptr);
 // The host forms of the graph and its split.
 void flow_to_host(FlowGraph& f, hipStream_t st, Graph& g, Split& s);
 
@@ -396,14 +400,16 @@ void graph_builder_destroy(GraphBuilder* gb);
 // Allocates the builder's device and pinned buffers for layouts of up to
 // about `nodes` nodes ahead of use (they still grow beyond).
 void graph_builder_reserve(GraphBuilder& gb, int32_t nodes);
-// Builds the CSR layout graph of `rects` on the device (the host's
-// prepare_layout first); se receives the stitch pairs when not null.  With
-// `split`, the simplification and sub-graph split (identical to
-// simplify_and_split(g, k, simplify)) run on the device too when
-// device_split_pays for the graph; returns whether *split was filled.
+// Builds the CSR layout graph of `rects` on the device.  With `split`, the
+// simplification and sub-graph split (identical to simplify_and_split(g, k,
+// simplify)) run on the device too when device_split_pays for the graph;
+// returns whether *split was filled.
 bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
-                               int32_t split_len, Graph& g, std::vector<int32_t>* se,
-                               Split* split = nullptr, int32_t k = 0, bool simplify = true);
+                               int32_t split_len, Graph& g, Split* split = nullptr, int32_t k = 0,
+                               bool simplify = true);
+// The same graph as pairs, u < v, sorted: conflict pairs, then stitch pairs.
+void build_layout_pairs_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
+                               int32_t split_len, DevicePairs& out);
 // simplify_and_split of a host graph, computed on the device.
 void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simplify, Split& s);
 // Whether the device split is worth it for a graph of n nodes with

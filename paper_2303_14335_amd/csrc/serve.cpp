@@ -105,10 +105,9 @@ void HipExecutor::front_end(Request* r) {
         GraphBuilder* gb = gbuilders[gb_next.fetch_add(1) % gbuilders.size()];
         if (device_split) {   // simplification and split behind the pair search
           split_done = build_layout_graph_device(*gb, r->rects.data(), nr, r->dmin, r->split, r->g,
-                                                 nullptr, &r->s, r->opt.k,
-                                                 r->opt.flags & MPLD_SIMPLIFY);
+                                                 &r->s, r->opt.k, r->opt.flags & MPLD_SIMPLIFY);
         } else {
-          build_layout_graph_device(*gb, r->rects.data(), nr, r->dmin, r->split, r->g, nullptr);
+          build_layout_graph_device(*gb, r->rects.data(), nr, r->dmin, r->split, r->g);
         }
         built = true;
       } else {

@@ -71,3 +71,37 @@ def test_invalid_rectangle_rejected(ctx):
     with pytest.raises(mp.MpldError) as e:
         mp.mpld_build_graph_device(ctx, np.array([[10, 0, 0, 5]], np.int32), 80, 0)
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("reach", [8, 15, 16, 17])
+@pytest.mark.parametrize("n", [2, 255, 256, 257, 2047, 2048, 2049, 5000])
+def test_list_and_tile_borders(ctx, n, reach):
+    """A row of squares, each in conflict with `reach` on either side: lists
+    around the kept length, node counts around the tiles; ids shuffled, every
+    third square long enough to be cut."""
+    say("device graph, row", n, reach)
+    rng = np.random.default_rng(n * 100 + reach)
+    x = np.arange(n)[rng.permutation(n)] * 10
+    h = np.where(rng.random(n) < 0.33, 9, 2)
+    r = np.stack([x, np.zeros(n), x, h], 1).astype(np.int32)
+    same_graph(ctx, r, 10 * reach + 1, 0)
+    same_graph(ctx, r, 10 * reach + 1, 5)
+
+
+@pytest.mark.parametrize("n,side,dmin", [(4096, 3800, 100), (4300, 2600, 120)])
+def test_served_dense_layouts(ctx, n, side, dmin):
+    """The full lists (both directions) of dense layouts, through a server."""
+    import paper_2303_14335_amd as mp
+    rects, _ = workload.generate(n, side, 5)
+    say("served dense layout", n, side, dmin)
+    og = oracle.build_graph(rects, dmin, 0)
+    ref = oracle.decompose(og, 3, 2000)
+    c = mp.Context(0)
+    try:
+        srv = mp.Server(c)
+        got = srv.wait(srv.submit_layout(rects, dmin, 0, 3, 2000))
+        srv.close()
+    finally:
+        c.close()
+    assert np.array_equal(got.colors, ref.colors) and np.array_equal(got.component_of, ref.comp_of)
+    assert np.array_equal(got.components["nodes"], ref.comps["nodes"])
