@@ -50,11 +50,14 @@ void check_options(const mpld_options* opt) {
   if (opt->min_budget < 0) fail(MPLD_E_INVALID, "min_budget must be >= 0 (0 = 10000)");
 }
 
-// Graphs of at least this many nodes go through the device's flow: some 35
-// launches, about 0.25 ms, whatever the size.  Host against device: 3000 nodes
-// at k = 3 0.39 / 0.53 ms, 6000 0.66 / 0.67, 8000 0.78 / 0.68, 32000 2.05 / 0.89;
-// at k = 4 with stitches (1.5 nodes a rectangle) 6000 rectangles 1.42 / 1.26.
-constexpr int32_t kFlowMinNodes = 6144;
+// Graphs of at least this many nodes and pairs together go through the
+// device's flow: some 35 launches, 0.25 ms whatever the size, where the host's
+// passes take time in proportion to both.  Host against device, ms: k = 3,
+// 3000 nodes and 3300 pairs 0.39 / 0.45, 5000 and 5500 0.57 / 0.58, 8000 and
+// 8700 0.76 / 0.61, 32000 and 35000 2.05 / 0.86; k = 4 with stitches, 5900 and
+// 6600 0.69 / 0.69, 11800 and 13200 1.49 / 1.20; packed windows, 700 and 7400
+// 0.54 / 0.57, 2000 and 21000 1.2 / 0.6, 8000 and 85000 3.4 / 0.85.
+constexpr int64_t kFlowMinSize = 11000;
 
 void use_device(mpld_context* ctx) {
   if (!ctx) fail(MPLD_E_INVALID, "context is NULL");
@@ -69,9 +72,9 @@ void batch_build(mpld_context* ctx, const mpld_graph* g, const mpld_options* opt
   b->ctx = ctx;
   b->opt = *opt;
   const bool simplify = opt->flags & MPLD_SIMPLIFY;
-  // large sparse graphs are validated, simplified, split and packed on the
+  // large graphs are validated, simplified, split and packed on the
   // device (identical results)
-  if (g->num_nodes >= kFlowMinNodes && device_split_pays(g->num_nodes, 2 * g->num_ce, opt->k)) {
+  if ((int64_t)g->num_nodes + g->num_ce >= kFlowMinSize) {
     if (!ctx->graph_builder) ctx->graph_builder = graph_builder_create(ctx, false);
     (void)flow_build(b->flow, *ctx->graph_builder, *g, opt->k, simplify);
   }

@@ -52,26 +52,26 @@ struct SplitArgs {
   int32_t* order;       // n: core nodes by component, local order
   int32_t* comp_ptr;    // n + 1
   int32_t* local;       // n: local index, -1 if removed
-  // scratch: n + 1 each
-  int32_t *qpos, *stamp, *trig, *cand, *parent, *root, *cid, *csize, *fill, *list, *rank, *fa, *fb,
-      *gex, *cnt, *cbase, *tail;
+  // scratch: n + 1 each (mids, bigs, giants: components of more than 64 nodes;
+  // words: the giants' scans)
+  int32_t *qpos, *parent, *root, *cid, *csize, *fill, *list, *rank, *mids, *bigs, *giants, *words;
   int32_t* ctl;         // the peeling's level ranges and tickets
 };
 
 // int32 words of the split's outputs (counts (2), queue, comp_of, order (n
 // each), comp_ptr (n + 1), local (n)) and of its scratch.
 inline size_t split_out_words(int64_t n) { return 2 + 5 * (size_t)n + 1; }
-constexpr int kSplitScratch = 18;
+constexpr int kSplitScratch = 13;
 inline size_t split_scratch_words(int64_t n) {   // ctl needs up to 64
   return kSplitScratch * std::max<size_t>((size_t)n + 1, 64);
 }
 
 // Enqueues the split of the CSR at dptr / dadj (device, int32) on the
 // builder's stream, outputs at `out`; no host synchronisation.  Returns the
-// addresses it used.  fault (may be null): a device word that, nonzero, makes
+// addresses it used.  adj_entries: about how many dadj holds.  fault (may be null): a device word that, nonzero, makes
 // the graph one without pairs (dptr, as ptr_w, is cleared).
 SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                        int32_t k, bool simplify, int32_t* out, int32_t* scratch, const int32_t* fault,
+                        int64_t adj_entries, int32_t k, bool simplify, int32_t* out, int32_t* scratch, const int32_t* fault,
                         int32_t* ptr_w);
 
 }  // namespace mpld

@@ -390,10 +390,17 @@ __global__ __launch_bounds__(256) void neighbour_write_kernel(
 // under the smaller (so each root is its component's smallest id), numbered
 // by root id with a scan.  BFS: one wave per component of at most 64 nodes
 // (ranks by id, neighbour masks over the ranks, the queue kept in a lane
-// register); larger components on one workgroup, level by level, a node's
-// parent being its numbered neighbour of smallest local position.
+// register), a workgroup per larger component, several for the largest.
 constexpr int kSplitThreads = 1024;   // the one-workgroup kernels
 constexpr int kSplitGrid = 2048;      // grid-stride kernels: blocks of 256
+// BFS of the components above 64 nodes: those above kGiantNodes by several
+// workgroups, one component after another, the others by one workgroup each;
+// those above kBigNodes by several too where there are no more than kFewBigs
+// (dense components of 2000 and 4000 nodes: 0.3 against 0.9 and 1.2 ms).
+constexpr int kMidThreads = 512;
+constexpr int kMidGrid = 512;
+constexpr int32_t kBigNodes = 512, kFewBigs = 3, kGiantNodes = 4096;
+constexpr int kGiantBlocks = 128;
 constexpr int kLevelGrid = 1024;      // level kernels: blocks of 256 taking tiles by ticket
 
 // Levels 1 .. kWideLevels are found by launches over the device.
@@ -401,7 +408,11 @@ constexpr int kWideLevels = 5;
 // SplitArgs.ctl: [2L], [2L + 1] the queue range of level L, [kCtlTicket + L]
 // the ticket of the launch that pops level L.
 constexpr int kCtlTicket = 2 * (kWideLevels + 2);
-constexpr int kCtlWords = kCtlTicket + kWideLevels + 2;
+// ... then the lengths of the lists of larger components, and the meetings of
+// the workgroups that number the largest.
+constexpr int kCtlMids = kCtlTicket + kWideLevels + 2, kCtlBigs = kCtlMids + 1, kCtlGiants = kCtlMids + 2,
+              kCtlMeet = kCtlMids + 3, kCtlLost = kCtlMids + 4;
+constexpr int kCtlWords = kCtlMids + 5;
 static_assert(kCtlWords <= 64, "ctl is 64 words at least");
 
 #define SPLIT_FOR(v, n)                                                                 \
@@ -422,8 +433,7 @@ __global__ __launch_bounds__(256) void split_init_kernel(SplitArgs a, const int3
     a.fill[v] = 0;
     a.qpos[v] = -1;
     a.parent[v] = v;
-    a.stamp[v] = -1;
-    a.trig[v] = -1;
+    a.words[v] = 0;
     a.local[v] = -1;
     a.comp_of[v] = -1;
   }
@@ -460,39 +470,59 @@ __device__ __forceinline__ bool queues(const SplitArgs& a, int32_t w, int32_t p)
   return r == want;
 }
 
-// The children of one node per group of G lanes (the lanes share its list,
-// chunk by chunk).  `hit` keeps the first 64 neighbours' answers.
-template <int G>
-__device__ __forceinline__ int32_t count_children(const SplitArgs& a, int32_t u, int32_t p, uint64_t& hit) {
+// One node per group of G lanes, which share its list chunk by chunk: how
+// many neighbours w have test(w) (every lane of the group gets it), then
+// put(w, place) for them in list order from place `at` on.  `hit` keeps the
+// first 64 neighbours' answers.
+template <int G, class F>
+__device__ __forceinline__ int32_t group_count(const SplitArgs& a, int32_t u, uint64_t& hit, F&& test) {
   const int32_t j = (int32_t)threadIdx.x & (G - 1), shift = (int32_t)(threadIdx.x & 63u) - j;
   const int32_t t0 = u >= 0 ? a.ptr[u] : 0, t1 = u >= 0 ? a.ptr[u + 1] : 0;
   int32_t c = 0;
   hit = 0;
   for (int32_t t = t0, ch = 0; t < t1; t += G, ch += G) {
-    const bool h = t + j < t1 && queues(a, a.adj[t + j], p);
+    const bool h = t + j < t1 && test(a.adj[t + j]);
     const uint64_t b = (__ballot(h) >> shift) & ((1ull << G) - 1);
     c += __builtin_popcountll(b);
     if (ch < 64) hit |= b << ch;
   }
   return c;
 }
-template <int G>
-__device__ __forceinline__ void write_children(const SplitArgs& a, int32_t u, int32_t p, uint64_t hit, int32_t at) {
+template <int G, class F, class P>
+__device__ __forceinline__ void group_put(const SplitArgs& a, int32_t u, uint64_t hit, int32_t at, F&& test, P&& put) {
   const int32_t j = (int32_t)threadIdx.x & (G - 1), shift = (int32_t)(threadIdx.x & 63u) - j;
   const int32_t t0 = a.ptr[u], t1 = a.ptr[u + 1];
   for (int32_t t = t0, ch = 0; t < t1; t += G, ch += G) {
     uint64_t b = (hit >> (ch & 63)) & ((1ull << G) - 1);
-    if (ch >= 64)
-      b = (__ballot(t + j < t1 && queues(a, a.adj[t + j], p)) >> shift) & ((1ull << G) - 1);
-    if ((b >> j) & 1u) {
-      const int32_t w = a.adj[t + j], q = at + __builtin_popcountll(b & ((1ull << j) - 1));
-      if (q < a.n) {   // always: places are a permutation
-        a.queue[q] = w;
-        a.qpos[w] = q;
-      }
-    }
+    if (ch >= 64) b = (__ballot(t + j < t1 && test(a.adj[t + j])) >> shift) & ((1ull << G) - 1);
+    if ((b >> j) & 1u) put(a.adj[t + j], at + __builtin_popcountll(b & ((1ull << j) - 1)));
     at += __builtin_popcountll(b);
   }
+}
+// `at` of the group's first lane.
+template <int G>
+__device__ __forceinline__ int32_t of_group(int32_t at) {
+  return G > 1 ? __shfl(at, (int32_t)(threadIdx.x & 63u) & ~(G - 1), 64) : at;
+}
+template <int G>
+__device__ __forceinline__ bool leads_group() {
+  return ((int32_t)threadIdx.x & (G - 1)) == 0;
+}
+
+// The children of the node at place p, and their places.
+template <int G>
+__device__ __forceinline__ int32_t count_children(const SplitArgs& a, int32_t u, int32_t p, uint64_t& hit) {
+  return group_count<G>(a, u, hit, [&](int32_t w) { return queues(a, w, p); });
+}
+template <int G>
+__device__ __forceinline__ void write_children(const SplitArgs& a, int32_t u, int32_t p, uint64_t hit, int32_t at) {
+  group_put<G>(a, u, hit, at, [&](int32_t w) { return queues(a, w, p); },
+               [&](int32_t w, int32_t q) {
+                 if (q < a.n) {   // always: places are a permutation
+                   a.queue[q] = w;
+                   a.qpos[w] = q;
+                 }
+               });
 }
 
 // Pops level L: level L + 1 behind it.  Groups of G lanes share a node (one
@@ -515,10 +545,9 @@ __global__ __launch_bounds__(kScanBlock) void split_level_kernel(SplitArgs a, in
     const int32_t u = p < hi ? a.queue[p] : -1;
     uint64_t hit;
     const int32_t c = count_children<G>(a, u, p, hit);
-    const bool lead = ((int32_t)threadIdx.x & (G - 1)) == 0;
     int32_t end;
-    int32_t at = hi + device_excl_scan(lead ? c : 0, status, epoch, tile, sh, end);
-    if (G > 1) at = __shfl(at, (int32_t)(threadIdx.x & 63u) & ~(G - 1), 64);
+    const int32_t at =
+        of_group<G>(hi + device_excl_scan(leads_group<G>() ? c : 0, status, epoch, tile, sh, end));
     if (c) write_children<G>(a, u, p, hit, at);
     if (tile == tiles - 1 && threadIdx.x == 0) {
       a.ctl[2 * L + 2] = hi;
@@ -539,10 +568,9 @@ __global__ __launch_bounds__(kSplitThreads) void split_peel_kernel(SplitArgs a) 
       const int32_t u = p < hi ? a.queue[p] : -1;
       uint64_t hit;
       const int32_t c = count_children<G>(a, u, p, hit);
-      const bool lead = ((int32_t)threadIdx.x & (G - 1)) == 0;
       int32_t total;
-      int32_t at = next + block_excl_scan<kSplitThreads>(lead ? c : 0, wsum, total);
-      at = __shfl(at, (int32_t)(threadIdx.x & 63u) & ~(G - 1), 64);
+      const int32_t at =
+          of_group<G>(next + block_excl_scan<kSplitThreads>(leads_group<G>() ? c : 0, wsum, total));
       if (c) write_children<G>(a, u, p, hit, at);
       next += total;
     }
@@ -571,11 +599,17 @@ __device__ int32_t uf_find(int32_t* parent, int32_t x) {
 }
 
 // Hooks the larger of two roots under the smaller; a failed CAS means that
-// root was just hooked elsewhere: find again.
+// root was just hooked elsewhere: find again.  G lanes share a node's list:
+// 4 on sparse graphs, where the time is each node's chain of loads (24 us with
+// one lane on 296k nodes of 2.5 neighbours); one on dense graphs, whose pairs
+// soon all ask for the same few roots' words (872k entries over one component
+// took 0.17 ms with one lane a node, 1.7 ms with 16).
+template <int G>
 __global__ __launch_bounds__(256) void uf_unite_kernel(SplitArgs a) {
-  SPLIT_FOR(v, a.n) {
+  const int32_t groups = (int32_t)(gridDim.x * blockDim.x) / G;
+  for (int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x) / G; v < a.n; v += groups) {
     if (a.qpos[v] >= 0) continue;
-    for (int32_t t = a.ptr[v]; t < a.ptr[v + 1]; ++t) {
+    for (int32_t t = a.ptr[v] + ((int32_t)threadIdx.x & (G - 1)); t < a.ptr[v + 1]; t += G) {
       const int32_t w = a.adj[t];
       if (w < v || a.qpos[w] >= 0) continue;
       for (;;) {
@@ -601,7 +635,7 @@ __global__ __launch_bounds__(kScanBlock) void uf_root_kernel(SplitArgs a, int32_
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
     const int64_t v = (int64_t)tile * kScanTile + j * kScanBlock + threadIdx.x;
-    int32_t r = -1;
+    int32_t r = -1;   // (removed nodes have no parent)
     if (v < a.n && a.qpos[v] < 0) {
       r = (int32_t)v;
       for (int32_t p = a.parent[r]; p != r; p = a.parent[r]) r = p;
@@ -625,7 +659,8 @@ __global__ __launch_bounds__(kScanBlock) void uf_root_kernel(SplitArgs a, int32_
 }
 
 // Component of every core node (roots numbered in id order), its size, and
-// the root of every component.
+// the root of every component.  A wave whose nodes are all of one component
+// adds them at once: a component of 40k nodes is one address.
 __global__ __launch_bounds__(256) void comp_kernel(SplitArgs a) {
   SPLIT_FOR(v, a.n) {
     const int32_t r = a.root[v];
@@ -633,16 +668,32 @@ __global__ __launch_bounds__(256) void comp_kernel(SplitArgs a) {
     const int32_t c = a.cid[r];
     a.comp_of[v] = c;
     if (r == v) a.parent[c] = v;   // parent[] is free now: root of component c
-    atomicAdd(a.csize + c, 1);
+    const uint64_t active = __ballot(true);
+    if (__ballot(c == __builtin_amdgcn_readfirstlane(c)) == active) {
+      if ((threadIdx.x & 63u) == (unsigned)__builtin_ctzll(active))
+        atomicAdd(a.csize + c, __builtin_popcountll(active));
+    } else {
+      atomicAdd(a.csize + c, 1);
+    }
   }
 }
 
-// Core nodes listed per component (any order within it).
+// Core nodes of the components of at most 64 nodes listed per component (any
+// order within it); the larger components in two lists, by who numbers them.
 __global__ __launch_bounds__(256) void comp_list_kernel(SplitArgs a) {
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[1] = a.cid[a.n];
   SPLIT_FOR(v, a.n) {
     const int32_t c = a.comp_of[v];
     if (c < 0) continue;
-    a.list[a.comp_ptr[c] + atomicAdd(a.fill + c, 1)] = v;
+    const int32_t base = a.comp_ptr[c], sz = a.comp_ptr[c + 1] - base;
+    if (sz <= 64)
+      a.list[base + atomicAdd(a.fill + c, 1)] = v;
+    else if (a.root[v] == v && sz <= kBigNodes)
+      a.mids[atomicAdd(a.ctl + kCtlMids, 1)] = c;
+    else if (a.root[v] == v && sz <= kGiantNodes)
+      a.bigs[atomicAdd(a.ctl + kCtlBigs, 1)] = c;
+    else if (a.root[v] == v)
+      a.giants[atomicAdd(a.ctl + kCtlGiants, 1)] = c;
   }
 }
 
@@ -712,112 +763,137 @@ __global__ __launch_bounds__(256) void bfs_small_kernel(SplitArgs a) {
   }
 }
 
-// BFS numbering of the components of more than 64 nodes, on one workgroup,
-// all of them at once; the frontier stays ordered by (component, position).
-__global__ __launch_bounds__(kSplitThreads) void bfs_big_kernel(SplitArgs a) {
-  __shared__ int32_t wsum[kSplitThreads / 64];
-  __shared__ int32_t ncand;
-  const int32_t tid = (int32_t)threadIdx.x, T = kSplitThreads;
-  const int32_t* __restrict__ ptr = a.ptr;
-  const int32_t* __restrict__ adj = a.adj;
-  const int32_t ncomp = a.cid[a.n];
-  int32_t* F = a.fa;
-  int32_t* NF = a.fb;
-  // the roots of the big components, in component order
-  int32_t fn = 0;
-  for (int32_t base = 0; base < ncomp; base += T) {
-    const int32_t c = base + tid;
-    const int32_t big = c < ncomp && a.comp_ptr[c + 1] - a.comp_ptr[c] > 64 ? 1 : 0;
-    int32_t total;
-    const int32_t ex = block_excl_scan<kSplitThreads>(big, wsum, total);
-    if (big) {
-      const int32_t r = a.parent[c];
-      F[fn + ex] = r;
-      a.local[r] = 0;
-      a.order[a.comp_ptr[c]] = r;
-      a.tail[c] = 1;
+// BFS numbering of larger components.  As in the peeling, no levels are
+// marked: the node u at position p numbers its unnumbered neighbour w exactly
+// when no neighbour of w has a position before p, positions given meanwhile
+// being behind p.  A level of the queue is counted, scanned and written.
+// AGENT: positions are written and read across workgroups.
+template <bool AGENT>
+__device__ __forceinline__ int32_t ld_local(const SplitArgs& a, int32_t v) {
+  return AGENT ? ld_agent(a.local + v) : a.local[v];
+}
+template <bool AGENT>
+__device__ __forceinline__ bool numbers(const SplitArgs& a, int32_t w, int32_t p) {
+  const int32_t gone = a.qpos[w], at = ld_local<AGENT>(a, w), t0 = a.ptr[w], t1 = a.ptr[w + 1];
+  bool before = gone >= 0 || (uint32_t)at <= (uint32_t)p;   // removed, or numbered by then
+  if (before) return false;
+#pragma unroll 4
+  for (int32_t t = t0; t < t1; ++t) before |= (uint32_t)ld_local<AGENT>(a, a.adj[t]) < (uint32_t)p;
+  return !before;
+}
+
+// A workgroup each.
+__global__ __launch_bounds__(kMidThreads) void bfs_mid_kernel(SplitArgs a) {
+  __shared__ int32_t wsum[kMidThreads / 64];
+  constexpr int32_t G = 8, kNodes = kMidThreads / G;
+  const int32_t mids = a.ctl[kCtlMids], bigs = a.ctl[kCtlBigs];
+  const int32_t first = bigs > kFewBigs ? bigs : 0;   // the larger ones first
+  for (int32_t i = (int32_t)blockIdx.x; i < first + mids; i += (int32_t)gridDim.x) {
+    const int32_t c = i < first ? a.bigs[i] : a.mids[i - first], sz = a.comp_ptr[c + 1] - a.comp_ptr[c];
+    int32_t* order = a.order + a.comp_ptr[c];
+    if (threadIdx.x == 0) {
+      order[0] = a.parent[c];
+      a.local[a.parent[c]] = 0;
     }
-    fn += total;
+    __syncthreads();
+    for (int32_t lo = 0, hi = 1; lo < hi;) {
+      int32_t next = hi;
+      for (int32_t base = lo; base < hi; base += kNodes) {
+        const int32_t p = base + (int32_t)threadIdx.x / G;
+        const int32_t u = p < hi ? order[p] : -1;
+        const auto test = [&](int32_t w) { return numbers<false>(a, w, p); };
+        uint64_t hit;
+        const int32_t found = group_count<G>(a, u, hit, test);
+        int32_t total;
+        const int32_t at =
+            of_group<G>(next + block_excl_scan<kMidThreads>(leads_group<G>() ? found : 0, wsum, total));
+        if (found)
+          group_put<G>(a, u, hit, at, test, [&](int32_t w, int32_t q) {
+            if (q < sz) {
+              order[q] = w;
+              a.local[w] = q;
+            }
+          });
+        next += total;
+      }
+      __syncthreads();   // the next level reads what this one wrote
+      lo = hi;
+      hi = next;
+    }
   }
-  __syncthreads();
-  for (int32_t d = 0; fn > 0; ++d) {
-    if (tid == 0) ncand = 0;
+}
+
+// Larger ones, one after another on kGiantBlocks workgroups that meet after
+// each level: a level of some 400 nodes of 22 neighbours (a packed window)
+// is 50 blocks' work of one wave-wide step, and one workgroup took 140 us for
+// it.  Positions and order go past the caches of one compute unit (agent
+// scope); every wait ends: all blocks of this launch fit the device at once,
+// and a block that has waited far too long reports it and leaves, as do the
+// others after it.
+__global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
+  __shared__ ScanShared sh;
+  __shared__ int32_t lost;
+  constexpr int32_t G = 32, kNodes = kScanBlock / G;
+  const int32_t giants = a.ctl[kCtlGiants], bigs = a.ctl[kCtlBigs];
+  const int32_t count = giants + (bigs > kFewBigs ? 0 : bigs);
+  uint64_t* status = reinterpret_cast<uint64_t*>(((uintptr_t)a.words + 7) & ~(uintptr_t)7);
+  uint32_t tag = 0;
+  int32_t met = 0;
+  if (threadIdx.x == 0) lost = 0;
+  const auto meet = [&] {
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);   // this wave's stores are out
     __syncthreads();
-    for (int32_t i = tid; i < fn; i += T) {
-      const int32_t u = F[i];
-      for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
-        const int32_t w = adj[t];
-        if (a.qpos[w] < 0 && a.local[w] < 0 && atomicMax(a.stamp + w, d) < d)
-          a.cand[atomicAdd(&ncand, 1)] = w;
-      }
-    }
-    __syncthreads();
-    const int32_t nc = ncand;
-    // parent: the numbered neighbour of smallest local position (all of
-    // them are in level d)
-    for (int32_t j = tid; j < nc; j += T) {
-      const int32_t w = a.cand[j];
-      int32_t best = -1, bp = INT32_MAX;
-      for (int32_t t = ptr[w]; t < ptr[w + 1]; ++t) {
-        const int32_t x = adj[t];
-        const int32_t p = a.local[x];
-        if (a.qpos[x] < 0 && p >= 0 && p < bp) {
-          bp = p;
-          best = x;
+    if (threadIdx.x == 0) {
+      met += (int32_t)gridDim.x;
+      atomicAdd(a.ctl + kCtlMeet, 1);
+      for (int32_t spin = 0; ld_agent(a.ctl + kCtlMeet) < met; ++spin)
+        if (spin > (1 << 22) || ld_agent(a.ctl + kCtlLost)) {
+          atomicOr(a.ctl + kCtlLost, 1);
+          a.counts[0] = a.n;   // no split: the host refuses the component count
+          a.counts[1] = -1;
+          lost = 1;
+          break;
         }
+    }
+    __syncthreads();
+    asm volatile("" ::: "memory");
+    return lost == 0;
+  };
+  for (int32_t g = 0; g < count; ++g) {
+    const int32_t c = g < giants ? a.giants[g] : a.bigs[g - giants], sz = a.comp_ptr[c + 1] - a.comp_ptr[c];
+    int32_t* order = a.order + a.comp_ptr[c];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+      __hip_atomic_store(order, a.parent[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(a.local + a.parent[c], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (!meet()) return;
+    for (int32_t lo = 0, hi = 1; lo < hi;) {
+      ++tag;
+      const int32_t tiles = (hi - lo + kNodes - 1) / kNodes;
+      for (int32_t tile = (int32_t)blockIdx.x; tile < tiles; tile += (int32_t)gridDim.x) {
+        const int32_t p = lo + tile * kNodes + (int32_t)threadIdx.x / G;
+        const int32_t u = p < hi ? ld_agent(order + p) : -1;
+        const auto test = [&](int32_t w) { return numbers<true>(a, w, p); };
+        uint64_t hit;
+        const int32_t found = group_count<G>(a, u, hit, test);
+        int32_t end;
+        const int32_t at =
+            of_group<G>(hi + device_excl_scan(leads_group<G>() ? found : 0, status, tag, tile, sh, end));
+        if (found)
+          group_put<G>(a, u, hit, at, test, [&](int32_t w, int32_t q) {
+            if (q < sz) {
+              __hip_atomic_store(order + q, w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              __hip_atomic_store(a.local + w, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+          });
       }
-      a.trig[w] = best;
+      if (!meet()) return;
+      const uint64_t last = __hip_atomic_load(status + tiles - 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      lo = hi;
+      hi += (int32_t)(uint32_t)last;   // the last tile's prefix with its own: the level's total
     }
-    __syncthreads();
-    int32_t carry = 0;
-    for (int32_t base = 0; base < fn; base += T) {
-      const int32_t i = base + tid;
-      const int32_t u = i < fn ? F[i] : -1;
-      int32_t c = 0;
-      if (u >= 0)
-        for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
-          const int32_t w = adj[t];
-          c += a.qpos[w] < 0 && a.local[w] < 0 && a.trig[w] == u ? 1 : 0;
-        }
-      int32_t total;
-      const int32_t ex = carry + block_excl_scan<kSplitThreads>(c, wsum, total);
-      if (u >= 0) {
-        a.gex[i] = ex;
-        a.cnt[i] = c;
-        const int32_t cu = a.comp_of[u];
-        if (i == 0 || a.comp_of[F[i - 1]] != cu) a.cbase[cu] = ex;
-      }
-      carry += total;
-    }
-    __syncthreads();
-    for (int32_t i = tid; i < fn; i += T) {
-      if (a.cnt[i] == 0) continue;
-      const int32_t u = F[i], cu = a.comp_of[u];
-      int32_t p = a.tail[cu] + a.gex[i] - a.cbase[cu], g = a.gex[i];
-      for (int32_t t = ptr[u]; t < ptr[u + 1]; ++t) {
-        const int32_t w = adj[t];
-        if (a.qpos[w] < 0 && a.local[w] < 0 && a.trig[w] == u && g < a.n &&
-            a.comp_ptr[cu] + p < a.comp_ptr[cu + 1]) {
-          a.local[w] = p;
-          a.order[a.comp_ptr[cu] + p] = w;
-          NF[g] = w;
-          ++p;
-          ++g;
-        }
-      }
-    }
-    __syncthreads();
-    for (int32_t i = tid; i < fn; i += T) {
-      const int32_t cu = a.comp_of[F[i]];
-      if (i == fn - 1 || a.comp_of[F[i + 1]] != cu) a.tail[cu] += a.gex[i] + a.cnt[i] - a.cbase[cu];
-    }
-    __syncthreads();
-    int32_t* tmp = F;
-    F = NF;
-    NF = tmp;
-    fn = carry;
   }
-  if (tid == 0) a.counts[1] = ncomp;
 }
 
 // ---- host side --------------------------------------------------------------
@@ -875,7 +951,7 @@ void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
 }
 
 SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                        int32_t k, bool simplify, int32_t* out, int32_t* scratch_at, const int32_t* fault,
+                        int64_t adj_entries, int32_t k, bool simplify, int32_t* out, int32_t* scratch_at, const int32_t* fault,
                         int32_t* ptr_w) {
   const size_t nn = (size_t)n;
   SplitArgs a{};
@@ -892,9 +968,9 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
   a.local = a.comp_ptr + nn + 1;
   const size_t stride = split_scratch_words(n) / kSplitScratch;
   int32_t* q = scratch_at;
-  int32_t** scratch[kSplitScratch] = {&a.qpos, &a.stamp, &a.trig, &a.cand,  &a.parent, &a.root, &a.cid,
-                                      &a.csize, &a.fill, &a.list, &a.rank,  &a.fa,     &a.fb,   &a.gex,
-                                      &a.cnt,  &a.cbase, &a.tail, &a.ctl};
+  int32_t** scratch[kSplitScratch] = {&a.qpos, &a.parent, &a.root, &a.cid,  &a.csize,  &a.fill,
+                                      &a.list, &a.rank,   &a.mids, &a.bigs, &a.giants, &a.words,
+                                      &a.ctl};
   for (int32_t** d : scratch) {
     *d = q;
     q += stride;
@@ -919,7 +995,11 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
       hipLaunchKernelGGL(split_level_kernel<8>, lg, dim3(kScanBlock), 0, st, a, L, sa.status, sa.epoch);
   }
   hipLaunchKernelGGL(split_peel_kernel, dim3(1), dim3(kSplitThreads), 0, st, a);
-  wide(uf_unite_kernel);
+  if (adj_entries > 8 * (int64_t)n)
+    wide(uf_unite_kernel<1>);
+  else
+    hipLaunchKernelGGL(uf_unite_kernel<4>, dim3((unsigned)std::min<int64_t>((n + 63) / 64, 2 * kSplitGrid)), dim3(256),
+                       0, st, a);
   sa = scan_args(gb, tiles, tiles);     // component ids; cid[n] = components
   hipLaunchKernelGGL(uf_root_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, st, a, sa.ticket, sa.base,
                      sa.status, sa.epoch);
@@ -927,17 +1007,20 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
   scan(gb, a.csize, n, a.comp_ptr);
   wide(comp_list_kernel);
   wide(bfs_small_kernel);
-  hipLaunchKernelGGL(bfs_big_kernel, dim3(1), dim3(kSplitThreads), 0, st, a);
+  hipLaunchKernelGGL(bfs_mid_kernel, dim3((unsigned)std::min<int64_t>(kMidGrid, n / 65 + 1)), dim3(kMidThreads), 0,
+                     st, a);
+  if (n > kBigNodes)
+    hipLaunchKernelGGL(bfs_giant_kernel, dim3(kGiantBlocks), dim3(kScanBlock), 0, st, a);
   check_hip(hipGetLastError(), "device split");
   return a;
 }
 
 // The same in the builder's own workspace: outputs at its front.
 static void enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                          int32_t k, bool simplify) {
+                          int64_t adj_entries, int32_t k, bool simplify) {
   grow(gb.split_ws, gb.ctx, sizeof(int32_t) * (split_out_words(n) + split_scratch_words(n)));
   int32_t* w = gb.split_ws.as<int32_t>();
-  enqueue_split(gb, n, dptr, dadj, k, simplify, w, w + split_out_words(n), nullptr, nullptr);
+  enqueue_split(gb, n, dptr, dadj, adj_entries, k, simplify, w, w + split_out_words(n), nullptr, nullptr);
 }
 
 // Split from the copied-back words of split_ws.
@@ -1007,7 +1090,7 @@ void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simpli
     check_hip(hipMemcpyAsync(gb.adj.p, hp + nb + 1, sizeof(int32_t) * (size_t)m2,
                              hipMemcpyHostToDevice, st),
               "device split: upload lists");
-  enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), k, simplify);
+  enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), m2, k, simplify);
   const size_t out_bytes = sizeof(int32_t) * split_out_words(nn);
   if (!grow_pinned(gb.hout, out_bytes)) fail(MPLD_E_NOMEM, "device split: pinned host memory");
   check_hip(hipMemcpyAsync(gb.hout.p, gb.split_ws.p, out_bytes, hipMemcpyDeviceToHost, st),
@@ -1148,7 +1231,7 @@ bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
   const size_t nb = (size_t)nn;
   const int32_t total = layout_lists<false>(gb, L);
   if (split && !device_split_pays(nn, total, k)) split = nullptr;   // the caller splits on the host
-  if (split) enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), k, simplify);
+  if (split) enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), total, k, simplify);
   const size_t split_words = split ? split_out_words(nn) : 0;
   const size_t out_bytes = sizeof(int32_t) * ((nb + 1) + nb + (size_t)total + split_words);
   if (!grow_pinned(gb.hout, out_bytes)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");

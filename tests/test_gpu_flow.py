@@ -71,10 +71,12 @@ MIXED = SMALL + [65, 100, 700, 2047, 2048, 2049]
 
 @pytest.mark.parametrize("k", [2, 3, 4, 6])
 @pytest.mark.parametrize("n,sizes,flags", [
-    (6144, SMALL, SIMPLIFY | TRACE), (6145, SMALL, TRACE), (7001, SMALL, SIMPLIFY | TRACE | STITCH),
+    (10000, SMALL, SIMPLIFY | TRACE), (10001, SMALL, TRACE), (9001, SMALL, SIMPLIFY | TRACE | STITCH),
     (20000, MIXED, SIMPLIFY | TRACE), (20001, MIXED, SIMPLIFY | TRACE | STITCH | MARK),
-    (6200, SMALL, SIMPLIFY | TRACE | STITCH | MINIMIZE), (7000, SMALL, SIMPLIFY | TRACE | FORCE_LDS),
-    (20000, [17] * 5 + [40] * 4, SIMPLIFY | TRACE)])
+    (9002, SMALL, SIMPLIFY | TRACE | STITCH | MINIMIZE), (9003, SMALL, SIMPLIFY | TRACE | FORCE_LDS),
+    (20000, [17] * 5 + [40] * 4, SIMPLIFY | TRACE),
+    (6000, [600, 513, 900], SIMPLIFY | TRACE), (6000, [600, 513, 900, 700, 512], SIMPLIFY | TRACE),
+    (9000, [4500, 800, 100], SIMPLIFY | TRACE | STITCH), (9010, [4200] + [600] * 4 + [80] * 5, TRACE)])
 def test_clusters(ctx, k, n, sizes, flags):
     import paper_2303_14335_amd as mp
     degree = min(1.25 * k + 0.9, 2.3 * k - 2.0)
@@ -99,8 +101,8 @@ def test_no_pairs_and_no_core(ctx):
     import paper_2303_14335_amd as mp
     say("no pairs; a forest")
     none = np.zeros((0, 2), np.int32)
-    n, ce, se = clustered(6500, [], 0, True, 3)
-    for args in ((6500, none, none), (6500, none, np.array([[6499, 0]], np.int32)), (n, ce, se)):
+    n, ce, se = clustered(9500, [], 0, True, 3)
+    for args in ((11000, none, none), (11001, none, np.array([[6499, 0]], np.int32)), (n, ce, se)):
         for flags in (SIMPLIFY | TRACE, TRACE):
             ref = oracle.decompose(oracle.Graph(*args), 3, 1000, bool(flags & SIMPLIFY))
             compare(mp.mpld_decompose(ctx, mp.Graph(*args), 3, 1000, flags), ref)
@@ -133,7 +135,7 @@ def test_hub(ctx):
         hub = np.stack([np.zeros(d), np.arange(1, d + 1)], 1)
         ring = np.stack([np.arange(1, 400), np.arange(2, 401)], 1)
         ce = np.concatenate([hub, ring]).astype(np.int32)
-        args = (6500, ce, np.array([[0, 6499]], np.int32))
+        args = (11000, ce, np.array([[0, 6499]], np.int32))
         ref = oracle.decompose(oracle.Graph(*args), 2, 1000)
         compare(mp.mpld_decompose(ctx, mp.Graph(*args), 2, 1000, SIMPLIFY | TRACE), ref)
 
@@ -141,7 +143,7 @@ def test_hub(ctx):
 def test_faults(ctx):
     import paper_2303_14335_amd as mp
     say("faults in a large graph")
-    n, ce, se = clustered(6500, SMALL, 4.0, True, 11)
+    n, ce, se = clustered(9004, SMALL, 4.0, True, 11)
 
     def refused(ce, se, what):
         with pytest.raises(mp.MpldError) as e:
