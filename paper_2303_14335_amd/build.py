@@ -13,7 +13,7 @@ BUILD = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libmpld.so")
 
 SOURCES = ["frontend.cpp", "runtime.cpp", "abi.cpp", "serve.cpp", "serve_core.cpp", "autotune.cpp", "search_reg.hip",
-           "search_lds.hip", "search_device.hip", "graph_device.hip", "flow_device.hip", "search_min.hip",
+           "search_lds.hip", "search_device.hip", "graph_device.hip", "flow_device.hip", "seq_engine.hip", "search_min.hip",
            "noalloc.hip", "measure.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")

@@ -65,6 +65,12 @@ static DevDesc image_enter(Image& im, mpld_context* ctx, int32_t n, int64_t m, i
     const int64_t small = lds_bytes_for(n, k, adj_words, max_deg, false, stitch);
     const int64_t big = lds_bytes_for(n, k, adj_words, max_deg, true, stitch);
     const int64_t limit = std::min<int64_t>(kLdsSmallLimit, ctx->lds_per_block);
+    im.csr_shape.resize((size_t)id + 1);
+    CsrShape& sh = im.csr_shape[(size_t)id];
+    const int64_t wide_bytes = lds_wide_bytes(n, k, adj_words, max_deg, stitch);
+    sh.small_bytes = n <= kLds1MaxN && small <= ctx->lds_per_block ? small : -1;
+    sh.wide_bytes = wide_bytes <= ctx->lds_per_block ? wide_bytes : -1;
+    sh.stack_words = lds_stack_words(n, k, adj_words);
     im.mark_lds = std::max(im.mark_lds, mark_lds_bytes(n, k));
     if (force_dev) {
       im.dev_stack_words = std::max(im.dev_stack_words, device_tier_stack_words(n, max_deg));
@@ -256,6 +262,9 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   ordered.clear();
   ordered.reserve(db.host_queue.size());
   for (int32_t c : db.host_queue) ordered.push_back(im.desc[c]);
+  db.csr_shape.clear();
+  for (size_t i = (size_t)db.n_reg; i < db.host_queue.size(); ++i)
+    db.csr_shape.push_back(im.csr_shape[(size_t)db.host_queue[i]]);
   // root split: the largest register-tier items (a prefix of the launch
   // order when it is largest first) get a workgroup each, at most
   // root_split_max of them (0: every item of at least root_split_min_n nodes)
@@ -688,11 +697,12 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
     else std::memset(e.colors, -1, (size_t)d.n);
     wb.push_back(e);
   }
-  for (int32_t item : rerun) {
-    ++db.sp_reruns;
-    check_hip(launch_reg_single(trace, db.k, db.reg_items(), item, db.recs.as<DevRecord>(),
-                                db.colors.as<int8_t>(), s), "heavy: sequential re-run");
-  }
+  // cut by its budget (or past the engine's memory): in sequence order
+  db.sp_reruns += (int64_t)rerun.size();
+  if (!seq_solve(db, rerun, trace))
+    for (int32_t item : rerun)
+      check_hip(launch_reg_single(trace, db.k, db.reg_items(), item, db.recs.as<DevRecord>(),
+                                  db.colors.as<int8_t>(), s), "heavy: sequential re-run");
   if (!wb.empty()) {
     if (!db.sp_host_writes.reserve(sizeof(HeavyWrite) * wb.size()))
       fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
@@ -723,9 +733,24 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
 // budget).  Every row exhausted: INFEASIBLE with acc nodes.  The trace hash
 // follows the same order: the root node's, then each counted subtree's
 // appended (trace S then T: h(S) B^|T| + h(T)).
+//
+// One-wave components take the sequence engine instead (their root rows are
+// no limit to it: 48 components of 65 to 2048 nodes, a third of them cut by
+// budgets of 10^5 nodes, took 145 ms as root-row tasks, nearly all of it in
+// each first row's subtree); what is left here are stitch-ordered ones, the
+// workgroup layout's, and any that the engine had no memory for.
 static void csr_split(DeviceBatch& db, bool trace) {
   const int32_t first = db.n_reg, count = db.n_lds + db.n_big;
   if (count == 0) return;
+  const int32_t one_wave = db.csr_stitch ? 0 : db.n_lds + db.n_wide;
+  bool by_seq = false;
+  if (one_wave) {
+    std::vector<int32_t> positions((size_t)one_wave);
+    for (int32_t i = 0; i < one_wave; ++i) positions[(size_t)i] = first + i;
+    by_seq = seq_solve(db, positions, trace);
+    if (by_seq && one_wave == count) return;
+  }
+  const int32_t skip = by_seq ? one_wave : 0;   // these have their results
   mpld_context* ctx = db.ctx;
   hipStream_t s = ctx->stream;
   struct Comp {
@@ -748,6 +773,10 @@ static void csr_split(DeviceBatch& db, bool trace) {
     cp.res.out_off = d.out_off;
     cp.res.n = d.n;
     cp.res.src_off = -1;
+    if (i < skip) {
+      cp.done = true;
+      continue;
+    }
     if (d.n == 0) {   // no column: the root is a solution
       cp.res.rec.status = MPLD_FEASIBLE;
       cp.res.rec.nodes = 1;
@@ -906,7 +935,7 @@ static void csr_split(DeviceBatch& db, bool trace) {
   // write back records and colors
   std::vector<LdsResolved> w;
   w.reserve(comps.size());
-  for (const Comp& cp : comps) w.push_back(cp.res);
+  for (int32_t i = skip; i < count; ++i) w.push_back(comps[(size_t)i].res);
   const size_t wb = sizeof(LdsResolved) * w.size();
   if (db.ct_resolved.bytes < wb) db.ct_resolved.alloc(ctx, wb);
   if (!db.ct_host.reserve(wb)) fail(MPLD_E_NOMEM, "subtree tasks: pinned host memory");

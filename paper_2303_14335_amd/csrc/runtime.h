@@ -75,6 +75,14 @@ hipError_t launch_lds_tasks(bool trace, bool big, bool stitch, int waves, int gr
 // out_off[i]).
 hipError_t launch_csr_writeback(const LdsResolved* w, int32_t count, const int8_t* src,
                                 DevRecord* recs, int8_t* colors, hipStream_t s);
+// The sequence engine's tasks (seq_types.h): a round's run list of one tier,
+// or with `finish` the results of the tier's components (records, colors).
+struct SeqArgs;
+hipError_t launch_seq_reg(bool trace, int k, int grid, const SeqArgs& a, RegItems items, int32_t parity,
+                          bool finish, DevRecord* recs, int8_t* colors, hipStream_t s);
+hipError_t launch_seq_csr(bool trace, int k, int grid, int lds_bytes, const SeqArgs& a,
+                          const DevDesc* descs, const uint32_t* adj32, uint64_t* stack, uint64_t stack_words,
+                          int32_t parity, bool finish, DevRecord* recs, int8_t* colors, hipStream_t s);
 // Waves per workgroup for big LDS-tier components of at most max_n nodes.
 // The big-tier launchers take waves = 0 for the one-wave wide layout
 // (lds_wide_bytes of LDS).
@@ -189,6 +197,11 @@ struct PinnedBuf {
   T* as() const { return static_cast<T*>(p); }
 };
 
+// What a CSR component takes in the one-wave layouts (-1: not in that one).
+struct CsrShape {
+  int64_t small_bytes = -1, wide_bytes = -1, stack_words = 0;
+};
+
 // Host-side packed exact-cover image of a set of components.
 struct Image {
   std::vector<DevDesc> desc;       // by component id
@@ -206,6 +219,7 @@ struct Image {
   int64_t core_edges = 0;
   int64_t lds_bytes_small = 0;     // largest footprint on the LDS tier
   int64_t lds_bytes_big = 0;       // largest footprint on the big tier
+  std::vector<CsrShape> csr_shape;   // by component id, CSR tiers
   // per component id, big tier: its LDS bytes in the workgroup layout and
   // in the one-wave layout (-1: that layout does not take it)
   std::vector<int64_t> big_bytes_wg, big_bytes_wide;
@@ -270,6 +284,7 @@ struct DeviceBatch {
   PinnedBuf sp_host_tasks, sp_host_out, sp_host_pool, sp_host_writes, sp_host_recs;
   DevBuf en_meta, en_tasks, en_blocks, en_pool;     // device-resident rounds
   DevBuf ct_tasks, ct_recs, ct_colors, ct_resolved; // LDS/big-tier subtree tasks
+  DevBuf sq_mem;                                    // sequence engine
   PinnedBuf ct_host;
   std::vector<uint8_t> sp_host_copy;                // engine results in ordinary memory
   int64_t sp_rounds = 0, sp_tasks_run = 0, sp_heavy = 0, sp_reruns = 0;  // last solve's stats
@@ -305,6 +320,7 @@ struct DeviceBatch {
   float last_roundtrip_ms = 0.f;
   std::vector<int32_t> host_queue;  // component ids in launch order (all tiers)
   std::vector<DevDesc> host_desc;   // descriptors in launch order
+  std::vector<CsrShape> csr_shape;  // by launch position past the register tier
   ~DeviceBatch();
 };
 
@@ -359,6 +375,13 @@ void assemble_result(const Graph& g, const Split& s, const Image& im, const mpld
 // (device_solve with `flags`), records and local colors D2H, between two
 // events (read by device_time into last_roundtrip_ms).
 void device_roundtrip(DeviceBatch& db, const Image& im, uint32_t flags);
+// Searches the components at these launch positions (register tier, LDS tier,
+// one-wave big tier) with the sequence engine and writes their records and
+// colors; waits for the rounds.  False: some were given up for lack of memory
+// (their records are not written).
+bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trace);
+constexpr int32_t kSeqRoundsPerCheck = 3;      // rounds enqueued between looks at the head
+constexpr int32_t kSeqMaxRounds = 1 << 16;     // then the callers search one component after another
 // Reads the last solve's event time if the stream has passed it.
 bool device_time(DeviceBatch& db);
 // Waits, then copies records and colors back (and, when the batch was

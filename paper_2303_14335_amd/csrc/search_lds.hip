@@ -34,6 +34,7 @@
 
 #include "device_types.h"
 #include "mpld.h"
+#include "seq_types.h"
 #include "trace.h"
 #include "wave_ops.h"
 
@@ -131,6 +132,104 @@ __device__ __forceinline__ uint64_t make_hdr(uint32_t v, uint32_t c, uint32_t ro
   return (uint64_t)v | ((uint64_t)c << 24) | ((uint64_t)rows << 28) | ((uint64_t)est << 36);
 }
 
+// put(i, get(i)) for i < count over the wave, eight reads in flight: one at
+// a time, a component's lists came to LDS at about one memory latency per 64
+// words (some 80 us at n = 1800).
+template <class G, class P>
+__device__ __forceinline__ void load_words(uint32_t count, G&& get, P&& put) {
+  const uint32_t lane = __lane_id();
+  for (uint32_t i0 = lane; i0 < count; i0 += 64u * 8u) {
+    uint32_t x[8];
+#pragma unroll
+    for (uint32_t q = 0; q < 8u; ++q) x[q] = i0 + 64u * q < count ? get(i0 + 64u * q) : 0u;
+#pragma unroll
+    for (uint32_t q = 0; q < 8u; ++q)
+      if (i0 + 64u * q < count) put(i0 + 64u * q, x[q]);
+  }
+}
+
+// A sequence-engine task on a CSR tier (the SEQ instances of the one-wave
+// solvers below): where it starts, how far it may go, and what becomes of it.
+struct SeqIo {
+  SeqArgs a;
+  SeqTask task;
+  int32_t id;          // its result: a.results[id]
+  uint64_t stop;       // nodes it counts before it is cut, if it may be
+  uint64_t limit;      // nodes after which the search's budget is out
+  bool load;           // the component's lists are not in LDS yet
+  bool cuts;           // at `stop` it is cut (false: saved whole, one piece)
+  bool force;          // without room for that it goes on to `limit` (false: it is left as it was)
+};
+
+// Room for `pieces` pieces of a stack of `depth` levels and `ents` log entries;
+// the first task and arena byte, false when there is none.
+__device__ __forceinline__ bool seq_reserve(const SeqIo& io, uint32_t pieces, uint32_t n, uint32_t plane_bytes,
+                                            uint32_t depth, uint32_t ents, int32_t& child, int64_t& at) {
+  const uint64_t bytes =
+      ((uint64_t)pieces * (plane_bytes + 64u) + 8ull * depth + 4ull * ents + n + 127u) & ~63ull;
+  int32_t c = 0;
+  uint64_t p = 0;
+  if (__lane_id() == 63u) {
+    p = atomicAdd(&io.a.head->arena, bytes);
+    c = atomicAdd(&io.a.head->tasks, (int32_t)pieces);
+  }
+  c = (int32_t)rdlane((uint32_t)c, 63u);
+  p = rdlane64((uint32_t)p, (uint32_t)(p >> 32), 63u);
+  child = c;
+  at = (int64_t)p;
+  return p + bytes <= (uint64_t)io.a.arena_cap && c + (int32_t)pieces <= io.a.task_cap;
+}
+// Pieces that a stack with `open` untried levels is cut into.
+__device__ __forceinline__ uint32_t seq_pieces(const SeqIo& io, uint32_t open) {
+  if (!io.cuts || open <= (uint32_t)kSeqFirstLevels) return 1u;
+  const uint32_t singles = open - (uint32_t)kSeqFirstLevels;
+  return 1u + (singles < (uint32_t)kSeqPieces - 1u ? singles : (uint32_t)kSeqPieces - 1u);
+}
+// Room for n colors; -1: none.
+__device__ __forceinline__ int64_t seq_reserve_colors(const SeqIo& io, uint32_t n) {
+  const uint64_t bytes = (n + 63u) & ~63u;
+  uint64_t p = 0;
+  if (__lane_id() == 63u) p = atomicAdd(&io.a.head->arena, bytes);
+  p = rdlane64((uint32_t)p, (uint32_t)(p >> 32), 63u);
+  return p + bytes <= (uint64_t)io.a.arena_cap ? (int64_t)p : -1;
+}
+// Colors of the nodes below the piece, from its predecessor's array.
+__device__ __forceinline__ void seq_copy_colors(const SeqIo& io, int64_t to, uint32_t n) {
+  if (io.task.col < 0) return;
+  const uint4* src = reinterpret_cast<const uint4*>(io.a.arena + io.task.col);
+  uint4* dst = reinterpret_cast<uint4*>(io.a.arena + to);
+  for (uint32_t i = __lane_id(); i < (n + 15u) / 16u; i += 64u) dst[i] = src[i];
+}
+// Every lane writes the same record.
+__device__ __forceinline__ void seq_put_piece(const SeqIo& io, int32_t id, int32_t kind, uint32_t dbase,
+                                              uint32_t levels, uint32_t nent, uint32_t row_in, int64_t at,
+                                              int64_t col) {
+  SeqTask t;
+  t.comp = io.task.comp;
+  t.kind = kind;
+  t.dbase = dbase;
+  t.levels = levels;
+  t.nent = nent;
+  t.row_in = row_in;
+  t.at = at;
+  t.col = col;
+  t.open = 0;
+  io.a.tasks[id] = t;
+  io.a.results[id].status = kSeqWaiting;
+}
+__device__ __forceinline__ void seq_put_result(const SeqIo& io, int32_t status, uint32_t depth, uint64_t nodes,
+                                               uint64_t hash, int64_t sol, int32_t child, int32_t nchild) {
+  SeqResult r;
+  r.status = status;
+  r.depth = (int32_t)depth;
+  r.nodes = nodes;
+  r.hash = hash;
+  r.sol = sol;
+  r.child = child;
+  r.nchild = nchild;
+  io.a.results[io.id] = r;
+}
+
 // ---- one-wave tier --------------------------------------------------------
 //
 // Components of at most kLds1MaxN nodes: one wave, 32-bit plane words, one
@@ -204,10 +303,11 @@ struct Lds1Words {
 // STITCH: the stitch-aware row order (a column whose stitch partner is on
 // the path tries the partner's color first when that row is open, then the
 // others ascending); the CSR block then ends with the partners.
-template <bool TRACE, int K, bool STITCH>
+template <bool TRACE, int K, bool STITCH, bool SEQ = false>
 __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, char* lds,
                           int8_t* __restrict__ colors, DevRecord* __restrict__ rec,
-                          int32_t root_row = -1, uint64_t task_budget = 0) {
+                          int32_t root_row = -1, uint64_t task_budget = 0,
+                          const SeqIo* io = nullptr) {
   constexpr uint32_t S = lds1_stride(K);
   constexpr uint32_t kLS = S == 4u ? 2u : (S == 8u ? 3u : 4u);   // log2(S)
   constexpr int NB = bits_for(K);
@@ -223,16 +323,17 @@ __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, c
   uint32_t* ent = reinterpret_cast<uint32_t*>(lds + L.ent_off);
   uint16_t* spart = reinterpret_cast<uint16_t*>(lds + L.part_off);
   uint8_t* scol = reinterpret_cast<uint8_t*>(lds + L.col_off);
-  for (uint32_t v = lane; v < n; v += 64) {
-    const uint32_t b = gadj[v], e = gadj[v + 1];
-    offs[v] = b | ((e - b) << 16);
-    if (STITCH) {
-      const uint32_t p = gadj[n + 1 + m2 + 1 + v];
-      spart[v] = p < n ? (uint16_t)p : (uint16_t)0xffffu;
-    }
+  if (!SEQ || io->load) {
+    load_words(n, [&](uint32_t v) { return gadj[v] | ((gadj[v + 1] - gadj[v]) << 16); },
+               [&](uint32_t v, uint32_t x) { offs[v] = x; });
+    if (STITCH)
+      load_words(n, [&](uint32_t v) { return gadj[n + 1 + m2 + 1 + v]; },
+                 [&](uint32_t v, uint32_t p) { spart[v] = p < n ? (uint16_t)p : (uint16_t)0xffffu; });
   }
-  for (uint32_t i = lane; i < m2; i += 64) ids[i] = (uint16_t)gadj[n + 1 + i];
-  {
+  if (!SEQ || io->load)
+    load_words(m2, [&](uint32_t i) { return gadj[n + 1 + i]; },
+               [&](uint32_t i, uint32_t x) { ids[i] = (uint16_t)x; });
+  if (!SEQ || io->task.kind == kSeqRoot) {
     // every node uncovered with all k colors open; words past n are empty
     const uint32_t base = lane * 32u;
     const uint32_t cnt = base >= n ? 0u : (n - base >= 32u ? 32u : n - base);
@@ -247,6 +348,35 @@ __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, c
   int32_t status = -1;
   uint32_t areg = 0;   // untried-rows bit of depth 32 * lane + b
   const uint64_t budget = root_row >= 0 ? task_budget : (uint64_t)d.budget;
+  // SEQ: `depth` counts from the task's stack, dbase levels up
+  const uint32_t dbase = SEQ ? uni(io->task.dbase) : 0u;
+  uint64_t stop = SEQ ? uni64(io->stop) : 0;
+  const uint64_t limit = SEQ ? uni64(io->limit) : 0;
+  bool next_first = SEQ && io->task.kind == kSeqNext;
+  int32_t child = 0;
+  int64_t arena_at = 0;
+  bool cut = false;
+  uint32_t max_pieces = 1;
+  const uint32_t saved_bytes = (n + 31u) / 32u * S * 4u;   // planes of a saved state: whole words only
+  if (SEQ && io->task.kind != kSeqRoot) {
+    const uint8_t* at = io->a.arena + io->task.at;
+    depth = uni(io->task.levels);
+    esp = uni(io->task.nent);
+    row_in = uni(io->task.row_in);
+    uint4* pw = reinterpret_cast<uint4*>(PL);
+    for (uint32_t i = lane; i < 16u * S; i += 64u)
+      pw[i] = i < saved_bytes / 16u ? reinterpret_cast<const uint4*>(at)[i] : make_uint4(0u, 0u, 0u, 0u);
+    const uint2* hs = reinterpret_cast<const uint2*>(at + saved_bytes);
+    const uint32_t* es = reinterpret_cast<const uint32_t*>(hs + depth);
+    for (uint32_t i = lane; i < esp; i += 64u) ent[i] = es[i];
+    for (uint32_t b = 0; b < depth; b += 64u) {
+      uint2 hd = make_uint2(0u, 0u);
+      if (b + lane < depth) hdr[b + lane] = hd = hs[b + lane];
+      const uint64_t bal = __builtin_amdgcn_ballot_w64(((hd.y >> 16) & 0xffu) != 0u);
+      areg = lane == (b >> 5) ? (uint32_t)bal : (lane == (b >> 5) + 1u ? (uint32_t)(bal >> 32) : areg);
+    }
+    asm volatile("" ::: "memory");
+  }
   Lds1Words<K> W;
 
   // Take row (v, c) at `depth`: the level's header and untried-rows bit,
@@ -327,9 +457,42 @@ __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, c
     W.load(PL, lane);
   }
 
+  // This lane's untried-rows bits of the levels below `d`.
+  auto open_bits = [&](uint32_t d) {
+    const uint32_t d1 = d - 1u, dw = d1 >> 5;
+    const uint32_t below = ~0u >> (31u - (d1 & 31u));
+    return d == 0u ? 0u : (lane < dw ? areg : (lane == dw ? areg & below : 0u));
+  };
+  // The deepest level below `d` whose column has an untried row.
+  auto deepest_open = [&](uint32_t d) {
+    uint32_t f = kNoneL;
+    if (d != 0) {
+      const uint32_t m = open_bits(d);
+      const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
+      if (bal) {
+        const uint32_t l = 63u - (uint32_t)__builtin_clzll(bal);
+        f = l * 32u + 31u - (uint32_t)__builtin_clz(rdlane(m, l));
+      }
+    }
+    return f;
+  };
+
   while (status < 0) {
+    uint32_t v = 0, size = 0, r = 0, pre = 0, prp = 0xffffu;
+    if (SEQ && next_first) {   // straight to the deepest untried row
+      next_first = false;
+    } else {
     // ---- one search node
-    if (nodes == budget) { status = MPLD_BUDGET_EXHAUSTED; break; }
+    if (SEQ) {
+      if (nodes == stop) {
+        if (nodes == limit) { status = MPLD_BUDGET_EXHAUSTED; break; }
+        max_pieces = seq_pieces(*io, wave_sum_u32((uint32_t)__popc(open_bits(depth))));
+        cut = seq_reserve(*io, max_pieces, n, saved_bytes, depth, esp, child, arena_at);
+        if (cut) break;
+        if (!io->force) { status = kSeqWaiting; break; }   // no room: as it was
+        stop = limit;
+      }
+    } else if (nodes == budget) { status = MPLD_BUDGET_EXHAUSTED; break; }
     ++nodes;
     // column choice: bit-sliced counts of this lane's word, narrowed from
     // the top count bit to the lowest-count uncovered columns
@@ -356,23 +519,23 @@ __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, c
     }
     const uint32_t bit = (uint32_t)__builtin_ctz(cand | 0x80000000u);
     const uint32_t vl = (lane << 5) | bit;
-    uint32_t r = 0;
 #pragma unroll
     for (int c = 0; c < K; ++c) r |= __builtin_amdgcn_ubfe(W.a[c], bit, 1u) << c;
     const uint32_t vc = vl < n ? vl : 0u;   // lanes past n read node 0's words
-    const uint32_t pre = offs[vc];
-    const uint32_t prp = STITCH ? (uint32_t)spart[vc] : 0xffffu;
+    pre = offs[vc];
+    prp = STITCH ? (uint32_t)spart[vc] : 0xffffu;
     // issue those reads before the minimum (which they then overlap)
     asm volatile("" ::: "memory");
     const uint32_t key = wave_min(p ? ((t << 24) | vl) : kNoKey);
     if (key == kNoKey) {   // no uncovered column: the levels hold a solution
-      if (TRACE) h = trace_node(h, depth, row_in, kNoneL, 0);
+      if (TRACE) h = trace_node(h, dbase + depth, row_in, kNoneL, 0);
       status = MPLD_FEASIBLE;
       break;
     }
-    uint32_t v = key & 0xffffffu;
-    const uint32_t size = key >> 24;
-    if (TRACE) h = trace_node(h, depth, row_in, v, size);
+    v = key & 0xffffffu;
+    size = key >> 24;
+    if (TRACE) h = trace_node(h, dbase + depth, row_in, v, size);
+    }
     uint32_t rows, offv, est, lane_lo, c;
     if (size != 0) {
       const uint32_t wl = v >> 5;
@@ -393,17 +556,7 @@ __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, c
       rows &= ~(1u << c);   // the level's untried rows
     } else {
       // dead end: back to the deepest level whose column has an untried row
-      uint32_t f = kNoneL;
-      if (depth != 0) {
-        const uint32_t d1 = depth - 1u, dw = d1 >> 5;
-        const uint32_t below = ~0u >> (31u - (d1 & 31u));
-        const uint32_t m = lane < dw ? areg : (lane == dw ? areg & below : 0u);
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
-        if (bal) {
-          const uint32_t l = 63u - (uint32_t)__builtin_clzll(bal);
-          f = l * 32u + 31u - (uint32_t)__builtin_clz(rdlane(m, l));
-        }
-      }
+      const uint32_t f = deepest_open(depth);
       if (f == kNoneL) { status = MPLD_INFEASIBLE; break; }
       const uint2 hd = hdr[f];
       offv = uni(hd.x);
@@ -429,6 +582,70 @@ __device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, c
     ++depth;
   }
   __syncthreads();
+  if constexpr (SEQ) {
+    int64_t sol = -1;
+    int32_t pieces = 0;
+    // the colors of this task's levels, over those of the nodes below it
+    const auto put_colors = [&](int64_t to) {
+      seq_copy_colors(*io, to, n);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      uint8_t* out = io->a.arena + to;
+      for (uint32_t f = lane; f < depth; f += 64) {
+        const uint32_t d1w = hdr[f].y;
+        out[ent[d1w & 0xffffu] & kNodeMask] = (uint8_t)((d1w >> 24) & 0xfu);
+      }
+    };
+    if (status == MPLD_FEASIBLE) {
+      sol = seq_reserve_colors(*io, n);
+      if (sol < 0) status = kSeqLost;
+      else put_colors(sol);
+    } else if (cut) {
+      status = kSeqCapped;
+      // (a piece that keeps the whole stack keeps the colors below it too)
+      if (max_pieces > 1u) put_colors(arena_at);
+      const int64_t col = max_pieces > 1u ? arena_at : io->task.col;
+      int64_t at = arena_at + ((n + 63u) & ~63u);
+      for (uint32_t top = depth;;) {
+        const uint32_t want = pieces == 0 ? (uint32_t)kSeqFirstLevels : 1u;
+        uint32_t lo = top, got = 0;
+        for (; got < want; ++got) {
+          const uint32_t f = deepest_open(lo);
+          if (f == kNoneL) break;
+          lo = f;
+        }
+        if (pieces != 0 && got == 0) break;   // nothing untried below
+        if (pieces == (int32_t)max_pieces - 1) lo = 0;   // the rest
+        const uint32_t elo = lo < top ? uni(hdr[lo].y) & 0xffffu : esp;
+        uint8_t* out = io->a.arena + at;
+        const uint4* pw = reinterpret_cast<const uint4*>(PL);
+        for (uint32_t i = lane; i < saved_bytes / 16u; i += 64u) reinterpret_cast<uint4*>(out)[i] = pw[i];
+        uint2* hs = reinterpret_cast<uint2*>(out + saved_bytes);
+        for (uint32_t i = lane; i < top - lo; i += 64u) {
+          const uint2 hd = hdr[lo + i];
+          hs[i] = make_uint2(hd.x, hd.y - elo);   // the log starts at 0 (16 bits, no borrow)
+        }
+        uint32_t* es = reinterpret_cast<uint32_t*>(hs + (top - lo));
+        for (uint32_t i = elo + lane; i < esp; i += 64u) es[i - elo] = ent[i];
+        seq_put_piece(*io, child + pieces, pieces == 0 ? kSeqNode : kSeqNext, dbase + lo, top - lo, esp - elo,
+                      row_in, at, col);
+        ++pieces;
+        at += (int64_t)((saved_bytes + 8u * (top - lo) + 4u * (esp - elo) + 63u) & ~63u);
+        if (lo == 0) break;
+        // back to before level lo's row: its rows and column, and all above
+        asm volatile("" ::: "memory");
+        for (uint32_t i = elo + lane; i < esp; i += 64u) {
+          const uint32_t e = ent[i], u = e & kNodeMask;
+          atomicOr(&PL[(u >> 5) * S + (e >> kEntryNodeBits)], 1u << (u & 31u));
+        }
+        asm volatile("" ::: "memory");
+        esp = elo;
+        top = lo;
+      }
+    }
+    seq_put_result(*io, status, dbase + depth, nodes, h, sol, child, pieces);
+    __syncthreads();
+    return;
+  }
   if (status == MPLD_FEASIBLE) {
     for (uint32_t f = lane; f < depth; f += 64) {
       const uint32_t d1w = hdr[f].y;
@@ -525,11 +742,11 @@ __device__ __forceinline__ uint32_t wide_key(const Lds1Words<K>& W, uint32_t w) 
   return p ? (t << 28) | (((w << 5) | bit) << 8) | r : kNoKey;
 }
 
-template <bool TRACE, int K, bool STITCH>
+template <bool TRACE, int K, bool STITCH, bool SEQ = false>
 __device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ gadj, char* lds,
                                uint64_t* gstack, int8_t* __restrict__ colors,
                                DevRecord* __restrict__ rec, int32_t root_row = -1,
-                               uint64_t task_budget = 0) {
+                               uint64_t task_budget = 0, const SeqIo* io = nullptr) {
   constexpr uint32_t S = lds1_stride(K);
   constexpr uint32_t kLS = S == 4u ? 2u : (S == 8u ? 3u : 4u);   // log2(S)
   constexpr uint32_t NW = (uint32_t)kWideMaxWords;
@@ -552,16 +769,17 @@ __device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ ga
   uint8_t* scol = reinterpret_cast<uint8_t*>(lds + L.col_off);
   uint2* hdr = reinterpret_cast<uint2*>(gstack);
   uint32_t* ent = reinterpret_cast<uint32_t*>(gstack + n);
-  for (uint32_t v = lane; v < n; v += 64) {
-    const uint32_t b = gadj[v], e = gadj[v + 1];
-    offs[v] = b | ((e - b) << kWideBegBits);
-    if (STITCH) {
-      const uint32_t p = gadj[n + 1 + m2 + 1 + v];
-      spart[v] = p < n ? (uint16_t)p : (uint16_t)0xffffu;
-    }
+  if (!SEQ || io->load) {
+    load_words(n, [&](uint32_t v) { return gadj[v] | ((gadj[v + 1] - gadj[v]) << kWideBegBits); },
+               [&](uint32_t v, uint32_t x) { offs[v] = x; });
+    if (STITCH)
+      load_words(n, [&](uint32_t v) { return gadj[n + 1 + m2 + 1 + v]; },
+                 [&](uint32_t v, uint32_t p) { spart[v] = p < n ? (uint16_t)p : (uint16_t)0xffffu; });
   }
-  for (uint32_t i = lane; i < m2; i += 64) ids[i] = (uint16_t)gadj[n + 1 + i];
-  for (uint32_t w = lane; w < 64u * nwl; w += 64) {
+  if (!SEQ || io->load)
+    load_words(m2, [&](uint32_t i) { return gadj[n + 1 + i]; },
+               [&](uint32_t i, uint32_t x) { ids[i] = (uint16_t)x; });
+  if (!SEQ || io->task.kind == kSeqRoot) for (uint32_t w = lane; w < 64u * nwl; w += 64) {
     // every node uncovered with all k colors open; words past n are empty
     const uint32_t base = w * 32u;
     const uint32_t cnt = base >= n ? 0u : (n - base >= 32u ? 32u : n - base);
@@ -577,6 +795,37 @@ __device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ ga
   uint64_t nodes = 0, h = 0;
   int32_t status = -1;
   const uint64_t budget = root_row >= 0 ? task_budget : (uint64_t)d.budget;
+  // SEQ: `depth` counts from the task's stack, dbase levels up
+  const uint32_t dbase = SEQ ? uni(io->task.dbase) : 0u;
+  const uint32_t plane_bytes = 256u * S * nwl;
+  uint64_t stop = SEQ ? uni64(io->stop) : 0;
+  const uint64_t limit = SEQ ? uni64(io->limit) : 0;
+  bool next_first = SEQ && io->task.kind == kSeqNext;
+  int32_t child = 0;
+  int64_t arena_at = 0;
+  bool cut = false;
+  uint32_t max_pieces = 1;
+  const uint32_t saved_bytes = (n + 31u) / 32u * S * 4u;   // planes of a saved state: whole words only
+  if (SEQ && io->task.kind != kSeqRoot) {
+    const uint8_t* at = io->a.arena + io->task.at;
+    depth = uni(io->task.levels);
+    esp = uni(io->task.nent);
+    row_in = uni(io->task.row_in);
+    uint4* pw = reinterpret_cast<uint4*>(PL);
+    for (uint32_t i = lane; i < plane_bytes / 16u; i += 64u)
+      pw[i] = i < saved_bytes / 16u ? reinterpret_cast<const uint4*>(at)[i] : make_uint4(0u, 0u, 0u, 0u);
+    const uint2* hs = reinterpret_cast<const uint2*>(at + saved_bytes);
+    const uint32_t* es = reinterpret_cast<const uint32_t*>(hs + depth);
+    for (uint32_t i = lane; i < esp; i += 64u) ent[i] = es[i];
+    for (uint32_t b = 0; b < depth; b += 64u) {
+      uint2 hd = make_uint2(0u, 0u);
+      if (b + lane < depth) hdr[b + lane] = hd = hs[b + lane];
+      const uint64_t bal = __builtin_amdgcn_ballot_w64(((hd.y >> 16) & 0xffu) != 0u);
+      if (lane < 2u && (b >> 5) + lane < (n + 31u) / 32u)
+        dbits[(b >> 5) + lane] = lane == 0u ? (uint32_t)bal : (uint32_t)(bal >> 32);
+    }
+    asm volatile("" ::: "memory");
+  }
   Lds1Words<K> W;
   // every key of this lane's words, from the planes
   auto all_keys = [&]() {
@@ -686,26 +935,70 @@ __device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ ga
     read_keys();
   }
 
-  for (;;) {   // every exit sets the status
+  // The deepest level below `d` whose column has an untried row.
+  auto deepest_open = [&](uint32_t d) {
+    uint32_t f = kNoneL;
+    if (d != 0) {
+      const uint32_t d1 = d - 1u, top = d1 >> 5;
+      const uint32_t below = ~0u >> (31u - (d1 & 31u));
+      for (uint32_t base = 0; base <= top && f == kNoneL; base += 64u) {
+        // lane l looks at word top - base - l
+        const bool in = base + lane <= top;
+        const uint32_t wi = in ? top - base - lane : 0u;
+        uint32_t m = in ? dbits[wi] : 0u;
+        if (in && wi == top) m &= below;
+        const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
+        if (bal) {
+          const uint32_t l = (uint32_t)__builtin_ctzll(bal);
+          f = (top - base - l) * 32u + 31u - (uint32_t)__builtin_clz(rdlane(m, l));
+        }
+      }
+    }
+    return f;
+  };
+
+  // How many levels below `d` have one.
+  auto open_levels = [&](uint32_t d) {
+    uint32_t c = 0;
+    for (uint32_t w = lane; w * 32u < d; w += 64u)
+      c += (uint32_t)__popc(dbits[w] & (d - w * 32u >= 32u ? ~0u : (1u << (d - w * 32u)) - 1u));
+    return wave_sum_u32(c);
+  };
+
+  for (;;) {   // every exit sets the status (SEQ: or `cut`)
+    uint32_t v = 0, size = 0, key = 0, pre = 0;
+    if (SEQ && next_first) {   // straight to the deepest untried row
+      next_first = false;
+    } else {
     // ---- one search node
-    if (nodes == budget) { status = MPLD_BUDGET_EXHAUSTED; break; }
+    if (SEQ) {
+      if (nodes == stop) {
+        if (nodes == limit) { status = MPLD_BUDGET_EXHAUSTED; break; }
+        max_pieces = seq_pieces(*io, open_levels(depth));
+        cut = seq_reserve(*io, max_pieces, n, saved_bytes, depth, esp, child, arena_at);
+        if (cut) break;
+        if (!io->force) { status = kSeqWaiting; break; }   // no room: as it was
+        stop = limit;
+      }
+    } else if (nodes == budget) { status = MPLD_BUDGET_EXHAUSTED; break; }
     ++nodes;
     // column choice: the lowest key of this lane's words, then of the wave
     const uint32_t best = min(min(min(ka.x, ka.y), min(ka.z, ka.w)),
                               min(min(kb.x, kb.y), min(kb.z, kb.w)));
     // (kNoKey's node field is past n: read node 0's words instead)
     const uint32_t vl = (best >> 8) & 0xfffffu, vc = vl < n ? vl : 0u;
-    const uint32_t pre = offs[vc];
+    pre = offs[vc];
     asm volatile("" ::: "memory");
-    const uint32_t key = wave_min(best);
+    key = wave_min(best);
     if (key == kNoKey) {   // no uncovered column: the levels hold a solution
-      if (TRACE) h = trace_node(h, depth, row_in, kNoneL, 0);
+      if (TRACE) h = trace_node(h, dbase + depth, row_in, kNoneL, 0);
       status = MPLD_FEASIBLE;
       break;
     }
-    uint32_t v = (key >> 8) & 0xfffffu;
-    const uint32_t size = key >> 28;
-    if (TRACE) h = trace_node(h, depth, row_in, v, size);
+    v = (key >> 8) & 0xfffffu;
+    size = key >> 28;
+    if (TRACE) h = trace_node(h, dbase + depth, row_in, v, size);
+    }
     uint32_t rows, offv, est, lane_lo, c;
     bool full;
     if (size != 0) {
@@ -731,23 +1024,7 @@ __device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ ga
       // (the workgroup's waves share the CU's write-through vector cache)
       __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
       // back to the deepest level below `depth` whose column has an untried row
-      uint32_t f = kNoneL;
-      if (depth != 0) {
-        const uint32_t d1 = depth - 1u, top = d1 >> 5;
-        const uint32_t below = ~0u >> (31u - (d1 & 31u));
-        for (uint32_t base = 0; base <= top && f == kNoneL; base += 64u) {
-          // lane l looks at word top - base - l
-          const bool in = base + lane <= top;
-          const uint32_t wi = in ? top - base - lane : 0u;
-          uint32_t m = in ? dbits[wi] : 0u;
-          if (in && wi == top) m &= below;
-          const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
-          if (bal) {
-            const uint32_t l = (uint32_t)__builtin_ctzll(bal);
-            f = (top - base - l) * 32u + 31u - (uint32_t)__builtin_clz(rdlane(m, l));
-          }
-        }
-      }
+      const uint32_t f = deepest_open(depth);
       if (f == kNoneL) { status = MPLD_INFEASIBLE; break; }
       const uint2 hd = hdr[f];
       est = uni(hd.x);
@@ -786,6 +1063,70 @@ __device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ ga
   }
   __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
   __syncthreads();
+  if constexpr (SEQ) {
+    int64_t sol = -1;
+    int32_t pieces = 0;
+    // the colors of this task's levels, over those of the nodes below it
+    const auto put_colors = [&](int64_t to) {
+      seq_copy_colors(*io, to, n);
+      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+      uint8_t* out = io->a.arena + to;
+      for (uint32_t f = lane; f < depth; f += 64) {
+        const uint32_t y = hdr[f].y;
+        out[y & 0xffffu] = (uint8_t)((y >> 24) & 0xfu);
+      }
+    };
+    if (status == MPLD_FEASIBLE) {
+      sol = seq_reserve_colors(*io, n);
+      if (sol < 0) status = kSeqLost;
+      else put_colors(sol);
+    } else if (cut) {
+      status = kSeqCapped;
+      // (a piece that keeps the whole stack keeps the colors below it too)
+      if (max_pieces > 1u) put_colors(arena_at);
+      const int64_t col = max_pieces > 1u ? arena_at : io->task.col;
+      int64_t at = arena_at + ((n + 63u) & ~63u);
+      for (uint32_t top = depth;;) {
+        const uint32_t want = pieces == 0 ? (uint32_t)kSeqFirstLevels : 1u;
+        uint32_t lo = top, got = 0;
+        for (; got < want; ++got) {
+          const uint32_t f = deepest_open(lo);
+          if (f == kNoneL) break;
+          lo = f;
+        }
+        if (pieces != 0 && got == 0) break;   // nothing untried below
+        if (pieces == (int32_t)max_pieces - 1) lo = 0;   // the rest
+        const uint32_t elo = lo < top ? uni(hdr[lo].x) : esp;
+        uint8_t* out = io->a.arena + at;
+        const uint4* pw = reinterpret_cast<const uint4*>(PL);
+        for (uint32_t i = lane; i < saved_bytes / 16u; i += 64u) reinterpret_cast<uint4*>(out)[i] = pw[i];
+        uint2* hs = reinterpret_cast<uint2*>(out + saved_bytes);
+        for (uint32_t i = lane; i < top - lo; i += 64u) {
+          const uint2 hd = hdr[lo + i];
+          hs[i] = make_uint2(hd.x - elo, hd.y);   // the log starts at 0
+        }
+        uint32_t* es = reinterpret_cast<uint32_t*>(hs + (top - lo));
+        for (uint32_t i = elo + lane; i < esp; i += 64u) es[i - elo] = ent[i];
+        seq_put_piece(*io, child + pieces, pieces == 0 ? kSeqNode : kSeqNext, dbase + lo, top - lo, esp - elo,
+                      row_in, at, col);
+        ++pieces;
+        at += (int64_t)((saved_bytes + 8u * (top - lo) + 4u * (esp - elo) + 63u) & ~63u);
+        if (lo == 0) break;
+        // back to before level lo's row: its rows and column, and all above
+        asm volatile("" ::: "memory");
+        for (uint32_t i = elo + lane; i < esp; i += 64u) {
+          const uint32_t e = ent[i], u = e & kNodeMask;
+          atomicOr(&PL[(u >> 5) * S + (e >> kEntryNodeBits)], 1u << (u & 31u));
+        }
+        asm volatile("" ::: "memory");
+        esp = elo;
+        top = lo;
+      }
+    }
+    seq_put_result(*io, status, dbase + depth, nodes, h, sol, child, pieces);
+    __syncthreads();
+    return;
+  }
   if (status == MPLD_FEASIBLE) {
     for (uint32_t f = lane; f < depth; f += 64) {
       const uint32_t y = hdr[f].y;
@@ -1111,6 +1452,88 @@ __global__ __launch_bounds__(BIG ? 1024 : 64) void lds_task_kernel(
   }
 }
 
+// Sequence-engine tasks of the CSR tiers: one wave per workgroup over a
+// round's run list, or, FINISH, over the tiers' components: a component cut by
+// its budget searches its last task once more with what was left, then record
+// and colors are written.  A component keeps the layout that it was given.
+template <bool TRACE, int K, bool FINISH>
+__global__ __launch_bounds__(64) void seq_csr_kernel(const SeqArgs a, const DevDesc* __restrict__ descs,
+                                                     const uint32_t* __restrict__ adj32, uint64_t* stack,
+                                                     uint64_t stack_words, int32_t parity,
+                                                     DevRecord* __restrict__ recs, int8_t* __restrict__ colors) {
+  extern __shared__ __align__(16) char lds[];
+  uint64_t* my_stack = stack + (uint64_t)blockIdx.x * stack_words;
+  const auto run = [&](SeqIo& io, const DevDesc& d, bool wide) {
+    const uint32_t* g = adj32 + d.nbr_off;
+    if constexpr (K <= kWideMaxK) {
+      if (wide) {
+        solve_lds_wide<TRACE, K, false, true>(d, g, lds, my_stack, nullptr, nullptr, -1, 0, &io);
+        return;
+      }
+    }
+    solve_lds<TRACE, K, false, true>(d, g, lds, nullptr, nullptr, -1, 0, &io);
+  };
+  if constexpr (!FINISH) {
+    const int32_t* list = a.runs + (int64_t)(parity * kSeqTiers + kSeqCsr) * a.run_cap;
+    const int32_t count = min((int32_t)uni((uint32_t)a.head->run[parity][kSeqCsr]), a.run_cap);
+    int32_t loaded = -1;
+    for (int32_t r = (int32_t)uni(blockIdx.x); r < count;) {
+      SeqIo io;
+      io.a = a;
+      const uint32_t entry = uni((uint32_t)list[r]);
+      io.id = (int32_t)(entry & (uint32_t)kSeqTaskMask);
+      io.task = a.tasks[io.id];
+      const int32_t pos = (int32_t)uni((uint32_t)a.comps[io.task.comp].pos);
+      const bool wide = uni((uint32_t)a.comps[io.task.comp].wide) != 0;
+      const DevDesc d = descs[pos];
+      io.limit = (uint64_t)d.budget;
+      // a root first goes all the way down
+      const uint64_t cap = (uint64_t)a.cap[kSeqCsr] + (io.task.kind == kSeqRoot ? (uint64_t)d.n : 0ull);
+      io.stop = cap < io.limit ? cap : io.limit;
+      io.load = io.task.comp != loaded;
+      io.cuts = (entry & (uint32_t)kSeqCut) != 0;
+      io.force = (entry & (uint32_t)kSeqForce) != 0;
+      loaded = io.task.comp;
+      run(io, d, wide);
+      if ((int32_t)gridDim.x >= count) break;
+      int32_t q = 0;
+      if (__lane_id() == 0) q = atomicAdd(&a.head->pop[parity][kSeqCsr], 1);
+      r = (int32_t)gridDim.x + (int32_t)uni((uint32_t)q);
+    }
+  } else {
+    for (int32_t ci = (int32_t)uni(blockIdx.x); ci < a.ncomps; ci += (int32_t)gridDim.x) {
+      const SeqComp c = a.comps[ci];
+      if (c.tier != kSeqCsr || c.status == kSeqLost) continue;
+      const DevDesc d = descs[c.pos];
+      int32_t depth = c.status == MPLD_FEASIBLE ? d.n : (c.status == MPLD_INFEASIBLE ? 0 : c.depth);
+      uint64_t hash = c.hash;
+      if (c.cross >= 0) {
+        SeqIo io;
+        io.a = a;
+        io.id = c.cross;
+        io.task = a.tasks[c.cross];
+        io.stop = io.limit = c.left;
+        io.load = true;
+        io.cuts = io.force = false;   // (it stops at `limit`)
+        run(io, d, uni((uint32_t)c.wide) != 0);
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
+        const SeqResult r = a.results[c.cross];
+        depth = r.depth;
+        if (TRACE) hash = trace_concat(hash, r.hash, c.left);
+      }
+      int8_t* out = colors + d.out_off;
+      const int8_t* sol = reinterpret_cast<const int8_t*>(a.arena + (c.status == MPLD_FEASIBLE ? c.sol : 0));
+      for (int32_t v = (int32_t)__lane_id(); v < d.n; v += 64)
+        out[v] = c.status == MPLD_FEASIBLE ? sol[v] : (int8_t)-1;
+      DevRecord* rec = recs + d.comp;
+      rec->status = c.status;
+      rec->depth = depth;
+      rec->nodes = c.acc;
+      rec->hash = TRACE ? hash : 0;
+    }
+  }
+}
+
 // Conflict marking (Algorithm 1: a column left with no related row is a
 // conflict candidate (cl, cl'), cl' the column whose cover removed cl's
 // final row) for a component whose search ended without a solution: one
@@ -1240,6 +1663,51 @@ hipError_t launch_mark_lds(int grid, int lds_bytes, const DevDesc* descs, const 
   return hipGetLastError();
 }
 
+// Calls f(trace, K, finish) with each as a std::integral_constant.
+template <typename F>
+static hipError_t seq_dispatch(bool trace, int k, bool finish, F&& f) {
+  const auto with_k = [&](auto t, auto fin) {
+    switch (k) {
+      case 2: f(t, std::integral_constant<int, 2>(), fin); break;
+      case 3: f(t, std::integral_constant<int, 3>(), fin); break;
+      case 4: f(t, std::integral_constant<int, 4>(), fin); break;
+      case 5: f(t, std::integral_constant<int, 5>(), fin); break;
+      case 6: f(t, std::integral_constant<int, 6>(), fin); break;
+      case 7: f(t, std::integral_constant<int, 7>(), fin); break;
+      default: f(t, std::integral_constant<int, 8>(), fin); break;
+    }
+  };
+  const auto with_f = [&](auto t) {
+    if (finish) with_k(t, std::true_type{});
+    else with_k(t, std::false_type{});
+  };
+  if (trace) with_f(std::true_type{});
+  else with_f(std::false_type{});
+  return hipGetLastError();
+}
+
+hipError_t launch_seq_csr(bool trace, int k, int grid, int lds_bytes, const SeqArgs& a, const DevDesc* descs,
+                          const uint32_t* adj32, uint64_t* stack, uint64_t stack_words, int32_t parity,
+                          bool finish, DevRecord* recs, int8_t* colors, hipStream_t s) {
+  if (grid < 1) return hipErrorInvalidValue;
+  return seq_dispatch(trace, k, finish, [&](auto t, auto kk, auto fin) {
+    hipLaunchKernelGGL((seq_csr_kernel<decltype(t)::value, decltype(kk)::value, decltype(fin)::value>),
+                       dim3(grid), dim3(64), (size_t)lds_bytes, s, a, descs, adj32, stack, stack_words, parity,
+                       recs, colors);
+  });
+}
+
+static void seq_attr(int bytes) {
+  for (int k = 2; k <= 8; ++k)
+    for (int m = 0; m < 4; ++m)
+      (void)seq_dispatch(m & 1, k, m & 2, [&](auto t, auto kk, auto fin) {
+        (void)hipFuncSetAttribute(
+            reinterpret_cast<const void*>(
+                &seq_csr_kernel<decltype(t)::value, decltype(kk)::value, decltype(fin)::value>),
+            hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+      });
+}
+
 void lds_configure(int bytes) {
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(&mark_lds_kernel),
                             hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
@@ -1251,6 +1719,7 @@ void lds_configure(int bytes) {
   lds_attr<true, false, true>(bytes);
   lds_attr<false, true, true>(bytes);
   lds_attr<false, false, true>(bytes);
+  seq_attr(bytes);
   (void)hipGetLastError();
 }
 

@@ -35,6 +35,7 @@
 #include "min_core.h"
 #include "mpld.h"
 #include "reg_items.h"
+#include "seq_types.h"
 #include "trace.h"
 #include "wave_ops.h"
 
@@ -924,6 +925,170 @@ __global__ __launch_bounds__(256) void reg_split_kernel(
   }
 }
 
+// ---- sequence engine ----------------------------------------------------------
+//
+// A task's state: the frames' snapshots make every level's state restorable
+// from the lanes, so the pieces of a cut stack share one saved state and
+// differ in the untried levels that they own (the state's bit set A).
+template <bool TRACE, int K, bool STITCH>
+__device__ __forceinline__ void seq_reg_start(RegState<K>& s, const SeqArgs& a, const SeqTask& task,
+                                              const RegItems& items, const int32_t it, const DevDesc& d,
+                                              const uint32_t nb_lo, const uint32_t nb_hi, bool& dead) {
+  dead = false;
+  if (task.kind == kSeqRoot) {
+    reg_init(s, d.n, d.k);
+    if (STITCH) s.pc = (item_partner(items, it, __lane_id()) << 8) | 0xffu;
+    return;
+  }
+  reg_load<K, STITCH>(s, a.arena + task.at);
+  s.A = uniform64(task.open);
+  s.nodes = 0;
+  s.h = 0;
+  if (task.kind == kSeqNext) {   // the deepest untried row of the piece
+    uint32_t v = 0, c = 0, tried = 0;
+    uint64_t alt = 0;
+    dead = !retreat<K, STITCH>(s, 0, v, c, alt, tried);
+    if (!dead) {
+      take_row<K, STITCH>(s, rdlane64(nb_lo, nb_hi, v), v, c, alt, tried);
+      s.row_in = v * (uint32_t)d.k + c;
+    }
+  }
+}
+
+template <bool TRACE, int K, bool STITCH>
+__global__ __launch_bounds__(256) void seq_reg_kernel(const SeqArgs a, const RegItems items, int32_t parity) {
+  const uint32_t lane = __lane_id();
+  const int32_t waves = (int32_t)(gridDim.x * 4u);
+  const int32_t* list = a.runs + (int64_t)(parity * kSeqTiers + kSeqReg) * a.run_cap;
+  const int32_t count = min((int32_t)uniform((uint32_t)a.head->run[parity][kSeqReg]), a.run_cap);
+  for (int32_t r = (int32_t)uniform(blockIdx.x * 4u + (threadIdx.x >> 6)); r < count;) {
+    const uint32_t entry = uniform((uint32_t)list[r]);
+    const int32_t id = (int32_t)(entry & (uint32_t)kSeqTaskMask);
+    const SeqTask task = a.tasks[id];
+    const int32_t it = (int32_t)uniform((uint32_t)a.comps[task.comp].pos);
+    const DevDesc d = item_desc(items, it);
+    const uint64_t nb = item_mask(items, it, lane);
+    const uint32_t nb_lo = (uint32_t)nb, nb_hi = (uint32_t)(nb >> 32);
+    RegState<K> s;
+    bool dead;
+    seq_reg_start<TRACE, K, STITCH>(s, a, task, items, it, d, nb_lo, nb_hi, dead);
+    SeqResult res;
+    res.status = MPLD_INFEASIBLE;
+    res.depth = 0;
+    res.nodes = 0;
+    res.hash = 0;
+    res.sol = -1;
+    res.child = 0;
+    res.nchild = 0;
+    if (!dead) {
+      const uint64_t limit = (uint64_t)d.budget;
+      uint64_t stop = (uint64_t)a.cap[kSeqReg] < limit ? (uint64_t)a.cap[kSeqReg] : limit;
+      for (;;) {
+        reg_run<TRACE, K, STITCH>(s, nb_lo, nb_hi, d.k, limit, stop);
+        res.status = s.status;
+        if (s.status != -1) break;
+        // cut what is left: the deepest levels, single ones, the rest
+        const uint64_t open = s.A & below(s.depth);
+        uint64_t m = (entry & (uint32_t)kSeqCut) != 0 ? open : 0ull;
+        for (int j = 0; j < kSeqFirstLevels && m != 0; ++j) m &= ~(1ull << (63u - (uint32_t)__builtin_clzll(m)));
+        const int32_t singles = (int32_t)__builtin_popcountll(m);
+        const int32_t pieces = 1 + (singles < kSeqPieces - 1 ? singles : kSeqPieces - 1);
+        const uint64_t bytes = (uint64_t)seq_reg_state_bytes(K, STITCH);
+        uint64_t p = 0;
+        int32_t ch = 0;
+        if (lane == 63u) {   // as in the engine rounds, all of the atomics in one branch
+          p = atomicAdd(&a.head->arena, bytes);
+          ch = atomicAdd(&a.head->tasks, pieces);
+        }
+        p = (uint64_t)rdlane((uint32_t)p, 63u) | ((uint64_t)rdlane((uint32_t)(p >> 32), 63u) << 32);
+        ch = (int32_t)rdlane((uint32_t)ch, 63u);
+        if (p + bytes > (uint64_t)a.arena_cap || ch + pieces > a.task_cap) {
+          res.status = kSeqWaiting;   // no room: as it was
+          if ((entry & (uint32_t)kSeqForce) == 0) break;
+          stop = limit;
+          continue;
+        }
+        reg_save<K, STITCH>(s, a.arena + p);
+        uint64_t rest = m;
+        for (int32_t j = 0; j < pieces; ++j) {   // every lane writes the same records
+          SeqTask t = task;
+          t.kind = j == 0 ? kSeqNode : kSeqNext;
+          t.at = (int64_t)p;
+          if (j == 0) {
+            t.open = open & ~m;   // (all of it when it is not cut)
+          } else if (j == kSeqPieces - 1) {
+            t.open = rest;
+          } else {
+            t.open = 1ull << (63u - (uint32_t)__builtin_clzll(rest));
+            rest &= ~t.open;
+          }
+          a.tasks[ch + j] = t;
+          a.results[ch + j].status = kSeqWaiting;
+        }
+        res.child = ch;
+        res.nchild = pieces;
+        break;
+      }
+      res.depth = (int32_t)s.depth;
+      res.nodes = s.nodes;
+      res.hash = s.h;
+      if (res.status == MPLD_FEASIBLE) {
+        uint64_t p = 0;
+        if (lane == 63u) p = atomicAdd(&a.head->arena, 64ull);
+        p = (uint64_t)rdlane((uint32_t)p, 63u) | ((uint64_t)rdlane((uint32_t)(p >> 32), 63u) << 32);
+        if (p + 64u <= (uint64_t)a.arena_cap) {
+          if (lane < s.depth && (s.fr & 0xffu) < (uint32_t)d.n)
+            a.arena[p + (s.fr & 0xffu)] = (uint8_t)((s.fr >> 8) & 0xffu);
+          res.sol = (int64_t)p;
+        } else {
+          res.status = kSeqLost;
+        }
+      }
+    }
+    a.results[id] = res;
+    if (waves >= count) break;
+    int32_t q = 0;
+    if (lane == 0) q = atomicAdd(&a.head->pop[parity][kSeqReg], 1);
+    r = waves + (int32_t)uniform((uint32_t)q);
+  }
+}
+
+// The components' records and colors; one cut by its budget searches its last
+// task once more with what was left.
+template <bool TRACE, int K, bool STITCH>
+__global__ __launch_bounds__(256) void seq_reg_finish_kernel(const SeqArgs a, const RegItems items,
+                                                             DevRecord* __restrict__ recs,
+                                                             int8_t* __restrict__ colors) {
+  const uint32_t lane = __lane_id();
+  const int32_t waves = (int32_t)(gridDim.x * 4u);
+  for (int32_t ci = (int32_t)uniform(blockIdx.x * 4u + (threadIdx.x >> 6)); ci < a.ncomps; ci += waves) {
+    const SeqComp c = a.comps[ci];
+    if (c.tier != kSeqReg || c.status == kSeqLost) continue;
+    const DevDesc d = item_desc(items, c.pos);
+    int32_t depth = c.status == MPLD_FEASIBLE ? d.n : (c.status == MPLD_INFEASIBLE ? 0 : c.depth);
+    uint64_t hash = c.hash;
+    if (c.cross >= 0) {
+      const uint64_t nb = item_mask(items, c.pos, lane);
+      const uint32_t nb_lo = (uint32_t)nb, nb_hi = (uint32_t)(nb >> 32);
+      const SeqTask task = a.tasks[c.cross];
+      const uint64_t left = uniform64(c.left);
+      RegState<K> s;
+      bool dead;
+      seq_reg_start<TRACE, K, STITCH>(s, a, task, items, c.pos, d, nb_lo, nb_hi, dead);
+      reg_run<TRACE, K, STITCH>(s, nb_lo, nb_hi, d.k, left, left);
+      depth = (int32_t)s.depth;
+      if (TRACE) hash = trace_concat(hash, s.h, left);
+    }
+    if (lane < (uint32_t)d.n)
+      colors[d.out_off + (int32_t)lane] = c.status == MPLD_FEASIBLE ? (int8_t)a.arena[c.sol + lane] : (int8_t)-1;
+    DevRecord* rec = recs + d.comp;
+    rec->status = c.status;
+    rec->depth = depth;
+    rec->nodes = c.acc;
+    rec->hash = TRACE ? hash : 0;
+  }
+}
+
 __global__ void fill_i32_kernel(int32_t* __restrict__ p, int32_t count, int32_t value) {
   const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
   if (i < count) p[i] = value;
@@ -1304,6 +1469,27 @@ hipError_t launch_engine_round(int k, int grid, EngineHead* head, EngineTask* ta
       hipLaunchKernelGGL((engine_round_kernel<false, K, false>), dim3(grid), dim3(256), 0, s, head,
                          tasks, task_cap, blocks, pool, pool_cap, regitems, hc_nodes, hc_limit, cap,
                          levels);
+  });
+  return hipGetLastError();
+}
+
+hipError_t launch_seq_reg(bool trace, int k, int grid, const SeqArgs& a, RegItems items, int32_t parity,
+                          bool finish, DevRecord* recs, int8_t* colors, hipStream_t s) {
+  if (grid < 1) return hipErrorInvalidValue;
+  const bool stitch = items.part_off != 0;
+  with_planes(k, [&](auto kp) {
+    constexpr int K = decltype(kp)::value;
+    const auto go = [&](auto t, auto st) {
+      constexpr bool T = decltype(t)::value, S = decltype(st)::value;
+      if (finish)
+        hipLaunchKernelGGL((seq_reg_finish_kernel<T, K, S>), dim3(grid), dim3(256), 0, s, a, items, recs, colors);
+      else
+        hipLaunchKernelGGL((seq_reg_kernel<T, K, S>), dim3(grid), dim3(256), 0, s, a, items, parity);
+    };
+    if (trace && stitch) go(std::true_type{}, std::true_type{});
+    else if (trace) go(std::true_type{}, std::false_type{});
+    else if (stitch) go(std::false_type{}, std::true_type{});
+    else go(std::false_type{}, std::false_type{});
   });
   return hipGetLastError();
 }
