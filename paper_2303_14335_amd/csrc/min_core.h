@@ -11,27 +11,30 @@
 
 namespace mpld {
 
+// What bounds it: one wave's chain of dependent instructions, a node after
+// another.  A lane's penalties of all colors are bytes of one word (two for
+// k > 4): byte c = 2 x (colored neighbours of color c) + 1 if the stitch
+// partner has another color, at most 127 and in the order of the penalties
+// 10 conflicts + stitches; colors past k hold 127.  So the least penalty is a
+// minimum of bytes, the open colors are counted with one addition, coloring a
+// node is one conditional addition in its neighbours' lanes (the mask comes
+// from the node's own lane), the bound's sum is population counts of ballots
+// and the branching node three steps of narrowing them; the colors of the
+// branching node are tried side by side in lanes.  With counters and partner
+// colors apart, the sums and minima over the wave in DPP steps and the colors
+// one after another a node took 0.79 us (k = 4, components that run to 10^4
+// nodes), this way MEASURED.
 template <int K>
-struct MinLane {
-  uint64_t nb;     // conflict neighbours
-  uint32_t part;   // stitch partner, 0xff none
-  int32_t col;     // color, -1 uncolored
-  uint64_t cnt;    // byte c: colored neighbours of color c
-  int32_t pcol;    // partner's color, -1 none or uncolored
+struct MinWords {
+  static constexpr int N = (K + 3) / 4;
+  uint32_t w[N];
 };
 
-template <int K>
-__device__ __forceinline__ uint32_t min_pen(const MinLane<K>& L, uint32_t c) {
-  return 10u * (uint32_t)((L.cnt >> (8 * c)) & 0xffu) + ((L.pcol >= 0 && L.pcol != (int32_t)c) ? 1u : 0u);
-}
-
-// Colors node v with c (on = true) or takes the color back.
-template <int K>
-__device__ __forceinline__ void min_set(MinLane<K>& L, uint32_t lane, uint32_t v, uint32_t c, bool on) {
-  const uint64_t one = 1ull << (8 * c);
-  if ((L.nb >> v) & 1ull) L.cnt = on ? L.cnt + one : L.cnt - one;
-  if (L.part == v) L.pcol = on ? (int32_t)c : -1;
-  if (lane == v) L.col = on ? (int32_t)c : -1;
+// on ? x : 0 in the lanes of `mask`.
+__device__ __forceinline__ uint32_t lanes_of(uint64_t mask, uint32_t x) {
+  uint32_t r;
+  asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(x), "s"(mask));
+  return r;
 }
 
 // Minimises the component of descriptor d (lane u holding u's neighbour
@@ -43,12 +46,11 @@ template <int K>
 __device__ int32_t minimize_core(const DevDesc& d, const uint64_t nb,
                                  const uint8_t* __restrict__ partners,
                                  int8_t* __restrict__ colors_base, uint32_t budget) {
+  constexpr int N = MinWords<K>::N;
   const uint32_t lane = __lane_id();
   const uint32_t n = uniform((uint32_t)d.n);
   const bool in = lane < n;
-  MinLane<K> L;
-  L.nb = nb;
-  L.part = in ? (uint32_t)partners[d.nbr_off + lane] : 0xffu;
+  const uint32_t part = in ? (uint32_t)partners[d.nbr_off + lane] : 0xffu;
   const int32_t inc = in ? (int32_t)colors_base[d.out_off + lane] : 0;
   // incumbent cost: conflict ends of each lane (each edge twice) and the
   // stitch pairs seen from their lower end
@@ -58,91 +60,119 @@ __device__ int32_t minimize_core(const DevDesc& d, const uint64_t nb,
     const uint64_t m = __ballot(in && inc == c);
     if (in && inc == c) same = m;
   }
-  const uint32_t pinc = (uint32_t)__shfl(inc, (int)(L.part & 63u));
-  const uint32_t ends = in ? (uint32_t)__popcll(L.nb & same) : 0u;
-  const uint32_t st = (in && L.part != 0xffu && L.part > lane && pinc != (uint32_t)inc) ? 1u : 0u;
+  const uint32_t pinc = (uint32_t)__shfl(inc, (int)(part & 63u));
+  const uint32_t ends = in ? (uint32_t)__popcll(nb & same) : 0u;
+  const uint32_t st = (in && part != 0xffu && part > lane && pinc != (uint32_t)inc) ? 1u : 0u;
   const uint32_t cost0 = uniform(10u * (wave_sum_u32(ends) / 2u) + wave_sum_u32(st));
   if (cost0 == 0u) return 0;
 
-  L.col = -1;
-  L.cnt = 0;
-  L.pcol = -1;
+  MinWords<K> X;
+  uint32_t ones[N];   // 1 in every color's byte
+#pragma unroll
+  for (int j = 0; j < N; ++j) {
+    ones[j] = 0;
+    X.w[j] = 0;
+    for (int c = 0; c < 4; ++c) {
+      if (4 * j + c < K) ones[j] |= 1u << (8 * c);
+      else X.w[j] |= 127u << (8 * c);
+    }
+  }
+  const uint32_t nb_lo = (uint32_t)nb, nb_hi = (uint32_t)(nb >> 32);
+  // Node v takes color c (or gives it back): its neighbours' byte c by 2, its
+  // partner's other bytes by 1.
+  const auto color = [&](uint32_t v, uint32_t c, bool on) {
+    const uint64_t nv = rdlane64(nb_lo, nb_hi, v);
+    const uint32_t p = rdlane(part, v), byte = 1u << (8u * (c & 3u));
+    const uint64_t pm = p < 64u ? 1ull << p : 0ull;
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      const uint32_t mine = (c >> 2) == (uint32_t)j ? byte : 0u;
+      const uint32_t x = lanes_of(nv, 2u * mine) + lanes_of(pm, ones[j] & ~mine);
+      X.w[j] = on ? X.w[j] + x : X.w[j] - x;
+    }
+  };
+  const auto penalty = [](uint32_t b) { return 10u * (b >> 1) + (b & 1u); };
+
+  uint64_t unc = n >= 64u ? ~0ull : (1ull << n) - 1ull;   // uncolored nodes
+  uint32_t col = 0;                                       // lane u: u's color on the path
   int32_t best_col = inc;
   uint32_t best = cost0, cost = 0, depth = 0, nodes = 0;
   bool stopped = false;
-  uint32_t fr = 0, flb = 0, fmp = 0, fcost = 0;   // stack, lane = depth
-  uint32_t v = 0, c0 = 0, lb = 0, mpv = 0;
-  bool enter = true;
+  uint32_t fr = 0, fb = 0;   // stack, lane = depth: node | color << 8 | least byte << 16; bound, cost
   for (;;) {
+    // ---- one node
+    if (nodes == budget) {
+      stopped = true;
+      break;
+    }
+    ++nodes;
+    uint32_t v = 0, c0 = 0, least = 0, lb = 0;
     bool down = false;
-    if (enter) {
-      if (nodes == budget) {
-        stopped = true;
-        break;
-      }
-      ++nodes;
-      const bool unc = in && L.col < 0;
-      if (__ballot(unc) == 0ull) {   // every node colored: cheaper than the incumbent?
-        if (cost < best) {
-          best = cost;
-          best_col = L.col;
-        }
-      } else {
-        uint32_t mp = 0xffffffffu, open = 0;
-#pragma unroll
-        for (int c = 0; c < K; ++c) {
-          mp = min(mp, min_pen<K>(L, (uint32_t)c));
-          open += ((L.cnt >> (8 * c)) & 0xffu) == 0u ? 1u : 0u;
-        }
-        lb = uniform(cost + wave_sum_u32(unc ? mp : 0u));
-        if (lb < best) {
-          const uint32_t key = wave_min_u32(unc ? (open << 8) | lane : 0xffffffffu);
-          v = uniform(key & 0xffu);
-          mpv = uniform(rdlane(mp, v));
-          c0 = 0;
-          down = true;
-        }
+    if (unc == 0ull) {   // every node colored: cheaper than the incumbent?
+      if (cost < best) {
+        best = cost;
+        best_col = (int32_t)col;
       }
     } else {
-      down = true;
+      uint32_t x = 127u, shut = 0;
+#pragma unroll
+      for (int j = 0; j < N; ++j) {
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x = min(x, (X.w[j] >> (8 * c)) & 0xffu);
+        shut += (uint32_t)__popc((X.w[j] + 0x7e7e7e7eu) & 0x80808080u);   // bytes of 2 and more
+      }
+      const uint32_t open = 4u * (uint32_t)N - shut;   // colors without a conflict: 0 .. K
+      uint32_t sum = (uint32_t)__builtin_popcountll(__ballot((x & 1u) != 0u) & unc) +
+                     10u * (uint32_t)__builtin_popcountll(__ballot((x & 2u) != 0u) & unc) +
+                     20u * (uint32_t)__builtin_popcountll(__ballot((x & 4u) != 0u) & unc);
+      const uint64_t more = __ballot(x >= 8u) & unc;   // four conflicts at least: rare
+      if (more != 0ull) sum += 10u * uniform(wave_sum_u32(lanes_of(more, x >> 3 << 2)));
+      uint64_t cand = unc;
+#pragma unroll
+      for (int b = K < 4 ? 1 : (K < 8 ? 2 : 3); b >= 0; --b) {
+        const uint64_t less = cand & ~__ballot(((open >> b) & 1u) != 0u);
+        cand = less != 0ull ? less : cand;
+      }
+      lb = cost + sum;
+      if (lb < best) {
+        v = low_bit(cand);
+        least = rdlane(x, v);
+        down = true;
+      }
     }
-    if (down) {
-      // the next color of v whose child bound stays below the incumbent
-      const uint64_t cntv = rdlane64((uint32_t)L.cnt, (uint32_t)(L.cnt >> 32), v);
-      const int32_t pcv = (int32_t)rdlane((uint32_t)L.pcol, v);
-      uint32_t take = K, pen = 0;
-      for (uint32_t c = c0; c < (uint32_t)K; ++c) {
-        const uint32_t p = 10u * (uint32_t)((cntv >> (8 * c)) & 0xffu) + ((pcv >= 0 && pcv != (int32_t)c) ? 1u : 0u);
-        if (lb - mpv + p < best) {
-          take = c;
-          pen = p;
+    for (;;) {
+      if (down) {
+        // the next color of v whose child bound stays below the incumbent
+        const uint32_t w0 = rdlane(X.w[0], v), w1 = rdlane(X.w[N - 1], v);
+        const uint32_t word = lane >= 4u ? w1 : w0;
+        const uint32_t pen = penalty((word >> (8u * (lane & 3u))) & 0xffu);
+        const uint64_t fits = __ballot(lane >= c0 && lane < (uint32_t)K && lb - penalty(least) + pen < best);
+        if (fits != 0ull) {
+          const uint32_t c = low_bit(fits);
+          fr = wrlane(fr, depth, v | (c << 8) | (least << 16));
+          fb = wrlane(fb, depth, lb | (cost << 16));
+          color(v, c, true);
+          col = wrlane(col, v, c);
+          unc &= ~(1ull << v);
+          cost += rdlane(pen, c);
+          ++depth;
           break;
         }
       }
-      if (take < (uint32_t)K) {
-        fr = wrlane(fr, depth, v | (take << 8));
-        flb = wrlane(flb, depth, lb);
-        fmp = wrlane(fmp, depth, mpv);
-        fcost = wrlane(fcost, depth, cost);
-        min_set<K>(L, lane, v, take, true);
-        cost += pen;
-        ++depth;
-        enter = true;
-        continue;
-      }
+      // back up one level: undo its row, go on with its next color
+      if (depth == 0u) break;
+      --depth;
+      const uint32_t f = uniform(rdlane(fr, depth)), b = uniform(rdlane(fb, depth));
+      v = f & 0xffu;
+      least = f >> 16;
+      lb = b & 0xffffu;
+      cost = b >> 16;
+      color(v, (f >> 8) & 0xffu, false);
+      unc |= 1ull << v;
+      c0 = ((f >> 8) & 0xffu) + 1u;
+      down = true;
     }
-    // back up one level: undo its row, go on with its next color
     if (depth == 0u) break;
-    --depth;
-    const uint32_t f = uniform(rdlane(fr, depth));
-    v = f & 0xffu;
-    const uint32_t c = f >> 8;
-    lb = uniform(rdlane(flb, depth));
-    mpv = uniform(rdlane(fmp, depth));
-    cost = uniform(rdlane(fcost, depth));
-    min_set<K>(L, lane, v, c, false);
-    c0 = c + 1;
-    enter = false;
   }
   if (in) colors_base[d.out_off + lane] = (int8_t)best_col;
   return stopped ? -(int32_t)nodes : (int32_t)nodes;
