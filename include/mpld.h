@@ -488,7 +488,7 @@ typedef struct {
   int32_t host_threads;    /* front-end threads; 0 = min(16, host cores)    */
   int32_t graph_builders;  /* device graph builders (own stream each) taken
                               in turn by layout requests of >= 4096 rects;
-                              0 = 1, < 0 = none (the host builds every graph) */
+                              0 = 2, < 0 = none (the host builds every graph) */
   int32_t device_split;    /* >= 0: device-built layouts whose average
                               conflict degree is below k are also simplified
                               and split on the device (mpld_split_graph_device's

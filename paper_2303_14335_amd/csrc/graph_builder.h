@@ -6,12 +6,20 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <condition_variable>
+#include <memory>
 #include <mutex>
+#include <vector>
 
 #include "internal.h"
 #include "runtime.h"
 
 namespace mpld {
+
+// Page-locked copies of one layout's rectangles and graph.
+struct Staging {
+  PinnedBuf in, out;
+};
 
 struct GraphBuilder {
   mpld_context* ctx = nullptr;
@@ -24,9 +32,47 @@ struct GraphBuilder {
   DevBuf split_ws;   // split outputs then scratch (int32)
   DevBuf flow_ws;    // scratch of the whole-layout flow
   PinnedBuf hin, hout;
+  // Layouts are copied in before and out after the builder's lock, from
+  // staging of their own, so that the device works for one caller while the
+  // others copy: kStagings layouts at most are on the way (four took the same
+  // 5.2 ms for a burst of 48 layouts, and twice the pinned memory).
+  static constexpr int kStagings = 2;
+  std::mutex smu;
+  std::condition_variable scv;
+  std::vector<std::unique_ptr<Staging>> spare;
+  int stagings = 0;   // made so far
   ~GraphBuilder() {
     if (own_stream && stream) (void)hipStreamDestroy(stream);
   }
+};
+
+// A staging taken from a builder, given back at the end of the scope.
+class StagingUse {
+ public:
+  explicit StagingUse(GraphBuilder& gb) : gb_(gb) {
+    std::unique_lock<std::mutex> lk(gb.smu);
+    gb.scv.wait(lk, [&] { return !gb.spare.empty() || gb.stagings < GraphBuilder::kStagings; });
+    if (gb.spare.empty()) {
+      gb.spare.emplace_back(new Staging());
+      ++gb.stagings;
+    }
+    st_ = std::move(gb.spare.back());
+    gb.spare.pop_back();
+  }
+  ~StagingUse() {
+    {
+      std::lock_guard<std::mutex> lk(gb_.smu);
+      gb_.spare.push_back(std::move(st_));
+    }
+    gb_.scv.notify_one();
+  }
+  StagingUse(const StagingUse&) = delete;
+  StagingUse& operator=(const StagingUse&) = delete;
+  Staging& operator*() { return *st_; }
+
+ private:
+  GraphBuilder& gb_;
+  std::unique_ptr<Staging> st_;
 };
 
 // Buffers grow geometrically: a reallocation (and, for pinned host memory,

@@ -1058,9 +1058,16 @@ void graph_builder_reserve(GraphBuilder& gb, int32_t nodes) {
   grow(gb.adj, ctx, 4 * adj);
   (void)scan_args(gb, (int64_t)std::max(cells / kScanTile, n / 32) + 1, 0);
   grow(gb.split_ws, ctx, 4 * (split_out_words((int64_t)n) + split_scratch_words((int64_t)n)));
-  if (!grow_pinned(gb.hin, 16 * n + 4 * (n + 1 + adj)) ||
-      !grow_pinned(gb.hout, 4 * (2 * n + 1 + adj + split_out_words((int64_t)n))))
-    fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+  for (int i = 0; i < GraphBuilder::kStagings; ++i) {
+    std::unique_ptr<Staging> sg(new Staging());
+    if (!grow_pinned(sg->in, 16 * n) ||
+        !grow_pinned(sg->out, 4 * (2 * n + 1 + adj + split_out_words((int64_t)n))))
+      fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+    std::lock_guard<std::mutex> sl(gb.smu);
+    if (gb.stagings == GraphBuilder::kStagings) break;
+    gb.spare.push_back(std::move(sg));
+    ++gb.stagings;
+  }
 }
 
 void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simplify, Split& s) {
@@ -1099,15 +1106,22 @@ void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simpli
   collect_split(gb.hout.as<int32_t>(), nn, s);
 }
 
-// Nodes, stitch pairs and search grid of a layout, on the device, and its
-// nodes in cell order; waits once, for the grid's bounds.  Returns the number
-// of nodes.  Caller holds the lock.
+// Copies the rectangles to the staging (before the builder's lock).
+static void stage_rects(Staging& sg, const mpld_rect* rects, int32_t n) {
+  const size_t bytes = sizeof(mpld_rect) * (size_t)n;
+  if (!grow_pinned(sg.in, bytes)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+  std::memcpy(sg.in.p, rects, bytes);
+}
+
+// Nodes, stitch pairs and search grid of a staged layout, on the device, and
+// its nodes in cell order; waits once, for the grid's bounds.  Returns the
+// number of nodes.  Caller holds the lock.
 struct LayoutGrid {
   GridParams g{};
   int32_t nn = 0, nse = 0;
   int64_t d2 = 0;
 };
-static LayoutGrid layout_cells(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
+static LayoutGrid layout_cells(GraphBuilder& gb, Staging& sg, const mpld_rect* rects, int32_t n, int32_t dmin,
                                int32_t split_len) {
   mpld_context* ctx = gb.ctx;
   hipStream_t s = gb.stream;
@@ -1119,13 +1133,11 @@ static LayoutGrid layout_cells(GraphBuilder& gb, const mpld_rect* rects, int32_t
   grow(gb.box, ctx, sizeof(int4) * most);
   grow(gb.partner, ctx, sizeof(int32_t) * most);
   grow(gb.se, ctx, sizeof(int32_t) * most);
-  if (!grow_pinned(gb.hin, sizeof(int4) * nr) || !grow_pinned(gb.hout, sizeof(LayoutHead)))
-    fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+  if (!grow_pinned(sg.out, sizeof(LayoutHead))) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
   auto* head = gb.rects.as<LayoutHead>();
   auto* drects = reinterpret_cast<int4*>(gb.rects.as<uint8_t>() + sizeof(LayoutHead));
   hipLaunchKernelGGL(layout_head_kernel, dim3(1), dim3(1), 0, s, head);
-  std::memcpy(gb.hin.p, rects, sizeof(int4) * nr);
-  check_hip(hipMemcpyAsync(drects, gb.hin.p, sizeof(int4) * nr, hipMemcpyHostToDevice, s),
+  check_hip(hipMemcpyAsync(drects, sg.in.p, sizeof(int4) * nr, hipMemcpyHostToDevice, s),
             "graph builder: upload rectangles");
   const int64_t tiles = (n + kScanTile - 1) / kScanTile;
   const ScanArgs sa = scan_args(gb, tiles, tiles);
@@ -1133,11 +1145,11 @@ static LayoutGrid layout_cells(GraphBuilder& gb, const mpld_rect* rects, int32_t
                      gb.box.as<int4>(), gb.partner.as<int32_t>(), gb.se.as<int2>(), head, sa.ticket, sa.base,
                      sa.status, sa.epoch);
   check_hip(hipGetLastError(), "graph builder: nodes");
-  check_hip(hipMemcpyAsync(gb.hout.p, head, sizeof(LayoutHead), hipMemcpyDeviceToHost, s),
+  check_hip(hipMemcpyAsync(sg.out.p, head, sizeof(LayoutHead), hipMemcpyDeviceToHost, s),
             "graph builder: bounds");
   check_hip(hipStreamSynchronize(s), "graph builder: bounds");
   LayoutHead h;
-  std::memcpy(&h, gb.hout.p, sizeof(h));
+  std::memcpy(&h, sg.out.p, sizeof(h));
   if (h.bad) {   // the host names the rectangle
     LayoutPrep lp;
     prepare_layout(rects, n, dmin, split_len, lp);
@@ -1182,7 +1194,7 @@ static LayoutGrid layout_cells(GraphBuilder& gb, const mpld_rect* rects, int32_t
 // nodes in cell order: offsets in gb.ptr, lists in gb.adj; waits for their
 // total, which it returns.
 template <bool UP>
-static int32_t layout_lists(GraphBuilder& gb, const LayoutGrid& L) {
+static int32_t layout_lists(GraphBuilder& gb, Staging& sg, const LayoutGrid& L) {
   hipStream_t s = gb.stream;
   const dim3 blocks((unsigned)((L.nn + 255) / 256));
   constexpr int64_t kWords = UP ? 2 : 1;
@@ -1190,7 +1202,7 @@ static int32_t layout_lists(GraphBuilder& gb, const LayoutGrid& L) {
                      gb.start.as<int32_t>(), L.nn, L.g, L.d2, gb.deg.as<int32_t>(), gb.kept.as<int32_t>());
   scan(gb, gb.deg.as<int32_t>(), L.nn, gb.ptr.as<int32_t>());
   int32_t total = 0;
-  check_hip(hipMemcpyAsync(gb.hout.p, gb.ptr.as<int32_t>() + L.nn, sizeof(int32_t), hipMemcpyDeviceToHost, s),
+  check_hip(hipMemcpyAsync(sg.out.p, gb.ptr.as<int32_t>() + L.nn, sizeof(int32_t), hipMemcpyDeviceToHost, s),
             "graph builder: edge total");
   // the lists go where the last layouts' went while the total is on its way;
   // a longer one is written again once its room is known
@@ -1203,7 +1215,7 @@ static int32_t layout_lists(GraphBuilder& gb, const LayoutGrid& L) {
     check_hip(hipGetLastError(), "graph builder: neighbours");
     if (pass == 0) {
       check_hip(hipStreamSynchronize(s), "graph builder: counts");
-      std::memcpy(&total, gb.hout.p, sizeof(total));
+      std::memcpy(&total, sg.out.p, sizeof(total));
       if (total <= room) break;
       grow(gb.adj, gb.ctx, 4 * (size_t)kWords * (size_t)total);
     }
@@ -1224,40 +1236,44 @@ bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
     }
     return split != nullptr;
   }
-  std::lock_guard<std::mutex> lk(gb.mu);
-  const LayoutGrid L = layout_cells(gb, rects, n, dmin, split_len);
-  hipStream_t s = gb.stream;
-  const int32_t nn = L.nn;
-  const size_t nb = (size_t)nn;
-  const int32_t total = layout_lists<false>(gb, L);
-  if (split && !device_split_pays(nn, total, k)) split = nullptr;   // the caller splits on the host
-  if (split) enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), total, k, simplify);
-  const size_t split_words = split ? split_out_words(nn) : 0;
-  const size_t out_bytes = sizeof(int32_t) * ((nb + 1) + nb + (size_t)total + split_words);
-  if (!grow_pinned(gb.hout, out_bytes)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
-  int32_t* hptr = static_cast<int32_t*>(gb.hout.p);
-  int32_t* hmate = hptr + nb + 1;
-  int32_t* hadj = hmate + nb;
-  int32_t* hsplit = hadj + total;
-  if (split)
-    check_hip(hipMemcpyAsync(hsplit, gb.split_ws.p, sizeof(int32_t) * split_words,
-                             hipMemcpyDeviceToHost, s),
-              "graph builder: download split");
-  check_hip(hipMemcpyAsync(hptr, gb.ptr.p, sizeof(int32_t) * (nb + 1), hipMemcpyDeviceToHost, s),
-            "graph builder: download offsets");
-  check_hip(hipMemcpyAsync(hmate, gb.partner.p, sizeof(int32_t) * nb, hipMemcpyDeviceToHost, s),
-            "graph builder: download partners");
-  if (total)
-    check_hip(hipMemcpyAsync(hadj, gb.adj.p, sizeof(int32_t) * (size_t)total,
-                             hipMemcpyDeviceToHost, s),
-              "graph builder: download lists");
-  check_hip(hipStreamSynchronize(s), "graph builder");
+  StagingUse use(gb);
+  Staging& sg = *use;
+  stage_rects(sg, rects, n);
+  int32_t nn = 0, total = 0;
+  size_t nb = 0;
+  {
+    std::lock_guard<std::mutex> lk(gb.mu);
+    const LayoutGrid L = layout_cells(gb, sg, rects, n, dmin, split_len);
+    hipStream_t s = gb.stream;
+    nn = L.nn;
+    nb = (size_t)nn;
+    total = layout_lists<false>(gb, sg, L);
+    if (split && !device_split_pays(nn, total, k)) split = nullptr;   // the caller splits on the host
+    if (split) enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), total, k, simplify);
+    const size_t split_words = split ? split_out_words(nn) : 0;
+    const size_t out_bytes = sizeof(int32_t) * ((nb + 1) + nb + (size_t)total + split_words);
+    if (!grow_pinned(sg.out, out_bytes)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+    int32_t* h = sg.out.as<int32_t>();
+    const auto down = [&](int32_t* to, const void* p, size_t words) {
+      if (words)
+        check_hip(hipMemcpyAsync(to, p, sizeof(int32_t) * words, hipMemcpyDeviceToHost, s),
+                  "graph builder: download");
+    };
+    down(h, gb.ptr.p, nb + 1);
+    down(h + nb + 1, gb.partner.p, nb);
+    down(h + 2 * nb + 1, gb.adj.p, (size_t)total);
+    down(h + 2 * nb + 1 + total, gb.split_ws.p, split_words);
+    check_hip(hipStreamSynchronize(s), "graph builder");
+  }
+  const int32_t* hptr = sg.out.as<int32_t>();
+  const int32_t* hmate = hptr + nb + 1;
+  const int32_t* hadj = hmate + nb;
   g.n = nn;
   g.ptr.assign(hptr, hptr + nb + 1);
   g.partner.assign(hmate, hmate + nb);
   g.adj.assign(hadj, hadj + total);
   g.num_ce = total / 2;
-  if (split) collect_split(hsplit, nn, *split);
+  if (split) collect_split(hadj + total, nn, *split);
   return split != nullptr;
 }
 
@@ -1269,23 +1285,30 @@ void build_layout_pairs_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
     prepare_layout(rects, n, dmin, split_len, lp);
     return;
   }
-  std::lock_guard<std::mutex> lk(gb.mu);
-  const LayoutGrid L = layout_cells(gb, rects, n, dmin, split_len);
-  hipStream_t s = gb.stream;
-  const size_t total = (size_t)layout_lists<true>(gb, L), nse = (size_t)L.nse;
-  if (!grow_pinned(gb.hout, 8 * (total + nse) + 8)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
-  int32_t* h = gb.hout.as<int32_t>();
-  if (total)
-    check_hip(hipMemcpyAsync(h, gb.adj.p, 8 * total, hipMemcpyDeviceToHost, s), "graph builder: download pairs");
-  if (nse)
-    check_hip(hipMemcpyAsync(h + 2 * total, gb.se.p, 8 * nse, hipMemcpyDeviceToHost, s),
-              "graph builder: download stitch pairs");
-  out.num_nodes = L.nn;
+  StagingUse use(gb);
+  Staging& sg = *use;
+  stage_rects(sg, rects, n);
+  size_t total = 0, nse = 0;
+  {
+    std::lock_guard<std::mutex> lk(gb.mu);
+    const LayoutGrid L = layout_cells(gb, sg, rects, n, dmin, split_len);
+    hipStream_t s = gb.stream;
+    total = (size_t)layout_lists<true>(gb, sg, L);
+    nse = (size_t)L.nse;
+    out.num_nodes = L.nn;
+    if (!grow_pinned(sg.out, 8 * (total + nse) + 8)) fail(MPLD_E_NOMEM, "graph builder: pinned host memory");
+    int32_t* h = sg.out.as<int32_t>();
+    if (total)
+      check_hip(hipMemcpyAsync(h, gb.adj.p, 8 * total, hipMemcpyDeviceToHost, s), "graph builder: download pairs");
+    if (nse)
+      check_hip(hipMemcpyAsync(h + 2 * total, gb.se.p, 8 * nse, hipMemcpyDeviceToHost, s),
+                "graph builder: download stitch pairs");
+    out.ce.reset(new int32_t[2 * (total + nse) + 1]);
+    check_hip(hipStreamSynchronize(s), "graph builder");
+  }
   out.num_ce = (int64_t)total;
   out.num_se = (int64_t)nse;
-  out.ce.reset(new int32_t[2 * (total + nse) + 1]);
-  check_hip(hipStreamSynchronize(s), "graph builder");
-  std::memcpy(out.ce.get(), h, 8 * (total + nse));
+  std::memcpy(out.ce.get(), sg.out.p, 8 * (total + nse));
 }
 
 }  // namespace mpld

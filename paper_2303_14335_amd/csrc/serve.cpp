@@ -564,9 +564,13 @@ int32_t mpld_server_create(mpld_context* ctx, const mpld_server_options* opt, mp
       check_hip(hipStreamCreate(&x->lds_stream), "serve: LDS stream");
       check_hip(hipEventCreateWithFlags(&x->up_ev, hipEventDisableTiming), "serve: event");
       x->counter.alloc(ctx, sizeof(int32_t) * 4);
-      // one builder by default: with four, the measured p99 latency of a
-      // Poisson mix of layout requests rose by about a third
-      const int nb = o.graph_builders == 0 ? 1 : std::max(0, o.graph_builders);
+      // two builders by default: each is a chain of some thirty short
+      // launches and two waits per layout, which leaves most of the device
+      // idle.  A burst of 48 layouts of 100 to 50,000 rects: one 7.8 ms, two
+      // 5.3, three 5.8; 1,000 Poisson arrivals at 500/s, three traces, p99:
+      // one 2.04 / 2.02 / 2.34 ms, two 2.07 / 1.94 / 2.04, three 1.89 / 1.93
+      // / 2.16
+      const int nb = o.graph_builders == 0 ? 2 : std::max(0, o.graph_builders);
       for (int i = 0; i < nb; ++i) {
         x->gbuilders.push_back(graph_builder_create(ctx, true));
         // sized ahead for layouts of up to 64k nodes: growing a builder

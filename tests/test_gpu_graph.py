@@ -105,3 +105,27 @@ def test_served_dense_layouts(ctx, n, side, dmin):
         c.close()
     assert np.array_equal(got.colors, ref.colors) and np.array_equal(got.component_of, ref.comp_of)
     assert np.array_equal(got.components["nodes"], ref.comps["nodes"])
+
+
+@pytest.mark.parametrize("builders", [1, 0])
+def test_served_more_layouts_than_stagings(builders):
+    """Layouts of growing and falling sizes wait for the builders' staging
+    (two layouts each): every answer is the one of its own layout."""
+    import paper_2303_14335_amd as mp
+    sizes = [4096, 5200, 9000, 4100, 20000, 4500, 12000, 4096, 16000, 6000]
+    layouts = [workload.generate(n, int((n * 33.3e3) ** 0.5), 40 + i)[0] for i, n in enumerate(sizes)]
+    refs = [oracle.decompose(oracle.build_graph(r, 100, 0), 3, 2000) for r in layouts]
+    say("served bursts, builders", builders)
+    c = mp.Context(0)
+    try:
+        srv = mp.Server(c, graph_builders=builders)
+        for _ in range(2):
+            tickets = [srv.submit_layout(r, 100, 0, 3, 2000) for r in layouts]
+            for t, ref in zip(tickets, refs):
+                got = srv.wait(t)
+                assert np.array_equal(got.colors, ref.colors)
+                assert np.array_equal(got.component_of, ref.comp_of)
+                assert np.array_equal(got.components["nodes"], ref.comps["nodes"])
+        srv.close()
+    finally:
+        c.close()
