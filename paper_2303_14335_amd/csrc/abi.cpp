@@ -259,6 +259,8 @@ int32_t mpld_context_destroy(mpld_context* ctx) {
   if (ctx->graph_builder) graph_builder_destroy(ctx->graph_builder);
   for (auto& e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
+  if (ctx->up) (void)hipHostFree(ctx->up);
+  if (ctx->down) (void)hipHostFree(ctx->down);
   if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
   delete ctx;
   return MPLD_OK;

@@ -28,25 +28,25 @@ constexpr size_t kScratchBytes = MPLD_NOALLOC_SCRATCH_BYTES;
 constexpr int32_t kNoallocMaxComps = MPLD_NOALLOC_MAX_COMPONENTS;
 constexpr int kNoallocMaxDevices = 64;
 
-static __device__ __align__(256) uint8_t scratch[kScratchBytes];
-
-// Clears `n` 32-bit words (a kernel, not a memset, so that a caller may
-// capture the call in a HIP graph).
-__global__ void noalloc_clear_kernel(uint32_t* p, uint32_t n) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) p[i] = 0u;
-}
+// 256 bytes more than the limit: the items' end is rounded up before the records
+static __device__ __align__(256) uint8_t scratch[kScratchBytes + 256];
 
 namespace {
 
-// Host staging, static: packed items, launch order, component offsets and
-// the records read back.
+constexpr size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Up to this many bytes of colors are read back with the records in one copy:
+// a second one of a few hundred bytes takes some 20 us by itself.
+constexpr size_t kTogetherBytes = 64 << 10;
+
+// Host staging, static: the scratch's front as uploaded (queue counter and
+// packed items), launch order, component offsets and what is read back.
 struct NoallocStage {
   std::mutex mu;
-  uint8_t items[kScratchBytes];
+  uint8_t front[kScratchBytes];
   int32_t order[kNoallocMaxComps];
   int32_t offs[kNoallocMaxComps];
-  DevRecord recs[kNoallocMaxComps];
+  uint8_t back[up256(sizeof(DevRecord) * kNoallocMaxComps) + kTogetherBytes];
 };
 NoallocStage g_stage;
 
@@ -65,8 +65,6 @@ uint8_t* scratch_on(int dev) {
   }
   return static_cast<uint8_t*>(g_addr[dev]);
 }
-
-constexpr size_t up256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 void solve_noalloc(mpld_context* ctx, const mpld_component* comps, int32_t count,
                    const mpld_options* opt, mpld_comp_record* out, int8_t* colors_out) {
@@ -100,9 +98,13 @@ void solve_noalloc(mpld_context* ctx, const mpld_component* comps, int32_t count
   }
   const uint32_t width = reg_item_width(max_n);
   const size_t stride = kRegItemHead + 8u * (size_t)width;
-  const size_t off_recs = 256, off_colors = off_recs + up256(sizeof(DevRecord) * (size_t)count),
-               off_items = off_colors + up256((size_t)total_nodes),
-               need = off_items + stride * (size_t)count;
+  // the queue counter and the items, uploaded by one copy; the records and
+  // the colors behind them
+  const size_t off_items = 256, items_end = off_items + stride * (size_t)count,
+               off_recs = up256(items_end),
+               off_colors = off_recs + up256(sizeof(DevRecord) * (size_t)count),
+               need = off_items + up256(sizeof(DevRecord) * (size_t)count) +
+                      up256((size_t)total_nodes) + stride * (size_t)count;
   if (need > kScratchBytes)
     fail(MPLD_E_INVALID, "the components need " + std::to_string(need) +
                              " bytes of device scratch; the allocation-free solve has " +
@@ -124,7 +126,7 @@ void solve_noalloc(mpld_context* ctx, const mpld_component* comps, int32_t count
   for (int32_t i = 0; i < count; ++i) {
     const int32_t c = g_stage.order[i];
     const mpld_component& cp = comps[c];
-    uint8_t* it = g_stage.items + stride * (size_t)i;
+    uint8_t* it = g_stage.front + off_items + stride * (size_t)i;
     DevDesc d{};
     d.n = cp.n;
     d.k = opt->k;
@@ -152,11 +154,8 @@ void solve_noalloc(mpld_context* ctx, const mpld_component* comps, int32_t count
   DevRecord* recs = reinterpret_cast<DevRecord*>(dev + off_recs);
   int8_t* colors = reinterpret_cast<int8_t*>(dev + off_colors);
   uint8_t* items = dev + off_items;
-  hipLaunchKernelGGL(noalloc_clear_kernel, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(dev),
-                     64u);
-  check_hip(hipGetLastError(), "clear the queue counter");
-  check_hip(hipMemcpyAsync(items, g_stage.items, stride * (size_t)count, hipMemcpyHostToDevice, s),
-            "upload items");
+  std::memset(g_stage.front, 0, off_items);
+  check_hip(hipMemcpyAsync(dev, g_stage.front, items_end, hipMemcpyHostToDevice, s), "upload items");
   const RegItems ri{items, width, (uint32_t)stride, 0u};
   const bool trace = opt->flags & MPLD_TRACE_HASH;
   const int cap = ctx->num_cus * ctx->reg_blocks_per_cu;
@@ -164,15 +163,20 @@ void solve_noalloc(mpld_context* ctx, const mpld_component* comps, int32_t count
   check_hip(launch_reg_batched(trace, opt->k, grid, 4, ri, count, counter, recs, colors, ~0ull, 0, 16u,
                                (opt->flags & MPLD_MARK_CONFLICTS) != 0, s),
             "register-tier launch");
-  check_hip(hipMemcpyAsync(g_stage.recs, recs, sizeof(DevRecord) * (size_t)count,
+  const bool together = (size_t)total_nodes <= kTogetherBytes;
+  check_hip(hipMemcpyAsync(g_stage.back, recs,
+                           together ? off_colors - off_recs + (size_t)total_nodes
+                                    : sizeof(DevRecord) * (size_t)count,
                            hipMemcpyDeviceToHost, s), "download records");
-  if (total_nodes)
+  if (!together)
     check_hip(hipMemcpyAsync(colors_out, colors, (size_t)total_nodes, hipMemcpyDeviceToHost, s),
               "download colors");
   check_hip(hipStreamSynchronize(s), "allocation-free solve");
+  if (together) std::memcpy(colors_out, g_stage.back + (off_colors - off_recs), (size_t)total_nodes);
   const bool colored_marked = opt->flags & MPLD_MARK_CONFLICTS;
   for (int32_t c = 0; c < count; ++c) {
-    const DevRecord& dr = g_stage.recs[c];
+    DevRecord dr;
+    std::memcpy(&dr, g_stage.back + sizeof(DevRecord) * (size_t)c, sizeof(dr));
     if (dr.status < 0 || dr.status > MPLD_BUDGET_EXHAUSTED)
       fail(MPLD_E_INTERNAL, "search reported a broken state");
     mpld_comp_record& r = out[c];

@@ -164,6 +164,34 @@ void image_finish(Image& im, int order) {
 
 // ---------------------------------------------------------------------------
 
+static uint8_t* stage(void*& p, size_t& bytes, size_t n, PinnedBuf& own) {
+  if (n > kStageMax) {
+    if (!own.reserve(n)) fail(MPLD_E_NOMEM, "page-locked staging");
+    return own.as<uint8_t>();
+  }
+  if (n > bytes) {
+    const size_t want = std::min(kStageMax, std::max({kStageMin, 2 * bytes, n}));
+    if (p) (void)hipHostFree(p);
+    p = nullptr;
+    bytes = 0;
+    if (hipHostMalloc(&p, want, hipHostMallocDefault) != hipSuccess) {
+      p = nullptr;
+      fail(MPLD_E_NOMEM, "page-locked staging");
+    }
+    bytes = want;
+  }
+  return static_cast<uint8_t*>(p);
+}
+
+uint8_t* stage_up(mpld_context* ctx, size_t n, PinnedBuf& own) {
+  check_hip(hipStreamSynchronize(ctx->stream), "staging");
+  return stage(ctx->up, ctx->up_bytes, n, own);
+}
+
+uint8_t* stage_down(mpld_context* ctx, size_t n, PinnedBuf& own) {
+  return stage(ctx->down, ctx->down_bytes, n, own);
+}
+
 DeviceBatch::~DeviceBatch() {
   if (graph) hipGraphExecDestroy(graph);
   for (hipEvent_t e : rt_ev)
@@ -177,6 +205,8 @@ static int blocks_for_lds(mpld_context* ctx, int lds_bytes) {
   by_lds = std::max(1, std::min(by_lds, 32));
   return by_lds * ctx->num_cus;
 }
+
+static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tune& tune,
                    FlowGraph* flow) {
@@ -296,12 +326,36 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
     }
   }
 
-  db.desc.alloc(ctx, sizeof(DevDesc) * ordered.size());
-  db.regitems.alloc(ctx, item_bytes);
-  db.adj32.alloc(ctx, sizeof(uint32_t) * (size_t)im.adj_words);
-  db.counters.alloc(ctx, sizeof(int32_t) * 8);
-  db.recs.alloc(ctx, sizeof(DevRecord) * im.desc.size());
-  db.colors.alloc(ctx, (size_t)im.total_nodes);
+  const size_t desc_bytes = sizeof(DevDesc) * ordered.size();
+  const size_t adj_bytes = sizeof(uint32_t) * (size_t)im.adj_words;
+  size_t used = 0;
+  const auto place = [&](size_t n) {
+    const size_t at = used;
+    used += align256(n ? n : 256);
+    return at;
+  };
+  const size_t at_counters = place(sizeof(int32_t) * 8), at_desc = place(desc_bytes),
+               at_items = place(item_bytes), at_adj = place(adj_bytes), up_bytes = used;
+  const size_t at_recs = place(sizeof(DevRecord) * im.desc.size()),
+               at_colors = place((size_t)im.total_nodes);
+  const size_t min_bytes = im.minimize ? sizeof(int32_t) * std::max<size_t>(im.desc.size(), 1) : 0,
+               partner_bytes = im.minimize ? std::max<size_t>((size_t)im.mask_words, 1) : 0;
+  const size_t at_min = im.minimize ? place(min_bytes) : 0,
+               at_partners = im.minimize ? place(partner_bytes) : 0;
+  db.mem.alloc(ctx, used);
+  db.counters.view(db.mem, at_counters, sizeof(int32_t) * 8);
+  db.desc.view(db.mem, at_desc, desc_bytes);
+  db.regitems.view(db.mem, at_items, item_bytes);
+  db.adj32.view(db.mem, at_adj, adj_bytes);
+  db.recs.view(db.mem, at_recs, sizeof(DevRecord) * im.desc.size());
+  db.colors.view(db.mem, at_colors, (size_t)im.total_nodes);
+  db.partners.release();
+  db.min_out.release();
+  if (im.minimize) {
+    db.min_out.view(db.mem, at_min, min_bytes);
+    db.partners.view(db.mem, at_partners, partner_bytes);
+  }
+  db.got.clear();
   db.gstack.release();
   db.dev_keys.release();
   db.dev_stacks.release();
@@ -313,42 +367,43 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   }
 
   hipStream_t s = ctx->stream;
-  if (!ordered.empty())
-    check_hip(hipMemcpyAsync(db.desc.p, ordered.data(), sizeof(DevDesc) * ordered.size(),
-                             hipMemcpyHostToDevice, s), "upload descriptors");
-  if (!items.empty())
-    check_hip(hipMemcpyAsync(db.regitems.p, items.data(), items.size(),
-                             hipMemcpyHostToDevice, s), "upload register items");
-  if (!im.adj32.empty())
-    check_hip(hipMemcpyAsync(db.adj32.p, im.adj32.data(), sizeof(uint32_t) * im.adj32.size(),
-                             hipMemcpyHostToDevice, s), "upload adjacency");
-  check_hip(hipMemsetAsync(db.counters.p, 0, sizeof(int32_t) * 8, s), "clear counters");
+  // the counters' zeros and all that is packed here, in one copy where it
+  // fits the staging
+  const size_t staged = flow ? at_items : up_bytes;
+  if (staged <= kStageMin) {
+    uint8_t* up = stage_up(ctx, staged, db.sp_host_tasks);
+    std::memset(up, 0, sizeof(int32_t) * 8);
+    if (desc_bytes) std::memcpy(up + at_desc, ordered.data(), desc_bytes);
+    if (!items.empty()) std::memcpy(up + at_items, items.data(), items.size());
+    if (!im.adj32.empty()) std::memcpy(up + at_adj, im.adj32.data(), sizeof(uint32_t) * im.adj32.size());
+    check_hip(hipMemcpyAsync(db.mem.p, up, staged, hipMemcpyHostToDevice, s), "upload");
+  } else {
+    if (!ordered.empty())
+      check_hip(hipMemcpyAsync(db.desc.p, ordered.data(), desc_bytes, hipMemcpyHostToDevice, s),
+                "upload descriptors");
+    if (!items.empty())
+      check_hip(hipMemcpyAsync(db.regitems.p, items.data(), items.size(),
+                               hipMemcpyHostToDevice, s), "upload register items");
+    if (!im.adj32.empty())
+      check_hip(hipMemcpyAsync(db.adj32.p, im.adj32.data(), sizeof(uint32_t) * im.adj32.size(),
+                               hipMemcpyHostToDevice, s), "upload adjacency");
+    check_hip(hipMemsetAsync(db.counters.p, 0, sizeof(int32_t) * 8, s), "clear counters");
+  }
   if (db.n_dev)
     check_hip(hipMemsetAsync(db.dev_keys.p, 0xff, sizeof(uint64_t) * 4, s), "clear keys");
   db.device_packed = flow != nullptr;
   db.rt_ready = false;
-  db.partners.release();
-  db.min_out.release();
-  if (im.minimize) {
-    db.partners.alloc(ctx, std::max<size_t>((size_t)im.mask_words, 1));
-    db.min_out.alloc(ctx, sizeof(int32_t) * std::max<size_t>(im.desc.size(), 1));
-  }
   if (flow) {   // the descriptors' copy is staged; nothing else waits
     db.host_items.clear();
     flow_pack(*flow, db, s);
     return;
   }
-  check_hip(hipStreamSynchronize(s), "upload");
+  if (im.minimize && !im.partner8.empty())
+    check_hip(hipMemcpyAsync(db.partners.p, im.partner8.data(), im.partner8.size(),
+                             hipMemcpyHostToDevice, s), "upload stitch partners");
+  if (staged > kStageMin || im.minimize) check_hip(hipStreamSynchronize(s), "upload");
   db.host_items = std::move(items);
-  if (im.minimize) {
-    if (!im.partner8.empty())
-      check_hip(hipMemcpyAsync(db.partners.p, im.partner8.data(), im.partner8.size(),
-                               hipMemcpyHostToDevice, s), "upload stitch partners");
-    check_hip(hipStreamSynchronize(s), "upload");
-  }
 }
-
-static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 void device_roundtrip(DeviceBatch& db, const Image& im, uint32_t flags) {
   mpld_context* ctx = db.ctx;
@@ -535,17 +590,32 @@ constexpr int32_t kEnginePoolCap = 1 << 21;   // split items (16 B each)
 constexpr int32_t kEngineMaxRounds = 96;      // depth <= 64: far more than needed
 constexpr int32_t kEngineRoundsPerCheck = 3;  // rounds enqueued between looks at the head
 
-static void heavy_engine_device(DeviceBatch& db, bool trace) {
+// Records of the first pass, by component.  last: no launch follows if no
+// component stopped at the first cap, so the colors come along (where both
+// are small) and are kept for device_fetch.
+static const DevRecord* first_pass(DeviceBatch& db, bool last) {
+  mpld_context* ctx = db.ctx;
+  const size_t nr = sizeof(DevRecord) * (size_t)db.num_comps, all = db.result_bytes(false);
+  const bool whole = last && all <= kStageMin;
+  uint8_t* h = stage_down(ctx, std::max<size_t>(whole ? all : nr, 1), db.sp_host_recs);
+  check_hip(hipMemcpyAsync(h, db.recs.p, whole ? all : nr, hipMemcpyDeviceToHost, ctx->stream),
+            "heavy: records");
+  check_hip(hipStreamSynchronize(ctx->stream), "heavy: first pass");
+  const auto* recs = reinterpret_cast<const DevRecord*>(h);
+  if (whole) {
+    for (int32_t i = 0; i < db.n_reg; ++i)
+      if (recs[db.host_desc[(size_t)i].comp].status < 0) return recs;
+    db.got.assign(h, h + all);
+  }
+  return recs;
+}
+
+static void heavy_engine_device(DeviceBatch& db, bool trace, bool last) {
   mpld_context* ctx = db.ctx;
   hipStream_t s = ctx->stream;
   db.sp_rounds = db.sp_tasks_run = db.sp_heavy = db.sp_reruns = 0;
   // which register-tier components stopped at the first cap
-  if (!db.sp_host_recs.reserve(sizeof(DevRecord) * (size_t)std::max(1, db.num_comps)))
-    fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
-  const DevRecord* recs = db.sp_host_recs.as<DevRecord>();
-  check_hip(hipMemcpyAsync(db.sp_host_recs.p, db.recs.p, sizeof(DevRecord) * (size_t)db.num_comps,
-                           hipMemcpyDeviceToHost, s), "heavy: records");
-  check_hip(hipStreamSynchronize(s), "heavy: first pass");
+  const DevRecord* recs = first_pass(db, last);
   std::vector<int32_t> heavy;   // launch-order register items
   for (int32_t i = 0; i < db.n_reg; ++i)
     if (recs[db.host_desc[i].comp].status < 0) heavy.push_back(i);
@@ -575,8 +645,7 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
   // staging: the meta area, then the root tasks
   const size_t roots_at = (meta_bytes + 255) / 256 * 256;
   const size_t stage_bytes = roots_at + sizeof(EngineTask) * (size_t)H;
-  if (!db.sp_host_tasks.reserve(stage_bytes)) fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
-  uint8_t* st = db.sp_host_tasks.as<uint8_t>();
+  uint8_t* st = stage_up(ctx, stage_bytes, db.sp_host_tasks);
   std::memset(st, 0, stage_bytes);
   EngineHead* h0 = reinterpret_cast<EngineHead*>(st);
   h0->alloc = H;
@@ -598,7 +667,7 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
   auto* blocks = db.en_blocks.as<uint8_t>();
   auto* pool = db.en_pool.as<EngineItem>();
   // head read back into the result staging area
-  if (!db.sp_host_out.reserve(sizeof(EngineHead))) fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
+  uint8_t* hd = stage_down(ctx, sizeof(EngineHead), db.sp_host_out);
   EngineHead hh{};
   for (int32_t r = 0;;) {
     for (int i = 0; i < kEngineRoundsPerCheck; ++i, ++r) {
@@ -608,10 +677,10 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
                                     (uint64_t)db.tune.heavy_round_cap, (uint32_t)levels, trace, s),
                 "heavy: round");
     }
-    check_hip(hipMemcpyAsync(db.sp_host_out.p, head, sizeof(EngineHead), hipMemcpyDeviceToHost, s),
+    check_hip(hipMemcpyAsync(hd, head, sizeof(EngineHead), hipMemcpyDeviceToHost, s),
               "heavy: engine head");
     check_hip(hipStreamSynchronize(s), "heavy: rounds");
-    std::memcpy(&hh, db.sp_host_out.p, sizeof(hh));
+    std::memcpy(&hh, hd, sizeof(hh));
     if (std::min(hh.alloc, kEngineTaskCap) == hh.end) break;   // the last round added no task
     if (r >= kEngineMaxRounds) fail(MPLD_E_INTERNAL, "heavy-component engine: too many rounds");
   }
@@ -621,19 +690,18 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
   db.sp_tasks_run = ntasks;
   const size_t blocks_bytes = (size_t)kSplitBlockBytes * (size_t)ntasks;
   const size_t items_at = (blocks_bytes + 255) / 256 * 256;
-  if (!db.sp_host_out.reserve(items_at + sizeof(EngineItem) * (size_t)nitems))
-    fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
-  check_hip(hipMemcpyAsync(db.sp_host_out.p, blocks, blocks_bytes, hipMemcpyDeviceToHost, s),
+  hd = stage_down(ctx, items_at + sizeof(EngineItem) * (size_t)nitems, db.sp_host_out);
+  check_hip(hipMemcpyAsync(hd, blocks, blocks_bytes, hipMemcpyDeviceToHost, s),
             "heavy: result blocks");
   if (nitems > 0)
-    check_hip(hipMemcpyAsync(db.sp_host_out.as<uint8_t>() + items_at, pool, sizeof(EngineItem) * (size_t)nitems,
+    check_hip(hipMemcpyAsync(hd + items_at, pool, sizeof(EngineItem) * (size_t)nitems,
                              hipMemcpyDeviceToHost, s), "heavy: items");
   check_hip(hipStreamSynchronize(s), "heavy: results");
   // one sequential copy out of the page-locked staging area: the walk
   // below reads the blocks and items in tree order, and scattered reads of
   // page-locked memory cost several times more than of ordinary memory
   db.sp_host_copy.resize(items_at + sizeof(EngineItem) * (size_t)nitems);
-  std::memcpy(db.sp_host_copy.data(), db.sp_host_out.p, db.sp_host_copy.size());
+  std::memcpy(db.sp_host_copy.data(), hd, db.sp_host_copy.size());
   const uint8_t* hb = db.sp_host_copy.data();
   const EngineItem* hi = reinterpret_cast<const EngineItem*>(hb + items_at);
   auto result = [&](int32_t t) {
@@ -704,12 +772,11 @@ static void heavy_engine_device(DeviceBatch& db, bool trace) {
       check_hip(launch_reg_single(trace, db.k, db.reg_items(), item, db.recs.as<DevRecord>(),
                                   db.colors.as<int8_t>(), s), "heavy: sequential re-run");
   if (!wb.empty()) {
-    if (!db.sp_host_writes.reserve(sizeof(HeavyWrite) * wb.size()))
-      fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
+    uint8_t* up = stage_up(ctx, sizeof(HeavyWrite) * wb.size(), db.sp_host_writes);
     if (db.sp_writes.bytes < sizeof(HeavyWrite) * wb.size())
       db.sp_writes.alloc(ctx, sizeof(HeavyWrite) * wb.size());
-    std::memcpy(db.sp_host_writes.p, wb.data(), sizeof(HeavyWrite) * wb.size());
-    check_hip(hipMemcpyAsync(db.sp_writes.p, db.sp_host_writes.p, sizeof(HeavyWrite) * wb.size(),
+    std::memcpy(up, wb.data(), sizeof(HeavyWrite) * wb.size());
+    check_hip(hipMemcpyAsync(db.sp_writes.p, up, sizeof(HeavyWrite) * wb.size(),
                              hipMemcpyHostToDevice, s), "heavy: write-back upload");
     check_hip(launch_heavy_writeback(db.sp_writes.as<HeavyWrite>(), (int32_t)wb.size(),
                                      db.recs.as<DevRecord>(), db.colors.as<int8_t>(), s),
@@ -949,29 +1016,24 @@ static void csr_split(DeviceBatch& db, bool trace) {
   check_hip(hipStreamSynchronize(s), "subtree tasks: write-back");
 }
 
-static void heavy_engine_host(DeviceBatch& db);
+static void heavy_engine_host(DeviceBatch& db, bool last);
 
 // The device-resident engine also follows the stitch-aware order (its
 // tasks rebuild each path's row order and tried sets) and carries trace
 // hashes; the host-driven one replays rows in ascending order only and
 // counts nodes only, so stitch-ordered or traced batches always take the
 // device engine.
-static void heavy_engine(DeviceBatch& db, bool trace) {
-  if (db.tune.heavy_device || db.reg_stitch || trace) heavy_engine_device(db, trace);
-  else heavy_engine_host(db);
+static void heavy_engine(DeviceBatch& db, bool trace, bool last) {
+  if (db.tune.heavy_device || db.reg_stitch || trace) heavy_engine_device(db, trace, last);
+  else heavy_engine_host(db, last);
 }
 
-static void heavy_engine_host(DeviceBatch& db) {
+static void heavy_engine_host(DeviceBatch& db, bool last) {
   mpld_context* ctx = db.ctx;
   hipStream_t s = ctx->stream;
   db.sp_rounds = db.sp_tasks_run = db.sp_heavy = db.sp_reruns = 0;
   // which register-tier components stopped at the first cap
-  if (!db.sp_host_recs.reserve(sizeof(DevRecord) * (size_t)std::max(1, db.num_comps)))
-    fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
-  DevRecord* recs = db.sp_host_recs.as<DevRecord>();
-  check_hip(hipMemcpyAsync(recs, db.recs.p, sizeof(DevRecord) * (size_t)db.num_comps,
-                           hipMemcpyDeviceToHost, s), "heavy: records");
-  check_hip(hipStreamSynchronize(s), "heavy: first pass");
+  const DevRecord* recs = first_pass(db, last);
   std::vector<HComp> hcs;
   std::vector<HTask> tasks;
   std::vector<int32_t> pending;   // tasks not run yet, in creation order
@@ -1152,12 +1214,11 @@ static void heavy_engine_host(DeviceBatch& db) {
     wb.push_back(w);
   }
   if (!wb.empty()) {
-    if (!db.sp_host_writes.reserve(sizeof(HeavyWrite) * wb.size()))
-      fail(MPLD_E_NOMEM, "heavy-component engine: pinned host memory");
+    uint8_t* up = stage_up(ctx, sizeof(HeavyWrite) * wb.size(), db.sp_host_writes);
     if (db.sp_writes.bytes < sizeof(HeavyWrite) * wb.size())
       db.sp_writes.alloc(ctx, sizeof(HeavyWrite) * wb.size());
-    std::memcpy(db.sp_host_writes.p, wb.data(), sizeof(HeavyWrite) * wb.size());
-    check_hip(hipMemcpyAsync(db.sp_writes.p, db.sp_host_writes.p, sizeof(HeavyWrite) * wb.size(),
+    std::memcpy(up, wb.data(), sizeof(HeavyWrite) * wb.size());
+    check_hip(hipMemcpyAsync(db.sp_writes.p, up, sizeof(HeavyWrite) * wb.size(),
                              hipMemcpyHostToDevice, s), "heavy: write-back upload");
     check_hip(launch_heavy_writeback(db.sp_writes.as<HeavyWrite>(), (int32_t)wb.size(),
                                      db.recs.as<DevRecord>(), db.colors.as<int8_t>(), s),
@@ -1208,7 +1269,10 @@ void device_solve(DeviceBatch& db, uint32_t flags) {
   const bool split = (flags & MPLD_SPLIT_HEAVY) && !(flags & MPLD_PLAIN);
   const uint64_t cap = split && db.n_reg > 0 ? (uint64_t)db.tune.heavy_first_cap : ~0ull;
   const bool timed = !(flags & MPLD_UNTIMED) || (flags & MPLD_PLAIN);
+  // no launch after the register tier's, unless components are heavy
+  const bool last = !mark && !minimize && db.n_reg == (int32_t)db.host_queue.size();
   db.timed = false;
+  db.got.clear();
   if (flags & MPLD_PLAIN) {
     // one launch per component, same search code
     const auto* desc = db.desc.as<DevDesc>();
@@ -1245,7 +1309,7 @@ void device_solve(DeviceBatch& db, uint32_t flags) {
     enqueue_batched(db, trace, cap, s, split, mark && !split);
     if (split) {
       db.sp_rounds = db.sp_tasks_run = db.sp_heavy = db.sp_reruns = 0;
-      if (db.n_reg) heavy_engine(db, trace);
+      if (db.n_reg) heavy_engine(db, trace, last);
       csr_split(db, trace);
     }
     if (mark) enqueue_mark(db, s, split);
@@ -1279,7 +1343,7 @@ void device_solve(DeviceBatch& db, uint32_t flags) {
     check_hip(hipGraphLaunch(db.graph, s), "graph launch");
     if (split) {
       db.sp_rounds = db.sp_tasks_run = db.sp_heavy = db.sp_reruns = 0;
-      if (db.n_reg) heavy_engine(db, trace);
+      if (db.n_reg) heavy_engine(db, trace, last);
       csr_split(db, trace);
     }
     if (mark) enqueue_mark(db, s, split);
@@ -1314,11 +1378,38 @@ void device_fetch(DeviceBatch& db, std::vector<DevRecord>& recs, std::vector<int
                   std::vector<int32_t>* min_nodes) {
   mpld_context* ctx = db.ctx;
   hipStream_t s = ctx->stream;
-  (void)ctx;
-  check_hip(hipStreamSynchronize(s), "search");
-  device_time(db);
   recs.resize((size_t)db.num_comps);
   colors.resize((size_t)db.total_nodes);
+  const size_t nr = sizeof(DevRecord) * recs.size();
+  const size_t at_colors = (size_t)(db.colors.as<uint8_t>() - db.recs.as<uint8_t>());
+  const bool mins = min_nodes && db.min_out.p && db.n_reg;
+  if (db.result_bytes(mins) <= kStageMin) {   // one copy, or none if the solve has made it
+    const bool have = !db.got.empty() && !mins;
+    const uint8_t* h = db.got.data();
+    if (!have) {
+      uint8_t* d = stage_down(ctx, db.result_bytes(mins), db.sp_host_recs);
+      check_hip(hipMemcpyAsync(d, db.recs.p, db.result_bytes(mins), hipMemcpyDeviceToHost, s), "download");
+      h = d;
+    }
+    check_hip(hipStreamSynchronize(s), "search");
+    device_time(db);
+    if (nr) std::memcpy(recs.data(), h, nr);
+    if (db.total_nodes) std::memcpy(colors.data(), h + at_colors, colors.size());
+    if (min_nodes) min_nodes->assign((size_t)db.num_comps, 0);
+    if (mins) {
+      const uint8_t* m = h + (db.min_out.as<uint8_t>() - db.recs.as<uint8_t>());
+      for (int32_t i = 0; i < db.n_reg; ++i) {   // only register-tier items write their entry
+        const int32_t c = db.host_queue[(size_t)i];
+        std::memcpy(&(*min_nodes)[(size_t)c], m + sizeof(int32_t) * (size_t)c, sizeof(int32_t));
+      }
+    }
+    for (const auto& r : recs)
+      if (r.status < 0 || r.status > MPLD_BUDGET_EXHAUSTED)
+        fail(MPLD_E_INTERNAL, "search reported a broken state");
+    return;
+  }
+  check_hip(hipStreamSynchronize(s), "search");
+  device_time(db);
   if (db.num_comps)
     check_hip(hipMemcpyAsync(recs.data(), db.recs.p, sizeof(DevRecord) * recs.size(),
                              hipMemcpyDeviceToHost, s), "download records");

@@ -137,6 +137,10 @@ struct mpld_context {
   int lds_per_block = 0;
   hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
   mpld::GraphBuilder* graph_builder = nullptr;   // device layout-graph builder (lazy)
+  // page-locked staging of the calls on this context, one copy up and one
+  // down at a time (stage_up, stage_down): at most kStageMax bytes each
+  void *up = nullptr, *down = nullptr;
+  size_t up_bytes = 0, down_bytes = 0;
 
   void* dev_alloc(size_t bytes);
   void dev_free(void* p);
@@ -163,6 +167,13 @@ struct DevBuf {
     ctx = c;
     bytes = n ? n : 256;
     p = c->dev_alloc(bytes);
+  }
+  // `n` bytes of `of` from byte `at` on; not owned
+  void view(const DevBuf& of, size_t at, size_t n) {
+    release();
+    ctx = nullptr;
+    bytes = n ? n : 256;
+    p = of.as<uint8_t>() + at;
   }
   template <class T>
   T* as() const { return static_cast<T*>(p); }
@@ -196,6 +207,16 @@ struct PinnedBuf {
   template <class T>
   T* as() const { return static_cast<T*>(p); }
 };
+
+// Page-locked memory of at least n bytes for one copy on the context's
+// stream: the context's own staging up to kStageMax bytes, `own` beyond.
+// Allocating and freeing a page-locked buffer takes some 45 us, as long as a
+// small batch's search and copies together; the context keeps its staging
+// until it is destroyed.  stage_up waits for the stream, so that the copy
+// before has been read; what is staged down is taken out before the next use.
+constexpr size_t kStageMin = 256 << 10, kStageMax = 4 << 20;
+uint8_t* stage_up(mpld_context* ctx, size_t n, PinnedBuf& own);
+uint8_t* stage_down(mpld_context* ctx, size_t n, PinnedBuf& own);
 
 // What a CSR component takes in the one-wave layouts (-1: not in that one).
 struct CsrShape {
@@ -268,7 +289,18 @@ void image_finish(Image& im, int order = 0);
 // Device copy of an image plus its outputs and queue counters.
 struct DeviceBatch {
   mpld_context* ctx = nullptr;
-  DevBuf desc, regitems, adj32, counters, recs, colors, gstack;  // desc in launch order
+  // one block of device memory: counters | desc | regitems | adj32, filled by
+  // one copy where they fit the staging, then recs | colors | min_out, read
+  // back by one
+  DevBuf mem;
+  DevBuf desc, regitems, adj32, counters, recs, colors;  // views of mem; desc in launch order
+  DevBuf gstack;
+  std::vector<uint8_t> got;   // recs | colors of the last solve, where its check for
+                              // heavy components has read them already
+  size_t result_bytes(bool with_min) const {
+    return (size_t)((with_min ? min_out : colors).as<uint8_t>() - recs.as<uint8_t>()) +
+           (with_min ? min_out : colors).bytes;
+  }
   uint32_t reg_width = 1;   // masks per register-tier item
   bool reg_stitch = false;  // items carry stitch partners
   bool csr_stitch = false;  // CSR blocks end with stitch partners (LDS and big tiers)
@@ -278,7 +310,7 @@ struct DeviceBatch {
                     reg_stitch ? kRegItemHead + 8u * reg_width : 0u};
   }
   DevBuf dev_keys, dev_stacks;      // device-wide tier
-  DevBuf partners, min_out;         // MPLD_MINIMIZE: stitch partners, per-component node counts
+  DevBuf partners, min_out;         // MPLD_MINIMIZE: stitch partners, per-component node counts (views)
   uint32_t min_budget = 10000;      // MPLD_MINIMIZE: nodes per component
   DevBuf sp_tasks, sp_out, sp_pool, sp_writes;      // heavy-component engine
   PinnedBuf sp_host_tasks, sp_host_out, sp_host_pool, sp_host_writes, sp_host_recs;
