@@ -51,12 +51,13 @@ void check_options(const mpld_options* opt) {
 }
 
 // Graphs of at least this many nodes and pairs together go through the
-// device's flow: some 35 launches, 0.25 ms whatever the size, where the host's
+// device's flow: some 35 launches, 0.2 ms whatever the size, where the host's
 // passes take time in proportion to both.  Host against device, ms: k = 3,
-// 3000 nodes and 3300 pairs 0.39 / 0.45, 5000 and 5500 0.57 / 0.58, 8000 and
-// 8700 0.76 / 0.61, 32000 and 35000 2.05 / 0.86; k = 4 with stitches, 5900 and
-// 6600 0.69 / 0.69, 11800 and 13200 1.49 / 1.20; packed windows, 700 and 7400
-// 0.54 / 0.57, 2000 and 21000 1.2 / 0.6, 8000 and 85000 3.4 / 0.85.
+// 4100 nodes and 4400 pairs 0.24 / 0.35, 6000 and 6300 0.41 / 0.45, 8000 and
+// 8500 0.54 / 0.47, 32000 and 34500 1.72 / 0.60; sparser, 8000 and 5100 0.31 /
+// 0.31; k = 4 with stitches, 6000 and 6900 0.41 / 0.42, 8800 and 9900 0.71 /
+// 0.58, 23500 and 26700 1.63 / 0.77.  The two meet at 12,000 to 14,000; the
+// line stays a little below, where large clusters' numbering is the device's.
 constexpr int64_t kFlowMinSize = 11000;
 
 void use_device(mpld_context* ctx) {

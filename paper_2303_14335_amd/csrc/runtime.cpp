@@ -341,7 +341,8 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   const size_t min_bytes = im.minimize ? sizeof(int32_t) * std::max<size_t>(im.desc.size(), 1) : 0,
                partner_bytes = im.minimize ? std::max<size_t>((size_t)im.mask_words, 1) : 0;
   const size_t at_min = im.minimize ? place(min_bytes) : 0,
-               at_partners = im.minimize ? place(partner_bytes) : 0;
+               at_partners = im.minimize ? place(partner_bytes) : 0,
+               at_list = im.minimize ? place(sizeof(int32_t) * (size_t)db.n_reg) : 0;
   db.mem.alloc(ctx, used);
   db.counters.view(db.mem, at_counters, sizeof(int32_t) * 8);
   db.desc.view(db.mem, at_desc, desc_bytes);
@@ -351,9 +352,11 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   db.colors.view(db.mem, at_colors, (size_t)im.total_nodes);
   db.partners.release();
   db.min_out.release();
+  db.min_list.release();
   if (im.minimize) {
     db.min_out.view(db.mem, at_min, min_bytes);
     db.partners.view(db.mem, at_partners, partner_bytes);
+    db.min_list.view(db.mem, at_list, sizeof(int32_t) * (size_t)db.n_reg);
   }
   db.got.clear();
   db.gstack.release();
@@ -1233,9 +1236,11 @@ static void heavy_engine_host(DeviceBatch& db, bool last) {
 static void enqueue_minimize(DeviceBatch& db, hipStream_t s) {
   if (!db.n_reg) return;
   if (!db.min_out.p) fail(MPLD_E_INTERNAL, "batch was not packed for MPLD_MINIMIZE");
-  check_hip(launch_min_reg(db.k, std::min(db.n_reg, 65535), db.reg_items(),
+  // counters 4 and 5: the list's length and the workgroups done with it
+  check_hip(launch_min_reg(db.k, std::min(db.n_reg, 65535), db.ctx->num_cus, db.reg_items(),
                            db.n_reg, db.partners.as<uint8_t>(), db.colors.as<int8_t>(),
-                           db.min_out.as<int32_t>(), db.min_budget, s),
+                           db.min_out.as<int32_t>(), db.min_budget, db.counters.as<int32_t>() + 4,
+                           db.min_list.as<int32_t>(), s),
             "Eq. 1 minimisation (register tier)");
 }
 

@@ -99,8 +99,9 @@ int64_t mark_lds_bytes(int32_t n, int32_t k);
 // incumbent colors in `colors`; partners: stitch partner byte per node
 // (indexed like the masks, 0xff none); min_out[comp]: nodes, negated when
 // stopped by `budget`, 0 when the incumbent costs nothing.
-hipError_t launch_min_reg(int k, int grid, RegItems items, int32_t qlen, const uint8_t* partners,
-                          int8_t* colors, int32_t* min_out, uint32_t budget, hipStream_t s);
+hipError_t launch_min_reg(int k, int grid, int num_cus, RegItems items, int32_t qlen, const uint8_t* partners,
+                          int8_t* colors, int32_t* min_out, uint32_t budget, int32_t* list_len, int32_t* list,
+                          hipStream_t s);
 // LDS bytes of one LDS-tier component (adj_words = n + 1 + 2m) and the
 // global stack words of a big one.
 int64_t lds_bytes_for(int32_t n, int32_t k, int64_t adj_words, int32_t max_deg, bool big,
@@ -311,6 +312,7 @@ struct DeviceBatch {
   }
   DevBuf dev_keys, dev_stacks;      // device-wide tier
   DevBuf partners, min_out;         // MPLD_MINIMIZE: stitch partners, per-component node counts (views)
+  DevBuf min_list;                  // MPLD_MINIMIZE: items that one wave leaves to a workgroup (view)
   uint32_t min_budget = 10000;      // MPLD_MINIMIZE: nodes per component
   DevBuf sp_tasks, sp_out, sp_pool, sp_writes;      // heavy-component engine
   PinnedBuf sp_host_tasks, sp_host_out, sp_host_pool, sp_host_writes, sp_host_recs;

@@ -130,3 +130,50 @@ def test_unsupported_and_invalid(ctx):
         srv.submit(g, 3, 100, MINIMIZE, min_budget=-1)
     assert e.value.code == -1
     srv.close()
+
+
+def many_components(rng, count, n_lo, n_hi, least, most):
+    """One graph of `count` connected-ish random components and stitch pairs."""
+    ce, se, at = [], [], 0
+    for _ in range(count):
+        n = int(rng.integers(n_lo, n_hi + 1))
+        e = np.asarray(random_graph(rng, n, min(0.95, float(rng.uniform(least, most)) / n)), np.int32).reshape(-1, 2)
+        path = np.stack([np.arange(n - 1), np.arange(1, n)], 1).astype(np.int32)
+        e = np.unique(np.sort(np.concatenate([e, path]), 1), axis=0)
+        ce.append(e + at)
+        se.append(with_partners(rng, n, e.tolist(), 0.6) + at)
+        at += n
+    return at, np.concatenate(ce), np.concatenate(se)
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 6, 7, 8])
+@pytest.mark.parametrize("budget", [63, 64, 65, 1000, 6000])
+def test_long_searches(ctx, k, budget):
+    """Searches on both sides of what one wave does alone, ended by the
+    search itself, by the budget and by cheaper colorings found on the way;
+    all byte widths of the penalties, nodes of many conflicts."""
+    import paper_2303_14335_amd as mp
+    rng = np.random.default_rng(9000 + 10 * k)
+    n, ce, se = many_components(rng, 48, k + 4, k + 20 if k < 7 else 64, 1.6 * k, 3.2 * k)
+    say("long minimisations, k", k, "budget", budget)
+    for simplify in (False, True):
+        flags = MINIMIZE | (SIMPLIFY if simplify else 0)
+        got = mp.mpld_decompose(ctx, mp.Graph(n, ce, se), k, 500, flags, min_budget=budget)
+        ref = oracle.decompose(oracle.Graph(n, ce, se), k, 500, simplify=simplify, minimize=True,
+                               min_budget=budget)
+        compare(got, ref)
+    assert budget < 1000 or np.any(np.abs(ref.comps["min_nodes"]) > 64)
+
+
+@pytest.mark.parametrize("count", [200, 300, 1500])
+def test_many_long_searches(ctx, count):
+    """More listed components than workgroups, and so many that every wave
+    takes one of its own; twice, as the list is empty again after a call."""
+    import paper_2303_14335_amd as mp
+    rng = np.random.default_rng(count)
+    n, ce, se = many_components(rng, count, 10, 22, 6.0, 11.0)
+    say("many minimisations", count)
+    ref = oracle.decompose(oracle.Graph(n, ce, se), 3, 500, simplify=False, minimize=True, min_budget=400)
+    assert np.sum(np.abs(ref.comps["min_nodes"]) > 64) > 0.7 * count
+    for _ in range(2):
+        compare(mp.mpld_decompose(ctx, mp.Graph(n, ce, se), 3, 500, MINIMIZE, min_budget=400), ref)
