@@ -505,7 +505,7 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
   check_hip(hipStreamSynchronize(st), "layout flow: front-end");
   FlowHead h;
   std::memcpy(&h, ho, sizeof(h));
-  if (h.flags) return false;
+  if (h.flags || h.ncomp == -1) return false;   // a fault or a hub; a split that the device gave up
   if (h.removed < 0 || h.removed > n || h.ncomp < 0 || h.ncomp > n - h.removed)
     fail(MPLD_E_INTERNAL, "layout flow: bad counts");
   f.removed = h.removed;

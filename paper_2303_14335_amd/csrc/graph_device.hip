@@ -828,15 +828,20 @@ __global__ __launch_bounds__(kMidThreads) void bfs_mid_kernel(SplitArgs a) {
 // is 50 blocks' work of one wave-wide step, and one workgroup took 140 us for
 // it.  Positions and order go past the caches of one compute unit (agent
 // scope); every wait ends: all blocks of this launch fit the device at once,
-// and a block that has waited far too long reports it and leaves, as do the
-// others after it.
+// and a block that has waited far too long (others' kernels kept the rest of
+// the blocks out) reports it and leaves, as do the others after it; the graph
+// is then split on the host.
 __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
   __shared__ ScanShared sh;
   __shared__ int32_t lost;
   constexpr int32_t G = 32, kNodes = kScanBlock / G;
   const int32_t giants = a.ctl[kCtlGiants], bigs = a.ctl[kCtlBigs];
   const int32_t count = giants + (bigs > kFewBigs ? 0 : bigs);
-  uint64_t* status = reinterpret_cast<uint64_t*>(((uintptr_t)a.words + 7) & ~(uintptr_t)7);
+  // tiles' words of even and of odd levels: a block that has met the others
+  // after a level may write the next level's before a slow one has read the
+  // last of this level's, so they are apart (a block is never two levels ahead)
+  uint64_t* const words = reinterpret_cast<uint64_t*>(((uintptr_t)a.words + 7) & ~(uintptr_t)7);
+  const int32_t level_words = a.n / kNodes + 1;
   uint32_t tag = 0;
   int32_t met = 0;
   if (threadIdx.x == 0) lost = 0;
@@ -850,7 +855,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
       for (int32_t spin = 0; ld_agent(a.ctl + kCtlMeet) < met; ++spin)
         if (spin > (1 << 22) || ld_agent(a.ctl + kCtlLost)) {
           atomicOr(a.ctl + kCtlLost, 1);
-          a.counts[0] = a.n;   // no split: the host refuses the component count
+          a.counts[0] = a.n;   // no split: the host does it
           a.counts[1] = -1;
           lost = 1;
           break;
@@ -870,6 +875,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
     if (!meet()) return;
     for (int32_t lo = 0, hi = 1; lo < hi;) {
       ++tag;
+      uint64_t* const status = words + (tag & 1u ? level_words : 0);
       const int32_t tiles = (hi - lo + kNodes - 1) / kNodes;
       for (int32_t tile = (int32_t)blockIdx.x; tile < tiles; tile += (int32_t)gridDim.x) {
         const int32_t p = lo + tile * kNodes + (int32_t)threadIdx.x / G;
@@ -931,6 +937,8 @@ struct ScanArgs {
 static ScanArgs scan_args(GraphBuilder& gb, int64_t tiles, int64_t tickets) {
   const size_t bytes = 64 + 8 * (size_t)tiles;
   if (gb.tiles.bytes < bytes || gb.epoch >= (1u << 30) - 1) {
+    // launches on the way still use the words that go back
+    if (gb.tiles.p) check_hip(hipStreamSynchronize(gb.stream), "graph builder: scan");
     grow(gb.tiles, gb.ctx, bytes);
     gb.epoch = 0;
     gb.tickets = 0;
@@ -1023,8 +1031,8 @@ static void enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, cons
   enqueue_split(gb, n, dptr, dadj, adj_entries, k, simplify, w, w + split_out_words(n), nullptr, nullptr);
 }
 
-// Split from the copied-back words of split_ws.
-static void collect_split(const int32_t* h, int32_t n, Split& s) {
+// Split from the copied-back words of split_ws; false if the device gave up.
+static bool collect_split(const int32_t* h, int32_t n, Split& s) {
   const size_t nn = (size_t)n;
   const int32_t removed = h[0], ncomp = h[1];
   const int32_t* queue = h + 2;
@@ -1032,6 +1040,7 @@ static void collect_split(const int32_t* h, int32_t n, Split& s) {
   const int32_t* order = comp_of + nn;
   const int32_t* comp_ptr = order + nn;
   const int32_t* local = comp_ptr + nn + 1;
+  if (ncomp == -1) return false;
   if (removed < 0 || removed > n || ncomp < 0 || ncomp > n)
     fail(MPLD_E_INTERNAL, "device split returned bad counts");
   s = Split();
@@ -1040,6 +1049,7 @@ static void collect_split(const int32_t* h, int32_t n, Split& s) {
   s.comp_ptr.assign(comp_ptr, comp_ptr + ncomp + 1);
   s.order.assign(order, order + s.comp_ptr.back());
   s.local.assign(local, local + nn);
+  return true;
 }
 
 void graph_builder_reserve(GraphBuilder& gb, int32_t nodes) {
@@ -1103,7 +1113,7 @@ void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simpli
   check_hip(hipMemcpyAsync(gb.hout.p, gb.split_ws.p, out_bytes, hipMemcpyDeviceToHost, st),
             "device split: download");
   check_hip(hipStreamSynchronize(st), "device split");
-  collect_split(gb.hout.as<int32_t>(), nn, s);
+  if (!collect_split(gb.hout.as<int32_t>(), nn, s)) s = simplify_and_split(g, k, simplify);
 }
 
 // Copies the rectangles to the staging (before the builder's lock).
@@ -1273,8 +1283,7 @@ bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
   g.partner.assign(hmate, hmate + nb);
   g.adj.assign(hadj, hadj + total);
   g.num_ce = total / 2;
-  if (split) collect_split(hadj + total, nn, *split);
-  return split != nullptr;
+  return split && collect_split(hadj + total, nn, *split);
 }
 
 void build_layout_pairs_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,

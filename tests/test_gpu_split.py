@@ -85,3 +85,47 @@ def test_edge_cases(ctx):
         mp.mpld_split_graph_device(ctx, mp.Graph(3, np.array([[0, 3]], np.int32),
                                                  np.zeros((0, 2), np.int32)), 3)
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("n,width", [(6000, 40), (20000, 8)])
+def test_large_components_side_by_side(n, width):
+    """Single components whose numbering takes many workgroups and levels,
+    split by three contexts at once: their workgroups share the device and
+    drift apart."""
+    import threading
+
+    import paper_2303_14335_amd as mp
+    rng = np.random.default_rng(n)
+    # a band: node i meets some of the `width` before it, and always i - 1
+    pairs = {(i - 1, i) for i in range(1, n)}
+    for i in range(2, n):
+        for j in rng.integers(max(0, i - width), i - 1, 5).tolist():
+            pairs.add((j, i))
+    ids = rng.permutation(n)
+    ce = np.sort(ids[np.array(sorted(pairs))], axis=1)
+    ce = np.ascontiguousarray(ce[np.lexsort((ce[:, 1], ce[:, 0]))].astype(np.int32))
+    se = np.zeros((0, 2), np.int32)
+    rem, comp_of, comps = oracle.simplify(oracle.Graph(n, ce, se), 3, True)
+    assert len(comps) == 1 and len(comps[0]) > 4096
+    say("large components side by side", n, width)
+    bad = []
+
+    def work():
+        c = mp.Context(0)
+        try:
+            for _ in range(8):
+                grem, gcomp_of, gcomps = mp.mpld_split_graph_device(c, mp.Graph(n, ce, se), 3, True)
+                if not (np.array_equal(grem, rem) and np.array_equal(gcomp_of, comp_of)
+                        and len(gcomps) == 1 and np.array_equal(gcomps[0], comps[0])):
+                    bad.append("differs")
+        except Exception as e:   # noqa: BLE001
+            bad.append(repr(e))
+        finally:
+            c.close()
+
+    threads = [threading.Thread(target=work) for _ in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad, bad
