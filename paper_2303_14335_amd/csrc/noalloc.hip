@@ -158,9 +158,15 @@ void solve_noalloc(mpld_context* ctx, const mpld_component* comps, int32_t count
   check_hip(hipMemcpyAsync(dev, g_stage.front, items_end, hipMemcpyHostToDevice, s), "upload items");
   const RegItems ri{items, width, (uint32_t)stride, 0u};
   const bool trace = opt->flags & MPLD_TRACE_HASH;
-  const int cap = ctx->num_cus * ctx->reg_blocks_per_cu;
-  const int grid = std::max(1, std::min((count + 3) / 4, cap));
-  check_hip(launch_reg_batched(trace, opt->k, grid, 4, ri, count, counter, recs, colors, ~0ull, 0, 16u,
+  // the largest components' root rows on a wave each, as a batch's own launch
+  // has them, up to what the device holds at once
+  const Tune tune;
+  const int32_t cap = ctx->num_cus * ctx->reg_blocks_per_cu;
+  int32_t split = 0;
+  while (split < std::min(count, cap) && comps[g_stage.order[split]].n >= tune.root_split_min_n) ++split;
+  const int grid = split ? split + (count - split + 3) / 4 : std::max(1, std::min((count + 3) / 4, cap));
+  check_hip(launch_reg_batched(trace, opt->k, grid, 4, ri, count, counter, recs, colors, ~0ull, split,
+                               (uint32_t)tune.root_split_chunk,
                                (opt->flags & MPLD_MARK_CONFLICTS) != 0, s),
             "register-tier launch");
   const bool together = (size_t)total_nodes <= kTogetherBytes;
