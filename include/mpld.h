@@ -116,16 +116,19 @@ enum {
                                   hash are recomputed exactly from the
                                   subtrees' counts and hashes in search order
                                   (each subtree's hash appended with the
-                                  concatenation rule of the trace hash; a
-                                  component cut by its budget is re-run
-                                  sequentially).  LDS-tier and big-tier
-                                  components are searched as k subtree tasks,
+                                  concatenation rule of the trace hash).
+                                  LDS-tier and one-wave big-tier components,
+                                  and register-tier ones cut by their budget,
+                                  are searched as an ordered list of pieces of
+                                  the search's stack, run ahead by many waves
+                                  and counted in order.  Stitch-ordered ones
+                                  past the register tier, and the big tier's
+                                  workgroup layout, run as k subtree tasks,
                                   one per root row (the root column is node
-                                  0), each on its own wave or workgroup; their
-                                  counts and hashes are added in row order,
-                                  and a budget crossed inside a later row's
-                                  subtree is found by searching that subtree
-                                  again with the budget left.  Makes
+                                  0), added in row order; a budget crossed
+                                  inside a later row's subtree is found by
+                                  searching that subtree again with the budget
+                                  left.  Makes
                                   mpld_batch_solve wait.  mpld_decompose and
                                   mpld_solve_components, which wait anyway,
                                   use it for every solve whether or not the
@@ -281,10 +284,10 @@ const char* mpld_last_error(void);            /* thread-local detail */
 int32_t mpld_build_graph(const mpld_rect* rects, int32_t n, int32_t dmin_nm,
                          int32_t split_len_nm, mpld_owned_graph** out);
 /* The same layout graph (identical pairs, stitch pairs and node count)
- * built on the context's device: the host validates, splits and picks the
- * search grid, the device sorts the nodes into grid cells and tests every
- * node against its 3x3 cell neighbourhood.  For large layouts, where the
- * host pair search dominates.  Synchronous on the context's stream.
+ * built on the context's device: it validates and splits the rectangles,
+ * sorts the nodes into grid cells, tests every node against its 3x3 cell
+ * neighbourhood and writes the sorted pairs; the host picks the grid from
+ * the bounds.  Synchronous on the context's stream.
  * Errors as mpld_build_graph, plus MPLD_E_DEVICE / MPLD_E_NOMEM. */
 int32_t mpld_build_graph_device(mpld_context* ctx, const mpld_rect* rects, int32_t n,
                                 int32_t dmin_nm, int32_t split_len_nm, mpld_owned_graph** out);
@@ -298,11 +301,11 @@ int32_t mpld_build_graph_device(mpld_context* ctx, const mpld_rect* rects, int32
  * removal_order (num_nodes; the first *num_removed are used), comp_of
  * (num_nodes; -1 = removed), bfs_order (num_nodes; core nodes grouped by
  * component, each in local order), comp_ptr (num_nodes + 1; component c is
- * bfs_order[comp_ptr[c] .. comp_ptr[c + 1])).  Wide passes (the first peel
- * levels, union-find, numbering) run over the whole device, the small tail
- * of the peeling and the BFS of components above 64 nodes on one workgroup,
- * the BFS of smaller components one wave each.  Synchronous on the
- * context's stream.  Errors: MPLD_E_INVALID
+ * bfs_order[comp_ptr[c] .. comp_ptr[c + 1])).  The first peel levels,
+ * union-find and numbering run over the whole device, the small tail of the
+ * peeling on one workgroup; BFS takes a wave per component of at most 64
+ * nodes, a workgroup up to 4096 and many workgroups above.  Synchronous on
+ * the context's stream.  Errors: MPLD_E_INVALID
  * for a bad graph (as mpld_decompose), k outside [2, MPLD_MAX_K] or a NULL
  * output; MPLD_E_DEVICE / MPLD_E_NOMEM. */
 int32_t mpld_split_graph_device(mpld_context* ctx, const mpld_graph* g, int32_t k, uint32_t flags,

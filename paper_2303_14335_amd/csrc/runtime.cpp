@@ -343,6 +343,7 @@ void device_upload(mpld_context* ctx, const Image& im, DeviceBatch& db, const Tu
   const size_t at_min = im.minimize ? place(min_bytes) : 0,
                at_partners = im.minimize ? place(partner_bytes) : 0,
                at_list = im.minimize ? place(sizeof(int32_t) * (size_t)db.n_reg) : 0;
+  if (db.mem.p) check_hip(hipStreamSynchronize(ctx->stream), "upload");   // a solve may still use it
   db.mem.alloc(ctx, used);
   db.counters.view(db.mem, at_counters, sizeof(int32_t) * 8);
   db.desc.view(db.mem, at_desc, desc_bytes);
@@ -807,7 +808,7 @@ static void heavy_engine_device(DeviceBatch& db, bool trace, bool last) {
 // One-wave components take the sequence engine instead (their root rows are
 // no limit to it: 48 components of 65 to 2048 nodes, a third of them cut by
 // budgets of 10^5 nodes, took 145 ms as root-row tasks, nearly all of it in
-// each first row's subtree); what is left here are stitch-ordered ones, the
+// each first row's subtree, and take 12 ms so); what is left here are stitch-ordered ones, the
 // workgroup layout's, and any that the engine had no memory for.
 static void csr_split(DeviceBatch& db, bool trace) {
   const int32_t first = db.n_reg, count = db.n_lds + db.n_big;

@@ -262,7 +262,8 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
       // the wide layout keeps headers and log in global memory: 20 to 25%
       // slower a node, but a third of the LDS from a few hundred nodes on, so
       // three times the tasks at once (48 traced components of 65 to 2048
-      // nodes: 24 ms a solve with each tier's own layout, two launches a round)
+      // nodes: 24 ms a solve with each tier's own layout, two launches a round,
+      // 12 so)
       const CsrShape& sh = db.csr_shape[(size_t)(pos - db.n_reg)];
       c.wide = sh.wide_bytes >= 0 && (sh.small_bytes > kSeqSmallLds || pos >= db.n_reg + db.n_lds);
       lds = std::max<int32_t>(lds, (int32_t)(c.wide ? sh.wide_bytes : sh.small_bytes));
