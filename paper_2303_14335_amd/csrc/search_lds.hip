@@ -148,8 +148,8 @@ __device__ __forceinline__ void load_words(uint32_t count, G&& get, P&& put) {
   }
 }
 
-// A sequence-engine task on a CSR tier (the SEQ instances of the one-wave
-// solvers below): where it starts, how far it may go, and what becomes of it.
+// A sequence-engine task on a CSR tier (the *_seq forms of the one-wave
+// solvers): where it starts, how far it may go, and what becomes of it.
 struct SeqIo {
   SeqArgs a;
   SeqTask task;
@@ -303,366 +303,7 @@ struct Lds1Words {
 // STITCH: the stitch-aware row order (a column whose stitch partner is on
 // the path tries the partner's color first when that row is open, then the
 // others ascending); the CSR block then ends with the partners.
-template <bool TRACE, int K, bool STITCH, bool SEQ = false>
-__device__ void solve_lds(const DevDesc& d, const uint32_t* __restrict__ gadj, char* lds,
-                          int8_t* __restrict__ colors, DevRecord* __restrict__ rec,
-                          int32_t root_row = -1, uint64_t task_budget = 0,
-                          const SeqIo* io = nullptr) {
-  constexpr uint32_t S = lds1_stride(K);
-  constexpr uint32_t kLS = S == 4u ? 2u : (S == 8u ? 3u : 4u);   // log2(S)
-  constexpr int NB = bits_for(K);
-  constexpr uint32_t kNodeMask = (1u << kEntryNodeBits) - 1u;
-  const uint32_t lane = __lane_id();
-  const uint32_t n = (uint32_t)d.n;
-  const uint32_t m2 = uni(gadj[n]);
-  const Lds1Layout L = lds1_layout((int32_t)n, K, (int64_t)m2 + n + 1, STITCH);
-  uint32_t* PL = reinterpret_cast<uint32_t*>(lds);
-  uint32_t* offs = reinterpret_cast<uint32_t*>(lds + L.offs_off);
-  uint16_t* ids = reinterpret_cast<uint16_t*>(lds + L.ids_off);
-  uint2* hdr = reinterpret_cast<uint2*>(lds + L.hdr_off);
-  uint32_t* ent = reinterpret_cast<uint32_t*>(lds + L.ent_off);
-  uint16_t* spart = reinterpret_cast<uint16_t*>(lds + L.part_off);
-  uint8_t* scol = reinterpret_cast<uint8_t*>(lds + L.col_off);
-  if (!SEQ || io->load) {
-    load_words(n, [&](uint32_t v) { return gadj[v] | ((gadj[v + 1] - gadj[v]) << 16); },
-               [&](uint32_t v, uint32_t x) { offs[v] = x; });
-    if (STITCH)
-      load_words(n, [&](uint32_t v) { return gadj[n + 1 + m2 + 1 + v]; },
-                 [&](uint32_t v, uint32_t p) { spart[v] = p < n ? (uint16_t)p : (uint16_t)0xffffu; });
-  }
-  if (!SEQ || io->load)
-    load_words(m2, [&](uint32_t i) { return gadj[n + 1 + i]; },
-               [&](uint32_t i, uint32_t x) { ids[i] = (uint16_t)x; });
-  if (!SEQ || io->task.kind == kSeqRoot) {
-    // every node uncovered with all k colors open; words past n are empty
-    const uint32_t base = lane * 32u;
-    const uint32_t cnt = base >= n ? 0u : (n - base >= 32u ? 32u : n - base);
-    const uint32_t val = cnt == 32u ? ~0u : ((1u << cnt) - 1u);
-#pragma unroll
-    for (uint32_t c = 0; c < S; ++c) PL[lane * S + c] = c <= (uint32_t)K ? val : 0u;
-  }
-  __syncthreads();
-
-  uint32_t depth = 0, row_in = kNoneL, esp = 0;
-  uint64_t nodes = 0, h = 0;
-  int32_t status = -1;
-  uint32_t areg = 0;   // untried-rows bit of depth 32 * lane + b
-  const uint64_t budget = root_row >= 0 ? task_budget : (uint64_t)d.budget;
-  // SEQ: `depth` counts from the task's stack, dbase levels up
-  const uint32_t dbase = SEQ ? uni(io->task.dbase) : 0u;
-  uint64_t stop = SEQ ? uni64(io->stop) : 0;
-  const uint64_t limit = SEQ ? uni64(io->limit) : 0;
-  bool next_first = SEQ && io->task.kind == kSeqNext;
-  int32_t child = 0;
-  int64_t arena_at = 0;
-  bool cut = false;
-  uint32_t max_pieces = 1;
-  const uint32_t saved_bytes = (n + 31u) / 32u * S * 4u;   // planes of a saved state: whole words only
-  if (SEQ && io->task.kind != kSeqRoot) {
-    const uint8_t* at = io->a.arena + io->task.at;
-    depth = uni(io->task.levels);
-    esp = uni(io->task.nent);
-    row_in = uni(io->task.row_in);
-    uint4* pw = reinterpret_cast<uint4*>(PL);
-    for (uint32_t i = lane; i < 16u * S; i += 64u)
-      pw[i] = i < saved_bytes / 16u ? reinterpret_cast<const uint4*>(at)[i] : make_uint4(0u, 0u, 0u, 0u);
-    const uint2* hs = reinterpret_cast<const uint2*>(at + saved_bytes);
-    const uint32_t* es = reinterpret_cast<const uint32_t*>(hs + depth);
-    for (uint32_t i = lane; i < esp; i += 64u) ent[i] = es[i];
-    for (uint32_t b = 0; b < depth; b += 64u) {
-      uint2 hd = make_uint2(0u, 0u);
-      if (b + lane < depth) hdr[b + lane] = hd = hs[b + lane];
-      const uint64_t bal = __builtin_amdgcn_ballot_w64(((hd.y >> 16) & 0xffu) != 0u);
-      areg = lane == (b >> 5) ? (uint32_t)bal : (lane == (b >> 5) + 1u ? (uint32_t)(bal >> 32) : areg);
-    }
-    asm volatile("" ::: "memory");
-  }
-  Lds1Words<K> W;
-
-  // Take row (v, c) at `depth`: the level's header and untried-rows bit,
-  // then one atomic AND per neighbour of v on plane c (lanes 1 .. deg) and,
-  // if `lane_lo` is 0, on v's P bit (lane 0); the removed rows go to the log from
-  // `est` (v's P bit first), and the plane words of the next node are read
-  // right behind the atomics.
-  const uint16_t* ids_m1 = ids - 1;   // lane j reads neighbour j - 1
-  const uint32_t is_l0 = lane == 0u ? ~0u : 0u;
-  auto take_row = [&](uint32_t v, uint32_t c, uint32_t rows, uint32_t offv, uint32_t est,
-                      uint32_t lane_lo, bool more) {
-    const uint32_t beg = offv & 0xffffu, deg = offv >> 16;
-    const uint32_t first = deg < 63u ? deg : 63u;
-    // lane 0: v's P bit (lane_lo 0); lanes 1 .. first: the first neighbours
-    // (lane 0 reads the halfword before the list, a valid LDS word it ignores)
-    const bool act = lane >= lane_lo && lane <= first;
-    uint32_t old = 0u, bitm = 0u, entry = 0u;
-    if (act) {
-      const uint32_t idv = ids_m1[beg + lane];
-      const uint32_t u = (is_l0 & v) | (~is_l0 & idv);
-      const uint32_t pl4 = (is_l0 & ((uint32_t)K * 4u)) | (~is_l0 & (c * 4u));
-      bitm = 1u << (u & 31u);
-      old = atomicAnd(reinterpret_cast<uint32_t*>(lds + (((u >> 5) << (kLS + 2u)) | pl4)), ~bitm);
-      entry = (pl4 << 24) | u;
-    }
-    // the next node's plane words, behind the atomics (read again below
-    // when v has more than 63 neighbours); the empty asm keeps the use of
-    // the atomic's result after that read is issued
-    W.load(PL, lane);
-    asm volatile("" : "+v"(old) : : "memory");
-    if (lane == 0u) {
-      hdr[depth] = make_uint2(offv, est | (rows << 16) | (c << 24));
-      if (STITCH) scol[v] = (uint8_t)c;
-    }
-    {
-      const uint32_t dl = depth >> 5, db = 1u << (depth & 31u);
-      const uint32_t sel = lane == dl ? db : 0u;
-      areg = (sel & (more ? ~0u : 0u)) | (~sel & areg);
-    }
-    uint32_t slot = est + lane_lo;
-    auto log_hits = [&](bool hit, uint32_t e) {
-      const uint64_t bal = __builtin_amdgcn_ballot_w64(hit);
-      if (hit) {
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        ent[slot + rank] = e;
-      }
-      slot += (uint32_t)__popcll(bal);
-    };
-    log_hits((old & bitm) != 0u, entry);
-    if (deg > 63u) {
-      for (uint32_t ch = 63u; ch < deg; ch += 64u) {
-        bool hit = false;
-        uint32_t uu = 0;
-        if (ch + lane < deg) {
-          uu = ids[beg + ch + lane];
-          const uint32_t b = 1u << (uu & 31u);
-          hit = (atomicAnd(&PL[(uu >> 5) * S + c], ~b) & b) != 0u;
-        }
-        log_hits(hit, (c << kEntryNodeBits) | uu);
-      }
-      W.load(PL, lane);
-    }
-    esp = slot;
-    // One wave executes its LDS operations in order, so the next node's
-    // loads see these writes; this only keeps the compiler from caching
-    // LDS values across the loop.
-    asm volatile("" ::: "memory");
-  };
-
-  if (root_row >= 0) {
-    // row (0, root_row) at depth 0, with no alternative at that level
-    const uint32_t c = (uint32_t)root_row;
-    take_row(0u, c, 0u, uni(offs[0]), 0u, 0u, false);
-    depth = 1u;
-    row_in = c;
-  } else {
-    W.load(PL, lane);
-  }
-
-  // This lane's untried-rows bits of the levels below `d`.
-  auto open_bits = [&](uint32_t d) {
-    const uint32_t d1 = d - 1u, dw = d1 >> 5;
-    const uint32_t below = ~0u >> (31u - (d1 & 31u));
-    return d == 0u ? 0u : (lane < dw ? areg : (lane == dw ? areg & below : 0u));
-  };
-  // The deepest level below `d` whose column has an untried row.
-  auto deepest_open = [&](uint32_t d) {
-    uint32_t f = kNoneL;
-    if (d != 0) {
-      const uint32_t m = open_bits(d);
-      const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
-      if (bal) {
-        const uint32_t l = 63u - (uint32_t)__builtin_clzll(bal);
-        f = l * 32u + 31u - (uint32_t)__builtin_clz(rdlane(m, l));
-      }
-    }
-    return f;
-  };
-
-  while (status < 0) {
-    uint32_t v = 0, size = 0, r = 0, pre = 0, prp = 0xffffu;
-    if (SEQ && next_first) {   // straight to the deepest untried row
-      next_first = false;
-    } else {
-    // ---- one search node
-    if (SEQ) {
-      if (nodes == stop) {
-        if (nodes == limit) { status = MPLD_BUDGET_EXHAUSTED; break; }
-        max_pieces = seq_pieces(*io, wave_sum_u32((uint32_t)__popc(open_bits(depth))));
-        cut = seq_reserve(*io, max_pieces, n, saved_bytes, depth, esp, child, arena_at);
-        if (cut) break;
-        if (!io->force) { status = kSeqWaiting; break; }   // no room: as it was
-        stop = limit;
-      }
-    } else if (nodes == budget) { status = MPLD_BUDGET_EXHAUSTED; break; }
-    ++nodes;
-    // column choice: bit-sliced counts of this lane's word, narrowed from
-    // the top count bit to the lowest-count uncovered columns
-    uint32_t cnt[NB];
-#pragma unroll
-    for (int b = 0; b < NB; ++b) cnt[b] = 0u;
-#pragma unroll
-    for (int c = 0; c < K; ++c) {
-      uint32_t carry = W.a[c];
-#pragma unroll
-      for (int b = 0; b < bits_for(c + 1); ++b) {
-        const uint32_t t = cnt[b] & carry;
-        cnt[b] ^= carry;
-        carry = t;
-      }
-    }
-    const uint32_t p = W.a[K];
-    uint32_t cand = p, t = 0u;
-#pragma unroll
-    for (int b = NB - 1; b >= 0; --b) {
-      const uint32_t x = cand & ~cnt[b];
-      if (x) cand = x;
-      else t |= 1u << b;
-    }
-    const uint32_t bit = (uint32_t)__builtin_ctz(cand | 0x80000000u);
-    const uint32_t vl = (lane << 5) | bit;
-#pragma unroll
-    for (int c = 0; c < K; ++c) r |= __builtin_amdgcn_ubfe(W.a[c], bit, 1u) << c;
-    const uint32_t vc = vl < n ? vl : 0u;   // lanes past n read node 0's words
-    pre = offs[vc];
-    prp = STITCH ? (uint32_t)spart[vc] : 0xffffu;
-    // issue those reads before the minimum (which they then overlap)
-    asm volatile("" ::: "memory");
-    const uint32_t key = wave_min(p ? ((t << 24) | vl) : kNoKey);
-    if (key == kNoKey) {   // no uncovered column: the levels hold a solution
-      if (TRACE) h = trace_node(h, dbase + depth, row_in, kNoneL, 0);
-      status = MPLD_FEASIBLE;
-      break;
-    }
-    v = key & 0xffffffu;
-    size = key >> 24;
-    if (TRACE) h = trace_node(h, dbase + depth, row_in, v, size);
-    }
-    uint32_t rows, offv, est, lane_lo, c;
-    if (size != 0) {
-      const uint32_t wl = v >> 5;
-      rows = rdlane(r, wl);
-      offv = rdlane(pre, wl);
-      est = esp;
-      lane_lo = 0u;
-      c = (uint32_t)__builtin_ctz(rows);
-      if (STITCH) {
-        // the partner's color first when the partner is covered (its P bit,
-        // in its lane's word, is clear) and that row of v is open
-        const uint32_t p = rdlane(prp, wl);
-        if (p != 0xffffu && !((rdlane(W.a[K], p >> 5) >> (p & 31u)) & 1u)) {
-          const uint32_t cp = uni((uint32_t)scol[p]);
-          if ((rows >> cp) & 1u) c = cp;
-        }
-      }
-      rows &= ~(1u << c);   // the level's untried rows
-    } else {
-      // dead end: back to the deepest level whose column has an untried row
-      const uint32_t f = deepest_open(depth);
-      if (f == kNoneL) { status = MPLD_INFEASIBLE; break; }
-      const uint2 hd = hdr[f];
-      offv = uni(hd.x);
-      const uint32_t d1w = uni(hd.y);
-      est = d1w & 0xffffu;
-      // uncover every level above f, and the rows level f removed; the
-      // column stays covered (its P bit is entry est)
-      for (uint32_t i = est + 1u + lane; i < esp; i += 64) {
-        const uint32_t e = ent[i];
-        const uint32_t u = e & kNodeMask;
-        atomicOr(&PL[(u >> 5) * S + (e >> kEntryNodeBits)], 1u << (u & 31u));
-      }
-      if (TRACE || STITCH) v = uni(ent[est]) & kNodeMask;
-      // the next untried row of the level, in ascending order
-      rows = (d1w >> 16) & 0xffu;
-      c = (uint32_t)__builtin_ctz(rows);
-      rows &= rows - 1u;
-      depth = f;
-      lane_lo = 1u;
-    }
-    take_row(v, c, rows, offv, est, lane_lo, rows != 0u);
-    row_in = v * (uint32_t)K + c;
-    ++depth;
-  }
-  __syncthreads();
-  if constexpr (SEQ) {
-    int64_t sol = -1;
-    int32_t pieces = 0;
-    // the colors of this task's levels, over those of the nodes below it
-    const auto put_colors = [&](int64_t to) {
-      seq_copy_colors(*io, to, n);
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-      uint8_t* out = io->a.arena + to;
-      for (uint32_t f = lane; f < depth; f += 64) {
-        const uint32_t d1w = hdr[f].y;
-        out[ent[d1w & 0xffffu] & kNodeMask] = (uint8_t)((d1w >> 24) & 0xfu);
-      }
-    };
-    if (status == MPLD_FEASIBLE) {
-      sol = seq_reserve_colors(*io, n);
-      if (sol < 0) status = kSeqLost;
-      else put_colors(sol);
-    } else if (cut) {
-      status = kSeqCapped;
-      // (a piece that keeps the whole stack keeps the colors below it too)
-      if (max_pieces > 1u) put_colors(arena_at);
-      const int64_t col = max_pieces > 1u ? arena_at : io->task.col;
-      int64_t at = arena_at + ((n + 63u) & ~63u);
-      for (uint32_t top = depth;;) {
-        const uint32_t want = pieces == 0 ? (uint32_t)kSeqFirstLevels : 1u;
-        uint32_t lo = top, got = 0;
-        for (; got < want; ++got) {
-          const uint32_t f = deepest_open(lo);
-          if (f == kNoneL) break;
-          lo = f;
-        }
-        if (pieces != 0 && got == 0) break;   // nothing untried below
-        if (pieces == (int32_t)max_pieces - 1) lo = 0;   // the rest
-        const uint32_t elo = lo < top ? uni(hdr[lo].y) & 0xffffu : esp;
-        uint8_t* out = io->a.arena + at;
-        const uint4* pw = reinterpret_cast<const uint4*>(PL);
-        for (uint32_t i = lane; i < saved_bytes / 16u; i += 64u) reinterpret_cast<uint4*>(out)[i] = pw[i];
-        uint2* hs = reinterpret_cast<uint2*>(out + saved_bytes);
-        for (uint32_t i = lane; i < top - lo; i += 64u) {
-          const uint2 hd = hdr[lo + i];
-          hs[i] = make_uint2(hd.x, hd.y - elo);   // the log starts at 0 (16 bits, no borrow)
-        }
-        uint32_t* es = reinterpret_cast<uint32_t*>(hs + (top - lo));
-        for (uint32_t i = elo + lane; i < esp; i += 64u) es[i - elo] = ent[i];
-        seq_put_piece(*io, child + pieces, pieces == 0 ? kSeqNode : kSeqNext, dbase + lo, top - lo, esp - elo,
-                      row_in, at, col);
-        ++pieces;
-        at += (int64_t)((saved_bytes + 8u * (top - lo) + 4u * (esp - elo) + 63u) & ~63u);
-        if (lo == 0) break;
-        // back to before level lo's row: its rows and column, and all above
-        asm volatile("" ::: "memory");
-        for (uint32_t i = elo + lane; i < esp; i += 64u) {
-          const uint32_t e = ent[i], u = e & kNodeMask;
-          atomicOr(&PL[(u >> 5) * S + (e >> kEntryNodeBits)], 1u << (u & 31u));
-        }
-        asm volatile("" ::: "memory");
-        esp = elo;
-        top = lo;
-      }
-    }
-    seq_put_result(*io, status, dbase + depth, nodes, h, sol, child, pieces);
-    __syncthreads();
-    return;
-  }
-  if (status == MPLD_FEASIBLE) {
-    for (uint32_t f = lane; f < depth; f += 64) {
-      const uint32_t d1w = hdr[f].y;
-      colors[ent[d1w & 0xffffu] & kNodeMask] = (int8_t)((d1w >> 24) & 0xfu);
-    }
-  } else {
-    for (uint32_t v = lane; v < n; v += 64) colors[v] = -1;
-  }
-  // Every lane stores the same (uniform) record: no branch in the loop may
-  // share the queue pop's "lane 0" condition, or the compiler can thread the
-  // two across the loop back-edge and split the wave at the pop.
-  rec->status = status;
-  rec->depth = status == MPLD_INFEASIBLE ? 0 : (int32_t)depth;
-  rec->nodes = nodes;
-  rec->hash = h;
-  __syncthreads();
-}
+// (solve_lds itself: lds_one_wave.inc, included below)
 
 // ---- one-wave wide tier ---------------------------------------------------
 //
@@ -742,405 +383,12 @@ __device__ __forceinline__ uint32_t wide_key(const Lds1Words<K>& W, uint32_t w) 
   return p ? (t << 28) | (((w << 5) | bit) << 8) | r : kNoKey;
 }
 
-template <bool TRACE, int K, bool STITCH, bool SEQ = false>
-__device__ void solve_lds_wide(const DevDesc& d, const uint32_t* __restrict__ gadj, char* lds,
-                               uint64_t* gstack, int8_t* __restrict__ colors,
-                               DevRecord* __restrict__ rec, int32_t root_row = -1,
-                               uint64_t task_budget = 0, const SeqIo* io = nullptr) {
-  constexpr uint32_t S = lds1_stride(K);
-  constexpr uint32_t kLS = S == 4u ? 2u : (S == 8u ? 3u : 4u);   // log2(S)
-  constexpr uint32_t NW = (uint32_t)kWideMaxWords;
-  constexpr uint32_t kNodeMask = (1u << kEntryNodeBits) - 1u;
-  const uint32_t lane = __lane_id();
-  const uint32_t n = (uint32_t)d.n;
-  const uint32_t m2 = uni(gadj[n]);
-  const WideLayout L = wide_layout((int32_t)n, K, (int64_t)m2 + n + 1, STITCH);
-  const uint32_t nwl = wide_words((int32_t)n);   // node words per lane (uniform)
-  uint32_t* PL = reinterpret_cast<uint32_t*>(lds + L.pl_off);
-  // key of word w (lane w & 63, its j = w >> 6) at key_pos(w): a lane's keys
-  // j < 4 and j >= 4 each fill 16 contiguous bytes, and the lanes' blocks
-  // follow each other, so both ds_read_b128 of the keys are conflict-free
-  uint32_t* keys = reinterpret_cast<uint32_t*>(lds + L.key_off);
-  auto key_pos = [](uint32_t w) { return ((w >> 8) << 8) | ((w & 63u) << 2) | ((w >> 6) & 3u); };
-  uint32_t* dbits = reinterpret_cast<uint32_t*>(lds + L.bits_off);
-  uint32_t* offs = reinterpret_cast<uint32_t*>(lds + L.offs_off);
-  uint16_t* ids = reinterpret_cast<uint16_t*>(lds + L.ids_off);
-  uint16_t* spart = reinterpret_cast<uint16_t*>(lds + L.part_off);
-  uint8_t* scol = reinterpret_cast<uint8_t*>(lds + L.col_off);
-  uint2* hdr = reinterpret_cast<uint2*>(gstack);
-  uint32_t* ent = reinterpret_cast<uint32_t*>(gstack + n);
-  if (!SEQ || io->load) {
-    load_words(n, [&](uint32_t v) { return gadj[v] | ((gadj[v + 1] - gadj[v]) << kWideBegBits); },
-               [&](uint32_t v, uint32_t x) { offs[v] = x; });
-    if (STITCH)
-      load_words(n, [&](uint32_t v) { return gadj[n + 1 + m2 + 1 + v]; },
-                 [&](uint32_t v, uint32_t p) { spart[v] = p < n ? (uint16_t)p : (uint16_t)0xffffu; });
-  }
-  if (!SEQ || io->load)
-    load_words(m2, [&](uint32_t i) { return gadj[n + 1 + i]; },
-               [&](uint32_t i, uint32_t x) { ids[i] = (uint16_t)x; });
-  if (!SEQ || io->task.kind == kSeqRoot) for (uint32_t w = lane; w < 64u * nwl; w += 64) {
-    // every node uncovered with all k colors open; words past n are empty
-    const uint32_t base = w * 32u;
-    const uint32_t cnt = base >= n ? 0u : (n - base >= 32u ? 32u : n - base);
-    const uint32_t val = cnt == 32u ? ~0u : ((1u << cnt) - 1u);
-#pragma unroll
-    for (uint32_t c = 0; c < S; ++c) PL[w * S + c] = c <= (uint32_t)K ? val : 0u;
-  }
-#pragma unroll
-  for (uint32_t j = 0; j < NW; ++j) keys[j * 64u + lane] = kNoKey;
-  __syncthreads();
-
-  uint32_t depth = 0, row_in = kNoneL, esp = 0;
-  uint64_t nodes = 0, h = 0;
-  int32_t status = -1;
-  const uint64_t budget = root_row >= 0 ? task_budget : (uint64_t)d.budget;
-  // SEQ: `depth` counts from the task's stack, dbase levels up
-  const uint32_t dbase = SEQ ? uni(io->task.dbase) : 0u;
-  const uint32_t plane_bytes = 256u * S * nwl;
-  uint64_t stop = SEQ ? uni64(io->stop) : 0;
-  const uint64_t limit = SEQ ? uni64(io->limit) : 0;
-  bool next_first = SEQ && io->task.kind == kSeqNext;
-  int32_t child = 0;
-  int64_t arena_at = 0;
-  bool cut = false;
-  uint32_t max_pieces = 1;
-  const uint32_t saved_bytes = (n + 31u) / 32u * S * 4u;   // planes of a saved state: whole words only
-  if (SEQ && io->task.kind != kSeqRoot) {
-    const uint8_t* at = io->a.arena + io->task.at;
-    depth = uni(io->task.levels);
-    esp = uni(io->task.nent);
-    row_in = uni(io->task.row_in);
-    uint4* pw = reinterpret_cast<uint4*>(PL);
-    for (uint32_t i = lane; i < plane_bytes / 16u; i += 64u)
-      pw[i] = i < saved_bytes / 16u ? reinterpret_cast<const uint4*>(at)[i] : make_uint4(0u, 0u, 0u, 0u);
-    const uint2* hs = reinterpret_cast<const uint2*>(at + saved_bytes);
-    const uint32_t* es = reinterpret_cast<const uint32_t*>(hs + depth);
-    for (uint32_t i = lane; i < esp; i += 64u) ent[i] = es[i];
-    for (uint32_t b = 0; b < depth; b += 64u) {
-      uint2 hd = make_uint2(0u, 0u);
-      if (b + lane < depth) hdr[b + lane] = hd = hs[b + lane];
-      const uint64_t bal = __builtin_amdgcn_ballot_w64(((hd.y >> 16) & 0xffu) != 0u);
-      if (lane < 2u && (b >> 5) + lane < (n + 31u) / 32u)
-        dbits[(b >> 5) + lane] = lane == 0u ? (uint32_t)bal : (uint32_t)(bal >> 32);
-    }
-    asm volatile("" ::: "memory");
-  }
-  Lds1Words<K> W;
-  // every key of this lane's words, from the planes
-  auto all_keys = [&]() {
-#pragma unroll
-    for (uint32_t j = 0; j < NW; ++j) {
-      if (j < nwl) {
-        const uint32_t w = lane + 64u * j;
-        W.load(PL, w);
-        keys[key_pos(w)] = wide_key<K>(W, w);
-      }
-    }
-  };
-  all_keys();
-
-  // This lane's keys for the next node's column choice (words j >= nwl
-  // hold kNoKey).
-  uint4 ka, kb = make_uint4(kNoKey, kNoKey, kNoKey, kNoKey);
-  auto read_keys = [&]() {
-    ka = *reinterpret_cast<const uint4*>(keys + lane * 4u);
-    if (nwl > 4u) kb = *reinterpret_cast<const uint4*>(keys + 256u + lane * 4u);
-  };
-
-  // Take row (v, c) at `depth`: one atomic AND per neighbour of v on plane
-  // c (lanes 1 .. deg) and, if `lane_lo` is 0, on v's P bit (lane 0); then
-  // the keys of the words those atomics changed (every key when `full` or
-  // with more than 63 neighbours) and this lane's keys for the next node,
-  // read before the header, the untried-rows bit and the removed rows
-  // (global memory) are written, so that their latency overlaps that work.
-  const uint16_t* ids_m1 = ids - 1;   // lane j reads neighbour j - 1
-  const uint32_t is_l0 = lane == 0u ? ~0u : 0u;
-  auto take_row = [&](uint32_t v, uint32_t c, uint32_t rows, uint32_t offv, uint32_t est,
-                      uint32_t lane_lo, bool more, bool full) {
-    const uint32_t beg = offv & ((1u << kWideBegBits) - 1u), deg = offv >> kWideBegBits;
-    const uint32_t first = deg < 63u ? deg : 63u;
-    full = full || deg > 63u;
-    const bool act = lane >= lane_lo && lane <= first;
-    uint32_t old = 0u, bitm = 0u, entry = 0u, u = 0u;
-    if (act) {
-      const uint32_t idv = ids_m1[beg + lane];
-      u = (is_l0 & v) | (~is_l0 & idv);
-      const uint32_t pl4 = (is_l0 & ((uint32_t)K * 4u)) | (~is_l0 & (c * 4u));
-      bitm = 1u << (u & 31u);
-      old = atomicAnd(reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(PL) +
-                                                  (((u >> 5) << (kLS + 2u)) | pl4)),
-                      ~bitm);
-      entry = (pl4 << 24) | u;
-      // the changed word, read right behind the atomic (LDS operations of
-      // one wave complete in order)
-      if (!full) W.load(PL, u >> 5);
-    }
-    asm volatile("" : "+v"(old) : : "memory");
-    if (!full) {
-      // lanes on the same word compute the same key
-      if (act) {
-        const uint32_t w = u >> 5;
-        keys[key_pos(w)] = wide_key<K>(W, w);
-      }
-      read_keys();
-    }
-    asm volatile("" ::: "memory");
-    if (lane == 0u) {
-      hdr[depth] = make_uint2(est, v | (rows << 16) | (c << 24));
-      const uint32_t db = 1u << (depth & 31u);
-      atomicAnd(&dbits[depth >> 5], ~db);
-      if (more) atomicOr(&dbits[depth >> 5], db);
-      if (STITCH) scol[v] = (uint8_t)c;
-    }
-    uint32_t slot = est + lane_lo;
-    auto log_hits = [&](bool hit, uint32_t e) {
-      const uint64_t bal = __builtin_amdgcn_ballot_w64(hit);
-      if (hit) {
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-        ent[slot + rank] = e;
-      }
-      slot += (uint32_t)__popcll(bal);
-    };
-    log_hits((old & bitm) != 0u, entry);
-    if (deg > 63u) {
-      for (uint32_t ch = 63u; ch < deg; ch += 64u) {
-        bool hit = false;
-        uint32_t uu = 0;
-        if (ch + lane < deg) {
-          uu = ids[beg + ch + lane];
-          const uint32_t b = 1u << (uu & 31u);
-          hit = (atomicAnd(&PL[(uu >> 5) * S + c], ~b) & b) != 0u;
-        }
-        log_hits(hit, (c << kEntryNodeBits) | uu);
-      }
-    }
-    esp = slot;
-    asm volatile("" ::: "memory");
-    if (full) {
-      all_keys();
-      read_keys();
-    }
-    asm volatile("" ::: "memory");
-  };
-
-  if (root_row >= 0) {
-    // row (0, root_row) at depth 0, with no alternative at that level
-    const uint32_t c = (uint32_t)root_row;
-    take_row(0u, c, 0u, uni(offs[0]), 0u, 0u, false, false);
-    depth = 1u;
-    row_in = c;
-  } else {
-    read_keys();
-  }
-
-  // The deepest level below `d` whose column has an untried row.
-  auto deepest_open = [&](uint32_t d) {
-    uint32_t f = kNoneL;
-    if (d != 0) {
-      const uint32_t d1 = d - 1u, top = d1 >> 5;
-      const uint32_t below = ~0u >> (31u - (d1 & 31u));
-      for (uint32_t base = 0; base <= top && f == kNoneL; base += 64u) {
-        // lane l looks at word top - base - l
-        const bool in = base + lane <= top;
-        const uint32_t wi = in ? top - base - lane : 0u;
-        uint32_t m = in ? dbits[wi] : 0u;
-        if (in && wi == top) m &= below;
-        const uint64_t bal = __builtin_amdgcn_ballot_w64(m != 0u);
-        if (bal) {
-          const uint32_t l = (uint32_t)__builtin_ctzll(bal);
-          f = (top - base - l) * 32u + 31u - (uint32_t)__builtin_clz(rdlane(m, l));
-        }
-      }
-    }
-    return f;
-  };
-
-  // How many levels below `d` have one.
-  auto open_levels = [&](uint32_t d) {
-    uint32_t c = 0;
-    for (uint32_t w = lane; w * 32u < d; w += 64u)
-      c += (uint32_t)__popc(dbits[w] & (d - w * 32u >= 32u ? ~0u : (1u << (d - w * 32u)) - 1u));
-    return wave_sum_u32(c);
-  };
-
-  for (;;) {   // every exit sets the status (SEQ: or `cut`)
-    uint32_t v = 0, size = 0, key = 0, pre = 0;
-    if (SEQ && next_first) {   // straight to the deepest untried row
-      next_first = false;
-    } else {
-    // ---- one search node
-    if (SEQ) {
-      if (nodes == stop) {
-        if (nodes == limit) { status = MPLD_BUDGET_EXHAUSTED; break; }
-        max_pieces = seq_pieces(*io, open_levels(depth));
-        cut = seq_reserve(*io, max_pieces, n, saved_bytes, depth, esp, child, arena_at);
-        if (cut) break;
-        if (!io->force) { status = kSeqWaiting; break; }   // no room: as it was
-        stop = limit;
-      }
-    } else if (nodes == budget) { status = MPLD_BUDGET_EXHAUSTED; break; }
-    ++nodes;
-    // column choice: the lowest key of this lane's words, then of the wave
-    const uint32_t best = min(min(min(ka.x, ka.y), min(ka.z, ka.w)),
-                              min(min(kb.x, kb.y), min(kb.z, kb.w)));
-    // (kNoKey's node field is past n: read node 0's words instead)
-    const uint32_t vl = (best >> 8) & 0xfffffu, vc = vl < n ? vl : 0u;
-    pre = offs[vc];
-    asm volatile("" ::: "memory");
-    key = wave_min(best);
-    if (key == kNoKey) {   // no uncovered column: the levels hold a solution
-      if (TRACE) h = trace_node(h, dbase + depth, row_in, kNoneL, 0);
-      status = MPLD_FEASIBLE;
-      break;
-    }
-    v = (key >> 8) & 0xfffffu;
-    size = key >> 28;
-    if (TRACE) h = trace_node(h, dbase + depth, row_in, v, size);
-    }
-    uint32_t rows, offv, est, lane_lo, c;
-    bool full;
-    if (size != 0) {
-      rows = key & 0xffu;
-      offv = rdlane(pre, (v >> 5) & 63u);
-      est = esp;
-      lane_lo = 0u;
-      full = false;
-      c = (uint32_t)__builtin_ctz(rows);
-      if (STITCH) {
-        // the partner's color first when the partner is covered (its P bit
-        // is clear) and that row of v is open
-        const uint32_t p = uni((uint32_t)spart[v]);
-        if (p != 0xffffu && !((uni(PL[(p >> 5) * S + K]) >> (p & 31u)) & 1u)) {
-          const uint32_t cp = uni((uint32_t)scol[p]);
-          if ((rows >> cp) & 1u) c = cp;
-        }
-      }
-      rows &= ~(1u << c);   // the level's untried rows
-    } else {
-      // dead end: the headers and the log written so far must be visible
-      // to this wave's loads: a workgroup-scope fence waits for the stores
-      // (the workgroup's waves share the CU's write-through vector cache)
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-      // back to the deepest level below `depth` whose column has an untried row
-      const uint32_t f = deepest_open(depth);
-      if (f == kNoneL) { status = MPLD_INFEASIBLE; break; }
-      const uint2 hd = hdr[f];
-      est = uni(hd.x);
-      const uint32_t y = uni(hd.y);
-      v = y & 0xffffu;
-      offv = uni(offs[v]);
-      // uncover every level above f, and the rows level f removed; the
-      // column stays covered (its P bit is entry est); eight entries per
-      // lane in flight at a time
-      for (uint32_t i0 = est + 1u; i0 < esp; i0 += 64u * 8u) {
-        uint32_t e[8];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const uint32_t i = i0 + 64u * (uint32_t)q + lane;
-          e[q] = i < esp ? ent[i] : 0xffffffffu;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          if (e[q] != 0xffffffffu) {
-            const uint32_t uu = e[q] & kNodeMask;
-            atomicOr(&PL[(uu >> 5) * S + (e[q] >> kEntryNodeBits)], 1u << (uu & 31u));
-          }
-        }
-      }
-      // the next untried row of the level, in ascending order
-      rows = (y >> 16) & 0xffu;
-      c = (uint32_t)__builtin_ctz(rows);
-      rows &= rows - 1u;
-      depth = f;
-      lane_lo = 1u;
-      full = true;
-    }
-    take_row(v, c, rows, offv, est, lane_lo, rows != 0u, full);
-    row_in = v * (uint32_t)K + c;
-    ++depth;
-  }
-  __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-  __syncthreads();
-  if constexpr (SEQ) {
-    int64_t sol = -1;
-    int32_t pieces = 0;
-    // the colors of this task's levels, over those of the nodes below it
-    const auto put_colors = [&](int64_t to) {
-      seq_copy_colors(*io, to, n);
-      __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "workgroup");
-      uint8_t* out = io->a.arena + to;
-      for (uint32_t f = lane; f < depth; f += 64) {
-        const uint32_t y = hdr[f].y;
-        out[y & 0xffffu] = (uint8_t)((y >> 24) & 0xfu);
-      }
-    };
-    if (status == MPLD_FEASIBLE) {
-      sol = seq_reserve_colors(*io, n);
-      if (sol < 0) status = kSeqLost;
-      else put_colors(sol);
-    } else if (cut) {
-      status = kSeqCapped;
-      // (a piece that keeps the whole stack keeps the colors below it too)
-      if (max_pieces > 1u) put_colors(arena_at);
-      const int64_t col = max_pieces > 1u ? arena_at : io->task.col;
-      int64_t at = arena_at + ((n + 63u) & ~63u);
-      for (uint32_t top = depth;;) {
-        const uint32_t want = pieces == 0 ? (uint32_t)kSeqFirstLevels : 1u;
-        uint32_t lo = top, got = 0;
-        for (; got < want; ++got) {
-          const uint32_t f = deepest_open(lo);
-          if (f == kNoneL) break;
-          lo = f;
-        }
-        if (pieces != 0 && got == 0) break;   // nothing untried below
-        if (pieces == (int32_t)max_pieces - 1) lo = 0;   // the rest
-        const uint32_t elo = lo < top ? uni(hdr[lo].x) : esp;
-        uint8_t* out = io->a.arena + at;
-        const uint4* pw = reinterpret_cast<const uint4*>(PL);
-        for (uint32_t i = lane; i < saved_bytes / 16u; i += 64u) reinterpret_cast<uint4*>(out)[i] = pw[i];
-        uint2* hs = reinterpret_cast<uint2*>(out + saved_bytes);
-        for (uint32_t i = lane; i < top - lo; i += 64u) {
-          const uint2 hd = hdr[lo + i];
-          hs[i] = make_uint2(hd.x - elo, hd.y);   // the log starts at 0
-        }
-        uint32_t* es = reinterpret_cast<uint32_t*>(hs + (top - lo));
-        for (uint32_t i = elo + lane; i < esp; i += 64u) es[i - elo] = ent[i];
-        seq_put_piece(*io, child + pieces, pieces == 0 ? kSeqNode : kSeqNext, dbase + lo, top - lo, esp - elo,
-                      row_in, at, col);
-        ++pieces;
-        at += (int64_t)((saved_bytes + 8u * (top - lo) + 4u * (esp - elo) + 63u) & ~63u);
-        if (lo == 0) break;
-        // back to before level lo's row: its rows and column, and all above
-        asm volatile("" ::: "memory");
-        for (uint32_t i = elo + lane; i < esp; i += 64u) {
-          const uint32_t e = ent[i], u = e & kNodeMask;
-          atomicOr(&PL[(u >> 5) * S + (e >> kEntryNodeBits)], 1u << (u & 31u));
-        }
-        asm volatile("" ::: "memory");
-        esp = elo;
-        top = lo;
-      }
-    }
-    seq_put_result(*io, status, dbase + depth, nodes, h, sol, child, pieces);
-    __syncthreads();
-    return;
-  }
-  if (status == MPLD_FEASIBLE) {
-    for (uint32_t f = lane; f < depth; f += 64) {
-      const uint32_t y = hdr[f].y;
-      colors[y & 0xffffu] = (int8_t)((y >> 24) & 0xfu);
-    }
-  } else {
-    for (uint32_t v = lane; v < n; v += 64) colors[v] = -1;
-  }
-  rec->status = status;
-  rec->depth = status == MPLD_INFEASIBLE ? 0 : (int32_t)depth;
-  rec->nodes = nodes;
-  rec->hash = h;
-  __syncthreads();
-}
+#define LDS_SEQ 0
+#include "lds_one_wave.inc"
+#undef LDS_SEQ
+#define LDS_SEQ 1
+#include "lds_one_wave.inc"
+#undef LDS_SEQ
 
 // Big components: one workgroup of nw waves (nw = blockDim.x / 64).  Every
 // wave scans its share of the plane words; the per-wave minima meet in LDS
@@ -1467,11 +715,11 @@ __global__ __launch_bounds__(64) void seq_csr_kernel(const SeqArgs a, const DevD
     const uint32_t* g = adj32 + d.nbr_off;
     if constexpr (K <= kWideMaxK) {
       if (wide) {
-        solve_lds_wide<TRACE, K, false, true>(d, g, lds, my_stack, nullptr, nullptr, -1, 0, &io);
+        solve_lds_wide_seq<TRACE, K, false>(d, g, lds, my_stack, &io);
         return;
       }
     }
-    solve_lds<TRACE, K, false, true>(d, g, lds, nullptr, nullptr, -1, 0, &io);
+    solve_lds_seq<TRACE, K, false>(d, g, lds, &io);
   };
   if constexpr (!FINISH) {
     const int32_t* list = a.runs + (int64_t)(parity * kSeqTiers + kSeqCsr) * a.run_cap;
