@@ -97,7 +97,7 @@ uint32_t min_budget_of(const mpld_options* opt) {
 
 void batch_collect(mpld_batch* b, mpld_result* r) {
   if (b->flow.active) {
-    if (flow_collect(b->flow, *b->ctx->graph_builder, b->im, b->opt, b->db, r)) return;
+    if (flow_collect(b->flow, *b->ctx->graph_builder, b->opt, b->db, r)) return;
     // a recovery that the device gave up: this batch's host form from now on
     // (the packed components stay as they are)
     if (b->s.removal.empty()) flow_to_host(b->flow, b->ctx->stream, b->g, b->s);

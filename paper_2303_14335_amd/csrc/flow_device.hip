@@ -540,7 +540,7 @@ void flow_pack(FlowGraph& f, DeviceBatch& db, hipStream_t st) {
   check_hip(hipGetLastError(), "layout flow: packing");
 }
 
-bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_options& opt, DeviceBatch& db,
+bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, DeviceBatch& db,
                   mpld_result* r) {
   std::lock_guard<std::mutex> lk(gb.mu);
   mpld_context* ctx = gb.ctx;
@@ -618,7 +618,6 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_op
   r->stitches = (int64_t)h.stitches;
   r->conflicts = (int64_t)h.conflicts;
   r->uncolored = (int64_t)h.uncolored;
-  (void)im;
   return true;
 }
 

@@ -384,7 +384,7 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
 void flow_pack(FlowGraph& f, DeviceBatch& db, hipStream_t st);
 // Recovery, tallies and the result of a solved batch; waits.  False: the
 // recovery was given up (nothing in *r): the host does it.
-bool flow_collect(FlowGraph& f, GraphBuilder& gb, const Image& im, const mpld_options& opt, DeviceBatch& db,
+bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, DeviceBatch& db,
                   mpld_result* r);
 // The split in a caller's arrays (n, n, n, n + 1 entries; as many as it has are written); waits.
 void flow_split_out(FlowGraph& f, GraphBuilder& gb, int32_t* removal, int32_t* comp_of, int32_t* order,

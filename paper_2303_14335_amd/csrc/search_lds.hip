@@ -295,15 +295,7 @@ struct Lds1Words {
   }
 };
 
-// root_row >= 0: search only the subtree of root row (0, root_row) (a
-// subtree task of the heavy-component split): at the root every column has
-// all k rows, so the root column is node 0; its row is taken at depth 0
-// with no alternative left at that level, the root node itself is not
-// counted, and `budget` (> 0) replaces the component's.
-// STITCH: the stitch-aware row order (a column whose stitch partner is on
-// the path tries the partner's color first when that row is open, then the
-// others ascending); the CSR block then ends with the partners.
-// (solve_lds itself: lds_one_wave.inc, included below)
+// solve_lds itself is in lds_one_wave.inc, included below.
 
 // ---- one-wave wide tier ---------------------------------------------------
 //
