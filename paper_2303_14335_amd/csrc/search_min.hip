@@ -85,6 +85,11 @@ __global__ __launch_bounds__(64) void min_reg_kernel(const RegItems items, int32
 
 enum : uint8_t { kMinUnrun, kMinDone, kMinHead, kMinBetter, kMinGone };
 constexpr uint8_t kMinNone = 0xff;
+// MinPieces.finished.  A round takes at least the first piece off the list
+// (the first one left always runs, and runs to its end where it finds no room);
+// one that did not would be followed by the same again, so the search is then
+// done by one wave instead.
+enum : int32_t { kMinComplete = 1, kMinStuck = 2 };
 
 // A component's pieces.  An item is a piece not searched yet, one searched to
 // its end, or the searched front (head) of one whose rest became pieces.
@@ -112,6 +117,22 @@ __device__ __forceinline__ void min_wave_sync() {
 // Number of the lower lanes whose bit is set in m.
 __device__ __forceinline__ uint32_t lanes_below(uint64_t m) {
   return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// The front of the `want` spare ids taken off the top (a call by one lane), -1
+// if there are not as many.  In one step: taken with a subtraction that is given
+// back when it was too much, a third wave in between would find a count too low
+// but enough for it, and take ids from below the top that are spare still, or
+// in use already once the count is whole again.  No ids come back before the
+// round ends, so a try fails only for another's success.
+__device__ __forceinline__ int32_t min_take(int32_t* nspare, int32_t want) {
+  int32_t have = __hip_atomic_load(nspare, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  while (have >= want) {
+    const int32_t seen = atomicCAS(nspare, have, have - want);
+    if (seen == have) return have - want;
+    have = seen;
+  }
+  return -1;
 }
 
 // Exclusive sum over the wave; `total` the whole.
@@ -231,8 +252,10 @@ __device__ void min_fold(MinPieces& p, uint32_t budget) {
     p.improved = 0;
     ++p.round;
     if (over || left == 0) {
-      p.finished = 1;
+      p.finished = kMinComplete;
       p.result = over ? -(int32_t)budget : (int32_t)committed;
+    } else if (front == 0) {
+      p.finished = kMinStuck;
     }
   }
 }
@@ -278,18 +301,15 @@ __device__ __forceinline__ uint32_t min_piece(MinPieces& p, MinSearch<K>& s, uin
   if (stopped && !end) {
     const uint32_t levels = s.depth - lo;
     parts = levels < (uint32_t)kMinPieces ? levels : (uint32_t)kMinPieces;
-    int32_t have = 0;
-    if (lane == 0) {
-      have = atomicSub(&p.nspare, (int32_t)parts);
-      if (have < (int32_t)parts) atomicAdd(&p.nspare, (int32_t)parts);
-    }
-    have = (int32_t)uniform((uint32_t)have);
-    if (have < (int32_t)parts) {   // no room for its parts
+    int32_t at = 0;
+    if (lane == 0) at = min_take(&p.nspare, (int32_t)parts);
+    at = (int32_t)uniform((uint32_t)at);
+    if (at < 0) {   // no room for its parts
       if (!front) return s.nodes;  // searched again in a later round
       stopped = s.explore(lo, rest, true, 0, 0, 0, 0);
       parts = 0;
     } else {
-      ids = (uint32_t)have - parts;
+      ids = (uint32_t)at;
     }
   }
   if (front && s.best < best) {
@@ -386,7 +406,7 @@ __global__ __launch_bounds__(64 * kMinWaves) void min_pieces_kernel(const RegIte
         }
       }
       __syncthreads();
-      // every round counts or cuts the first piece, so the rounds end
+      // every round takes pieces off the front or is the last, so the rounds end
       for (;;) {
         const uint32_t share = kMinShare + 2u * uniform(p.round);
         const uint32_t most = share < kMinShareMost ? share : kMinShareMost;
@@ -404,8 +424,12 @@ __global__ __launch_bounds__(64 * kMinWaves) void min_pieces_kernel(const RegIte
         if (uniform((uint32_t)p.finished) != 0u) break;
       }
       if (wave == 0) {
-        if (in) colors[d.out_off + lane] = (int8_t)p.best_col[lane];
-        if (lane == 0) min_out[d.comp] = p.result;
+        int32_t r = (int32_t)uniform((uint32_t)p.result);
+        if (uniform((uint32_t)p.finished) == (uint32_t)kMinStuck)
+          r = minimize_core<K>(d, item_mask(items, item, lane), partners, colors, budget);
+        else if (in)
+          colors[d.out_off + lane] = (int8_t)p.best_col[lane];
+        if (lane == 0) min_out[d.comp] = r;
       }
     }
   }
