@@ -102,6 +102,7 @@ struct SplitArgs {
   // words: the giants' scans)
   int32_t *qpos, *parent, *root, *cid, *csize, *fill, *list, *rank, *mids, *bigs, *giants, *words;
   int32_t* ctl;         // the peeling's level ranges and tickets
+  int32_t spin;         // looks at a word after which the giants' workgroups give up waiting
 };
 
 // int32 words of the split's outputs (counts (2), queue, comp_of, order (n

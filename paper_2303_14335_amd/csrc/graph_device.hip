@@ -63,8 +63,13 @@ __device__ __forceinline__ uint64_t tile_word(uint32_t epoch, uint64_t state, in
 }
 
 // Exclusive prefix of tile `tile` (its sum: `sum`), by the lanes of one
-// wave; every lane gets it.
-__device__ int32_t look_back(uint64_t* status, uint32_t epoch, int32_t tile, int32_t sum) {
+// wave; every lane gets it.  -1: quit() said to wait no longer for the tiles
+// before (where blocks take tiles by ticket there is no need to).
+struct NeverQuit {
+  __device__ __forceinline__ bool operator()() const { return false; }
+};
+template <class Q>
+__device__ int32_t look_back(uint64_t* status, uint32_t epoch, int32_t tile, int32_t sum, Q&& quit) {
   const int32_t lane = (int32_t)(threadIdx.x & 63u);
   if (lane == 0)
     __hip_atomic_store(status + tile, tile_word(epoch, tile == 0 ? kTilePrefix : kTileSum, sum),
@@ -77,6 +82,7 @@ __device__ int32_t look_back(uint64_t* status, uint32_t epoch, int32_t tile, int
     for (;;) {
       if (at >= 0) w = __hip_atomic_load(status + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       if (__ballot((uint32_t)(w >> 34) != epoch || ((w >> 32) & 3u) == 0) == 0ull) break;
+      if (__ballot(quit()) != 0ull) return -1;
     }
     const uint64_t known = __ballot(((w >> 32) & 3u) == kTilePrefix);
     const int32_t stop = known ? (int32_t)__builtin_ctzll(known) : 63;
@@ -130,13 +136,14 @@ __device__ __forceinline__ int32_t take_tile(int32_t* ticket, uint32_t base, Sca
 }
 
 // Exclusive prefix, over the whole launch, of this thread's x; `end` =
-// prefix behind the block's last thread.
+// prefix behind the block's last thread.  sh.prefix = -1: quit() ended it.
+template <class Q = NeverQuit>
 __device__ __forceinline__ int32_t device_excl_scan(int32_t x, uint64_t* status, uint32_t epoch, int32_t tile,
-                                                    ScanShared& sh, int32_t& end) {
+                                                    ScanShared& sh, int32_t& end, Q&& quit = Q()) {
   int32_t total;
   const int32_t ex = block_excl_scan<kScanBlock>(x, sh.wsum, total);
   if (threadIdx.x < 64) {
-    const int32_t p = look_back(status, epoch, tile, total);
+    const int32_t p = look_back(status, epoch, tile, total, quit);
     if (threadIdx.x == 0) sh.prefix = p;
   }
   __syncthreads();
@@ -401,6 +408,7 @@ constexpr int kMidThreads = 512;
 constexpr int kMidGrid = 512;
 constexpr int32_t kBigNodes = 512, kFewBigs = 3, kGiantNodes = 4096;
 constexpr int kGiantBlocks = 128;
+constexpr int32_t kMeetSpin = 1 << 22;   // looks at a word before a wait is given up: some seconds
 constexpr int kLevelGrid = 1024;      // level kernels: blocks of 256 taking tiles by ticket
 
 // Levels 1 .. kWideLevels are found by launches over the device.
@@ -411,8 +419,8 @@ constexpr int kCtlTicket = 2 * (kWideLevels + 2);
 // ... then the lengths of the lists of larger components, and the meetings of
 // the workgroups that number the largest.
 constexpr int kCtlMids = kCtlTicket + kWideLevels + 2, kCtlBigs = kCtlMids + 1, kCtlGiants = kCtlMids + 2,
-              kCtlMeet = kCtlMids + 3, kCtlLost = kCtlMids + 4;
-constexpr int kCtlWords = kCtlMids + 5;
+              kCtlMeet = kCtlMids + 3;
+constexpr int kCtlWords = kCtlMids + 4;
 static_assert(kCtlWords <= 64, "ctl is 64 words at least");
 
 #define SPLIT_FOR(v, n)                                                                 \
@@ -648,7 +656,7 @@ __global__ __launch_bounds__(kScanBlock) void uf_root_kernel(SplitArgs a, int32_
     carry += total;
   }
   if (threadIdx.x < 64) {
-    const int32_t p = look_back(status, epoch, tile, carry);
+    const int32_t p = look_back(status, epoch, tile, carry, NeverQuit());
     if (threadIdx.x == 0) sh.prefix = p;
   }
   __syncthreads();
@@ -827,14 +835,18 @@ __global__ __launch_bounds__(kMidThreads) void bfs_mid_kernel(SplitArgs a) {
 // each level: a level of some 400 nodes of 22 neighbours (a packed window)
 // is 50 blocks' work of one wave-wide step, and one workgroup took 140 us for
 // it.  Positions and order go past the caches of one compute unit (agent
-// scope); every wait ends: all blocks of this launch fit the device at once,
-// and a block that has waited far too long (others' kernels kept the rest of
-// the blocks out) reports it and leaves, as do the others after it; the graph
-// is then split on the host.
+// scope).  All blocks of this launch fit the device at once; should others'
+// kernels keep some out, every wait ends all the same: a block that has waited
+// far too long sets kMeetLost in the word that counts the meetings, every wait
+// looks at that bit, and a meeting counts only if the word is read without it.
+// So a block that leaves is waited for by nobody, and the graph is then split
+// on the host.
+constexpr int32_t kMeetLost = 1 << 30;
 __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
   __shared__ ScanShared sh;
   __shared__ int32_t lost;
   constexpr int32_t G = 32, kNodes = kScanBlock / G;
+  int32_t* const word = a.ctl + kCtlMeet;
   const int32_t giants = a.ctl[kCtlGiants], bigs = a.ctl[kCtlBigs];
   const int32_t count = giants + (bigs > kFewBigs ? 0 : bigs);
   // tiles' words of even and of odd levels: a block that has met the others
@@ -844,26 +856,39 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
   const int32_t level_words = a.n / kNodes + 1;
   uint32_t tag = 0;
   int32_t met = 0;
-  if (threadIdx.x == 0) lost = 0;
+  const auto give_up = [&] {
+    a.counts[0] = a.n;   // no split: the host does it
+    a.counts[1] = -1;
+  };
   const auto meet = [&] {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0);   // this wave's stores are out
     __syncthreads();
     if (threadIdx.x == 0) {
       met += (int32_t)gridDim.x;
-      atomicAdd(a.ctl + kCtlMeet, 1);
-      for (int32_t spin = 0; ld_agent(a.ctl + kCtlMeet) < met; ++spin)
-        if (spin > (1 << 22) || ld_agent(a.ctl + kCtlLost)) {
-          atomicOr(a.ctl + kCtlLost, 1);
-          a.counts[0] = a.n;   // no split: the host does it
-          a.counts[1] = -1;
-          lost = 1;
-          break;
+      int32_t have = atomicAdd(word, 1) + 1;
+      for (int32_t spin = 0; have < met; ++spin) {
+        if (spin < a.spin) {
+          have = ld_agent(word);
+        } else {   // only while the meeting is incomplete: then nobody has passed it
+          const int32_t seen = atomicCAS(word, have, have | kMeetLost);
+          have = seen == have ? have | kMeetLost : seen;
         }
+      }
+      lost = have & kMeetLost;
+      if (lost) give_up();
     }
     __syncthreads();
     asm volatile("" ::: "memory");
     return lost == 0;
+  };
+  // in a level this block has not met the others yet: the meeting is incomplete
+  int32_t waited = 0;
+  const auto quit = [&] {
+    if (ld_agent(word) & kMeetLost) return true;
+    if (++waited < a.spin) return false;
+    atomicOr(word, kMeetLost);
+    return true;
   };
   for (int32_t g = 0; g < count; ++g) {
     const int32_t c = g < giants ? a.giants[g] : a.bigs[g - giants], sz = a.comp_ptr[c + 1] - a.comp_ptr[c];
@@ -875,6 +900,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
     if (!meet()) return;
     for (int32_t lo = 0, hi = 1; lo < hi;) {
       ++tag;
+      waited = 0;
       uint64_t* const status = words + (tag & 1u ? level_words : 0);
       const int32_t tiles = (hi - lo + kNodes - 1) / kNodes;
       for (int32_t tile = (int32_t)blockIdx.x; tile < tiles; tile += (int32_t)gridDim.x) {
@@ -885,7 +911,11 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
         const int32_t found = group_count<G>(a, u, hit, test);
         int32_t end;
         const int32_t at =
-            of_group<G>(hi + device_excl_scan(leads_group<G>() ? found : 0, status, tag, tile, sh, end));
+            of_group<G>(hi + device_excl_scan(leads_group<G>() ? found : 0, status, tag, tile, sh, end, quit));
+        if (sh.prefix < 0) {
+          if (threadIdx.x == 0) give_up();
+          return;
+        }
         if (found)
           group_put<G>(a, u, hit, at, test, [&](int32_t w, int32_t q) {
             if (q < sz) {
@@ -963,6 +993,7 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
                         int32_t* ptr_w) {
   const size_t nn = (size_t)n;
   SplitArgs a{};
+  a.spin = kMeetSpin;
   a.n = n;
   a.k = k;
   a.simplify = simplify ? 1 : 0;

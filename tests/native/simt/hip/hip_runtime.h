@@ -5,8 +5,8 @@
 // A lane is a fiber.  The lanes of a wave go on together from one cross-lane
 // operation to the next (all lanes of the wave have to reach it); which wave
 // of a workgroup goes on next is drawn at every such operation and at every
-// atomic one.  The workgroups of a launch run one after another, or, with
-// simt::concurrent, side by side in threads.
+// atomic one.  The workgroups of a launch run one after another, or, for launches
+// of simt::concurrent workgroups, side by side in threads.
 #pragma once
 
 #include <sys/mman.h>
@@ -98,7 +98,8 @@ struct Block {
 };
 
 inline thread_local Lane* cur = nullptr;
-inline bool concurrent = false;      // workgroups of a launch in threads
+inline unsigned concurrent = 0;      // launches of this many workgroups run them in threads
+inline unsigned grid_now = 0;        // workgroups of the launch that runs
 inline uint64_t seed = 1;
 inline uint64_t hold = 1;            // most turns that a lane waits before an atomic operation
 // Called by a lane before an atomic operation (a test may hold it up there).
@@ -251,7 +252,8 @@ inline void run_block(dim3 idx, dim3 grid, dim3 dim, const std::function<void()>
 }
 
 inline void launch(dim3 grid, dim3 dim, const std::function<void()>& body) {
-  if (!concurrent) {
+  grid_now = grid.x;
+  if (grid.x != concurrent) {
     for (unsigned i = 0; i < grid.x; ++i) run_block(dim3(i, 0, 0), grid, dim, body, seed * 1000003u + i);
     return;
   }

@@ -13,9 +13,9 @@ NATIVE = os.path.join(ROOT, "tests", "native")
 SELECT = 'asm("v_cndmask_b32_e64 %0, 0, %1, %2" : "=v"(r) : "v"(x), "s"(mask));'
 
 
-def build(folder, driver, edits=()):
+def build(folder, driver, edits=(), also=()):
     """The driver over a copy of the kernels' sources in `folder`; edits:
-    (file, text, other text), each there exactly once."""
+    (file, text, other text), each there exactly once; also: host sources."""
     gxx = shutil.which("g++")
     if gxx is None or os.uname().machine != "x86_64":
         pytest.skip("needs g++ on x86-64")
@@ -32,7 +32,9 @@ def build(folder, driver, edits=()):
         with open(path, "w") as f:
             f.write(s.replace(text, other))
     exe = os.path.join(str(folder), "run")
-    subprocess.run([gxx, "-x", "c++", "-std=c++17", "-O2", "-w", "-I", os.path.join(NATIVE, "simt"), "-I", src,
-                    "-I", os.path.join(ROOT, "include"), os.path.join(NATIVE, driver), "-o", exe, "-lpthread"],
-                   check=True, capture_output=True, text=True)
+    done = subprocess.run([gxx, "-x", "c++", "-std=c++17", "-O2", "-w", "-I", os.path.join(NATIVE, "simt"), "-I", src,
+                           "-I", os.path.join(ROOT, "include"), os.path.join(NATIVE, driver),
+                           *(os.path.join(CSRC, f) for f in also), "-o", exe, "-lpthread"],
+                          capture_output=True, text=True)
+    assert done.returncode == 0, done.stderr
     return exe
