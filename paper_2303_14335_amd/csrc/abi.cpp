@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
 #include <cstring>
 #include <exception>
 #include <new>
@@ -51,14 +52,34 @@ void check_options(const mpld_options* opt) {
 }
 
 // Graphs of at least this many nodes and pairs together go through the
-// device's flow: some 35 launches, 0.2 ms whatever the size, where the host's
-// passes take time in proportion to both.  Host against device, ms: k = 3,
-// 4100 nodes and 4400 pairs 0.24 / 0.35, 6000 and 6300 0.41 / 0.45, 8000 and
-// 8500 0.54 / 0.47, 32000 and 34500 1.72 / 0.60; sparser, 8000 and 5100 0.31 /
-// 0.31; k = 4 with stitches, 6000 and 6900 0.41 / 0.42, 8800 and 9900 0.71 /
-// 0.58, 23500 and 26700 1.63 / 0.77.  The two meet at 12,000 to 14,000; the
-// line stays a little below, where large clusters' numbering is the device's.
-constexpr int64_t kFlowMinSize = 11000;
+// device's flow: some 35 launches, 0.3 ms whatever the size, where the host's
+// passes take time in proportion to both, 20 to 25 ns each where a node's
+// neighbours lie anywhere in memory.  Host against device, ms: k = 3, 13,300
+// together 0.30 / 0.30, 19,800 0.44 / 0.31, 32,900 0.69 / 0.34, 82,700 1.5 /
+// 0.37; k = 4 with stitches, 19,800 0.92 / 0.74.
+// Where ids follow the layout the host takes 7 ns: a path of 40,000 together
+// 0.28 / 0.42, of 80,000 0.63 / 0.60, of 200,000 1.25 / 1.17.  That is told from
+// 64 of the pairs: in such a graph most join near ids.
+// A graph that the device gives up (split_limits in graph_device.hip: deep
+// peelings, long narrow components; a recovery that is one long chain) costs
+// the front of the flow besides.  Host alone / both, ms: lines with two
+// neighbours on either side (k = 3), ids in order, 60,000 0.43 / 0.43 (the host's
+// at once), 300,000 2.0 / 2.4, ids in no order, 24,000 0.39 / 0.62, 60,000 1.0 /
+// 1.3, 300,000 6.1 / 6.4; a packed window of 1:100, 50,000 2.0 / 2.4, 106,000
+// 4.0 / 4.4, 455,000 17.1 / 20.1.
+constexpr int64_t kFlowMinSize = 14000, kFlowMinOrdered = 60000;
+
+bool flow_pays(const mpld_context& ctx, const mpld_graph& g) {
+  const int64_t size = (int64_t)g.num_nodes + g.num_ce;
+  if (ctx.flow_from >= 0) return size >= ctx.flow_from;
+  if (size < kFlowMinSize || size >= kFlowMinOrdered || g.num_ce <= 0 || !g.ce) return size >= kFlowMinSize;
+  int near = 0;
+  for (int64_t i = 0; i < 64; ++i) {
+    const int32_t* e = g.ce + 2 * (i * g.num_ce / 64);
+    near += std::abs((int64_t)e[0] - e[1]) <= 64 ? 1 : 0;
+  }
+  return near < 48;
+}
 
 void use_device(mpld_context* ctx) {
   if (!ctx) fail(MPLD_E_INVALID, "context is NULL");
@@ -75,7 +96,7 @@ void batch_build(mpld_context* ctx, const mpld_graph* g, const mpld_options* opt
   const bool simplify = opt->flags & MPLD_SIMPLIFY;
   // large graphs are validated, simplified, split and packed on the
   // device (identical results)
-  if ((int64_t)g->num_nodes + g->num_ce >= kFlowMinSize) {
+  if (flow_pays(*ctx, *g)) {
     if (!ctx->graph_builder) ctx->graph_builder = graph_builder_create(ctx, false);
     (void)flow_build(b->flow, *ctx->graph_builder, *g, opt->k, simplify);
   }
@@ -96,11 +117,12 @@ uint32_t min_budget_of(const mpld_options* opt) {
 }
 
 void batch_collect(mpld_batch* b, mpld_result* r) {
-  if (b->flow.active) {
+  if (b->flow.active && !b->flow.host_form) {
     if (flow_collect(b->flow, *b->ctx->graph_builder, b->opt, b->db, r)) return;
     // a recovery that the device gave up: this batch's host form from now on
     // (the packed components stay as they are)
-    if (b->s.removal.empty()) flow_to_host(b->flow, b->ctx->stream, b->g, b->s);
+    flow_to_host(b->flow, *b->ctx->graph_builder, b->g, b->s);
+    b->flow.host_form = true;
   }
   std::vector<DevRecord> recs;
   std::vector<int8_t> lcol;
@@ -178,15 +200,28 @@ int32_t mpld_split_graph_device(mpld_context* ctx, const mpld_graph* g, int32_t 
       *num_comps = f.ncomp;
       return;
     }
-    const Graph gr = make_graph(*g);
-    Split s;
-    split_graph_device(*ctx->graph_builder, gr, k, flags & MPLD_SIMPLIFY, s);
+    const Split s = simplify_and_split(make_graph(*g), k, flags & MPLD_SIMPLIFY);
     std::copy(s.removal.begin(), s.removal.end(), removal_order);
     *num_removed = (int32_t)s.removal.size();
     std::copy(s.comp_of.begin(), s.comp_of.end(), comp_of);
     std::copy(s.order.begin(), s.order.end(), bfs_order);
     std::copy(s.comp_ptr.begin(), s.comp_ptr.end(), comp_ptr);
     *num_comps = (int32_t)s.comp_ptr.size() - 1;
+  });
+}
+
+// For tests, and not declared in the header: levels after which a split and
+// rounds after which a recovery are left to the host, and nodes and pairs from
+// which a graph goes to the device (-1: the rules); left: how often the host has
+// taken a split and a recovery back on this context.
+int32_t mpld_test_flow_limits(mpld_context* ctx, int32_t levels, int32_t rounds, int64_t from, int64_t* left) {
+  return guard([&] {
+    if (!ctx || !left) fail(MPLD_E_INVALID, "NULL argument");
+    ctx->split_levels = levels;
+    ctx->recover_rounds = rounds;
+    ctx->flow_from = from;
+    left[0] = ctx->splits_left;
+    left[1] = ctx->recoveries_left;
   });
 }
 

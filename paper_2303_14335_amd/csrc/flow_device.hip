@@ -268,7 +268,6 @@ __global__ __launch_bounds__(256) void flow_pack_csr_kernel(const DevDesc* descs
 // ---- recovery and tallies -----------------------------------------------------
 
 static constexpr int32_t kPending = -2;      // a removed node not colored yet
-static constexpr int32_t kRecoverSpin = 1024;
 
 __device__ __forceinline__ int32_t ld_color(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -296,9 +295,10 @@ __global__ __launch_bounds__(256) void flow_colors_kernel(int32_t n, int32_t rem
 // thread waits for exactly those neighbours (and its stitch partner).
 // Blocks take their place in the order by a ticket, so a block only ever
 // waits for blocks that already run; a chain of dependencies longer than
-// the wait (ids that run along a path of thousands of nodes) is given up
+// `rounds` (ids that run along a path of thousands of nodes) is given up
 // and left to the host.
-__global__ __launch_bounds__(256) void flow_recover_kernel(int32_t removed, int32_t k, FlowHead* head,
+__global__ __launch_bounds__(256) void flow_recover_kernel(int32_t removed, int32_t k, int32_t rounds,
+                                                           FlowHead* head,
                                                            const int32_t* ptr, const int32_t* adj,
                                                            const int32_t* partner, const int32_t* queue,
                                                            const int32_t* qpos, int32_t* col) {
@@ -335,7 +335,7 @@ __global__ __launch_bounds__(256) void flow_recover_kernel(int32_t removed, int3
   // A lane keeps what it has read and asks for one color a round.  It stores
   // its own inside the loop, not on its way out: lanes of its own wave may
   // be waiting for it.
-  for (int32_t spin = 0; spin < kRecoverSpin; ++spin) {
+  for (int32_t spin = 0; spin < rounds; ++spin) {
     while (!done) {
       if (w >= 0) {
         const int32_t c = ld_color(col + w);
@@ -357,7 +357,7 @@ __global__ __launch_bounds__(256) void flow_recover_kernel(int32_t removed, int3
       done = true;
     }
     if (__ballot(!done) == 0ull) break;
-    if ((spin & 63) == 63 && (ld_color(&head->flags) & kFlowChain)) break;
+    if ((spin & 15) == 15 && (ld_color(&head->flags) & kFlowChain)) break;
   }
   if (!done) atomicOr(&head->flags, kFlowChain);
 }
@@ -505,6 +505,7 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
   check_hip(hipStreamSynchronize(st), "layout flow: front-end");
   FlowHead h;
   std::memcpy(&h, ho, sizeof(h));
+  if (h.ncomp == -1) ++ctx->splits_left;
   if (h.flags || h.ncomp == -1) return false;   // a fault or a hub; a split that the device gave up
   if (h.removed < 0 || h.removed > n || h.ncomp < 0 || h.ncomp > n - h.removed)
     fail(MPLD_E_INTERNAL, "layout flow: bad counts");
@@ -540,6 +541,11 @@ void flow_pack(FlowGraph& f, DeviceBatch& db, hipStream_t st) {
   check_hip(hipGetLastError(), "layout flow: packing");
 }
 
+// Looks at a neighbour's color, 1 us each, after which a recovery is the
+// host's: as long as the host takes for its own (about 10 ns a node).  The
+// longest chain is 10 to 20 nodes where ids are in no order.
+static int32_t recover_rounds(int32_t removed) { return 32 + std::min(removed / 128, 1024 - 32); }
+
 bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, DeviceBatch& db,
                   mpld_result* r) {
   std::lock_guard<std::mutex> lk(gb.mu);
@@ -558,9 +564,10 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, Devic
   const unsigned gn = flow_grid(f.n);
   hipLaunchKernelGGL(flow_colors_kernel, dim3(gn), dim3(256), 0, st, f.n, f.removed, head, f.queue, f.comp_of,
                      f.comp_ptr, f.local, db.colors.as<int8_t>(), col, qpos, cstat, f.ncomp);
+  const int32_t rounds = ctx->recover_rounds >= 0 ? ctx->recover_rounds : recover_rounds(f.removed);
   if (f.simplify && f.removed)
     hipLaunchKernelGGL(flow_recover_kernel, dim3((unsigned)((f.removed + 255) / 256)), dim3(256), 0, st,
-                       f.removed, opt.k, head, f.ptr, f.adj, f.partner, f.queue, qpos, col);
+                       f.removed, opt.k, rounds, head, f.ptr, f.adj, f.partner, f.queue, qpos, col);
   hipLaunchKernelGGL(flow_tally_kernel, dim3(std::min(gn, 512u)), dim3(256), 0, st, f.n, f.ptr, f.adj, f.partner, f.comp_of,
                      col, colors, cstat, head);
   check_hip(hipGetLastError(), "layout flow: recovery");
@@ -585,7 +592,10 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, Devic
   device_time(db);
   FlowHead h;
   std::memcpy(&h, ho + o_head, sizeof(h));
-  if (h.flags & kFlowChain) return false;
+  if (h.flags & kFlowChain) {
+    ++ctx->recoveries_left;
+    return false;
+  }
   if (h.flags & kFlowNoColor) fail(MPLD_E_INTERNAL, "recovery found no free color");
   const auto* recs = reinterpret_cast<const DevRecord*>(ho + o_rec);
   const auto* stat = reinterpret_cast<const int32_t*>(ho + o_head + 4 * head_words);
@@ -646,34 +656,27 @@ void flow_split_out(FlowGraph& f, GraphBuilder& gb, int32_t* removal, int32_t* c
   std::memcpy(comp_ptr, h + 2 * nn, 4 * nptr);
 }
 
-void flow_to_host(FlowGraph& f, hipStream_t st, Graph& g, Split& s) {
-  const size_t nn = (size_t)f.n;
-  std::vector<int32_t> ptr(nn + 1);
+void flow_to_host(FlowGraph& f, GraphBuilder& gb, Graph& g, Split& s) {
+  std::lock_guard<std::mutex> lk(gb.mu);
+  const size_t nn = (size_t)f.n, words = (size_t)(f.local - f.ptr) + nn;
+  // everything that is kept, in one copy: eight apart took longer than the
+  // host's recovery of a small layout
+  if (!grow_pinned(gb.hout, 4 * words)) fail(MPLD_E_NOMEM, "layout flow: pinned host memory");
+  check_hip(hipMemcpyAsync(gb.hout.p, f.ptr, 4 * words, hipMemcpyDeviceToHost, gb.stream), "layout flow: download");
+  check_hip(hipStreamSynchronize(gb.stream), "layout flow: download");
+  const auto at = [&](const int32_t* p) { return gb.hout.as<int32_t>() + (p - f.ptr); };
   g = Graph();
   s = Split();
   g.n = f.n;
   g.num_ce = f.m;
-  g.adj.resize(2 * (size_t)f.m);
-  g.partner.resize(nn);
-  s.removal.resize((size_t)f.removed);
-  s.comp_of.resize(nn);
-  s.order.resize(nn - (size_t)f.removed);
-  s.comp_ptr.resize((size_t)f.ncomp + 1);
-  s.local.resize(nn);
-  auto down = [&](std::vector<int32_t>& v, const int32_t* p) {
-    if (!v.empty())
-      check_hip(hipMemcpyAsync(v.data(), p, 4 * v.size(), hipMemcpyDeviceToHost, st), "layout flow: download");
-  };
-  down(ptr, f.ptr);
-  down(g.adj, f.adj);
-  down(g.partner, f.partner);
-  down(s.removal, f.queue);
-  down(s.comp_of, f.comp_of);
-  down(s.order, f.order);
-  down(s.comp_ptr, f.comp_ptr);
-  down(s.local, f.local);
-  check_hip(hipStreamSynchronize(st), "layout flow: download");
-  g.ptr.assign(ptr.begin(), ptr.end());
+  g.ptr.assign(at(f.ptr), at(f.ptr) + nn + 1);
+  g.adj.assign(at(f.adj), at(f.adj) + 2 * (size_t)f.m);
+  g.partner.assign(at(f.partner), at(f.partner) + nn);
+  s.removal.assign(at(f.queue), at(f.queue) + f.removed);
+  s.comp_of.assign(at(f.comp_of), at(f.comp_of) + nn);
+  s.order.assign(at(f.order), at(f.order) + (nn - (size_t)f.removed));
+  s.comp_ptr.assign(at(f.comp_ptr), at(f.comp_ptr) + f.ncomp + 1);
+  s.local.assign(at(f.local), at(f.local) + nn);
 }
 
 }  // namespace mpld

@@ -87,6 +87,14 @@ inline bool grow_pinned(PinnedBuf& b, size_t bytes) {
 // Exclusive scan of in[0 .. n) into out[0 .. n], out[n] = the total.
 void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out);
 
+// Past one of these the device leaves a split to the host.
+struct SplitLimits {
+  int32_t peel, mid, giant;   // levels of the peeling's tail and of the numbering: of the components that
+                              // a workgroup takes, and of those that several number together
+  int32_t degree;             // a node's neighbours
+  int32_t spin;               // looks at a word before a wait among workgroups is given up
+};
+
 struct SplitArgs {
   int32_t n, k, simplify;
   const int32_t* ptr;   // n + 1 CSR offsets
@@ -102,7 +110,7 @@ struct SplitArgs {
   // words: the giants' scans)
   int32_t *qpos, *parent, *root, *cid, *csize, *fill, *list, *rank, *mids, *bigs, *giants, *words;
   int32_t* ctl;         // the peeling's level ranges and tickets
-  int32_t spin;         // looks at a word after which the giants' workgroups give up waiting
+  SplitLimits limits;
 };
 
 // int32 words of the split's outputs (counts (2), queue, comp_of, order (n

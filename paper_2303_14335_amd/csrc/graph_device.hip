@@ -419,13 +419,22 @@ constexpr int kCtlTicket = 2 * (kWideLevels + 2);
 // ... then the lengths of the lists of larger components, and the meetings of
 // the workgroups that number the largest.
 constexpr int kCtlMids = kCtlTicket + kWideLevels + 2, kCtlBigs = kCtlMids + 1, kCtlGiants = kCtlMids + 2,
-              kCtlMeet = kCtlMids + 3;
-constexpr int kCtlWords = kCtlMids + 4;
+              kCtlMeet = kCtlMids + 3, kCtlOver = kCtlMids + 4;
+constexpr int kCtlWords = kCtlMids + 5;
 static_assert(kCtlWords <= 64, "ctl is 64 words at least");
 
 #define SPLIT_FOR(v, n)                                                                 \
   for (int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x); v < (n);          \
        v += (int32_t)(gridDim.x * blockDim.x))
+
+// The split is left to the host (kCtlOver): the launches behind find nothing
+// to do, and the counts say so.
+__device__ __forceinline__ bool left_to_host(const SplitArgs& a) { return a.ctl[kCtlOver] != 0; }
+__device__ __forceinline__ void leave_to_host(const SplitArgs& a) {
+  a.ctl[kCtlOver] = 1;
+  a.counts[0] = a.n;
+  a.counts[1] = -1;
+}
 
 // fault (may be null): a nonzero word makes the graph one without pairs (the
 // kernels behind take ascending, symmetric lists for granted).
@@ -457,7 +466,11 @@ __global__ __launch_bounds__(kScanBlock) void split_seed_kernel(SplitArgs a, int
   uint32_t seeds = 0;
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j)
-    if (base + j < a.n && a.simplify && a.ptr[base + j + 1] - a.ptr[base + j] < a.k) seeds |= 1u << j;
+    if (base + j < a.n) {
+      const int32_t deg = a.ptr[base + j + 1] - a.ptr[base + j];
+      if (a.simplify && deg < a.k) seeds |= 1u << j;
+      if (deg > a.limits.degree) a.ctl[kCtlOver] = 1;
+    }
   int32_t end;
   int32_t run = device_excl_scan(__builtin_popcount(seeds), status, epoch, tile, sh, end);
 #pragma unroll
@@ -540,7 +553,8 @@ __global__ __launch_bounds__(kScanBlock) void split_level_kernel(SplitArgs a, in
                                                                  uint32_t epoch) {
   __shared__ ScanShared sh;
   constexpr int32_t kNodes = kScanBlock / G;
-  const int32_t lo = a.ctl[2 * L], hi = a.ctl[2 * L + 1], tiles = (hi - lo + kNodes - 1) / kNodes;
+  const int32_t lo = a.ctl[2 * L], hi = a.ctl[2 * L + 1];
+  const int32_t tiles = left_to_host(a) ? 0 : (hi - lo + kNodes - 1) / kNodes;
   if (tiles == 0 && blockIdx.x == 0 && threadIdx.x == 0) {
     a.ctl[2 * L + 2] = hi;
     a.ctl[2 * L + 3] = hi;
@@ -569,7 +583,12 @@ __global__ __launch_bounds__(kSplitThreads) void split_peel_kernel(SplitArgs a) 
   __shared__ int32_t wsum[kSplitThreads / 64];
   constexpr int32_t G = 8, kNodes = kSplitThreads / G;
   int32_t lo = a.ctl[2 * (kWideLevels + 1)], hi = a.ctl[2 * (kWideLevels + 1) + 1];
-  while (lo < hi) {
+  bool over = left_to_host(a);
+  for (int32_t levels = 0; lo < hi && !over; ++levels) {
+    if (levels == a.limits.peel) {
+      over = true;
+      break;
+    }
     int32_t next = hi;
     for (int32_t base = lo; base < hi; base += kNodes) {
       const int32_t p = base + (int32_t)threadIdx.x / G;
@@ -586,7 +605,11 @@ __global__ __launch_bounds__(kSplitThreads) void split_peel_kernel(SplitArgs a) 
     lo = hi;
     hi = next;
   }
-  if (threadIdx.x == 0) a.counts[0] = hi;
+  __syncthreads();   // (all have looked at the word)
+  if (threadIdx.x == 0) {
+    if (over) leave_to_host(a);
+    else a.counts[0] = hi;
+  }
 }
 
 __device__ __forceinline__ int32_t ld_agent(const int32_t* p) {
@@ -614,6 +637,7 @@ __device__ int32_t uf_find(int32_t* parent, int32_t x) {
 // took 0.17 ms with one lane a node, 1.7 ms with 16).
 template <int G>
 __global__ __launch_bounds__(256) void uf_unite_kernel(SplitArgs a) {
+  if (left_to_host(a)) return;
   const int32_t groups = (int32_t)(gridDim.x * blockDim.x) / G;
   for (int32_t v = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x) / G; v < a.n; v += groups) {
     if (a.qpos[v] >= 0) continue;
@@ -638,13 +662,14 @@ __global__ __launch_bounds__(kScanBlock) void uf_root_kernel(SplitArgs a, int32_
   const int32_t tile = take_tile(ticket, ticket_base, sh);
   // a thread's nodes are kScanBlock apart: neighbouring threads read
   // neighbouring parents, and the tile's order is kept by its rounds
+  const bool none = left_to_host(a);
   int32_t carry = 0;
   int32_t num[kScanItems];
 #pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
     const int64_t v = (int64_t)tile * kScanTile + j * kScanBlock + threadIdx.x;
     int32_t r = -1;   // (removed nodes have no parent)
-    if (v < a.n && a.qpos[v] < 0) {
+    if (v < a.n && a.qpos[v] < 0 && !none) {
       r = (int32_t)v;
       for (int32_t p = a.parent[r]; p != r; p = a.parent[r]) r = p;
     }
@@ -689,7 +714,7 @@ __global__ __launch_bounds__(256) void comp_kernel(SplitArgs a) {
 // Core nodes of the components of at most 64 nodes listed per component (any
 // order within it); the larger components in two lists, by who numbers them.
 __global__ __launch_bounds__(256) void comp_list_kernel(SplitArgs a) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[1] = a.cid[a.n];
+  if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[1] = left_to_host(a) ? -1 : a.cid[a.n];
   SPLIT_FOR(v, a.n) {
     const int32_t c = a.comp_of[v];
     if (c < 0) continue;
@@ -796,6 +821,7 @@ __global__ __launch_bounds__(kMidThreads) void bfs_mid_kernel(SplitArgs a) {
   constexpr int32_t G = 8, kNodes = kMidThreads / G;
   const int32_t mids = a.ctl[kCtlMids], bigs = a.ctl[kCtlBigs];
   const int32_t first = bigs > kFewBigs ? bigs : 0;   // the larger ones first
+  int32_t levels = 0;   // of all its components
   for (int32_t i = (int32_t)blockIdx.x; i < first + mids; i += (int32_t)gridDim.x) {
     const int32_t c = i < first ? a.bigs[i] : a.mids[i - first], sz = a.comp_ptr[c + 1] - a.comp_ptr[c];
     int32_t* order = a.order + a.comp_ptr[c];
@@ -805,6 +831,10 @@ __global__ __launch_bounds__(kMidThreads) void bfs_mid_kernel(SplitArgs a) {
     }
     __syncthreads();
     for (int32_t lo = 0, hi = 1; lo < hi;) {
+      if (++levels > a.limits.mid) {
+        if (threadIdx.x == 0) leave_to_host(a);
+        return;
+      }
       int32_t next = hi;
       for (int32_t base = lo; base < hi; base += kNodes) {
         const int32_t p = base + (int32_t)threadIdx.x / G;
@@ -848,7 +878,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
   constexpr int32_t G = 32, kNodes = kScanBlock / G;
   int32_t* const word = a.ctl + kCtlMeet;
   const int32_t giants = a.ctl[kCtlGiants], bigs = a.ctl[kCtlBigs];
-  const int32_t count = giants + (bigs > kFewBigs ? 0 : bigs);
+  const int32_t count = left_to_host(a) ? 0 : giants + (bigs > kFewBigs ? 0 : bigs);
   // tiles' words of even and of odd levels: a block that has met the others
   // after a level may write the next level's before a slow one has read the
   // last of this level's, so they are apart (a block is never two levels ahead)
@@ -856,10 +886,6 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
   const int32_t level_words = a.n / kNodes + 1;
   uint32_t tag = 0;
   int32_t met = 0;
-  const auto give_up = [&] {
-    a.counts[0] = a.n;   // no split: the host does it
-    a.counts[1] = -1;
-  };
   const auto meet = [&] {
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0);   // this wave's stores are out
@@ -868,7 +894,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
       met += (int32_t)gridDim.x;
       int32_t have = atomicAdd(word, 1) + 1;
       for (int32_t spin = 0; have < met; ++spin) {
-        if (spin < a.spin) {
+        if (spin < a.limits.spin) {
           have = ld_agent(word);
         } else {   // only while the meeting is incomplete: then nobody has passed it
           const int32_t seen = atomicCAS(word, have, have | kMeetLost);
@@ -876,7 +902,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
         }
       }
       lost = have & kMeetLost;
-      if (lost) give_up();
+      if (lost) leave_to_host(a);
     }
     __syncthreads();
     asm volatile("" ::: "memory");
@@ -886,7 +912,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
   int32_t waited = 0;
   const auto quit = [&] {
     if (ld_agent(word) & kMeetLost) return true;
-    if (++waited < a.spin) return false;
+    if (++waited < a.limits.spin) return false;
     atomicOr(word, kMeetLost);
     return true;
   };
@@ -898,8 +924,14 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
       __hip_atomic_store(a.local + a.parent[c], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (!meet()) return;
+    // a component that is growing so slowly that it will not get there: one as
+    // wide as it is long has a sixteenth of its nodes after a quarter of its levels
+    const uint32_t quarter = tag + (uint32_t)a.limits.giant / 4u;
     for (int32_t lo = 0, hi = 1; lo < hi;) {
-      ++tag;
+      if (++tag > (uint32_t)a.limits.giant || (tag == quarter && hi < sz / 12)) {   // all workgroups count alike
+        if (threadIdx.x == 0) leave_to_host(a);
+        return;
+      }
       waited = 0;
       uint64_t* const status = words + (tag & 1u ? level_words : 0);
       const int32_t tiles = (hi - lo + kNodes - 1) / kNodes;
@@ -913,7 +945,7 @@ __global__ __launch_bounds__(kScanBlock) void bfs_giant_kernel(SplitArgs a) {
         const int32_t at =
             of_group<G>(hi + device_excl_scan(leads_group<G>() ? found : 0, status, tag, tile, sh, end, quit));
         if (sh.prefix < 0) {
-          if (threadIdx.x == 0) give_up();
+          if (threadIdx.x == 0) leave_to_host(a);
           return;
         }
         if (found)
@@ -988,12 +1020,30 @@ void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
   check_hip(hipGetLastError(), "graph builder: scan");
 }
 
+// What a split may take on the device before the host is to do it (identical
+// results).  A level of the peeling's tail takes some 2.5 us, one of the
+// numbering 1.5 to 2 us in a workgroup and 10 us by many, whatever is in it, so
+// a deep graph would take as long as it is deep: lines with two neighbours on
+// either side (k = 3) peel from their two ends, 100,000 in 50,000 levels, over
+// 100 ms where the host's whole path takes 2 to 6.  Layouts of 8,000 to 200,000
+// rectangles have at most 8 levels in the tail, packed windows of 1,500, 5,000
+// and 40,000 (16,600, 57,000 and 476,000 nodes and pairs) at most 21, 34 and 96
+// in the numbering: these go through (26, 43 and 210 are allowed), and what is
+// given up has taken a fifth of the host's time at most.
+static SplitLimits split_limits(int64_t n, int64_t adj_entries) {
+  const int64_t size = n + adj_entries / 2;
+  const auto levels = [&](int64_t least, int64_t per) { return (int32_t)std::min<int64_t>(least + size / per, 1 << 20); };
+  return SplitLimits{levels(24, 4000), levels(32, 1000), levels(20, 2500), 2048, kMeetSpin};
+}
+
 SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
                         int64_t adj_entries, int32_t k, bool simplify, int32_t* out, int32_t* scratch_at, const int32_t* fault,
                         int32_t* ptr_w) {
   const size_t nn = (size_t)n;
   SplitArgs a{};
-  a.spin = kMeetSpin;
+  a.limits = split_limits(n, adj_entries);
+  if (gb.ctx->split_levels >= 0)
+    a.limits.peel = a.limits.mid = a.limits.giant = gb.ctx->split_levels;
   a.n = n;
   a.k = k;
   a.simplify = simplify ? 1 : 0;
@@ -1109,42 +1159,6 @@ void graph_builder_reserve(GraphBuilder& gb, int32_t nodes) {
     gb.spare.push_back(std::move(sg));
     ++gb.stagings;
   }
-}
-
-void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simplify, Split& s) {
-  const int32_t nn = g.n;
-  if (nn == 0) {
-    s = Split();
-    s.comp_ptr.push_back(0);
-    return;
-  }
-  const int64_t m2 = g.ptr[(size_t)nn];
-  if (m2 >= INT32_MAX) fail(MPLD_E_INVALID, "graph too large for the device split");
-  std::lock_guard<std::mutex> lk(gb.mu);
-  mpld_context* ctx = gb.ctx;
-  hipStream_t st = gb.stream;
-  check_hip(hipSetDevice(ctx->device), "hipSetDevice");
-  const size_t nb = (size_t)nn;
-  grow(gb.ptr, ctx, sizeof(int32_t) * (nb + 1));
-  grow(gb.adj, ctx, sizeof(int32_t) * (size_t)std::max<int64_t>(m2, 1));
-  const size_t in_bytes = sizeof(int32_t) * (nb + 1 + (size_t)m2);
-  if (!grow_pinned(gb.hin, in_bytes)) fail(MPLD_E_NOMEM, "device split: pinned host memory");
-  int32_t* hp = gb.hin.as<int32_t>();
-  for (size_t i = 0; i <= nb; ++i) hp[i] = (int32_t)g.ptr[i];
-  std::memcpy(hp + nb + 1, g.adj.data(), sizeof(int32_t) * (size_t)m2);
-  check_hip(hipMemcpyAsync(gb.ptr.p, hp, sizeof(int32_t) * (nb + 1), hipMemcpyHostToDevice, st),
-            "device split: upload offsets");
-  if (m2)
-    check_hip(hipMemcpyAsync(gb.adj.p, hp + nb + 1, sizeof(int32_t) * (size_t)m2,
-                             hipMemcpyHostToDevice, st),
-              "device split: upload lists");
-  enqueue_split(gb, nn, gb.ptr.as<int32_t>(), gb.adj.as<int32_t>(), m2, k, simplify);
-  const size_t out_bytes = sizeof(int32_t) * split_out_words(nn);
-  if (!grow_pinned(gb.hout, out_bytes)) fail(MPLD_E_NOMEM, "device split: pinned host memory");
-  check_hip(hipMemcpyAsync(gb.hout.p, gb.split_ws.p, out_bytes, hipMemcpyDeviceToHost, st),
-            "device split: download");
-  check_hip(hipStreamSynchronize(st), "device split");
-  if (!collect_split(gb.hout.as<int32_t>(), nn, s)) s = simplify_and_split(g, k, simplify);
 }
 
 // Copies the rectangles to the staging (before the builder's lock).
@@ -1314,7 +1328,10 @@ bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
   g.partner.assign(hmate, hmate + nb);
   g.adj.assign(hadj, hadj + total);
   g.num_ce = total / 2;
-  return split && collect_split(hadj + total, nn, *split);
+  if (!split) return false;
+  const bool done = collect_split(hadj + total, nn, *split);
+  if (!done) ++gb.ctx->splits_left;
+  return done;
 }
 
 void build_layout_pairs_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,

@@ -4,6 +4,7 @@
 
 #include <hip/hip_runtime_api.h>
 
+#include <atomic>
 #include <memory>
 #include <vector>
 
@@ -142,6 +143,12 @@ struct mpld_context {
   // down at a time (stage_up, stage_down): at most kStageMax bytes each
   void *up = nullptr, *down = nullptr;
   size_t up_bytes = 0, down_bytes = 0;
+  // for tests: levels after which a split and rounds after which a recovery are
+  // left to the host, nodes and pairs from which a graph goes to the device
+  // (-1: the rules), and how often the host took one back
+  int32_t split_levels = -1, recover_rounds = -1;
+  int64_t flow_from = -1;
+  std::atomic<int64_t> splits_left{0}, recoveries_left{0};
 
   void* dev_alloc(size_t bytes);
   void dev_free(void* p);
@@ -365,6 +372,7 @@ struct FlowComp {
 };
 struct FlowGraph {
   bool active = false;
+  bool host_form = false;   // the host has the graph and its split too, and collects
   int32_t n = 0, removed = 0, ncomp = 0;
   int64_t m = 0;
   bool simplify = true;
@@ -390,7 +398,7 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, Devic
 void flow_split_out(FlowGraph& f, GraphBuilder& gb, int32_t* removal, int32_t* comp_of, int32_t* order,
                     int32_t* comp_ptr);
 // The host forms of the graph and its split.
-void flow_to_host(FlowGraph& f, hipStream_t st, Graph& g, Split& s);
+void flow_to_host(FlowGraph& f, GraphBuilder& gb, Graph& g, Split& s);
 
 // flow: the components' data are packed by the device from that graph (im
 // then holds their shapes only); the copies are not waited for.
@@ -467,8 +475,6 @@ bool build_layout_graph_device(GraphBuilder& gb, const mpld_rect* rects, int32_t
 // The same graph as pairs, u < v, sorted: conflict pairs, then stitch pairs.
 void build_layout_pairs_device(GraphBuilder& gb, const mpld_rect* rects, int32_t n, int32_t dmin,
                                int32_t split_len, DevicePairs& out);
-// simplify_and_split of a host graph, computed on the device.
-void split_graph_device(GraphBuilder& gb, const Graph& g, int32_t k, bool simplify, Split& s);
 // Whether a server splits a device-built graph of n nodes with `adj_entries`
 // (= 2 |CE|) adjacency entries on the device too: below an average conflict
 // degree of k the peeling leaves small components.  Above it they can be large,

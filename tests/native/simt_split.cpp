@@ -1,8 +1,8 @@
 // The device's simplification and split on the CPU (simt/hip/hip_runtime.h),
 // against the host's.
-//   run SHAPE N K SIMPLIFY SEED HOLD: the graph (see make), HOLD >= 0: one
+//   run SHAPE N K SIMPLIFY SEED HOLD LEVELS: the graph (see make); HOLD >= 0: one
 //   workgroup of the giants' numbering sleeps before its HOLD-th atomic
-//   operation.  Prints "same", "given up" or what differs.
+//   operation; LEVELS: what the device may take, -1 by size.  Prints "same", "given up" or what differs.
 #include <atomic>
 #include <chrono>
 
@@ -61,7 +61,7 @@ static std::vector<int32_t> make(const std::string& shape, int32_t n, uint64_t s
 
 int main(int argc, char** argv) {
   using namespace mpld;
-  if (argc != 7) return 2;
+  if (argc != 8) return 2;
   const std::string shape = argv[1];
   const int32_t n = std::atoi(argv[2]), k = std::atoi(argv[3]);
   const bool simplify = std::atoi(argv[4]) != 0;
@@ -74,6 +74,7 @@ int main(int argc, char** argv) {
   const Graph g = make_graph(mg);
   const Split want = simplify_and_split(g, k, simplify);
   mpld_context ctx;
+  ctx.split_levels = std::atoi(argv[7]);
   GraphBuilder gb;
   gb.ctx = &ctx;
   std::vector<int32_t> ptr(g.ptr.begin(), g.ptr.end()), out(split_out_words(n)), scratch(split_scratch_words(n) + 2);

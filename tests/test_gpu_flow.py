@@ -5,10 +5,13 @@ each option, the batch calls on such a graph, and the graphs that the host
 takes back (a fault, a hub, a recovery that is one long chain).  All outputs
 are whole numbers: equal or wrong.
 """
+import ctypes
+
 import numpy as np
 import pytest
 
 import oracle
+import workload
 from algx_literal import random_graph
 
 pytestmark = pytest.mark.gpu
@@ -166,3 +169,67 @@ def test_faults(ctx):
     refused(ce, last, "both stitch and conflict")
     ref = oracle.decompose(oracle.Graph(n, ce, se), 3, 1000)   # and the graph itself still goes through
     compare(mp.mpld_decompose(ctx, mp.Graph(n, ce, se), 3, 1000, SIMPLIFY | TRACE), ref)
+
+
+def line(n, near, seed):
+    """Nodes in a row, each in conflict with `near` on either side; seed 0: ids
+    along the row."""
+    ids = np.random.default_rng(seed).permutation(n) if seed else np.arange(n)
+    ce = np.concatenate([np.stack([ids[:-d], ids[d:]], 1) for d in range(1, near + 1)]).astype(np.int32)
+    se = np.stack([ids[0:n - 9:9], ids[5:n - 4:9]], 1).astype(np.int32)
+    return n, ce, se
+
+
+def window(rects, aspect):
+    """A packed window, cut into `aspect` strips that are laid end to end."""
+    side = int(1000 * (rects / 277.0) ** 0.5)
+    r = workload.generate(rects, side, 21)[0].copy()
+    h = side // aspect
+    strip = np.minimum(r[:, 1] // h, aspect - 1)
+    r[:, [0, 2]] += (strip * side)[:, None].astype(r.dtype)
+    r[:, [1, 3]] -= (strip * h)[:, None].astype(r.dtype)
+    g = oracle.build_graph(r, 100, 0)
+    return g.num_nodes, g.ce, g.se
+
+
+# levels, rounds, and whether the host has to take the split or the recovery back
+@pytest.mark.parametrize("limits,taken", [((-1, -1), None), ((1 << 20, 1 << 20), (0, 0)), ((0, -1), (1, 0)),
+                                          ((1 << 20, 0), (0, 1))])
+@pytest.mark.parametrize("shape,k,flags", [
+    ("line", 3, SIMPLIFY | TRACE), ("shuffled", 3, SIMPLIFY | TRACE | STITCH), ("shuffled", 3, TRACE),
+    ("window", 3, SIMPLIFY | TRACE), ("window", 20, SIMPLIFY | TRACE), ("clusters", 3, SIMPLIFY | TRACE | MARK)])
+def test_depth(ctx, shape, k, flags, limits, taken):
+    """Deep peelings, long components and long lists, each given up by the
+    device where it may not take so many levels, and done there where it may."""
+    import paper_2303_14335_amd as mp
+    from paper_2303_14335_amd import _ffi
+    aspect, k = (k, 3) if shape == "window" else (1, k)
+    n, ce, se = {"line": lambda: line(1500, 2, 0), "shuffled": lambda: line(3001, 2, 5),
+                 "window": lambda: window(1500, aspect), "dense": lambda: line(700, 90, 4),
+                 "clusters": lambda: clustered(3000, [600, 513, 100, 70, 30, 9], 4.6, True, 8)}[shape]()
+    say("depth", shape, k, flags, limits)
+    left = (ctypes.c_int64 * 2)()
+    set_limits = _ffi.load().mpld_test_flow_limits
+
+    def limit(levels, rounds, start):
+        assert set_limits(ctx.handle, ctypes.c_int32(levels), ctypes.c_int32(rounds),
+                          ctypes.c_int64(start), left) == 0
+        return left[0], left[1]
+
+    ref = oracle.decompose(oracle.Graph(n, ce, se), k, 300, bool(flags & SIMPLIFY), bool(flags & MARK),
+                           bool(flags & STITCH))
+    before = limit(*limits, 1)
+    try:
+        b = mp.Batch(ctx, mp.Graph(n, ce, se), k, 300, flags)
+        for _ in range(2):
+            b.solve()
+            compare(b.result(), ref)
+        b.close()
+    finally:
+        after = limit(-1, -1, -1)
+    if taken is not None:
+        removed = int((ref.comp_of < 0).sum())
+        deep = shape in ("line", "shuffled") and flags & SIMPLIFY or len(ref.comps) and ref.comps["size"].max() > 64
+        # one recovery at most: the batch is the host's from then on
+        want = (int(bool(deep)) if taken[0] else 0, int(removed > 0) if taken[1] else 0)
+        assert (after[0] - before[0], after[1] - before[1]) == want

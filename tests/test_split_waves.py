@@ -30,8 +30,8 @@ def exes(tmp_path_factory):
     return get
 
 
-def run(exe, shape, n, k, simplify, seed, hold=-1):
-    out = subprocess.run([exe, shape, str(n), str(k), str(int(simplify)), str(seed), str(hold)],
+def run(exe, shape, n, k, simplify, seed, hold=-1, levels=1 << 20):
+    out = subprocess.run([exe, shape, str(n), str(k), str(int(simplify)), str(seed), str(hold), str(levels)],
                          capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stderr
     return out.stdout.strip()
@@ -49,3 +49,15 @@ def test_a_workgroup_held_up(exes, hold):
     """Whatever the others do meanwhile, the launch ends, with a right split
     or with none."""
     assert run(exes(IMPATIENT), "grid", 2500, 2, False, 8, hold) == "given up"
+
+
+@pytest.mark.parametrize("shape,n,k,simplify,levels,answer", [
+    ("line", 1500, 3, True, -1, "given up"), ("line", 1500, 3, True, 1000, "same"),
+    ("line", 1500, 3, True, 100, "given up"), ("strip", 2000, 2, False, 400, "given up"),
+    ("strip", 2000, 2, False, -1, "given up"), ("strip", 400, 2, False, 60, "given up"),
+    ("strip", 400, 2, False, 200, "same"), ("grid", 2500, 2, False, 40, "given up"),
+    ("random", 3000, 3, True, 0, "given up"), ("random", 300, 8, True, 0, "same")])
+def test_levels_are_bounded(exes, shape, n, k, simplify, levels, answer):
+    """A peeling or a numbering of more levels than it is allowed is left to
+    the host."""
+    assert run(exes(PATIENT), shape, n, k, simplify, 9 if shape == "random" else 0, levels=levels) == answer
