@@ -176,7 +176,7 @@ def line(n, near, seed):
     along the row."""
     ids = np.random.default_rng(seed).permutation(n) if seed else np.arange(n)
     ce = np.concatenate([np.stack([ids[:-d], ids[d:]], 1) for d in range(1, near + 1)]).astype(np.int32)
-    se = np.stack([ids[0:n - 9:9], ids[5:n - 4:9]], 1).astype(np.int32)
+    se = np.stack([ids[0:n - 9:9], ids[5:n - 4:9]], 1).astype(np.int32) if near < 5 else np.zeros((0, 2), np.int32)
     return n, ce, se
 
 
@@ -197,7 +197,8 @@ def window(rects, aspect):
                                           ((1 << 20, 0), (0, 1))])
 @pytest.mark.parametrize("shape,k,flags", [
     ("line", 3, SIMPLIFY | TRACE), ("shuffled", 3, SIMPLIFY | TRACE | STITCH), ("shuffled", 3, TRACE),
-    ("window", 3, SIMPLIFY | TRACE), ("window", 20, SIMPLIFY | TRACE), ("clusters", 3, SIMPLIFY | TRACE | MARK)])
+    ("window", 3, SIMPLIFY | TRACE), ("window", 20, SIMPLIFY | TRACE), ("clusters", 3, SIMPLIFY | TRACE | MARK),
+    ("dense", 3, SIMPLIFY | TRACE)])
 def test_depth(ctx, shape, k, flags, limits, taken):
     """Deep peelings, long components and long lists, each given up by the
     device where it may not take so many levels, and done there where it may."""
