@@ -293,6 +293,7 @@ int32_t mpld_context_destroy(mpld_context* ctx) {
   (void)hipSetDevice(ctx->device);
   if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
   if (ctx->graph_builder) graph_builder_destroy(ctx->graph_builder);
+  ctx->seq_give_back();
   for (auto& e : ctx->ev)
     if (e) (void)hipEventDestroy(e);
   if (ctx->up) (void)hipHostFree(ctx->up);
@@ -444,6 +445,10 @@ int32_t mpld_solve_components(mpld_context* ctx, const mpld_component* comps, in
       image_add(im, ctx, cp.n, pairs.data(), cp.m, opt->k, opt->node_budget, opt->flags);
     }
     image_finish(im);
+    struct GiveBack {
+      mpld_context* ctx;
+      ~GiveBack() { ctx->seq_give_back(); }
+    } give_back{ctx};
     DeviceBatch db;
     device_upload(ctx, im, db);
     db.min_budget = min_budget_of(opt);

@@ -1489,22 +1489,3 @@ void assemble_result(const Graph& g, const Split& s, const Image& im, const mpld
 }
 
 }  // namespace mpld
-
-void* mpld_context::dev_alloc(size_t bytes) {
-  void* p = nullptr;
-  if (has_alloc) {
-    p = alloc.alloc(bytes, alloc.user);
-    if (!p) mpld::fail(MPLD_E_NOMEM, "device allocator returned NULL for " + std::to_string(bytes) + " bytes");
-  } else {
-    mpld::check_hip(hipMalloc(&p, bytes), "hipMalloc");
-  }
-  return p;
-}
-
-void mpld_context::dev_free(void* p) {
-  if (!p) return;
-  if (has_alloc)
-    alloc.free(p, alloc.user);
-  else
-    (void)hipFree(p);
-}

@@ -6,6 +6,7 @@
 
 #include <atomic>
 #include <memory>
+#include <mutex>
 #include <vector>
 
 #include "device_types.h"
@@ -150,8 +151,23 @@ struct mpld_context {
   int64_t flow_from = -1;
   std::atomic<int64_t> splits_left{0}, recoveries_left{0};
 
+  // The sequence engine's workspace, one per context: up to 1.5 GiB where
+  // budgets are large, taken by a solve and given back when the call that
+  // asked for it ends (one-shot calls), with a batch, or when the context's
+  // memory runs out.
+  void* seq_mem = nullptr;
+  size_t seq_bytes = 0;
+  bool seq_used = false;   // a solve is between its launches
+  std::mutex seq_mu;
+
+  void* try_alloc(size_t bytes);   // null: there is not as much
   void* dev_alloc(size_t bytes);
   void dev_free(void* p);
+  // At least `bytes` of workspace for the launches to come on the stream;
+  // false: there is not as much.
+  bool seq_take(size_t bytes);
+  // Gives the workspace back, once the stream has passed its launches.
+  void seq_give_back();
 };
 
 namespace mpld {
@@ -325,7 +341,6 @@ struct DeviceBatch {
   PinnedBuf sp_host_tasks, sp_host_out, sp_host_pool, sp_host_writes, sp_host_recs;
   DevBuf en_meta, en_tasks, en_blocks, en_pool;     // device-resident rounds
   DevBuf ct_tasks, ct_recs, ct_colors, ct_resolved; // LDS/big-tier subtree tasks
-  DevBuf sq_mem;                                    // sequence engine
   PinnedBuf ct_host;
   std::vector<uint8_t> sp_host_copy;                // engine results in ordinary memory
   int64_t sp_rounds = 0, sp_tasks_run = 0, sp_heavy = 0, sp_reruns = 0;  // last solve's stats
@@ -447,7 +462,9 @@ struct mpld_batch {
   bool tuned_from_cache = false;
   // its buffers go back while nothing on the stream uses them
   ~mpld_batch() {
-    if (ctx) (void)hipStreamSynchronize(ctx->stream);
+    if (!ctx) return;
+    (void)hipStreamSynchronize(ctx->stream);
+    ctx->seq_give_back();
   }
 };
 

@@ -281,16 +281,24 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
   a.list_cap = std::max(1024, std::min(1 << 17, (1 << 21) / H));
   a.run_cap = 1 << 15;
   a.arena_cap = std::min<int64_t>(std::max<int64_t>(piece, 4 << 20), 1ll << 30);
-  const int32_t wide_workers = stack_words ? a.slots[kSeqCsr] : 0;
+  if (H > a.run_cap) return false;
   const size_t o_comps = seq_up(sizeof(SeqHead)), o_tasks = o_comps + seq_up(sizeof(SeqComp) * (size_t)H),
                o_res = o_tasks + seq_up(sizeof(SeqTask) * (size_t)a.task_cap),
                o_lists = o_res + seq_up(sizeof(SeqResult) * (size_t)a.task_cap),
                o_runs = o_lists + seq_up(8 * (size_t)H * (size_t)a.list_cap),
                o_stack = o_runs + seq_up(8 * (size_t)kSeqTiers * (size_t)a.run_cap),
-               o_arena = o_stack + seq_up(8 * (size_t)stack_words * (size_t)wide_workers),
+               o_arena = o_stack + seq_up(8 * (size_t)stack_words * (size_t)(stack_words ? a.slots[kSeqCsr] : 0)),
                total = o_arena + (size_t)a.arena_cap;
-  if (db.sq_mem.bytes < total) db.sq_mem.alloc(ctx, total);
-  uint8_t* m = db.sq_mem.as<uint8_t>();
+  if (!ctx->seq_take(total))
+    fail(MPLD_E_NOMEM, "sequence engine: no memory for " + std::to_string(total) + " bytes");
+  struct Use {   // not given back before the last launch is enqueued
+    mpld_context* ctx;
+    ~Use() {
+      std::lock_guard<std::mutex> lk(ctx->seq_mu);
+      ctx->seq_used = false;
+    }
+  } use{ctx};
+  uint8_t* m = static_cast<uint8_t*>(ctx->seq_mem);
   a.head = reinterpret_cast<SeqHead*>(m);
   a.comps = reinterpret_cast<SeqComp*>(m + o_comps);
   a.tasks = reinterpret_cast<SeqTask*>(m + o_tasks);
@@ -302,7 +310,6 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
   // the first run lists: every root
   std::vector<int32_t> first;
   int32_t run0[kSeqTiers] = {0, 0};
-  if (H > a.run_cap) return false;
   for (int32_t t = 0; t < kSeqTiers; ++t)
     for (int32_t i = 0; i < H; ++i)
       if (comps[(size_t)i].tier == t) {

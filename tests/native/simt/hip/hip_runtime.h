@@ -51,7 +51,6 @@ enum hipMemcpyKind { hipMemcpyHostToDevice, hipMemcpyDeviceToHost, hipMemcpyDevi
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline const char* hipGetErrorString(hipError_t) { return "error"; }
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
-inline hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
   *s = nullptr;
@@ -65,6 +64,15 @@ template <class T>
 inline hipError_t hipHostMalloc(T** p, size_t n, unsigned) {
   *p = static_cast<T*>(std::malloc(n));
   return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+template <class T>
+inline hipError_t hipMalloc(T** p, size_t n) {
+  *p = static_cast<T*>(std::malloc(n));
+  return *p ? hipSuccess : hipErrorOutOfMemory;
+}
+inline hipError_t hipFree(void* p) {
+  std::free(p);
+  return hipSuccess;
 }
 inline hipError_t hipHostFree(void* p) {
   std::free(p);
@@ -104,13 +112,15 @@ inline uint64_t seed = 1;
 inline uint64_t hold = 1;            // most turns that a lane waits before an atomic operation
 // Called by a lane before an atomic operation (a test may hold it up there).
 inline void (*on_atomic)(unsigned block, unsigned thread) = nullptr;
+// Called when the host waits for a stream.
+inline void (*on_sync)() = nullptr;
 
 // Saves the callee's registers on this stack, keeps its pointer in *from and
 // goes on with the stack `to`.
 extern "C" void simt_switch(void** from, void* to);
 asm(R"(
 .text
-.globl simt_switch
+.weak simt_switch
 .type simt_switch,@function
 simt_switch:
   pushq %rbp
@@ -264,6 +274,11 @@ inline void launch(dim3 grid, dim3 dim, const std::function<void()>& body) {
 }
 
 }  // namespace simt
+
+inline hipError_t hipStreamSynchronize(hipStream_t) {
+  if (simt::on_sync) simt::on_sync();
+  return hipSuccess;
+}
 
 #define threadIdx (simt::cur->tid)
 #define blockIdx (simt::cur->block->idx)

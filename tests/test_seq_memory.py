@@ -1,0 +1,19 @@
+"""The sequence engine's workspace, on the CPU with stand-ins for the searches:
+nothing is given back while launches that use it are on the way."""
+import subprocess
+
+import pytest
+
+import simt
+
+
+@pytest.fixture(scope="module")
+def exe(tmp_path_factory):
+    return simt.build(tmp_path_factory.mktemp("seq"), "simt_seq.cpp", also=["context.cpp"])
+
+
+@pytest.mark.parametrize("mib,least,most", [(4096, 8, 8)])
+def test_workspace(exe, mib, least, most):
+    out = subprocess.run([exe, str(mib)], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, (out.stdout, out.stderr)
+    assert least <= int(out.stdout) <= most
