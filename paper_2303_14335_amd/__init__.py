@@ -177,7 +177,10 @@ class _TorchAllocator:
         self.live = {}
 
         def alloc(nbytes, _user):
-            t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+            try:
+                t = torch.empty(int(nbytes), dtype=torch.uint8, device=self.device)
+            except torch.OutOfMemoryError:
+                return None
             p = t.data_ptr()
             self.live[p] = t
             return p

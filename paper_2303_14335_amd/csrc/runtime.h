@@ -434,8 +434,8 @@ void assemble_result(const Graph& g, const Split& s, const Image& im, const mpld
 void device_roundtrip(DeviceBatch& db, const Image& im, uint32_t flags);
 // Searches the components at these launch positions (register tier, LDS tier,
 // one-wave big tier) with the sequence engine and writes their records and
-// colors; waits for the rounds.  False: some were given up for lack of memory
-// (their records are not written).
+// colors; waits for the rounds.  False: there was no memory for it, or for some
+// of them (their records are not written).
 bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trace);
 constexpr int32_t kSeqRoundsPerCheck = 3;      // rounds enqueued between looks at the head
 constexpr int32_t kSeqMaxRounds = 1 << 16;     // then the callers search one component after another

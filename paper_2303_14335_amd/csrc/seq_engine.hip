@@ -15,6 +15,8 @@ namespace mpld {
 static constexpr int kFoldThreads = 256;
 // LDS bytes up to which a component keeps the one-wave tier's layout.
 static constexpr int64_t kSeqSmallLds = 16 * 1024;
+// The arena that the engine does not start without (bytes).
+static constexpr int64_t kSeqLeastArena = 1 << 20;
 
 // Every component starts as one task, its root.
 __global__ __launch_bounds__(256) void seq_init_kernel(SeqArgs a) {
@@ -282,15 +284,25 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
   a.run_cap = 1 << 15;
   a.arena_cap = std::min<int64_t>(std::max<int64_t>(piece, 4 << 20), 1ll << 30);
   if (H > a.run_cap) return false;
-  const size_t o_comps = seq_up(sizeof(SeqHead)), o_tasks = o_comps + seq_up(sizeof(SeqComp) * (size_t)H),
-               o_res = o_tasks + seq_up(sizeof(SeqTask) * (size_t)a.task_cap),
-               o_lists = o_res + seq_up(sizeof(SeqResult) * (size_t)a.task_cap),
-               o_runs = o_lists + seq_up(8 * (size_t)H * (size_t)a.list_cap),
-               o_stack = o_runs + seq_up(8 * (size_t)kSeqTiers * (size_t)a.run_cap),
-               o_arena = o_stack + seq_up(8 * (size_t)stack_words * (size_t)(stack_words ? a.slots[kSeqCsr] : 0)),
-               total = o_arena + (size_t)a.arena_cap;
-  if (!ctx->seq_take(total))
-    fail(MPLD_E_NOMEM, "sequence engine: no memory for " + std::to_string(total) + " bytes");
+  // the workspace, or what there is of it: with less of it more of the search
+  // is done by the tasks at the front, down to where the callers' own ways are
+  // the better ones
+  size_t o_comps, o_tasks, o_res, o_lists, o_runs, o_stack, o_arena;
+  for (;;) {
+    o_comps = seq_up(sizeof(SeqHead));
+    o_tasks = o_comps + seq_up(sizeof(SeqComp) * (size_t)H);
+    o_res = o_tasks + seq_up(sizeof(SeqTask) * (size_t)a.task_cap);
+    o_lists = o_res + seq_up(sizeof(SeqResult) * (size_t)a.task_cap);
+    o_runs = o_lists + seq_up(8 * (size_t)H * (size_t)a.list_cap);
+    o_stack = o_runs + seq_up(8 * (size_t)kSeqTiers * (size_t)a.run_cap);
+    o_arena = o_stack + seq_up(8 * (size_t)stack_words * (size_t)(stack_words ? a.slots[kSeqCsr] : 0));
+    if (ctx->seq_take(o_arena + (size_t)a.arena_cap)) break;
+    if (a.arena_cap / 4 < kSeqLeastArena) return false;
+    a.arena_cap /= 4;
+    a.task_cap = std::max(a.task_cap / 4, 1 << 10) + H;
+    a.list_cap = std::max(a.list_cap / 4, 1 << 10);
+    a.slots[kSeqCsr] = std::max(a.slots[kSeqCsr] / 2, ctx->num_cus);
+  }
   struct Use {   // not given back before the last launch is enqueued
     mpld_context* ctx;
     ~Use() {

@@ -83,3 +83,36 @@ def test_every_budget(ctx, tier):
         for f in ("status", "nodes", "trace_hash", "depth_at_stop"):
             assert np.array_equal(got.components[f], ref.comps[f]), (budget, f)
         assert np.array_equal(got.colors, ref.colors)
+
+
+@pytest.mark.parametrize("mib", [0, 2, 24, 200])
+def test_little_memory(ctx, monkeypatch, mib):
+    """The engine's workspace only as far as there is memory: the same answers
+    with less of it or none, and all of it given back."""
+    import torch
+
+    import paper_2303_14335_amd as mp
+    rng = np.random.default_rng(31)
+    comps = [component(s, 4.4, rng) for s in (40, 64, 64, 300, 700, 2000, 3000)]
+    say("little memory", mib)
+    n, ce = union(comps)
+    ref = oracle.decompose(oracle.Graph(n, ce, np.zeros((0, 2), np.int32)), 3, 20000, False)
+    g = mp.Graph(n, ce, np.zeros((0, 2), np.int32))
+    live = sum(t.numel() for t in ctx._alloc.live.values())
+    empty, refused = torch.empty, []
+
+    def limited(size, *args, **kw):
+        # (the heavy-component engine's own areas, of at most 64 MiB, are not meant)
+        if sum(t.numel() for t in ctx._alloc.live.values()) + size > live + (mib + 130 << 20):
+            refused.append(size)
+            raise torch.OutOfMemoryError("limited")
+        return empty(size, *args, **kw)
+
+    monkeypatch.setattr(torch, "empty", limited)
+    got = mp.mpld_decompose(ctx, g, 3, 20000, TRACE)
+    monkeypatch.undo()
+    for f in ("status", "nodes", "trace_hash", "depth_at_stop"):
+        assert np.array_equal(got.components[f], ref.comps[f]), f
+    assert np.array_equal(got.colors, ref.colors)
+    assert bool(refused) == (mib < 200)
+    assert sum(t.numel() for t in ctx._alloc.live.values()) == live

@@ -1,5 +1,6 @@
 """The sequence engine's workspace, on the CPU with stand-ins for the searches:
-nothing is given back while launches that use it are on the way."""
+nothing is given back while launches that use it are on the way, and a pool
+that has not as much is no error."""
 import subprocess
 
 import pytest
@@ -12,7 +13,7 @@ def exe(tmp_path_factory):
     return simt.build(tmp_path_factory.mktemp("seq"), "simt_seq.cpp", also=["context.cpp"])
 
 
-@pytest.mark.parametrize("mib,least,most", [(4096, 8, 8)])
+@pytest.mark.parametrize("mib,least,most", [(0, 0, 0), (1, 0, 0), (40, 1, 8), (300, 4, 8), (4096, 8, 8)])
 def test_workspace(exe, mib, least, most):
     out = subprocess.run([exe, str(mib)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, (out.stdout, out.stderr)
