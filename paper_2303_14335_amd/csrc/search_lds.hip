@@ -34,6 +34,7 @@
 
 #include "device_types.h"
 #include "mpld.h"
+#include "seq_reserve.h"
 #include "seq_types.h"
 #include "trace.h"
 #include "wave_ops.h"
@@ -167,17 +168,7 @@ __device__ __forceinline__ bool seq_reserve(const SeqIo& io, uint32_t pieces, ui
                                             uint32_t depth, uint32_t ents, int32_t& child, int64_t& at) {
   const uint64_t bytes =
       ((uint64_t)pieces * (plane_bytes + 64u) + 8ull * depth + 4ull * ents + n + 127u) & ~63ull;
-  int32_t c = 0;
-  uint64_t p = 0;
-  if (__lane_id() == 63u) {
-    p = atomicAdd(&io.a.head->arena, bytes);
-    c = atomicAdd(&io.a.head->tasks, (int32_t)pieces);
-  }
-  c = (int32_t)rdlane((uint32_t)c, 63u);
-  p = rdlane64((uint32_t)p, (uint32_t)(p >> 32), 63u);
-  child = c;
-  at = (int64_t)p;
-  return p + bytes <= (uint64_t)io.a.arena_cap && c + (int32_t)pieces <= io.a.task_cap;
+  return seq_take_room(io.a, bytes, (int32_t)pieces, child, at);
 }
 // Pieces that a stack with `open` untried levels is cut into.
 __device__ __forceinline__ uint32_t seq_pieces(const SeqIo& io, uint32_t open) {
@@ -188,10 +179,9 @@ __device__ __forceinline__ uint32_t seq_pieces(const SeqIo& io, uint32_t open) {
 // Room for n colors; -1: none.
 __device__ __forceinline__ int64_t seq_reserve_colors(const SeqIo& io, uint32_t n) {
   const uint64_t bytes = (n + 63u) & ~63u;
-  uint64_t p = 0;
-  if (__lane_id() == 63u) p = atomicAdd(&io.a.head->arena, bytes);
-  p = rdlane64((uint32_t)p, (uint32_t)(p >> 32), 63u);
-  return p + bytes <= (uint64_t)io.a.arena_cap ? (int64_t)p : -1;
+  int32_t none;
+  int64_t at;
+  return seq_take_room(io.a, bytes, 0, none, at) ? at : -1;
 }
 // Colors of the nodes below the piece, from its predecessor's array.
 __device__ __forceinline__ void seq_copy_colors(const SeqIo& io, int64_t to, uint32_t n) {

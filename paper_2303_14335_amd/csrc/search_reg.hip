@@ -35,6 +35,7 @@
 #include "min_core.h"
 #include "mpld.h"
 #include "reg_items.h"
+#include "seq_reserve.h"
 #include "seq_types.h"
 #include "trace.h"
 #include "wave_ops.h"
@@ -994,15 +995,9 @@ __global__ __launch_bounds__(256) void seq_reg_kernel(const SeqArgs a, const Reg
         const int32_t singles = (int32_t)__builtin_popcountll(m);
         const int32_t pieces = 1 + (singles < kSeqPieces - 1 ? singles : kSeqPieces - 1);
         const uint64_t bytes = (uint64_t)seq_reg_state_bytes(K, STITCH);
-        uint64_t p = 0;
-        int32_t ch = 0;
-        if (lane == 63u) {   // as in the engine rounds, all of the atomics in one branch
-          p = atomicAdd(&a.head->arena, bytes);
-          ch = atomicAdd(&a.head->tasks, pieces);
-        }
-        p = (uint64_t)rdlane((uint32_t)p, 63u) | ((uint64_t)rdlane((uint32_t)(p >> 32), 63u) << 32);
-        ch = (int32_t)rdlane((uint32_t)ch, 63u);
-        if (p + bytes > (uint64_t)a.arena_cap || ch + pieces > a.task_cap) {
+        int32_t ch;
+        int64_t p;
+        if (!seq_take_room(a, bytes, pieces, ch, p)) {
           res.status = kSeqWaiting;   // no room: as it was
           if ((entry & (uint32_t)kSeqForce) == 0) break;
           stop = limit;
@@ -1013,7 +1008,7 @@ __global__ __launch_bounds__(256) void seq_reg_kernel(const SeqArgs a, const Reg
         for (int32_t j = 0; j < pieces; ++j) {   // every lane writes the same records
           SeqTask t = task;
           t.kind = j == 0 ? kSeqNode : kSeqNext;
-          t.at = (int64_t)p;
+          t.at = p;
           if (j == 0) {
             t.open = open & ~m;   // (all of it when it is not cut)
           } else if (j == kSeqPieces - 1) {
@@ -1033,13 +1028,12 @@ __global__ __launch_bounds__(256) void seq_reg_kernel(const SeqArgs a, const Reg
       res.nodes = s.nodes;
       res.hash = s.h;
       if (res.status == MPLD_FEASIBLE) {
-        uint64_t p = 0;
-        if (lane == 63u) p = atomicAdd(&a.head->arena, 64ull);
-        p = (uint64_t)rdlane((uint32_t)p, 63u) | ((uint64_t)rdlane((uint32_t)(p >> 32), 63u) << 32);
-        if (p + 64u <= (uint64_t)a.arena_cap) {
+        int32_t none;
+        int64_t p;
+        if (seq_take_room(a, 64u, 0, none, p)) {
           if (lane < s.depth && (s.fr & 0xffu) < (uint32_t)d.n)
             a.arena[p + (s.fr & 0xffu)] = (uint8_t)((s.fr >> 8) & 0xffu);
-          res.sol = (int64_t)p;
+          res.sol = p;
         } else {
           res.status = kSeqLost;
         }

@@ -371,7 +371,7 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
     if (round >= kSeqMaxRounds) return false;
   }
   db.sp_rounds += h.rounds;
-  db.sp_tasks_run += h.tasks;
+  db.sp_tasks_run += std::min(h.tasks, a.task_cap);
   run_tiers(true);
   return h.lost == 0;
 }

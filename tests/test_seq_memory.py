@@ -18,3 +18,16 @@ def test_workspace(exe, mib, least, most):
     out = subprocess.run([exe, str(mib)], capture_output=True, text=True, timeout=120)
     assert out.returncode == 0, (out.stdout, out.stderr)
     assert least <= int(out.stdout) <= most
+
+
+@pytest.fixture(scope="module")
+def room(tmp_path_factory):
+    return simt.build(tmp_path_factory.mktemp("room"), "simt_room.cpp")
+
+
+@pytest.mark.parametrize("tasks,arena", [(2000, 1 << 20), (1 << 20, 1 << 18), (3000, 1 << 18), (24, 64)])
+def test_refused_requests_take_nothing(room, tasks, arena):
+    """Each place is given once, and the counts stand still once there is no
+    room, however often it is asked for."""
+    out = subprocess.run([room, str(tasks), str(arena), "7"], capture_output=True, text=True, timeout=120)
+    assert out.returncode == 0, (out.stdout, out.stderr)
