@@ -1005,10 +1005,11 @@ struct ScanArgs {
   uint32_t epoch;
 };
 
+constexpr uint32_t kLastEpoch = (1u << 30) - 1;   // of a tile's word
 // tickets: how many the launch takes (one a block), 0 when it has its own.
 static ScanArgs scan_args(GraphBuilder& gb, int64_t tiles, int64_t tickets) {
   const size_t bytes = 64 + 8 * (size_t)tiles;
-  if (gb.tiles.bytes < bytes || gb.epoch >= (1u << 30) - 1) {
+  if (gb.tiles.bytes < bytes || gb.epoch >= kLastEpoch) {
     // launches on the way still use the words that go back
     if (gb.tiles.p) check_hip(hipStreamSynchronize(gb.stream), "graph builder: scan");
     grow(gb.tiles, gb.ctx, bytes);
@@ -1022,12 +1023,21 @@ static ScanArgs scan_args(GraphBuilder& gb, int64_t tiles, int64_t tickets) {
   return a;
 }
 
+// Checks the launches so far.  One that failed took no tickets: the counts start
+// anew with the next scan, or its workgroups would look for tiles that are not
+// theirs.
+static void check_launches(GraphBuilder& gb, const char* what) {
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) gb.epoch = kLastEpoch;
+  check_hip(e, what);
+}
+
 void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
   const int64_t tiles = std::max<int64_t>(1, (n + kScanTile - 1) / kScanTile);
   const ScanArgs sa = scan_args(gb, tiles, tiles);
   hipLaunchKernelGGL(scan_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, gb.stream, in, n, out, sa.ticket,
                      sa.base, sa.status, sa.epoch);
-  check_hip(hipGetLastError(), "graph builder: scan");
+  check_launches(gb, "graph builder: scan");
 }
 
 // What a split may take on the device before the host is to do it (identical
@@ -1110,7 +1120,7 @@ SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const 
                      st, a);
   if (n > kBigNodes)
     hipLaunchKernelGGL(bfs_giant_kernel, dim3(kGiantBlocks), dim3(kScanBlock), 0, st, a);
-  check_hip(hipGetLastError(), "device split");
+  check_launches(gb, "device split");
   return a;
 }
 
@@ -1209,7 +1219,7 @@ static LayoutGrid layout_cells(GraphBuilder& gb, Staging& sg, const mpld_rect* r
   hipLaunchKernelGGL(layout_nodes_kernel, dim3((unsigned)tiles), dim3(kScanBlock), 0, s, drects, n, split_len,
                      gb.box.as<int4>(), gb.partner.as<int32_t>(), gb.se.as<int2>(), head, sa.ticket, sa.base,
                      sa.status, sa.epoch);
-  check_hip(hipGetLastError(), "graph builder: nodes");
+  check_launches(gb, "graph builder: nodes");
   check_hip(hipMemcpyAsync(sg.out.p, head, sizeof(LayoutHead), hipMemcpyDeviceToHost, s),
             "graph builder: bounds");
   check_hip(hipStreamSynchronize(s), "graph builder: bounds");

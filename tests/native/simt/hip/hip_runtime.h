@@ -48,7 +48,6 @@ typedef struct simt_graph* hipGraphExec_t;
 enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorOutOfMemory = 2 };
 enum { hipHostMallocDefault = 0, hipStreamNonBlocking = 1, hipFuncAttributeMaxDynamicSharedMemorySize = 8 };
 enum hipMemcpyKind { hipMemcpyHostToDevice, hipMemcpyDeviceToHost, hipMemcpyDeviceToDevice };
-inline hipError_t hipGetLastError() { return hipSuccess; }
 inline const char* hipGetErrorString(hipError_t) { return "error"; }
 inline hipError_t hipSetDevice(int) { return hipSuccess; }
 inline hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
@@ -112,6 +111,9 @@ inline uint64_t seed = 1;
 inline uint64_t hold = 1;            // most turns that a lane waits before an atomic operation
 // Called by a lane before an atomic operation (a test may hold it up there).
 inline void (*on_atomic)(unsigned block, unsigned thread) = nullptr;
+// Launches until one fails (0: none does): it does not run.
+inline int fail_launch = 0;
+inline int last_error = 0;
 // Called when the host waits for a stream.
 inline void (*on_sync)() = nullptr;
 
@@ -262,6 +264,10 @@ inline void run_block(dim3 idx, dim3 grid, dim3 dim, const std::function<void()>
 }
 
 inline void launch(dim3 grid, dim3 dim, const std::function<void()>& body) {
+  if (fail_launch > 0 && --fail_launch == 0) {
+    last_error = hipErrorOutOfMemory;
+    return;
+  }
   grid_now = grid.x;
   if (grid.x != concurrent) {
     for (unsigned i = 0; i < grid.x; ++i) run_block(dim3(i, 0, 0), grid, dim, body, seed * 1000003u + i);
@@ -280,6 +286,11 @@ inline hipError_t hipStreamSynchronize(hipStream_t) {
   return hipSuccess;
 }
 
+inline hipError_t hipGetLastError() {
+  const hipError_t e = simt::last_error;
+  simt::last_error = hipSuccess;
+  return e;
+}
 #define threadIdx (simt::cur->tid)
 #define blockIdx (simt::cur->block->idx)
 #define blockDim (simt::cur->block->dim)

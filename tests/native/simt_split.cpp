@@ -2,7 +2,8 @@
 // against the host's.
 //   run SHAPE N K SIMPLIFY SEED HOLD LEVELS: the graph (see make); HOLD >= 0: one
 //   workgroup of the giants' numbering sleeps before its HOLD-th atomic
-//   operation; LEVELS: what the device may take, -1 by size.  Prints "same", "given up" or what differs.
+//   operation; LEVELS: what the device may take, -1 by size.  A ninth word: the
+//   launch of a split before it that fails.  Prints "same", "given up" or what differs.
 #include <atomic>
 #include <chrono>
 
@@ -61,7 +62,7 @@ static std::vector<int32_t> make(const std::string& shape, int32_t n, uint64_t s
 
 int main(int argc, char** argv) {
   using namespace mpld;
-  if (argc != 8) return 2;
+  if (argc != 8 && argc != 9) return 2;
   const std::string shape = argv[1];
   const int32_t n = std::atoi(argv[2]), k = std::atoi(argv[3]);
   const bool simplify = std::atoi(argv[4]) != 0;
@@ -80,6 +81,16 @@ int main(int argc, char** argv) {
   std::vector<int32_t> ptr(g.ptr.begin(), g.ptr.end()), out(split_out_words(n)), scratch(split_scratch_words(n) + 2);
   simt::concurrent = (unsigned)kGiantBlocks;
   simt::on_atomic = slow_block;
+  // one of the split's launches has failed before
+  if (argc == 9) {
+    simt::fail_launch = std::atoi(argv[8]);
+    try {
+      enqueue_split(gb, n, ptr.data(), g.adj.data(), (int64_t)g.adj.size(), k, simplify, out.data(), scratch.data(),
+                    nullptr, nullptr);
+      return 2;
+    } catch (const Error&) {
+    }
+  }
   enqueue_split(gb, n, ptr.data(), g.adj.data(), (int64_t)g.adj.size(), k, simplify, out.data(), scratch.data(),
                 nullptr, nullptr);
   Split got;

@@ -30,9 +30,9 @@ def exes(tmp_path_factory):
     return get
 
 
-def run(exe, shape, n, k, simplify, seed, hold=-1, levels=1 << 20):
-    out = subprocess.run([exe, shape, str(n), str(k), str(int(simplify)), str(seed), str(hold), str(levels)],
-                         capture_output=True, text=True, timeout=60)
+def run(exe, shape, n, k, simplify, seed, hold=-1, levels=1 << 20, more=()):
+    out = subprocess.run([exe, shape, str(n), str(k), str(int(simplify)), str(seed), str(hold), str(levels),
+                          *map(str, more)], capture_output=True, text=True, timeout=60)
     assert out.returncode == 0, out.stderr
     return out.stdout.strip()
 
@@ -61,3 +61,9 @@ def test_levels_are_bounded(exes, shape, n, k, simplify, levels, answer):
     """A peeling or a numbering of more levels than it is allowed is left to
     the host."""
     assert run(exes(PATIENT), shape, n, k, simplify, 9 if shape == "random" else 0, levels=levels) == answer
+
+
+@pytest.mark.parametrize("launch", [3, 14, 15, 16])
+def test_after_a_failed_launch(exes, launch):
+    """A launch that failed has taken none of the tickets that it was given."""
+    assert run(exes(PATIENT), "random", 5000, 3, True, 10, more=[launch]) == "same"
