@@ -8,6 +8,7 @@
 #include <exception>
 #include <new>
 
+#include "graph_builder.h"
 #include "runtime.h"
 
 namespace mpld {
@@ -103,11 +104,22 @@ void batch_build(mpld_context* ctx, const mpld_graph* g, const mpld_options* opt
   if (b->flow.active) {
     b->s.comp_ptr.assign(1, 0);
     for (const FlowComp& c : b->flow.comps) b->s.comp_ptr.push_back(b->s.comp_ptr.back() + c.n);
-  } else {
-    b->g = make_graph(*g);
-    b->s = simplify_and_split(b->g, opt->k, simplify);
   }
   Tune t;
+  if (b->flow.active) {
+    tune_from_cache(b, nullptr, &t);
+    try {
+      batch_pack(b, t);
+      return;
+    } catch (const NoMemory&) {
+    }
+    // the components themselves may fit where they and the graph do not
+    b->flow.drop();
+    ctx->graph_builder->flow_ws.release();
+    t = Tune();
+  }
+  b->g = make_graph(*g);
+  b->s = simplify_and_split(b->g, opt->k, simplify);
   tune_from_cache(b, nullptr, &t);
   batch_pack(b, t);
 }

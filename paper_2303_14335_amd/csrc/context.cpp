@@ -20,9 +20,9 @@ void* mpld_context::dev_alloc(size_t bytes) {
     seq_give_back();
     p = try_alloc(bytes);
   }
-  if (!p && has_alloc)
-    mpld::fail(MPLD_E_NOMEM, "device allocator returned NULL for " + std::to_string(bytes) + " bytes");
-  if (!p) mpld::fail(MPLD_E_DEVICE, "hipMalloc: out of memory for " + std::to_string(bytes) + " bytes");
+  const std::string size = std::to_string(bytes) + " bytes";
+  if (!p && has_alloc) throw mpld::NoMemory{{MPLD_E_NOMEM, "device allocator returned NULL for " + size}};
+  if (!p) throw mpld::NoMemory{{MPLD_E_DEVICE, "hipMalloc: out of memory for " + size}};
   return p;
 }
 

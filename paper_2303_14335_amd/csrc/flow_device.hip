@@ -432,19 +432,28 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
   f.simplify = simplify;
   // what a later collection reads stays with the graph ...
   const size_t keep = (nn + 1) + 2 * mm + nn + split_out_words(n) + 2 * (nn + 1);
-  if (f.keep.bytes < 4 * keep) f.keep.alloc(ctx, 4 * keep);
+  // ... the rest is the builder's
+  const size_t head_words = (sizeof(FlowHead) + 24) / 4;   // the summary behind it, 16-byte aligned
+  const size_t pair_words = 2 * (mm + (size_t)ns);
+  const size_t scratch =
+      head_words + 4 * (nn + 1) + pair_words + 2 * mm + 2 * (nn + 1) + 4 * mm + split_scratch_words(n);
+  try {   // all of it, before the first launch
+    if (f.keep.bytes < 4 * keep) f.keep.alloc(ctx, 4 * keep);
+    grow(gb.flow_ws, ctx, 4 * scratch);
+    scan_reserve(gb, n);
+  } catch (const NoMemory&) {
+    f.keep.release();
+    return false;
+  }
+  if (!grow_pinned(gb.hin, std::max<size_t>(4 * pair_words, 4)) ||
+      !grow_pinned(gb.hout, sizeof(FlowHead) + 24 + sizeof(FlowComp) * nn + 5 * nn + 256))
+    return false;
   f.ptr = f.keep.as<int32_t>();
   f.adj = f.ptr + nn + 1;
   f.partner = f.adj + 2 * mm;
   f.cpre = f.partner + nn;       // n + 1
   f.cmax = f.cpre + nn + 1;      // n + 1
   int32_t* out = f.cmax + nn + 1;
-  // ... the rest is the builder's
-  const size_t head_words = (sizeof(FlowHead) + 24) / 4;   // the summary behind it, 16-byte aligned
-  const size_t pair_words = 2 * (mm + (size_t)ns);
-  const size_t scratch =
-      head_words + 4 * (nn + 1) + pair_words + 2 * mm + 2 * (nn + 1) + 4 * mm + split_scratch_words(n);
-  grow(gb.flow_ws, ctx, 4 * scratch);
   int32_t* w = gb.flow_ws.as<int32_t>();
   auto* head = reinterpret_cast<FlowHead*>(w);
   w += head_words;
@@ -460,9 +469,6 @@ bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k,
   int32_t* tmp = cdeg + nn + 1;
   int32_t* src = tmp + 2 * mm;
   int32_t* split_scratch = src + 2 * mm;
-  if (!grow_pinned(gb.hin, std::max<size_t>(4 * pair_words, 4)) ||
-      !grow_pinned(gb.hout, sizeof(FlowHead) + 24 + sizeof(FlowComp) * nn + 5 * nn + 256))
-    fail(MPLD_E_NOMEM, "layout flow: pinned host memory");
   const unsigned gn = flow_grid(n);
   hipLaunchKernelGGL(flow_init_kernel, dim3(gn), dim3(256), 0, st, n, head, deg, f.partner, f.cmax);
   if (m) {
@@ -554,7 +560,11 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, Devic
   const size_t nn = (size_t)f.n, nc = (size_t)f.ncomp;
   // scratch: head, component tallies, colors being recovered, places, bytes
   const size_t head_words = (sizeof(FlowHead) + 24) / 4;
-  grow(gb.flow_ws, ctx, 4 * (head_words + 2 * nc + 2 * nn + (nn + 3) / 4));
+  try {
+    grow(gb.flow_ws, ctx, 4 * (head_words + 2 * nc + 2 * nn + (nn + 3) / 4));
+  } catch (const NoMemory&) {
+    return false;
+  }
   int32_t* w = gb.flow_ws.as<int32_t>();
   auto* head = reinterpret_cast<FlowHead*>(w);
   auto* cstat = reinterpret_cast<int2*>(w + head_words);
@@ -633,6 +643,13 @@ bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, Devic
 
 FlowGraph::~FlowGraph() {
   if (keep.p && keep.ctx) (void)hipStreamSynchronize(keep.ctx->stream);
+}
+
+void FlowGraph::drop() {
+  if (keep.p && keep.ctx) (void)hipStreamSynchronize(keep.ctx->stream);
+  keep.release();
+  comps.clear();
+  active = false;
 }
 
 void flow_split_out(FlowGraph& f, GraphBuilder& gb, int32_t* removal, int32_t* comp_of, int32_t* order,

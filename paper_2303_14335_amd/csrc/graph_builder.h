@@ -84,6 +84,8 @@ inline bool grow_pinned(PinnedBuf& b, size_t bytes) {
   return bytes <= b.bytes || b.reserve(std::max(bytes + bytes / 4, 2 * b.bytes));
 }
 
+// The tiles' words for scans and splits of up to n entries.
+void scan_reserve(GraphBuilder& gb, int64_t n);
 // Exclusive scan of in[0 .. n) into out[0 .. n], out[n] = the total.
 void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out);
 

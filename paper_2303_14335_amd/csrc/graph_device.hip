@@ -1023,6 +1023,8 @@ static ScanArgs scan_args(GraphBuilder& gb, int64_t tiles, int64_t tickets) {
   return a;
 }
 
+void scan_reserve(GraphBuilder& gb, int64_t n) { (void)scan_args(gb, std::max<int64_t>(1, (n + 31) / 32), 0); }
+
 // Checks the launches so far.  One that failed took no tickets: the counts start
 // anew with the next scan, or its workgroups would look for tiles that are not
 // theirs.

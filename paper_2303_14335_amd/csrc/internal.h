@@ -16,6 +16,8 @@ struct Error {
   int32_t code;
   std::string what;
 };
+// The context had no device memory: some work has another way.
+struct NoMemory : Error {};
 [[noreturn]] void fail(int32_t code, const std::string& what);
 
 // Sets the thread-local detail string returned by mpld_last_error().

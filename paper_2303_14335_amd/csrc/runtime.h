@@ -189,8 +189,8 @@ struct DevBuf {
   void alloc(mpld_context* c, size_t n) {
     release();
     ctx = c;
-    bytes = n ? n : 256;
-    p = c->dev_alloc(bytes);
+    p = c->dev_alloc(n ? n : 256);
+    bytes = n ? n : 256;   // (none if that threw)
   }
   // `n` bytes of `of` from byte `at` on; not owned
   void view(const DevBuf& of, size_t at, size_t n) {
@@ -397,16 +397,19 @@ struct FlowGraph {
   int32_t *cpre = nullptr, *cmax = nullptr;   // core degrees' prefix over `order`; largest per component
   std::vector<FlowComp> comps;
   ~FlowGraph();   // waits for the stream: its memory may be in use
+  void drop();    // gives it back: the host path has the graph
 };
 struct GraphBuilder;
 // Validates and splits a caller's graph on the device.  False: the host path
-// is to take it (a fault to report, or nothing that the flow is made for).
+// is to take it (a fault to report, nothing that the flow is made for, or no
+// memory for it).
 bool flow_build(FlowGraph& f, GraphBuilder& gb, const mpld_graph& in, int32_t k, bool simplify);
 // Enqueues the packing of the batch's components (db laid out from their
 // shapes, its descriptors on the device).
 void flow_pack(FlowGraph& f, DeviceBatch& db, hipStream_t st);
 // Recovery, tallies and the result of a solved batch; waits.  False: the
-// recovery was given up (nothing in *r): the host does it.
+// recovery was given up, or there is no memory for it (nothing in *r): the host
+// does it.
 bool flow_collect(FlowGraph& f, GraphBuilder& gb, const mpld_options& opt, DeviceBatch& db,
                   mpld_result* r);
 // The split in a caller's arrays (n, n, n, n + 1 entries; as many as it has are written); waits.

@@ -234,3 +234,40 @@ def test_depth(ctx, shape, k, flags, limits, taken):
         # one recovery at most: the batch is the host's from then on
         want = (int(bool(deep)) if taken[0] else 0, int(removed > 0) if taken[1] else 0)
         assert (after[0] - before[0], after[1] - before[1]) == want
+
+
+@pytest.mark.parametrize("mib", [0, 1, 2, 4, 8, 64])
+def test_little_memory(monkeypatch, mib):
+    """A graph that the device has no memory for is the host's: the same
+    answers with any amount that the components fit in, and a call that was
+    refused leaves nothing behind that a later one takes for memory."""
+    import torch
+
+    import paper_2303_14335_amd as mp
+    say("little memory", mib)
+    n, ce, se = clustered(20000, MIXED, 4.4, True, 77)
+    args = (mp.Graph(n, ce, se), 3, 300, SIMPLIFY | TRACE)
+    ref = oracle.decompose(oracle.Graph(n, ce, se), 3, 300)
+    empty, taken = torch.empty, []
+
+    def limited(size, *a, **kw):
+        if sum(t.numel() for t in ctx._alloc.live.values()) + size > mib << 20:
+            raise torch.OutOfMemoryError("limited")
+        taken.append(size)
+        return empty(size, *a, **kw)
+
+    ctx = mp.Context(0)
+    monkeypatch.setattr(torch, "empty", limited)
+    if mib == 0:
+        with pytest.raises(mp.MpldError) as e:
+            mp.mpld_decompose(ctx, *args)
+        assert e.value.code == -2
+    else:
+        b = mp.Batch(ctx, *args)
+        for _ in range(2):   # (without the heavy-component engine's own 96 MiB)
+            b.solve()
+            compare(b.result(), ref)
+        b.close()
+    monkeypatch.undo()
+    compare(mp.mpld_decompose(ctx, *args), ref)
+    ctx.close()
