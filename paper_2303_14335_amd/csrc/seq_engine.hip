@@ -246,6 +246,7 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
   std::vector<SeqComp> comps((size_t)H);
   int32_t nt[kSeqTiers] = {0, 0};
   int64_t tasks = 0, piece = 0;   // tasks, and their bytes of a piece, summed over what the budgets may need
+  int64_t cut = 0, cuts = 0, cut_bytes = 0;   // largest cut; cuts that the budgets may need, and their bytes
   int32_t lds = 0;
   int64_t stack_words = 0;
   for (int32_t i = 0; i < H; ++i) {
@@ -276,9 +277,22 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
     const int64_t most = std::min<int64_t>(d.budget / 16 + 64, 1 << 16);
     tasks += most;
     piece += most * bytes + 64 * (int64_t)d.n;
+    // a cut keeps the stack's planes once a piece, its headers, log (about
+    // three entries a node) and colors once
+    const int64_t each = c.tier == kSeqReg ? 4096 : kSeqPieces * (bytes - 448) + (8 + 12 + 1) * (int64_t)d.n;
+    cut = std::max(cut, each);
+    cuts += d.budget / 32 + 64;
+    cut_bytes += (d.budget / 32 + 64) * each;
   }
   a.slots[kSeqReg] = ctx->num_cus * 16;
   a.slots[kSeqCsr] = std::max(1, std::min(16, 160 * 1024 / std::max(lds, 1))) * ctx->num_cus;
+  // and what a few rounds of all slots cut, which is soon more than small
+  // budgets come to (three components of 1200 to 2800 nodes, 43,000 nodes each:
+  // 52 MB and 22,000 tasks; with the 14 MB and 8,000 of their budgets alone
+  // the front went on by itself, 25 ms as root-row tasks, 65 so, 5.8 now)
+  const int64_t slots = a.slots[kSeqReg] * (nt[kSeqReg] ? 1 : 0) + a.slots[kSeqCsr] * (nt[kSeqCsr] ? 1 : 0);
+  tasks = std::max(tasks, kSeqPieces * std::min(cuts, 2 * slots));
+  piece = std::max(piece, std::min(cut_bytes, 2 * slots * cut));
   a.task_cap = (int32_t)std::min<int64_t>(tasks, 1 << 18) + H;
   a.list_cap = std::max(1024, std::min(1 << 17, (1 << 21) / H));
   a.run_cap = 1 << 15;

@@ -115,6 +115,9 @@ int main(int argc, char** argv) {
     // tiers ask for more
     solved += seq_solve(db, reg, false) ? 1 : 0;
     solved += seq_solve(db, csr, false) ? 1 : 0;
+    // few components: room for what the device's 2,048 places cut in a round or
+    // two (66 KB a cut of 2,000 nodes), not for the budgets' share alone
+    if (count == 3 && g_cap > (1ull << 30)) g_bad |= ctx.seq_bytes < (2ull * 2048 * 60000);
     if (solved == 8)
       for (const DevRecord& x : recs) g_bad |= x.status != MPLD_INFEASIBLE;
   }
