@@ -304,8 +304,10 @@ int32_t mpld_build_graph_device(mpld_context* ctx, const mpld_rect* rects, int32
  * bfs_order[comp_ptr[c] .. comp_ptr[c + 1])).  The first peel levels,
  * union-find and numbering run over the whole device, the small tail of the
  * peeling on one workgroup; BFS takes a wave per component of at most 64
- * nodes, a workgroup up to 4096 and many workgroups above.  Synchronous on
- * the context's stream.  Errors: MPLD_E_INVALID
+ * nodes, a workgroup up to 4096 and many workgroups above.  Graphs of more
+ * levels than pay off there, of nodes with over 2048 neighbours, or without
+ * device memory for them are split on the host.  Synchronous on the context's
+ * stream.  Errors: MPLD_E_INVALID
  * for a bad graph (as mpld_decompose), k outside [2, MPLD_MAX_K] or a NULL
  * output; MPLD_E_DEVICE / MPLD_E_NOMEM. */
 int32_t mpld_split_graph_device(mpld_context* ctx, const mpld_graph* g, int32_t k, uint32_t flags,

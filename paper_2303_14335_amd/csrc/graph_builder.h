@@ -125,10 +125,11 @@ inline size_t split_scratch_words(int64_t n) {   // ctl needs up to 64
 
 // Enqueues the split of the CSR at dptr / dadj (device, int32) on the
 // builder's stream, outputs at `out`; no host synchronisation.  Returns the
-// addresses it used.  adj_entries: about how many dadj holds.  fault (may be null): a device word that, nonzero, makes
-// the graph one without pairs (dptr, as ptr_w, is cleared).
-SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
-                        int64_t adj_entries, int32_t k, bool simplify, int32_t* out, int32_t* scratch, const int32_t* fault,
+// addresses it used.  adj_entries: about how many dadj holds.  fault (may be
+// null): a device word that, nonzero, makes the graph one without pairs (dptr,
+// as ptr_w, is cleared).  counts[1] = -1 afterwards: the host is to split it.
+SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj, int64_t adj_entries,
+                        int32_t k, bool simplify, int32_t* out, int32_t* scratch, const int32_t* fault,
                         int32_t* ptr_w);
 
 }  // namespace mpld
