@@ -305,8 +305,8 @@ int32_t mpld_build_graph_device(mpld_context* ctx, const mpld_rect* rects, int32
  * union-find and numbering run over the whole device, the small tail of the
  * peeling on one workgroup; BFS takes a wave per component of at most 64
  * nodes, a workgroup up to 4096 and many workgroups above.  Graphs of more
- * levels than pay off there, of nodes with over 2048 neighbours, or without
- * device memory for them are split on the host.  Synchronous on the context's
+ * levels or longer lists than pay off there, or without device memory for
+ * them, are split on the host.  Synchronous on the context's
  * stream.  Errors: MPLD_E_INVALID
  * for a bad graph (as mpld_decompose), k outside [2, MPLD_MAX_K] or a NULL
  * output; MPLD_E_DEVICE / MPLD_E_NOMEM. */

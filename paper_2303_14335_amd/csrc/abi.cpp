@@ -60,7 +60,9 @@ void check_options(const mpld_options* opt) {
 // 0.37; k = 4 with stitches, 19,800 0.92 / 0.74.
 // Where ids follow the layout the host takes 7 ns: a path of 40,000 together
 // 0.28 / 0.42, of 80,000 0.63 / 0.60, of 200,000 1.25 / 1.17.  That is told from
-// 64 of the pairs: in such a graph most join near ids.
+// 64 of the pairs: in such a graph most join near ids.  A node without pairs
+// costs the host a quarter of a pair (14,000 / 30,000 / 60,000 of them 0.10 /
+// 0.16 / 0.41, on the device 0.2), so there have to be 8,000 by that measure.
 // A graph that the device gives up (split_limits in graph_device.hip: deep
 // peelings, long narrow components; a recovery that is one long chain) costs
 // the front of the flow besides.  Host alone / both, ms: lines with two
@@ -68,12 +70,13 @@ void check_options(const mpld_options* opt) {
 // at once), 300,000 2.0 / 2.4, ids in no order, 24,000 0.39 / 0.62, 60,000 1.0 /
 // 1.3, 300,000 6.1 / 6.4; a packed window of 1:100, 50,000 2.0 / 2.4, 106,000
 // 4.0 / 4.4, 455,000 17.1 / 20.1.
-constexpr int64_t kFlowMinSize = 14000, kFlowMinOrdered = 60000;
+constexpr int64_t kFlowMinSize = 14000, kFlowMinOrdered = 60000, kFlowMinPairs = 8000;
 
 bool flow_pays(const mpld_context& ctx, const mpld_graph& g) {
   const int64_t size = (int64_t)g.num_nodes + g.num_ce;
   if (ctx.flow_from >= 0) return size >= ctx.flow_from;
-  if (size < kFlowMinSize || size >= kFlowMinOrdered || g.num_ce <= 0 || !g.ce) return size >= kFlowMinSize;
+  if (size < kFlowMinSize || (int64_t)g.num_nodes / 4 + g.num_ce < kFlowMinPairs) return false;
+  if (size >= kFlowMinOrdered || g.num_ce <= 0 || !g.ce) return true;
   int near = 0;
   for (int64_t i = 0; i < 64; ++i) {
     const int32_t* e = g.ce + 2 * (i * g.num_ce / 64);

@@ -1051,11 +1051,13 @@ void scan(GraphBuilder& gb, const int32_t* in, int64_t n, int32_t* out) {
 // rectangles have at most 8 levels in the tail, packed windows of 1,500, 5,000
 // and 40,000 (16,600, 57,000 and 476,000 nodes and pairs) at most 21, 34 and 96
 // in the numbering: these go through (26, 43 and 210 are allowed), and what is
-// given up has taken a fifth of the host's time at most.
+// given up has taken a fifth of the host's time at most.  A node of very many
+// neighbours takes 0.65 us for each over all passes, one load after another (one
+// of 1500 in 91,500 nodes and pairs: 1.4 ms a decomposition, 0.75 on the host).
 static SplitLimits split_limits(int64_t n, int64_t adj_entries) {
   const int64_t size = n + adj_entries / 2;
   const auto levels = [&](int64_t least, int64_t per) { return (int32_t)std::min<int64_t>(least + size / per, 1 << 20); };
-  return SplitLimits{levels(24, 4000), levels(32, 1000), levels(20, 2500), 2048, kMeetSpin};
+  return SplitLimits{levels(24, 4000), levels(32, 1000), levels(20, 2500), std::min(levels(256, 100), 2048), kMeetSpin};
 }
 
 SplitArgs enqueue_split(GraphBuilder& gb, int32_t n, const int32_t* dptr, const int32_t* dadj,
