@@ -460,11 +460,14 @@ int32_t mpld_solve_components(mpld_context* ctx, const mpld_component* comps, in
       image_add(im, ctx, cp.n, pairs.data(), cp.m, opt->k, opt->node_budget, opt->flags);
     }
     image_finish(im);
-    struct GiveBack {
-      mpld_context* ctx;
-      ~GiveBack() { ctx->seq_give_back(); }
-    } give_back{ctx};
     DeviceBatch db;
+    struct GiveBack {   // before db's memory, also after an error: nothing on the stream uses either
+      mpld_context* ctx;
+      ~GiveBack() {
+        (void)hipStreamSynchronize(ctx->stream);
+        ctx->seq_give_back();
+      }
+    } give_back{ctx};
     device_upload(ctx, im, db);
     db.min_budget = min_budget_of(opt);
     device_solve(db, opt->flags | MPLD_DIRECT | MPLD_SPLIT_HEAVY);

@@ -60,12 +60,12 @@ def test_ids_are_taken_once(exes, count):
 
 
 @pytest.mark.parametrize("items,k,budget,stuck", [
-    (192, 3, 1500, None), (192, 4, 4000, None), (60, 4, 4000, None), (40, 3, 1500, None), (24, 2, 1000, None),
-    (24, 4, 2500, None), (16, 5, 2000, None), (12, 4, 65, None), (192, 4, 1500, 1), (192, 3, 1500, 4)])
+    (192, 4, 3000, None), (60, 4, 3000, None), (40, 3, 1200, None), (24, 2, 1000, None), (16, 5, 1500, None),
+    (12, 4, 65, None), (192, 4, 800, 1), (192, 3, 800, 4)])
 def test_pieces(exes, items, k, budget, stuck):
     rng = np.random.default_rng(items * 100 + k)
     comps = []
-    while len(comps) < 4:
+    while len(comps) < 3:
         n, e, part = component(rng, k)
         inc = oracle.mark_conflicts(n, e, k)
         if abs(oracle.minimize_component(n, e, k, inc, budget, part).nodes) > 64:
