@@ -789,6 +789,24 @@ static void heavy_engine_device(DeviceBatch& db, bool trace, bool last) {
   check_hip(hipStreamSynchronize(s), "heavy: write back");
 }
 
+// Whether one-wave CSR components take the sequence engine rather than a task a
+// root row.  The first descent is one wave's either way, and a share or two after it are
+// not worth the rounds' launches: below the largest component's nodes and ten
+// shares of budget the root-row tasks are the better ones (12 components of 65
+// to 659 nodes, 2,211 of budget: 1.8 ms, 2.3 with the engine; 29 of 65 to 1596,
+// 5,409: 4.3 and 3.3; 2 of 2049 to 9131, 4,068: 2.8 and 3.3; 3 to 8103, 10,734:
+// 9.2 and 7.6).  A share that the caller has set is taken as it is.
+static bool seq_pays(const DeviceBatch& db, int32_t first, int32_t count) {
+  if (db.tune.heavy_round_cap != Tune().heavy_round_cap) return true;
+  int64_t most = 0, budget = 0;
+  for (int32_t i = 0; i < count; ++i) {
+    const DevDesc& d = db.host_desc[(size_t)(first + i)];
+    most = std::max<int64_t>(most, d.n);
+    budget = std::max(budget, d.budget);
+  }
+  return budget >= most + 10 * (int64_t)db.tune.heavy_round_cap;
+}
+
 // LDS-tier and big-tier components as subtree tasks.  At the
 // root every column has all k rows, so the root column is node 0 and the
 // root node's children are its k rows; task (component, c) searches the
@@ -815,7 +833,7 @@ static void csr_split(DeviceBatch& db, bool trace) {
   if (count == 0) return;
   const int32_t one_wave = db.csr_stitch ? 0 : db.n_lds + db.n_wide;
   bool by_seq = false;
-  if (one_wave) {
+  if (one_wave && seq_pays(db, first, one_wave)) {
     std::vector<int32_t> positions((size_t)one_wave);
     for (int32_t i = 0; i < one_wave; ++i) positions[(size_t)i] = first + i;
     by_seq = seq_solve(db, positions, trace);

@@ -116,3 +116,23 @@ def test_little_memory(ctx, monkeypatch, mib):
     assert np.array_equal(got.colors, ref.colors)
     assert bool(refused) == (mib < 200)
     assert sum(t.numel() for t in ctx._alloc.live.values()) == live
+
+
+def test_small_budgets(ctx):
+    """On both sides of the budget from which components are searched in
+    pieces (the largest one's nodes and ten shares)."""
+    import paper_2303_14335_amd as mp
+    rng = np.random.default_rng(12)
+    n, ce = union([component(s, 4.5, rng) for s in (70, 300, 411)])
+    g = mp.Graph(n, ce, np.zeros((0, 2), np.int32))
+    for budget, pieces in ((411 + 2559, False), (411 + 2560, True)):
+        say("small budgets", budget)
+        ref = oracle.decompose(oracle.Graph(n, ce, np.zeros((0, 2), np.int32)), 3, budget, False)
+        b = mp.Batch(ctx, g, 3, budget, TRACE)
+        b.solve(split=True)
+        got = b.result()
+        for f in ("status", "nodes", "trace_hash", "depth_at_stop"):
+            assert np.array_equal(got.components[f], ref.comps[f]), (budget, f)
+        assert np.array_equal(got.colors, ref.colors)
+        assert (b.info()["split_rounds"] > 0) == pieces
+        b.close()
