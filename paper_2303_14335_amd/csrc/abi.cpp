@@ -465,7 +465,7 @@ int32_t mpld_solve_components(mpld_context* ctx, const mpld_component* comps, in
       mpld_context* ctx;
       ~GiveBack() {
         (void)hipStreamSynchronize(ctx->stream);
-        ctx->seq_give_back();
+        ctx->seq_done();
       }
     } give_back{ctx};
     device_upload(ctx, im, db);

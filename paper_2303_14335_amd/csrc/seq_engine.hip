@@ -373,7 +373,8 @@ bool seq_solve(DeviceBatch& db, const std::vector<int32_t>& positions, bool trac
                 "sequence engine: CSR tiers");
   };
   for (int32_t round = 0;;) {
-    for (int32_t i = 0; i < kSeqRoundsPerCheck; ++i, ++round, parity ^= 1) {
+    // (many components are colored in their first descent: a look after that)
+    for (int32_t i = round == 0 ? kSeqRoundsPerCheck - 1 : 0; i < kSeqRoundsPerCheck; ++i, ++round, parity ^= 1) {
       run_tiers(false);
       hipLaunchKernelGGL(seq_fold_kernel, dim3((unsigned)H), dim3(kFoldThreads), 0, s, a, desc, parity);
     }
